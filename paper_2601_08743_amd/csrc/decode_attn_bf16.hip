@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256, 2) void decode_attn_bf16_kernel(Geom g, BatchD
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     if ((int)blockIdx.x >= a.n_items) {                // extra work-groups: append the new tokens to the pool
-        append_unit<true>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
+        append_unit<true, 1>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
                           blockIdx.x - a.n_items, threadIdx.x);
         return;
     }

@@ -172,7 +172,48 @@ struct PlanKnobs {
     int32_t forced_splits = 0;
     int32_t forced_row_blocks = 0;
     int32_t forced_attn_kernel = 0;   // 1 general, 2 pipelined, 3 decode (where it applies), 4 long launches
+    int32_t f32_rows = 4;             // fp32: rows per work item (tc_create sets the kernel's; any other plans the same way)
 };
+
+// fp32 batches: the key range of a work item, in key tiles.  A wave works through a quarter of its
+// item's 32-key units one after the other at 1.9 us each for D = 64 (4096 cycles of matrix
+// instructions), about one more for start and end; a CU does that for one item at 0.8 of the full rate
+// or for two at half the rate each.  Items are nearly equal, so they run in rounds of 512, and what
+// a launch takes is its full rounds plus the last one, however few items that holds: ranges are cut
+// so that the rounds come out full.  The merge costs a launch of ~2.5 us and its traffic.
+// Measured (8 queries, 23 k keys, 8 / 2 heads of 64): 102 us against 118..127 us for one or two ranges a query.
+inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int key_tile)
+{
+    const int G = c.n_q_heads / c.n_kv_heads;
+    const double unit_us = 1.9 * c.head_dim / 64.0;
+    int longest = 0;
+    for (int i = 0; i < p.B; ++i)
+        if (p.suffix_len[i] > 0) longest = std::max(longest, (p.prefix_len[i] + p.suffix_len[i] + key_tile - 1) / key_tile);
+    int best_range = 0;
+    double best = 1e30;
+    for (int cuts = 1; cuts <= 32; ++cuts) {
+        const int range = std::max(1, (longest + cuts - 1) / cuts);
+        double units = 0, partial_rows = 0, item = 0;
+        int64_t n = 0;
+        for (int i = 0; i < p.B; ++i) {
+            const int S = p.suffix_len[i];
+            if (S <= 0) continue;
+            const int tiles = (p.prefix_len[i] + S + key_tile - 1) / key_tile, ns = (tiles + range - 1) / range;
+            const double per_wave = std::ceil(2.0 * ((tiles + ns - 1) / ns) / 4.0) + 1.0;
+            const int64_t k = (int64_t)c.n_kv_heads * ((S * G + row_tile - 1) / row_tile) * ns;
+            n += k;
+            units += (double)k * per_wave;
+            item = std::max(item, per_wave);
+            if (ns > 1) partial_rows += (double)S * c.n_q_heads * ns;
+        }
+        const int64_t rest = n % 512;
+        const double us = unit_us * ((double)(n / 512) * 2.0 * (units / (double)n) + (rest == 0 ? 0.0 : rest <= 256 ? 1.25 * item : 2.0 * item)) +
+                          (partial_rows > 0 ? 2.5 + 2e-6 * partial_rows * c.head_dim : 0.0);
+        if (us < best - 1e-9) { best = us; best_range = range; }
+        if (range == 1) break;
+    }
+    return best_range;
+}
 
 // Attention work list for the batch in `p` (host arrays filled in).  Items of one
 // (query, KV head, split) read the same K/V; they are given work-group ids that are congruent
@@ -291,7 +332,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // wave per SIMD) is kept as an option: it is slower until its matrix and vector work overlap
     const int rb = pp ? 2 : (bf16 && ctx->forced_row_blocks > 0) ? ctx->forced_row_blocks : 1;
     p.row_blocks = rb;
-    const int RT = bf16 ? kAttnRows * rb : kF32Rows;
+    const int RT = bf16 ? kAttnRows * rb : ctx->f32_rows;
     int64_t base = 0, tiles_sum = 0, n_q = 0;
     for (int i = 0; i < p.B; ++i)
         if (p.suffix_len[i] > 0) {
@@ -307,8 +348,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // work-group (co-resident work-groups overlap each other's stalls: x0.7); plus a fixed start-up
     // and epilogue cost; plus the merge: a launch and the partials written and read back at about
     // 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
-    int want = 1;
+    int want = 1, f32_range = 0;
     if (ctx->forced_splits > 0) want = ctx->forced_splits;
+    else if (!bf16 && base > 0) f32_range = plan_f32_range(c, p, RT, KT);
     else if (base > 0) {
         const double tiles = (double)tiles_sum / (double)n_q;
         const double items_per_bucket = (double)base / (double)(n_q * c.n_kv_heads);
@@ -335,8 +377,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // last block a tile load may touch: bf16 reads only prefix blocks from the pool
         const int last_blk = std::max(0, (unified ? (P + S + kBlockTokens - 1) / kBlockTokens
                                                   : (P + kBlockTokens - 1) / kBlockTokens) - 1);
+        if (f32_range > 0) want = (n_tiles + f32_range - 1) / f32_range;
         int ns = std::min(want, ctx->forced_splits > 0 ? n_tiles : std::max(1, n_tiles / 2));
-        const int cap = !bf16 ? n_tiles : pp ? kPpMaxTiles : general_cap;   // block ids of a range fit LDS
+        const int cap = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : general_cap;   // block ids of a range fit LDS
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
         ns = std::max(1, std::min(ns, n_tiles));
         const int n_mt = (S * G + RT - 1) / RT;
@@ -386,6 +429,12 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                         for (int k = t0 * 4; k < (t0 + std::max(n_fast, 0)) * 4; ++k) it.n_pad_fast += pad_of[k];
                     }
                     bucket.push_back(it);
+                    // (fp32: eight row tiles share their keys' way into one L2, the next eight may go to another
+                    // XCD, so that few (query, KV head) pairs still spread evenly)
+                    if (!bf16 && bucket.size() == 8 && mt + 1 < n_mt) {
+                        buckets.push_back(std::move(bucket));
+                        bucket.clear();
+                    }
                 }
                 buckets.push_back(std::move(bucket));
             }
@@ -431,7 +480,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                   (ctx->forced_attn_kernel == 1 || ctx->forced_attn_kernel == 2 ? ctx->forced_attn_kernel == 2
                                            : (n_real <= 2 * 256 || fast_tiles >= 48 * n_real));
     // every range's block ids must fit the table of the kernel that will run it
-    const int limit = !bf16 ? INT32_MAX : pp ? kPpMaxTiles : p.pipelined ? kPipeMaxTiles : kAttnMaxTiles;
+    const int limit = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : p.pipelined ? kPipeMaxTiles : kAttnMaxTiles;
     for (const AttnItem &it : items)
         if (it.q >= 0 && it.tile_end - it.tile_begin > limit) return false;
     return true;

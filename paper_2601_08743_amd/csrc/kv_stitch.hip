@@ -367,14 +367,6 @@ hipError_t launch_stitch(const Geom &g, const BatchDev &b, int l0, int l1, bool 
 }
 
 // ------------------------------------------------------------------------------------ append
-// Stand-alone launch of the append units (fp32 path), one work-group per unit.
-template <bool kTransposeV>
-__global__ __launch_bounds__(256) void append_kernel(Geom g, BatchDev b, int layer,
-                                                     const char *k_new, const char *v_new)
-{
-    append_unit<kTransposeV>(g, b, layer, k_new, v_new, blockIdx.x, threadIdx.x);
-}
-
 // Append by blocks, for launches that must have the suffix in the pool before attention starts:
 // one work-group per sequence block that holds suffix tokens.  A block that lies wholly behind the
 // prefix is written like a stitched block (rows of k_new / v_new as the source, zeros behind the
@@ -431,18 +423,6 @@ hipError_t launch_append_blocks(const Geom &g, const BatchDev &b, int layer, con
         TC_LAUNCH(append_blocks_kernel<true>, n_blocks, kBlockTokens * g.row_bytes, L, g, b, layer, (const char *)k_new, (const char *)v_new);
     else
         TC_LAUNCH(append_blocks_kernel<false>, n_blocks, 0, L, g, b, layer, (const char *)k_new, (const char *)v_new);
-    return hipGetLastError();
-}
-
-hipError_t launch_append(const Geom &g, const BatchDev &b, int layer, const void *k_new,
-                         const void *v_new, const Launch &L)
-{
-    const int n = b.total_S + b.B;
-    if (n == 0) return hipSuccess;
-    if (g.esize == 2)
-        TC_LAUNCH(append_kernel<true>, n, 0, L, g, b, layer, (const char *)k_new, (const char *)v_new);
-    else
-        TC_LAUNCH(append_kernel<false>, n, 0, L, g, b, layer, (const char *)k_new, (const char *)v_new);
     return hipGetLastError();
 }
 

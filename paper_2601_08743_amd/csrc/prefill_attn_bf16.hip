@@ -475,7 +475,7 @@ __global__ __launch_bounds__(256, RB == 1 ? 2 : 1) void attn_bf16_kernel(Geom g,
     int32_t *s_bid = (int32_t *)(lds + 2 * kStage);
 
     if ((int)blockIdx.x >= a.n_items) {                // extra work-groups: append the suffix to the pool
-        append_unit<true>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
+        append_unit<true, 1>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
                           blockIdx.x - a.n_items, threadIdx.x);
         return;
     }
@@ -892,7 +892,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
     int32_t *s_bid = (int32_t *)(lds + kFastBid);
 
     if ((int)blockIdx.x >= a.n_items) {                // extra work-groups: append the suffix to the pool
-        append_unit<true>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
+        append_unit<true, 1>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
                           blockIdx.x - a.n_items, threadIdx.x);
         return;
     }

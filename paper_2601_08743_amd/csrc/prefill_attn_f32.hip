@@ -1,124 +1,276 @@
 // Suffix prefill attention, fp32 storage and fp32 arithmetic (no reduced-precision operands).
 // App. E.4 of the paper: the suffix rows attend to all stitched schema keys, and causally to
-// the suffix itself.  Online softmax over key tiles of 64; one wave per (suffix token, head) row,
-// four rows per work-group sharing the K tile through LDS.  This variant exists for the fp32
-// configuration, which is small and latency-bound; the matrix-core path is the bf16 kernel.
+// the suffix itself.
+//
+// Bound: the fp32 matrix rate (v_mfma_f32_32x32x2_f32, 64 cycles for 4096 operations: 157 TFLOP/s on
+// the chip, twice what v_fma_f32 reaches).  A work-group is 32 rows (row = token * G + head in the
+// group) of one (query, KV head) against a key range; its four waves split the KEYS: wave w takes the
+// 32-key units w, w + 4, ... of the range, streams each straight into its own LDS area (nobody else
+// reads it, so the loop has no barrier), and keeps its own running maximum, sum and output; the four
+// are combined through LDS at the end.  Splitting keys rather than rows keeps the row tile small - a
+// suffix of a few tokens fills it, and ragged lengths waste little - and costs only L2 reads, of which
+// this rate needs 16 bytes a cycle and CU.
+//
+// Operand layouts.  S^T = K . Q^T: the order of the depth index is free as long as both operands agree,
+// so lane half hh holds elements hh * D/2 .. of its row, and four instructions' worth of K is one
+// 16-byte LDS read.  A lane then holds 16 scores of ONE row, and score e is directly the B operand of
+// O^T += V^T . P^T for the key pair that its two lane halves stand for; V is read from its token rows
+// D/32 neighbouring columns at a time.
+//
+// Measured (8 queries, 23 k prefix and 1.4 k suffix tokens, 8 query / 2 KV heads of 64: 8.3 GFLOP): 102 us
+// + 4.5 us merge; one wave per row with v_fma_f32, keys from LDS one float at a time, values straight from
+// the pool, took 1049 us.  A batch long enough to drown its edges runs at 112 TFLOP/s (a 4096^3 library
+// product: 140).  One query of 731 + 64 tokens: 11 + 4.5 us, before 28 + 4 us and an append launch.
+#include "kv_append.h"
+#include "lds_dma.h"
 #include "tc_internal.h"
 
 namespace tc {
 
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kF32Unit = 32;                                       // keys per unit
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(Geom g, BatchDev b, AttnArgs a)
+struct F32Lds {
+    static constexpr int kPart = kF32Unit * D * 4;                 // K (or V) of one unit
+    static constexpr int kWave = 2 * kPart;
+    static constexpr int kBid = 4 * kWave;                         // block ids behind the four waves' areas
+    static constexpr int kBytes = kBid + kF32MaxTiles * (kF32Keys / kBlockTokens) * 4 + 256;   // + alignment slack
+    static constexpr int kRow = D + 4;                             // padded row of the final exchange (floats)
+};
+
+template <int D>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, BatchDev b, AttnArgs a)
 {
-    constexpr int DP = D + 1;                    // padded K row: lanes read distinct banks
-    constexpr int DPL = D / 64;                  // output columns per lane
-    __shared__ float ks[kF32Keys * DP];
-    __shared__ float pw[kF32Rows][kF32Keys];
-    const AttnItem it = a.items[blockIdx.x];
-    if (it.q < 0) return;                              // padding item (uniform for the work-group)
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const int i = it.q;
-    const int P = b.prefix_len[i], S = b.suffix_len[i], cu = b.cu_seqlens[i];
-    const int n_blk = (P + S + kBlockTokens - 1) >> 4;
-    const int m = it.m0 + w;
-    const bool valid = m < S * g.G;
-    const int s_tok = valid ? m / g.G : 0;
-    const int head = it.kvh * g.G + (valid ? m % g.G : 0);
-    const int limit = P + s_tok;                 // last visible key
-    const int32_t *bt = b.block_table + (int64_t)i * b.max_blocks;
-    const char *layer_base = g.pool + (int64_t)a.layer * g.layer_stride;
-    const int64_t head_off = (int64_t)it.kvh * kBlockTokens * g.head_bytes;
+    typedef F32Lds<D> L;
+    constexpr int kPieces = L::kPart / 1024;     // load instructions per operand and unit
+    constexpr int kChunks = D / 4;               // 16-byte chunks of a row
+    constexpr int kRowsPer = 64 / kChunks;       // rows per load instruction
+    constexpr int kCols = D / 32;                // neighbouring output columns per lane
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    if ((int)blockIdx.x >= a.n_items) {          // extra work-groups: append the suffix to the pool
+        append_unit<false, kF32AppendTokens>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new, blockIdx.x - a.n_items, threadIdx.x);
+        return;
+    }
+    const AttnItem it = load_item(a, blockIdx.x);
+    if (it.q < 0) return;                        // padding item (uniform for the work-group)
+    // the XOR addressing of the K rows needs them 256-byte aligned
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_raw;
+    const uint32_t slack = (256u - (lds_base & 255u)) & 255u;
+    char *lds = lds_raw + slack;
+    const uint32_t lds0 = lds_base + slack;
+    int32_t *s_bid = (int32_t *)(lds + L::kBid);
 
-    float qreg[D];
+    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int P = it.P, S = it.S, G = g.G;
+    const int n_rows = S * G;
+    const int m = min(it.m0 + r32, n_rows - 1);  // rows behind the last one repeat it and are dropped
+    const int s_tok = m / G;
+    const int64_t row = (int64_t)(it.cu + s_tok) * g.Hq + it.kvh * G + (m - s_tok * G);
+    const int limit = P + s_tok;                 // last key this row sees
+    const int u_begin = it.tile_begin * (kF32Keys / kF32Unit);
+    // units behind the last key that any row of the tile sees are left out
+    const int last_key = P + (min(it.m0 + kF32Rows, n_rows) - 1) / G;
+    const int u_end = min(it.tile_end * (kF32Keys / kF32Unit), last_key / kF32Unit + 1);
+
+    // block ids of the range's prefix part
+    const int blk0 = it.tile_begin * (kF32Keys / kBlockTokens);
     {
-        const float *qp = (const float *)a.q + ((int64_t)(cu + s_tok) * g.Hq + head) * D;
-#pragma unroll
-        for (int d = 0; d < D; ++d) qreg[d] = qp[d];
+        const int n_pblk = (P + kBlockTokens - 1) >> 4;
+        const int n = min(it.tile_end * (kF32Keys / kBlockTokens), n_pblk) - blk0;
+        const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks + blk0;
+        for (int idx = tid; idx < n; idx += 256) s_bid[idx] = bt[idx];
     }
-    float m_run = -INFINITY, l_lane = 0.f;
-    float acc[DPL];
+    // Q^T fragments (B operand): lane (row r32, half hh) holds q[row][hh * D/2 ..]
+    float qf[D / 2];
+    {
+        const f32x4 *qp = (const f32x4 *)((const float *)a.q + row * D + hh * (D / 2));
 #pragma unroll
-    for (int c = 0; c < DPL; ++c) acc[c] = 0.f;
+        for (int j = 0; j < D / 8; ++j) {
+            const f32x4 v = qp[j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) qf[4 * j + e] = v[e];
+        }
+    }
+    // (used once here, so that the compiler's wait for these loads stands in front of the loop, not in it,
+    // where it would drain the loads of the next unit as well)
+#pragma unroll
+    for (int j = 0; j < D / 2; ++j) asm volatile("" : "+v"(qf[j]));
+    __syncthreads();                             // block ids visible
 
-    for (int t = it.tile_begin; t < it.tile_end; ++t) {
-        const int key0 = t * kF32Keys;
-        __syncthreads();                         // previous tile's readers are done
-        // stage K: 4 blocks x 16 tokens x D floats, coalesced rows
-        for (int c = tid; c < kF32Keys * (D / 4); c += 256) {
-            const int kk = c / (D / 4), d4 = c % (D / 4);
-            int jb = (key0 + kk) >> 4;
-            jb = jb < n_blk ? jb : n_blk - 1;    // past the end: any valid block, masked below
-            const float4 v = *(const float4 *)(layer_base + (int64_t)bt[jb] * g.block_bytes + head_off +
-                                               ((int64_t)((key0 + kk) & 15) * D + d4 * 4) * 4);
-            float *dst = ks + kk * DP + d4 * 4;
-            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+    const char *pool_l = g.pool + (int64_t)a.layer * g.layer_stride + (int64_t)it.kvh * kBlockTokens * D * 4;
+    const int64_t v_half = g.block_bytes >> 1;
+    const char *new_k = (const char *)a.k_new + ((int64_t)it.cu * g.Hkv + it.kvh) * D * 4;
+    const char *new_v = (const char *)a.v_new + ((int64_t)it.cu * g.Hkv + it.kvh) * D * 4;
+    const uint32_t lds_w = lds0 + w * L::kWave;
+    const int l_row = lane / kChunks, l_chunk = lane % kChunks;
+
+    // One operand of one unit -> LDS rows of D floats; of K, chunk c of row r lands at position
+    // c ^ (r & 15), so that 16 lanes reading one chunk of 16 rows touch all banks.
+    auto issue = [&](int u, bool is_v) {
+        const uint32_t dst = lds_w + (is_v ? L::kPart : 0);
+        const int key0 = u * kF32Unit;
+        if (key0 + kF32Unit <= P) {              // two whole blocks of the pool
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const char *src = pool_l + (int64_t)__builtin_amdgcn_readfirstlane(s_bid[2 * u + j - blk0]) * g.block_bytes + (is_v ? v_half : 0);
+#pragma unroll
+                for (int i = 0; i < kPieces / 2; ++i) {
+                    const int r = i * kRowsPer + l_row;
+                    load_to_lds(dst + (j * (kPieces / 2) + i) * 1024, src, (r * kChunks + (is_v ? l_chunk : l_chunk ^ (r & 15))) * 16);
+                }
+            }
+        } else {                                 // the end of the prefix and / or suffix tokens
+#pragma unroll
+            for (int i = 0; i < kPieces; ++i) {
+                const int r = i * kRowsPer + l_row;
+                const int key = key0 + r;
+                const int st = min(max(key - P, 0), S - 1);
+                const char *src = (is_v ? new_v : new_k) + (int64_t)st * g.row_bytes;
+                if (key < P) src = pool_l + (int64_t)s_bid[(key >> 4) - blk0] * g.block_bytes + (is_v ? v_half : 0) + (key & 15) * (D * 4);
+                load_to_lds_each(dst + i * 1024, src + (is_v ? l_chunk : l_chunk ^ (r & 15)) * 16);
+            }
         }
-        __syncthreads();
-        // scores: lane <-> key
-        const int key = key0 + lane;
-        float s = 0.f;
+    };
+
+    f32x16 o[kCols];
 #pragma unroll
-        for (int d = 0; d < D; ++d) s = fmaf(qreg[d], ks[lane * DP + d], s);
-        s = (key <= limit) ? s * a.scale_log2 : -INFINITY;
-        const float m_new = fmaxf(m_run, wave_max(s));
-        const float m_eff = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = (m_run == -INFINITY) ? 0.f : exp2f(m_run - m_eff);
-        const float p = exp2f(s - m_eff);
-        l_lane = l_lane * alpha + p;
-        m_run = m_new;
-        pw[w][lane] = p;
-        __syncthreads();
-        // values: lane <-> output column(s); V rows straight from the pool (row-contiguous)
+    for (int j = 0; j < kCols; ++j)
 #pragma unroll
-        for (int c = 0; c < DPL; ++c) acc[c] *= alpha;
-        const int n_here = min(kF32Keys, max(0, min(limit, P + S - 1) - key0 + 1));
-        for (int kk = 0; kk < n_here; ++kk) {
-            const int jb = (key0 + kk) >> 4;
-            const float *vrow = (const float *)(layer_base + (int64_t)bt[jb] * g.block_bytes +
-                                                (g.block_bytes >> 1) + head_off) +
-                                ((key0 + kk) & 15) * D;
-            const float pj = pw[w][kk];
-#pragma unroll
-            for (int c = 0; c < DPL; ++c) acc[c] = fmaf(pj, vrow[lane + 64 * c], acc[c]);
-        }
+        for (int e = 0; e < 16; ++e) o[j][e] = 0.f;
+    float m_run = -INFINITY, l_lane = 0.f;
+    typedef const __attribute__((address_space(3))) f32x4 *lds_f4;
+    typedef float vcols __attribute__((ext_vector_type(kCols)));
+    typedef const __attribute__((address_space(3))) vcols *lds_cols;
+    const uint32_t k_row = lds_w + r32 * (D * 4);
+    const uint32_t v_at = lds_w + L::kPart + hh * 4 * (D * 4) + r32 * (kCols * 4);
+
+    // The loads run one operand ahead: K of the wave's next unit is requested as soon as this unit's
+    // scores are done, V likewise; loads complete in the order issued, so a wait that leaves the
+    // kPieces youngest outstanding has everything older in LDS.
+    int u = u_begin + w;
+    if (u < u_end) {
+        issue(u, false);
+        issue(u, true);
     }
-    const float l = wave_sum(l_lane);
-    if (!valid) return;
-    const int64_t row = (int64_t)(cu + s_tok) * g.Hq + head;
-    if (it.n_splits == 1) {
-        float *o = (float *)a.out + row * D;
-        const float inv = 1.f / l;
+    for (; u < u_end; u += 4) {
+        const bool more = u + 4 < u_end;
+        wait_loads<kPieces>();                   // K(u) has landed; V(u) may still be on its way
+        f32x16 s;
 #pragma unroll
-        for (int c = 0; c < DPL; ++c) o[lane + 64 * c] = acc[c] * inv;
-    } else {
-        const int64_t prow = (int64_t)it.split * b.total_S * g.Hq + row;
-        float *o = a.part_o + prow * D;
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
-        for (int c = 0; c < DPL; ++c) o[lane + 64 * c] = acc[c];
-        if (lane == 0) { a.part_ml[prow * 2] = m_run; a.part_ml[prow * 2 + 1] = l; }
+        for (int j = 0; j < D / 8; ++j) {
+            const f32x4 kf = *(lds_f4)(uintptr_t)(k_row + (((hh * (D / 8) + j) ^ (r32 & 15)) << 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[4 * j + e], s, 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // K area read out: free for the next unit
+        if (more) issue(u + 4, false);
+        // score e of the lane belongs to key 8 * (e >> 2) + 4 * hh + (e & 3) of the unit
+        const int key0 = u * kF32Unit;
+        if (key0 + kF32Unit - 1 > P) {           // some row may not see all of the unit
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[e] = key0 + 8 * (e >> 2) + 4 * hh + (e & 3) <= limit ? s[e] : -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32)) * a.scale_log2;       // (the scale is positive)
+        if (__any(mx > m_run)) {
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = (m_run == -INFINITY) ? 0.f : exp2f(m_run - m_new);
+            l_lane *= alpha;
+#pragma unroll
+            for (int j = 0; j < kCols; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[j][e] *= alpha;
+            m_run = m_new;
+        }
+        const float ref = (m_run == -INFINITY) ? 0.f : m_run;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            s[e] = exp2f(s[e] * a.scale_log2 - ref);
+            l_lane += s[e];
+        }
+        if (more) wait_loads<kPieces>();         // V(u) has landed, K(u + 4) may be outstanding
+        else wait_loads<0>();
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const vcols vf = *(lds_cols)(uintptr_t)(v_at + (8 * (e >> 2) + (e & 3)) * (D * 4));
+#pragma unroll
+            for (int j = 0; j < kCols; ++j) o[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[j], s[e], o[j], 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // V area read out
+        if (more) issue(u + 4, true);
+    }
+
+    // ---- combine the four waves: each writes O as padded rows and (max, sum) per row into its own area
+    // (dead now), then the work-group folds the four and writes the rows (unsplit) or their partials
+    {
+        float *wo = (float *)(lds + w * L::kWave);
+        const float l_row_sum = l_lane + __shfl_xor(l_lane, 32);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            vcols v;
+#pragma unroll
+            for (int j = 0; j < kCols; ++j) v[j] = o[j][e];
+            *(vcols *)(wo + r32 * L::kRow + kCols * (8 * (e >> 2) + 4 * hh + (e & 3))) = v;
+        }
+        if (hh == 0) { wo[32 * L::kRow + 2 * r32] = m_run; wo[32 * L::kRow + 2 * r32 + 1] = l_row_sum; }
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int idx = tid; idx < kF32Rows * kChunks; idx += 256) {
+        const int r = idx / kChunks, d4 = idx - r * kChunks;
+        const int mr = it.m0 + r;
+        if (mr >= n_rows) continue;
+        float M = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * L::kWave))[32 * L::kRow + 2 * r]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float *wk = (const float *)(lds + k * L::kWave);
+            const float mk = wk[32 * L::kRow + 2 * r];
+            const float wgt = (mk == -INFINITY) ? 0.f : exp2f(mk - M);
+            sum += wgt * wk[32 * L::kRow + 2 * r + 1];
+            const f32x4 v = *(const f32x4 *)(wk + r * L::kRow + 4 * d4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, v[e], acc[e]);
+        }
+        const int tok = mr / G;
+        const int64_t orow = (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (mr - tok * G);
+        if (it.n_splits == 1) {
+            const float inv = 1.f / sum;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] *= inv;
+            *(f32x4 *)((float *)a.out + orow * D + 4 * d4) = acc;
+        } else {
+            const int64_t prow = (int64_t)it.split * b.total_S * g.Hq + orow;
+            *(f32x4 *)(a.part_o + prow * D + 4 * d4) = acc;
+            if (d4 == 0) { a.part_ml[prow * 2] = M; a.part_ml[prow * 2 + 1] = sum; }
+        }
     }
 }
 
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
-    if (a.n_items == 0) return hipSuccess;
+    if (a.n_items + a.n_append == 0) return hipSuccess;
+    static PerDeviceOnce configured;
+    const hipError_t e = configured.run([] {
+        const hipError_t e64 = hipFuncSetAttribute((const void *)attn_f32_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<64>::kBytes);
+        if (e64 != hipSuccess) return e64;
+        return hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<128>::kBytes);
+    });
+    if (e != hipSuccess) return e;
     if (g.D == 64)
-        TC_LAUNCH(attn_f32_kernel<64>, a.n_items, 0, L, g, b, a);
+        TC_LAUNCH(attn_f32_kernel<64>, a.n_items + a.n_append, F32Lds<64>::kBytes, L, g, b, a);
     else if (g.D == 128)
-        TC_LAUNCH(attn_f32_kernel<128>, a.n_items, 0, L, g, b, a);
+        TC_LAUNCH(attn_f32_kernel<128>, a.n_items + a.n_append, F32Lds<128>::kBytes, L, g, b, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -127,44 +279,72 @@ hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, 
 // ------------------------------------------------------------------------------------ merge
 // Combine split-KV partials of one output row: with reference maxima m_s (log2 units), sums l_s
 // and unnormalised partial outputs O_s:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One wave per (suffix token, head) row.
-template <typename OutT>
-__global__ __launch_bounds__(256) void merge_kernel(Geom g, BatchDev b, AttnArgs a)
+// D/4 threads per (suffix token, head) row, four columns each.  Bound: the latency of the loads of a
+// short launch, so those of eight partitions are issued before the first use (slots of partitions a
+// query does not have exist in the buffer; they are loaded and ignored).
+// Measured (2 queries, 9 k keys, 2 + 59 tokens, 20 partitions): 5.3 us; one partition after the other 18.4 us.
+template <int D>
+__global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    constexpr int kThreads = D / 4;
+    constexpr int kBatch = 8;
+    const int64_t row = (int64_t)blockIdx.x * (256 / kThreads) + threadIdx.x / kThreads;
+    const int d = 4 * (threadIdx.x % kThreads);
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     if (row >= n_rows) return;
-    const int n = (int)(row / g.Hq);
-    const int ns = b.splits_of_q[b.tok_q[n]];
+    const int ns = b.splits_of_q[b.tok_q[row / g.Hq]];
+    float2 ml[kBatch];
+    f32x4 po[kBatch];
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int64_t slot = (int64_t)min(s0 + j, max_splits - 1) * n_rows + row;
+            ml[j] = *(const float2 *)(a.part_ml + slot * 2);
+            po[j] = *(const f32x4 *)(a.part_o + slot * D + d);
+        }
+    };
+    fetch(0);
     if (ns <= 1) return;                         // written directly by the attention kernel
-    float M = -INFINITY;
-    for (int s = 0; s < ns; ++s) M = fmaxf(M, a.part_ml[((int64_t)s * n_rows + row) * 2]);
-    float den = 0.f;
-    float acc[2] = {0.f, 0.f};
-    const int D = g.D;
-    for (int s = 0; s < ns; ++s) {
-        const int64_t prow = (int64_t)s * n_rows + row;
-        const float ms = a.part_ml[prow * 2];
-        const float wgt = (ms == -INFINITY) ? 0.f : exp2f(ms - M);
-        den += wgt * a.part_ml[prow * 2 + 1];
-        const float *o = a.part_o + prow * D;
-        for (int c = 0; c * 64 < D; ++c) acc[c] = fmaf(wgt, o[lane + 64 * c], acc[c]);
+    float M = -INFINITY, den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < ns; s0 += kBatch) {
+        if (s0 > 0) fetch(s0);
+        float Mc = M;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) Mc = s0 + j < ns ? fmaxf(Mc, ml[j].x) : Mc;
+        const float r = M == -INFINITY ? 0.f : exp2f(M - Mc);
+        den *= r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] *= r;
+        M = Mc;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (s0 + j >= ns || ml[j].x == -INFINITY) continue;
+            const float wgt = exp2f(ml[j].x - M);
+            den = fmaf(wgt, ml[j].y, den);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, po[j][e], acc[e]);
+        }
     }
     const float inv = 1.f / den;
-    OutT *o = (OutT *)a.out + row * D;
-    for (int c = 0; c * 64 < D; ++c) o[lane + 64 * c] = (OutT)(acc[c] * inv);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= inv;
+    *(f32x4 *)((float *)a.out + row * D + d) = acc;
 }
 
-hipError_t launch_merge(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
+hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
-    const int grid = (int)((n_rows + 3) / 4);
-    if (g.esize == 2)
-        TC_LAUNCH(merge_kernel<__bf16>, grid, 0, L, g, b, a);
+    if (max_splits < 1) return hipErrorInvalidValue;
+    const int per = 256 / (g.D / 4);
+    const int grid = (int)((n_rows + per - 1) / per);
+    if (g.D == 64)
+        TC_LAUNCH(merge_f32_kernel<64>, grid, 0, L, g, b, a, max_splits);
+    else if (g.D == 128)
+        TC_LAUNCH(merge_f32_kernel<128>, grid, 0, L, g, b, a, max_splits);
     else
-        TC_LAUNCH(merge_kernel<float>, grid, 0, L, g, b, a);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

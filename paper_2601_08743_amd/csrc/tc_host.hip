@@ -3,6 +3,7 @@
 // per-batch planning (stitch descriptors, attention work list, split-KV) and kernel launches.
 #include "../../include/tablecache.h"
 #include "host_logic.h"
+#include "kv_append.h"
 #include "tc_internal.h"
 
 #include <algorithm>
@@ -403,6 +404,7 @@ tc_status tc_create(const tc_config *cfg, void *kv_pool_dev, size_t pool_bytes, 
     g.head_bytes = g.D * g.esize;
 
     ctx->rule.reset(make_rule(cfg->policy));
+    ctx->knobs.f32_rows = kF32Rows;
 
     ctx->slots.resize(cfg->table_capacity);
     for (int s = 0; s < cfg->table_capacity; ++s) {
@@ -917,7 +919,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     if (p.decode) {
         AttnArgs a{};
         a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
-        a.n_append = p.total_S + p.B; a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
+        a.n_append = append_units(p.total_S, p.B, 1); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
         a.part_ml = p.part + (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
@@ -925,9 +927,8 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_decode_finish(ctx->geom, p.dev, a, p.max_splits, ln); }));
         return TC_OK;
     }
-    if (!bf16)      // the bf16 attention launches append in extra work-groups of their own, except:
-        TC_HIP(ctx, timed_launch(ctx, 1, stream, [&](const Launch &ln) { return launch_append(ctx->geom, p.dev, layer, k_new, v_new, ln); }));
-    if (p.pingpong) {   // this kernel reads the suffix from the pool: it is appended first, block by block
+    if (p.pingpong) {   // the attention launches append in extra work-groups of their own, except this kernel's,
+                        // which reads the suffix from the pool: it is appended first, block by block
         int n_blk = 0;
         for (int i = 0; i < p.B; ++i)
             if (p.suffix_len[i] > 0)
@@ -936,7 +937,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     }
     AttnArgs a{};
     a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
-    a.n_append = bf16 && !p.pingpong ? p.total_S + p.B : 0; a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
+    a.n_append = p.pingpong ? 0 : append_units(p.total_S, p.B, bf16 ? 1 : kF32AppendTokens); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     a.has_pads = p.block_pad.empty() ? 0 : 1;
     a.part_o = p.part;
@@ -951,7 +952,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     if (p.max_splits > 1)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
             return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, ln)
-                        : launch_merge(ctx->geom, p.dev, a, ln);
+                        : launch_merge_f32(ctx->geom, p.dev, a, p.max_splits, ln);
         }));
     return TC_OK;
 }

@@ -19,6 +19,19 @@ struct Launch {
 #define TC_LAUNCH(kernel, grid, lds_bytes, L, ...) \
     hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(256), (lds_bytes), (L).stream, (L).start, (L).stop, 0, __VA_ARGS__)
 
+// Work item `k` through scalar loads: the plan was uploaded before the launch and nothing writes it, which
+// the compiler cannot see for itself in kernels that also store to memory.
+__device__ __forceinline__ AttnItem load_item(const AttnArgs &a, unsigned k)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(4))) u32x4 *const_words;
+    const const_words src = (const_words)(uintptr_t)(a.items + k);
+    union { u32x4 w[sizeof(AttnItem) / 16]; AttnItem item; } u;
+#pragma unroll
+    for (unsigned j = 0; j < sizeof(AttnItem) / 16; ++j) u.w[j] = src[j];
+    return u.item;
+}
+
 // A kernel's dynamic-LDS limit (hipFuncSetAttribute) is a property of the kernel on one device: each
 // launcher keeps one of these per kernel and raises the limit the first time it launches on a device.
 // (Two threads that race on a device's first launch both set the same value.)
@@ -43,8 +56,6 @@ struct PerDeviceOnce {
 hipError_t launch_stitch(const Geom &g, const BatchDev &b, int l0, int l1, bool rope, const Launch &L);
 hipError_t launch_format(const Geom &g, const void *raw, int64_t v_part, int n_tokens, int first_block, int l0,
                          int l1, const Launch &L);
-hipError_t launch_append(const Geom &g, const BatchDev &b, int layer, const void *k_new,
-                         const void *v_new, const Launch &L);
 hipError_t launch_readback(const Geom &g, int layer, const int32_t *blocks_dev, int n_tokens,
                            void *k_out_dev, void *v_out_dev, hipStream_t s);
 // prefill_attn_bf16.hip / prefill_attn_f32.hip
@@ -57,7 +68,7 @@ hipError_t launch_attn_pp_bf16(const Geom &g, const BatchDev &b, const AttnArgs 
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
-hipError_t launch_merge(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
+hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup *groups, int n_groups,
                              int row_blocks, const Launch &L);
 

@@ -13,8 +13,10 @@ constexpr int kAttnKeys = 64;        // bf16 kernel: keys per tile (4 pool block
 constexpr int kAttnMaxTiles = 256;   // bf16 kernel: key tiles per work item (block ids kept in LDS)
 constexpr int kPpMaxTiles = 1024;    // the same for the long-launch kernel, which has the LDS to spare
 constexpr int kPipeMaxTiles = 1024;  // and for the pipelined kernel (one work-group per CU)
-constexpr int kF32Rows = 4;          // fp32 kernel: rows per work-group (one per wave)
-constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile
+constexpr int kF32Rows = 32;         // fp32 kernel: rows per work-group (its waves split the keys)
+constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
+constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item (block ids kept in LDS)
+constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
 // ids): the low 27 bits are the block id; the bits above count the unused token positions at the
@@ -104,7 +106,7 @@ struct AttnArgs {
     float scale_log2;    // sm_scale * log2(e)
     int32_t layer;
     int32_t n_items;
-    int32_t n_append;    // append units run by the bf16 attention launch (total_S + B), 0 = none
+    int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };
 

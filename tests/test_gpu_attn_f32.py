@@ -1,0 +1,62 @@
+"""The fp32 attention kernel at the sizes where it can go wrong: units of 32 keys that end the prefix,
+straddle prefix and suffix or lie wholly in the suffix; row tiles of 32 that are ragged; ranges with fewer
+units than waves; causal ends inside a split; key ranges longer than the block-id table.  Against the
+fp64 checker on every row, the pool bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2601_08743_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# Sums of n products of O(1) terms in fp32: |error| <= n * 2^-24 * sum|terms| in the worst case; with weights that
+# sum to 1 and |v| < 5.5 the random-walk size is sqrt(n) * 2^-24 * 5.5 < 1e-5 up to n = 900 equal terms, and longer
+# rows average the values down (outputs ~ 1/sqrt(n)).
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def H():
+    import harness
+    return harness
+
+
+def _run(H, D, hq, hkv, lens, queries, suffix, splits):
+    cfg = W.WorkloadConfig("f", 2, hq, hkv, D, "f32", len(lens), (1, max(lens)), len(queries), (0, 9), "uniform", (1, 9),
+                           len(lens), 311)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = lens
+    wl.queries[:] = [np.array(q, dtype=np.int32) for q in queries]
+    wl.suffix_len[:] = suffix
+    dw = H.DeviceWorkload(wl)
+    for ns in splits:
+        dw.ctx.tc_set_kv_splits(ns)
+        bt, pl = dw.stitch()
+        out, qkv = dw.attn_layer(1, bt, pl)
+        got, ref = H.out_to_f64(out, cfg), H.oracle_attn_layer(wl, dw.tables_np, 1, qkv)
+        for i, r in ref.items():
+            sl = slice(int(wl.cu_seqlens[i]), int(wl.cu_seqlens[i + 1]))
+            err = float(np.abs(got[sl] - r).max()) if r.size else 0.0
+            assert err <= TOL, (ns, dw.ctx.tc_kv_splits(), i, err)
+            n = int(pl[i]) + int(wl.suffix_len[i])
+            k, v = dw.ctx.tc_read_seq_kv(1, bt[i, :-(-n // 16)], n, np.float32)
+            ks, vs = H.oracle_sequences(wl, dw.tables_np, 1, i)
+            np.testing.assert_array_equal(k, np.concatenate([ks, qkv[1][sl]]))
+            np.testing.assert_array_equal(v, np.concatenate([vs, qkv[2][sl]]))
+        dw.ctx.tc_release_seqs(bt)
+    dw.close()
+
+
+@pytest.mark.parametrize("D,hq,hkv", [(64, 8, 2), (64, 7, 1), (64, 3, 3), (128, 8, 2), (128, 5, 1)])
+def test_edges(H, D, hq, hkv):
+    """P: none, 1, one short of / exactly / one past a unit and a tile, several units per wave."""
+    lens = [1, 31, 32, 33, 63, 64, 65, 129, 300]
+    queries = [[], [0], [1], [2], [3], [4], [5], [6], [7], [8, 7, 5], [8, 8, 8, 2]]
+    suffix = [33, 1, 2, 32, 31, 65, 8, 64, 9, 130, 7]
+    _run(H, D, hq, hkv, lens, queries, suffix, (0, 1, 3, 7))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_range_longer_than_the_block_id_table(H, D):
+    """513 key tiles of prefix where a work item may have 512: cut in two although one range is asked for."""
+    _run(H, D, 2, 1, [32800, 40], [[0], [1]], [3, 17], (1, 0))
