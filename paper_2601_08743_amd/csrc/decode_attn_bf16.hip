@@ -1,18 +1,30 @@
 // Decode-step attention: one new token per query attends to everything its sequence already holds
 // in the pool (the tables' tokens, the prompt's own suffix, the tokens generated so far) and to
 // itself.  With one token, a KV head has only G rows (its group's query heads), so the work is
-// reading K and V once: HBM-bound.  The prefill kernels serve this case too, but spend a 128-row
-// tile and a chain of work-group barriers per key tile on it.
+// reading K and V once: HBM-bound, and for short sequences bound by the chain of round trips from
+// the launch to the first keys.
 //
-// Here the four waves of a work-group split the KEYS: wave w takes key tiles w, w+4, ... of the
-// item's range, streams each straight into its own 32 KB of LDS (no work-group barrier in the
-// loop: a wave waits only for its own loads), computes S^T = K . Q^T and O^T += V^T . P^T with the
-// matrix cores exactly as the prefill kernels do (rows beyond G repeat row G-1 and are dropped)
-// and keeps its own running maximum and sum.  At the end the four waves' (max, sum, O) are
-// combined through LDS and the work-group writes one partial per row; a second kernel combines
-// the key partitions of a query, adds the new token itself (its key and value come from k_new /
-// v_new: one dot product and one scaled row per head) and writes the output.  The new token's
-// K/V are appended to the pool by extra work-groups of the first launch, as in prefill.
+// A work-group is one (query, KV head, key range); its four waves split the KEYS: wave w takes the
+// 32-key units w, w + 4, ... of the range, streams each straight into its own LDS ring of two units
+// (32 KB), computes S^T = K . Q^T and O^T += V^T . P^T with the matrix cores exactly as the prefill
+// kernels do (columns beyond G repeat row G-1 and are dropped) and keeps its own running maximum and
+// sum.  No wave waits for another before the end: the range's block ids, the query rows and the keys
+// all arrive by LDS-direct loads that the wave counts itself, the ids of a wave's first two units come
+// with the work item, and so the first keys are requested one scalar fetch after the kernel starts.
+// Units of 32 keys rather than 64 halve both the shortest useful range (a sequence of 4 k tokens
+// makes 132 work-groups instead of 44) and what a wave loses when a range does not divide by four.
+//
+// At the end the four waves' (max, sum, O) are combined through LDS and the work-group writes one
+// partial per row; a second kernel combines the key partitions of a query, adds the new token itself
+// (its key and value come from k_new / v_new: one dot product and one scaled row per head) and
+// writes the output.  The new token's K/V are appended to the pool by the first key range of each
+// (query, KV head): extra work-groups for it, as in prefill, would each wait for a CU's LDS.
+//
+// Measured per launch (28 / 4 heads unless said): one sequence of 4.2 k tokens, 8.6 MB: 6.2 us, with 64-key
+// tiles, block ids behind a barrier and ranges of six tiles 8.8 us (an empty launch reads 4.0 us in the same
+// events); 13 sequences of 0.6 k, 40 / 8 heads: 12.5 against 17.7 us, of which the append work-groups that
+// waited for a CU were 4; 32 sequences, 142 MB: 31.4 against 32.6 us; four of 25 k, 32 / 8 heads, 412 MB:
+// 63.5 against 67.9 us = 6.5 TB/s.
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
@@ -21,60 +33,96 @@ namespace tc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+constexpr int kDecUnit = 32;                         // keys per unit: two pool blocks
 constexpr int kDecHeadBlk = 4096;                    // one head's K (or V) in one block: 16 * 128 * 2
-constexpr int kDecK = kAttnKeys * 256;               // K tile of a wave: 64 rows of 256 B, 16-byte chunks XOR-swizzled
-constexpr int kDecWave = kDecK + 4 * kDecHeadBlk;    // + V tile: 32 KB per wave
-constexpr int kDecBid = 4 * kDecWave + 256;          // block ids behind the four waves' tiles (+ alignment slack)
-constexpr int kDecLds = kDecBid + kAttnMaxTiles * 4 * 4;
+constexpr int kDecPart = 2 * kDecHeadBlk;            // K of a unit: 32 rows of 256 B, 16-byte chunks XOR-swizzled; V: two blocks verbatim
+constexpr int kDecSlot = 2 * kDecPart;
+constexpr int kDecWave = 2 * kDecSlot;               // two units in flight per wave
+constexpr int kDecQ = 4 * kDecWave;                  // query rows (32 of 256 B), the same bytes written by every wave
+constexpr int kDecIds = kDecQ + 32 * 256;            // block ids of the range, likewise
+constexpr int kDecLds = kDecIds + kAttnMaxTiles * (kAttnKeys / kBlockTokens) * 4 + 256;    // + alignment slack
+constexpr int kDecRow = 132;                         // padded row of the final exchange (floats)
 constexpr float kDecRescale = 8.f;
 
-__global__ __launch_bounds__(256, 2) void decode_attn_bf16_kernel(Geom g, BatchDev b, AttnArgs a)
+__global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    if ((int)blockIdx.x >= a.n_items) {                // extra work-groups: append the new tokens to the pool
-        append_unit<true, 1>(g, b, a.layer, (const char *)a.k_new, (const char *)a.v_new,
-                          blockIdx.x - a.n_items, threadIdx.x);
-        return;
-    }
-    const AttnItem it = a.items[blockIdx.x];
+    const AttnItem it = load_item(a, blockIdx.x);
     if (it.q < 0) return;
-    // the XOR addressing of the K tiles needs them 256-byte aligned
+    // the XOR addressing of the K rows needs them 256-byte aligned
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_raw;
-    const uint32_t pad = (256u - (lds_base & 255u)) & 255u;
-    char *lds = lds_raw + pad;
-    const uint32_t lds0 = lds_base + pad;
-    int32_t *s_bid = (int32_t *)(lds + kDecBid - 256);
+    const uint32_t slack = (256u - (lds_base & 255u)) & 255u;
+    char *lds = lds_raw + slack;
+    const uint32_t lds0 = lds_base + slack;
 
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = g.G, P = it.P;
-    const int n_tiles = it.tile_end - it.tile_begin;
-
-    // block ids of the item's key range -> LDS (past the prefix: the last block, masked below)
-    {
-        const int last_pblk = max(((P + kBlockTokens - 1) >> 4) - 1, 0);
-        const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks;
-        for (int idx = tid; idx < n_tiles * 4; idx += 256) s_bid[idx] = bt[min(it.tile_begin * 4 + idx, last_pblk)];
-    }
-    // Q^T fragments (B operand): lane (row r32, half hh) holds q[row][16*ks + 8*hh .. +8]
-    const int head = it.kvh * G + min(r32, G - 1);
-    bf16x8 qf[8];
-    {
-        const char *qp = (const char *)a.q + ((int64_t)it.cu * g.Hq + head) * 256 + hh * 16;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qp + ks * 32);
-    }
-    __syncthreads();                                    // block ids visible
+    const int u_begin = it.tile_begin * (kAttnKeys / kDecUnit);
+    const int n_units = min(it.tile_end * (kAttnKeys / kDecUnit), (P + kDecUnit - 1) / kDecUnit) - u_begin;
+    const int n_mine = n_units > w ? (n_units - w + 3) >> 2 : 0;        // this wave's units: u_begin + w + 4 k
 
     const char *pool_l = g.pool + (int64_t)a.layer * g.layer_stride + (int64_t)it.kvh * kDecHeadBlk;
     const int64_t bb = g.block_bytes;
     const uint32_t v_half = (uint32_t)(g.block_bytes >> 1);
     const uint32_t lds_w = lds0 + w * kDecWave;
+    const int32_t *ids = (const int32_t *)(lds + kDecIds);
+    const int last_id = ((P + kBlockTokens - 1) >> 4) - 1 - 2 * u_begin;     // the prefix's last block, counted from the range's first
     const float c = a.scale_log2;
     typedef const __attribute__((address_space(3))) bf16x8 *lds_frag;
-    const uint32_t kb = lds_w + r32 * 256 + ((hh ^ (r32 & 15)) << 4);
-    const uint32_t vb = lds_w + kDecK + r32 * 32 + hh * 16;
+
+    // a unit's two block-table entries: the first two units' come with the item
+    const int2 e_first = load_bids(a, blockIdx.x, 2 * w), e_second = load_bids(a, blockIdx.x, 2 * w + 8);
+    auto read_entries = [&](int k) {                    // of a later unit, from LDS (the same for the whole wave)
+        const int i = 2 * (w + 4 * k);
+        return make_int2(ids[i], ids[min(i + 1, last_id)]);
+    };
+    // K of a unit: two blocks as four 1 KB pieces of four rows each (chunk c of row r at chunk
+    // position c ^ r); V verbatim; 8 load instructions per operand
+    const int k_off0 = (lane >> 4) * 256;
+    auto issue_k = [&](int k, int2 e) {
+        const uint32_t dst = lds_w + (k & 1) * kDecSlot;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const char *src = pool_l + (int64_t)entry_bid(j ? e.y : e.x) * bb;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                load_to_lds(dst + j * 4096 + i * 1024, src, k_off0 + i * 1024 + (((lane & 15) ^ (4 * i + (lane >> 4))) * 16));
+        }
+    };
+    auto issue_v = [&](int k, int2 e) {
+        const uint32_t dst = lds_w + (k & 1) * kDecSlot + kDecPart;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const char *src = pool_l + (int64_t)entry_bid(j ? e.y : e.x) * bb + v_half;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) load_to_lds(dst + j * 4096 + i * 1024, src + i * 1024, lane * 16);
+        }
+    };
+
+    // The first range of a (query, KV head) also appends the new token's K and V of that head: the
+    // loads are issued here, ahead of the counted ones, the stores come at the very end (a store counts
+    // as an outstanding memory operation).  Behind the token the block is zero, as after every append.
+    // K: thread -> 16 bytes of one token row.  V^T: thread d -> the 16 tokens of row d, merged.
+    const bool appends = it.split == 0;
+    const int t_new = P & 15;
+    char *k_dst = nullptr, *v_dst = nullptr;
+    uint4 k_put = make_uint4(0, 0, 0, 0), v_old0 = k_put, v_old1 = k_put;
+    uint32_t v_put = 0;
+    if (appends) {
+        const int phys = it.append_bid;
+        k_dst = const_cast<char *>(pool_l) + (int64_t)phys * bb + tid * 16;
+        v_dst = k_dst + v_half + tid * 16;             // (32 bytes per row d = tid)
+        const char *k_src = (const char *)a.k_new + ((int64_t)it.cu * g.Hkv + it.kvh) * 256;
+        if ((tid >> 4) == t_new) k_put = *(const uint4 *)(k_src + (tid & 15) * 16);
+        if (tid < 128) {
+            v_put = *((const uint16_t *)((const char *)a.v_new + ((int64_t)it.cu * g.Hkv + it.kvh) * 256) + tid);
+            v_old0 = *(const uint4 *)v_dst;
+            v_old1 = *(const uint4 *)(v_dst + 16);
+        }
+    }
 
     f32x16 o[4];
 #pragma unroll
@@ -83,123 +131,121 @@ __global__ __launch_bounds__(256, 2) void decode_attn_bf16_kernel(Geom g, BatchD
         for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
     float m_run = -INFINITY, l_lane = 0.f;
 
-    // the four blocks of a tile: K as four 1 KB pieces of four rows each (chunk c of row r at
-    // chunk position c ^ r), V verbatim; 16 load instructions per operand
-    auto issue_k = [&](int t) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const char *src = pool_l + (int64_t)entry_bid(__builtin_amdgcn_readfirstlane(s_bid[t * 4 + j])) * bb;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int rb = 4 * i + (lane >> 4);
-                load_to_lds(lds_w + j * 4096 + i * 1024, src, rb * 256 + (((lane & 15) ^ rb) * 16));
+    if (n_mine > 0) {
+        if (n_mine > 2) {                               // the range's block ids, 256 per load (rows of the table are padded to 16 bytes)
+            const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks + 2 * u_begin;
+            const int last_chunk = ((b.max_blocks - 2 * u_begin) >> 2) - 1;
+            for (int i = 0; i < 2 * n_units; i += 256)
+                load_to_lds(lds0 + kDecIds + i * 4, (const char *)bt, min((i >> 2) + lane, last_chunk) * 16);
+        }
+        {                                               // the group's query rows, four per load, chunk c of row r at c ^ r
+            const char *qp = (const char *)a.q + ((int64_t)it.cu * g.Hq + it.kvh * G) * 256;
+            for (int i = 0; i < (G + 3) >> 2; ++i) {
+                const int r = 4 * i + (lane >> 4);
+                load_to_lds(lds0 + kDecQ + i * 1024, qp, min(r, G - 1) * 256 + (((lane & 15) ^ (r & 15)) * 16));
             }
         }
-    };
-    auto issue_v = [&](int t) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const char *src = pool_l + (int64_t)entry_bid(__builtin_amdgcn_readfirstlane(s_bid[t * 4 + j])) * bb + v_half;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) load_to_lds(lds_w + kDecK + j * 4096 + i * 1024, src + i * 1024, lane * 16);
+        issue_k(0, e_first);
+        issue_v(0, e_first);
+        if (n_mine > 1) {
+            issue_k(1, e_second);
+            issue_v(1, e_second);
+            wait_loads<32>();
+        } else {
+            wait_loads<16>();
         }
-    };
-    // Nobody but the wave reads its tile area, so the loop needs no barrier.  The loads run one
-    // operand ahead: K of the next tile is requested as soon as this tile's K fragments sit in
-    // registers, V likewise; loads complete in the order issued, so a wait that leaves the 16
-    // younger ones outstanding has everything older in LDS.
-    if (w < n_tiles) {
-        issue_k(w);
-        issue_v(w);
-    }
-    for (int t = w; t < n_tiles; t += 4) {
-        const bool more = t + 4 < n_tiles;
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");      // K(t) has landed; V(t) may still be on its way
-
-        // all operand fragments of a product are read from LDS before its matrix instructions start
-        // (read one by one, each instruction would wait for its own LDS round trip)
-        f32x16 sacc[2];
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) sacc[mb][e] = 0.f;
+        // Q^T fragments (B operand): lane (row r32, half hh) holds q[row][16*ks + 8*hh .. +8]
+        bf16x8 qf[8];
         {
-            bf16x8 kf[16];
+            const int r = min(r32, G - 1);
+            const uint32_t qb = lds0 + kDecQ + r * 256 + ((hh ^ (r & 15)) << 4);
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb) kf[2 * ks + mb] = *(lds_frag)(uintptr_t)((kb ^ (ks << 5)) + mb * 32 * 256);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // K area read out: free for the next tile
-            if (more) issue_k(t + 4);
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-                    sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[2 * ks + mb], qf[ks], sacc[mb], 0, 0, 0);
+            for (int ks = 0; ks < 8; ++ks) qf[ks] = *(lds_frag)(uintptr_t)(qb ^ (ks << 5));
         }
-        if (more) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");      // V(t) landed, K(t+4) outstanding
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        bf16x8 vf[16];                                 // V^T fragments: in registers before the softmax starts
+        const uint32_t kb = lds_w + r32 * 256 + ((hh ^ (r32 & 15)) << 4);
+        const uint32_t vb = lds_w + kDecPart + r32 * 32 + hh * 16;
+
+        // K(k), V(k), K(k+1), V(k+1) are in flight when unit k starts; its operands are read into
+        // registers and their place in the ring is requested again for unit k + 2.  Loads complete
+        // in the order issued, so a wait that leaves N younger ones outstanding has everything
+        // older in LDS.
+        // The entries of unit k + 3 are read from LDS while unit k is worked on.
+        int2 e_now = e_first, e_next = e_second, e_read = n_mine > 2 ? read_entries(2) : make_int2(0, 0);
+        for (int k = 0; k < n_mine; ++k) {
+            const int left = n_mine - 1 - k;
+            const int2 e_load = make_int2(__builtin_amdgcn_readfirstlane(e_read.x), __builtin_amdgcn_readfirstlane(e_read.y));
+            if (left >= 3) e_read = read_entries(k + 3);
+            const uint32_t slot = (uint32_t)(k & 1) * kDecSlot;
+            if (left >= 1) wait_loads<24>();
+            else wait_loads<8>();
+            bf16x8 kf[8];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
+            for (int ks = 0; ks < 8; ++ks) kf[ks] = *(lds_frag)(uintptr_t)((kb + slot) ^ (ks << 5));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // K area read out
+            if (left >= 2) issue_k(k + 2, e_load);
+            f32x16 s;
 #pragma unroll
-            for (int db = 0; db < 4; ++db) vf[4 * kk + db] = *(lds_frag)(uintptr_t)(vb + kk * kDecHeadBlk + db * 1024);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // V area read out
-        if (more) issue_v(t + 4);
-        const int key0 = (it.tile_begin + t) * kAttnKeys;
-        // positions that hold no key: beyond the end of the sequence, and the unused tail of a
-        // table block read in place (its count rides in the block-table entry)
-        const int4 e4 = *(const int4 *)&s_bid[t * 4];
-        const int pad4 = entry_pad(e4.x) | (entry_pad(e4.y) << 8) | (entry_pad(e4.z) << 16) | (entry_pad(e4.w) << 24);
-        if (pad4 != 0 || key0 + kAttnKeys > P) {
+            for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
+            if (left >= 2) wait_loads<24>();
+            else if (left == 1) wait_loads<16>();
+            else wait_loads<0>();
+            bf16x8 vf[8];                              // V^T fragments: in registers before the softmax starts
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int db = 0; db < 4; ++db) vf[4 * kk + db] = *(lds_frag)(uintptr_t)(vb + slot + kk * kDecHeadBlk + db * 1024);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // V area read out
+            if (left >= 2) issue_v(k + 2, e_load);
+            // positions that hold no key: beyond the end of the sequence, and the unused tail of a
+            // table block read in place (its count rides in the block-table entry)
+            const int key0 = (u_begin + w + 4 * k) * kDecUnit;
+            const int pad0 = entry_pad(e_now.x), pad1 = entry_pad(e_now.y);
+            if ((pad0 | pad1) != 0 || key0 + kDecUnit > P) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int in_blk = 8 * ((e >> 2) & 1) + 4 * hh + (e & 3);
-                    const int pad = (pad4 >> (8 * (2 * mb + (e >> 3)))) & 255;
-                    const int key = key0 + 32 * mb + 8 * (e >> 2) + 4 * hh + (e & 3);
-                    sacc[mb][e] = (key >= P || in_blk >= kBlockTokens - pad) ? -INFINITY : sacc[mb][e];
+                    const int key = key0 + 8 * (e >> 2) + 4 * hh + (e & 3);
+                    s[e] = (key >= P || in_blk >= kBlockTokens - (e < 8 ? pad0 : pad1)) ? -INFINITY : s[e];
                 }
-        }
-        float mx = sacc[0][0];
+            }
+            float mx = s[0];
 #pragma unroll
-        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sacc[0][e]);
+            for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mxs = mx * c;
+            if (__any(mxs > m_run + kDecRescale)) {    // also taken while m_run is still -inf
+                const float m_new = fmaxf(m_run, mxs);
+                const float alpha = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+                l_lane *= alpha;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[1][e]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float mxs = mx * c;
-        if (__any(mxs > m_run + kDecRescale)) {        // also taken while m_run is still -inf
-            const float m_new = fmaxf(m_run, mxs);
-            const float alpha = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-            l_lane *= alpha;
+                for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-            m_run = m_new;
-        }
-        const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+                    for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+                m_run = m_new;
+            }
+            const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(sacc[mb][e], c, neg_m));
-                sacc[mb][e] = p;
-                l_lane += p;
+                s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c, neg_m));
+                l_lane += s[e];
             }
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            bf16x8 pf;
+            for (int kk = 0; kk < 2; ++kk) {
+                bf16x8 pf;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pf[e] = (__bf16)sacc[kk >> 1][8 * (kk & 1) + e];
+                for (int e = 0; e < 8; ++e) pf[e] = (__bf16)s[8 * kk + e];
 #pragma unroll
-            for (int db = 0; db < 4; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * kk + db], pf, o[db], 0, 0, 0);
+                for (int db = 0; db < 4; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * kk + db], pf, o[db], 0, 0, 0);
+            }
+            e_now = e_next;
+            e_next = e_load;
         }
     }
 
-    // ---- combine the four waves: each writes (max, sum) per row and O as [row][d] floats into its
-    // own tile area (dead now), then every thread folds the four for a few (row, d)
+    // ---- combine the four waves: each writes (max, sum) per row and O as padded rows of floats into
+    // its own ring (dead now), then every thread folds the four for a few (row, 4 columns)
     {
         float *wo = (float *)(lds + w * kDecWave);
         const float l_row = l_lane + __shfl_xor(l_lane, 32);
@@ -207,100 +253,142 @@ __global__ __launch_bounds__(256, 2) void decode_attn_bf16_kernel(Geom g, BatchD
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) wo[r32 * 128 + 32 * db + 8 * (e >> 2) + 4 * hh + (e & 3)] = o[db][e];
-            if (hh == 0) { wo[32 * 128 + 2 * r32] = m_run; wo[32 * 128 + 2 * r32 + 1] = l_row; }
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = o[db][4 * q + e];
+                    *(f32x4 *)(wo + r32 * kDecRow + 32 * db + 8 * q + 4 * hh) = v;
+                }
+            if (hh == 0) { wo[32 * kDecRow + 2 * r32] = m_run; wo[32 * kDecRow + 2 * r32 + 1] = l_row; }
         }
     }
     __syncthreads();
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
-    for (int idx = tid; idx < G * 128; idx += 256) {
-        const int row = idx >> 7, d = idx & 127;
+    for (int idx = tid; idx < G * 32; idx += 256) {
+        const int row = idx >> 5, d = 4 * (idx & 31);
         float M = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * kDecWave))[32 * 128 + 2 * row]);
-        float L = 0.f, acc = 0.f;
+        for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * kDecWave))[32 * kDecRow + 2 * row]);
+        float L = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float *wk = (const float *)(lds + k * kDecWave);
-            const float mk = wk[32 * 128 + 2 * row];
+            const float mk = wk[32 * kDecRow + 2 * row];
             const float wgt = (mk == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mk - M);
-            L += wgt * wk[32 * 128 + 2 * row + 1];
-            acc += wgt * wk[row * 128 + d];
+            L += wgt * wk[32 * kDecRow + 2 * row + 1];
+            const f32x4 v = *(const f32x4 *)(wk + row * kDecRow + d);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
         }
         const int64_t slot = (int64_t)it.split * n_rows + (int64_t)it.cu * g.Hq + it.kvh * G + row;
-        a.part_o[slot * 128 + d] = acc;
-        if (d == 0) { a.part_ml[slot * 2] = M; a.part_ml[slot * 2 + 1] = L; }
+        *(f32x4 *)(a.part_o + slot * 128 + d) = acc;
+        if (d == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(M, L);
+    }
+    if (appends) {
+        if ((tid >> 4) >= t_new) *(uint4 *)k_dst = k_put;
+        if (tid < 128) {
+            const uint32_t old[8] = {v_old0.x, v_old0.y, v_old0.z, v_old0.w, v_old1.x, v_old1.y, v_old1.z, v_old1.w};
+            uint32_t out[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {              // positions 2p and 2p + 1 hold tokens vperm(2p), vperm(2p + 1)
+                const int ta = vperm(2 * p), tb = vperm(2 * p + 1);
+                const uint32_t ea = ta < t_new ? old[p] & 0xffffu : ta == t_new ? v_put : 0u;
+                const uint32_t eb = tb < t_new ? old[p] >> 16 : tb == t_new ? v_put : 0u;
+                out[p] = ea | (eb << 16);
+            }
+            *(uint4 *)v_dst = make_uint4(out[0], out[1], out[2], out[3]);
+            *(uint4 *)(v_dst + 16) = make_uint4(out[4], out[5], out[6], out[7]);
+        }
     }
 }
 
-// One work-group of 128 threads per output row (token, head): combine the key partitions, add the
-// new token itself, normalise, write bf16.
-__global__ __launch_bounds__(128) void decode_finish_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
+// Combine the key partitions of an output row (token, head), add the new token itself, normalise, write
+// bf16.  Bound by the latency of its loads, so all of them are issued before the first use: kGroups
+// groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
+// row of up to 4 * kGroups partitions costs one round trip - and fold their results through LDS.  A
+// work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
+// threads would load what nobody needs.  (Slots of partitions that the query, but not the batch, lacks
+// exist in the buffer; they are loaded and ignored.)
+template <int kGroups>
+__global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
-    __shared__ float red[2];
-    const int row = blockIdx.x, d = threadIdx.x;
-    const int n = row / g.Hq, head = row - n * g.Hq, kvh = head / g.G;      // n: the token (queries may bring none)
+    constexpr int kBatch = 4, kRows = 8 / kGroups;
+    __shared__ float s_acc[8][132], s_ml[8][2];
+    const int tid = threadIdx.x, slot8 = tid >> 5, grp = slot8 % kGroups, d = 4 * (tid & 31);
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
-    // Every load of the kernel is issued before the first use, so that the row costs one round
-    // trip to memory: the query's partition count, the new token, and the first eight partitions'
-    // partials (slots of partitions the query does not have exist in the buffer; they are loaded
-    // and ignored).
-    const int ns = b.splits_of_q[b.tok_q[n]];
-    const unsigned short *q16 = (const unsigned short *)a.q + (int64_t)row * 128;
-    const unsigned short *k16 = (const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128;
-    const unsigned short *v16 = (const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128;
-    const float qd = __uint_as_float((unsigned)q16[d] << 16), kd = __uint_as_float((unsigned)k16[d] << 16);
-    const float vd = __uint_as_float((unsigned)v16[d] << 16);
-    float2 ml[8];
-    float po[8];
+    const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
+    const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
+    const int n = row / g.Hq, head = row - n * g.Hq, kvh = head / g.G;      // n: the token (queries may bring none)
+    float2 ml[kBatch];
+    f32x4 po[kBatch];
     auto fetch = [&](int s0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t slot = (int64_t)min(s0 + j, max_splits - 1) * n_rows + row;
+        for (int j = 0; j < kBatch; ++j) {
+            if (kGroups * j >= max_splits) break;
+            const int64_t slot = (int64_t)min(s0 + kGroups * j, max_splits - 1) * n_rows + row;
             ml[j] = *(const float2 *)(a.part_ml + slot * 2);
-            po[j] = a.part_o[slot * 128 + d];
+            po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
         }
     };
-    fetch(0);
-    // score of the new token against itself
-    float prod = qd * kd;
+    fetch(grp);
+    const uint2 q2 = *(const uint2 *)((const unsigned short *)a.q + (int64_t)row * 128 + d);
+    const uint2 k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
+    const uint2 v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
+    const int ns = b.splits_of_q[b.tok_q[n]];
+    float M = -INFINITY, L = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto fold = [&](float m, float l, f32x4 o) {
+        if (m == -INFINITY) return;
+        const float Mn = fmaxf(M, m);
+        const float r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn), wgt = __builtin_amdgcn_exp2f(m - Mn);
+        L = L * r + l * wgt;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) prod += __shfl_xor(prod, off);
-    if ((d & 63) == 0) red[d >> 6] = prod;
-    __syncthreads();
-    // running merge, started with the new token alone (weight 1 at its own score)
-    float M = (red[0] + red[1]) * a.scale_log2, L = 1.f, acc = vd;
-    for (int s0 = 0; s0 < ns; s0 += 8) {
-        if (s0 > 0) fetch(s0);
-        float Mc = M;
+        for (int e = 0; e < 4; ++e) acc[e] = acc[e] * r + o[e] * wgt;
+        M = Mn;
+    };
+    for (int s0 = grp; s0 < ns; s0 += kGroups * kBatch) {
+        if (s0 > grp) fetch(s0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) Mc = (s0 + j < ns) ? fmaxf(Mc, ml[j].x) : Mc;
-        const float r = __builtin_amdgcn_exp2f(M - Mc);
-        L *= r;
-        acc *= r;
-        M = Mc;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const bool live = s0 + j < ns && ml[j].x != -INFINITY;
-            const float wgt = __builtin_amdgcn_exp2f(ml[j].x - M);
-            L += live ? wgt * ml[j].y : 0.f;
-            acc += live ? wgt * po[j] : 0.f;
-        }
+        for (int j = 0; j < kBatch; ++j)
+            if (s0 + kGroups * j < ns) fold(ml[j].x, ml[j].y, po[j]);
     }
-    const __bf16 r = (__bf16)(acc / L);
-    ((unsigned short *)a.out)[(int64_t)row * 128 + d] = *(const unsigned short *)&r;
+    if (kGroups > 1) {
+        *(f32x4 *)&s_acc[slot8][d] = acc;
+        if (d == 0) { s_ml[slot8][0] = M; s_ml[slot8][1] = L; }
+        __syncthreads();
+    }
+    if (grp > 0 || want >= n_rows) return;
+    // the row's first group goes on: score of the new token against itself, then the other groups' results
+    auto lo = [](uint32_t x) { return __uint_as_float(x << 16); };
+    auto hi = [](uint32_t x) { return __uint_as_float(x & 0xffff0000u); };
+    float prod = lo(q2.x) * lo(k2.x) + hi(q2.x) * hi(k2.x) + lo(q2.y) * lo(k2.y) + hi(q2.y) * hi(k2.y);
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) prod += __shfl_xor(prod, off, 32);
+    fold(prod * a.scale_log2, 1.f, f32x4{lo(v2.x), hi(v2.x), lo(v2.y), hi(v2.y)});
+#pragma unroll
+    for (int k = 1; k < kGroups; ++k) fold(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
+    const float inv = 1.f / L;
+    unsigned short r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const __bf16 x = (__bf16)(acc[e] * inv);
+        r[e] = *(const unsigned short *)&x;
+    }
+    *(uint2 *)((unsigned short *)a.out + (int64_t)row * 128 + d) =
+        make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
 }
 
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
-    if (a.n_items + a.n_append == 0) return hipSuccess;
+    if (a.n_items == 0) return hipSuccess;
     if (g.D != 128 || g.esize != 2 || g.G > 32) return hipErrorInvalidValue;
     static PerDeviceOnce configured;
     const hipError_t e = configured.run([] {
         return hipFuncSetAttribute((const void *)decode_attn_bf16_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDecLds);
     });
     if (e != hipSuccess) return e;
-    TC_LAUNCH(decode_attn_bf16_kernel, a.n_items + a.n_append, kDecLds, L, g, b, a);
+    TC_LAUNCH(decode_attn_bf16_kernel, a.n_items, kDecLds, L, g, b, a);
     return hipGetLastError();
 }
 
@@ -309,7 +397,10 @@ hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs
     const int n_rows = b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
     if (max_splits < 1) return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(decode_finish_kernel, dim3(n_rows), dim3(128), 0, L.stream, L.start, L.stop, 0, g, b, a, max_splits);
+    if (max_splits <= 4) TC_LAUNCH(decode_finish_kernel<1>, (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH(decode_finish_kernel<2>, (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH(decode_finish_kernel<4>, (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH(decode_finish_kernel<8>, n_rows, 0, L, g, b, a, max_splits);
     return hipGetLastError();
 }
 

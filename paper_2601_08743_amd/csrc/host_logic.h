@@ -240,7 +240,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // the four waves of a work-group and over `ns` work-groups.  A work-group holds a CU (its ring of
     // tiles fills the LDS), and what a launch of this kind costs is how its loads get going and
     // drain, once per round of work-groups: so the ranges are cut for ONE round of equally long
-    // work-groups - the smallest range length L (in key tiles, at least six) for which
+    // work-groups - the smallest range length L (in key tiles, at least two: a unit for each wave) for which
     // sum over (query, KV head) of ceil(tiles / L) fits the 256 CUs; a long sequence is cut into
     // more ranges than a short one.  Batches that do not fit one round even at the longest range a
     // work item may have run in several, longest items first.  Unused block tails of sequences that
@@ -248,7 +248,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     if (bf16 && G <= 32 && p.total_S > 0 && ctx->forced_row_blocks == 0 &&
         (ctx->forced_attn_kernel == 0 || ctx->forced_attn_kernel == 3) &&
         std::all_of(p.suffix_len.begin(), p.suffix_len.end(), [](int32_t s) { return s <= 1; })) {
-        constexpr int kCus = 256, kMinRange = 6;
+        constexpr int kCus = 256, kMinRange = 2;
         auto tiles_of_q = [&](int i) { return (p.prefix_len[i] + KT - 1) / KT; };
         auto items_at = [&](int L) {
             int64_t n = 0;
@@ -280,13 +280,18 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             splits_of_q[i] = ns;
             p.max_splits = std::max(p.max_splits, ns);
             const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
+            const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
             for (int h = 0; h < c.n_kv_heads; ++h)
                 for (int s = 0; s < ns; ++s) {
                     AttnItem it{};
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
                     it.split = s; it.n_splits = ns; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
-                    for (int k = 0; k < 16; ++k) it.bid[k] = bt[0];
+                    it.append_bid = bt[P / kBlockTokens];
+                    for (int k = 0; k < 16; ++k) {          // entries of the range's first units, clamped to the prefix
+                        const int idx = std::min(it.tile_begin * (KT / kBlockTokens) + k, std::max((P + kBlockTokens - 1) / kBlockTokens - 1, 0));
+                        it.bid[k] = bt[idx] | (pad_of ? (int32_t)((uint32_t)pad_of[idx] << kPadShift) : 0);
+                    }
                     items.push_back(it);
                 }
         }

@@ -34,7 +34,7 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds_dst, const char *base, 
                  : "s"(__builtin_amdgcn_readfirstlane(lds_dst)), "v"(voff), "s"(sb) : "memory");
 }
 
-// The same with an address of its own per lane (for rows that come from different buffers).
+// 16 bytes per lane, each from an address of its own (for rows that come from different buffers).
 __device__ __forceinline__ void load_to_lds_each(uint32_t lds_dst, const char *src)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"

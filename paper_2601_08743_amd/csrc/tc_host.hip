@@ -239,7 +239,9 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     const size_t B = p.B, nseg = segs.size();
     size_t off = 0;
     auto take = [&](size_t n) { size_t o = off; off += align8(n); return o; };
-    const size_t o_bt = take(B * p.max_blocks), o_cu = take(B + 1), o_pl = take(B), o_sl = take(B);
+    // rows of the device's block table are padded to whole 16-byte chunks (the decode kernel fetches them so)
+    const size_t bt_row = (size_t)(p.max_blocks + 3) & ~size_t(3);
+    const size_t o_bt = take(B * bt_row), o_cu = take(B + 1), o_pl = take(B), o_sl = take(B);
     const size_t o_ss = take(nseg), o_sn = take(nseg), o_st = take(nseg), o_se = take(B);
     const size_t o_sb = take(sblk.size() * 4), o_sp = take(B), o_tq = take(p.total_S);
     const size_t o_it = take(items.size() * (sizeof(AttnItem) / 4));
@@ -261,9 +263,10 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     int32_t *h = ctx->h_stage;
     std::memset(h, 0, total * sizeof(int32_t));
     if (B) {
-        std::memcpy(h + o_bt, p.block_table.data(), B * p.max_blocks * 4);
+        for (size_t i = 0; i < B; ++i)
+            std::memcpy(h + o_bt + i * bt_row, p.block_table.data() + i * p.max_blocks, (size_t)p.max_blocks * 4);
         for (size_t k = 0; k < p.block_pad.size(); ++k)
-            if (p.block_pad[k]) h[o_bt + k] |= (int32_t)((uint32_t)p.block_pad[k] << kPadShift);
+            if (p.block_pad[k]) h[o_bt + k / p.max_blocks * bt_row + k % p.max_blocks] |= (int32_t)((uint32_t)p.block_pad[k] << kPadShift);
         std::memcpy(h + o_cu, p.cu_seqlens.data(), (B + 1) * 4);
         std::memcpy(h + o_pl, p.prefix_len.data(), B * 4);
         std::memcpy(h + o_sl, p.suffix_len.data(), B * 4);
@@ -296,7 +299,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.dev.tok_q = d + o_tq;
     p.dev.rope_pos0 = p.rope ? d + o_rp : nullptr;
     p.dev.rope_rev_freq = p.rope ? (const double *)(d + o_rf) : nullptr;
-    p.dev.B = p.B; p.dev.max_blocks = p.max_blocks; p.dev.total_S = p.total_S;
+    p.dev.B = p.B; p.dev.max_blocks = (int32_t)bt_row; p.dev.total_S = p.total_S;
     p.dev.n_stitch_blk = (int32_t)sblk.size();
     p.n_stitch_blk = (int32_t)sblk.size();
     p.items_dev = (const AttnItem *)(d + o_it);
@@ -919,7 +922,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     if (p.decode) {
         AttnArgs a{};
         a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
-        a.n_append = append_units(p.total_S, p.B, 1); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
+        a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
         a.part_ml = p.part + (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * ctx->cfg.head_dim;

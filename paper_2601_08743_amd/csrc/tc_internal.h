@@ -32,6 +32,15 @@ __device__ __forceinline__ AttnItem load_item(const AttnArgs &a, unsigned k)
     return u.item;
 }
 
+// Two neighbouring block-table entries of item `k`, from bid[j] (j even, the same for the whole wave) on.
+__device__ __forceinline__ int2 load_bids(const AttnArgs &a, unsigned k, int j)
+{
+    typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(4))) i32x2 *const_pair;
+    const i32x2 v = *(const_pair)(uintptr_t)(&a.items[k].bid[j]);
+    return make_int2(v.x, v.y);
+}
+
 // A kernel's dynamic-LDS limit (hipFuncSetAttribute) is a property of the kernel on one device: each
 // launcher keeps one of these per kernel and raises the limit the first time it launches on a device.
 // (Two threads that race on a device's first launch both set the same value.)

@@ -54,7 +54,7 @@ struct StitchBlk {
 
 // Device-side view of the current batch (all arrays int32, one upload per batch).
 struct BatchDev {
-    const int32_t *block_table;   // [B][max_blocks]
+    const int32_t *block_table;   // [B][max_blocks], max_blocks here a multiple of 4
     const int32_t *cu_seqlens;    // [B+1]
     const int32_t *prefix_len;    // [B]
     const int32_t *suffix_len;    // [B]
@@ -86,7 +86,8 @@ struct AttnItem {
     int32_t n_groups;    // total number of groups in the batch
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
-    int32_t rsv[3];
+    int32_t append_bid;  // decode step: the block that takes the new token
+    int32_t rsv[2];
 };
 static_assert(sizeof(AttnItem) == 128, "AttnItem layout");
 
