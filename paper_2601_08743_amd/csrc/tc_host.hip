@@ -82,9 +82,11 @@ struct tc_ctx {
     hipStream_t raw_stream = nullptr;      // on this stream
     bool raw_pending = false;
     Plan plan;
-    int32_t *h_stage = nullptr; size_t h_stage_ints = 0;
+    int32_t *h_stage = nullptr; size_t h_stage_ints = 0;    // pinned; plans that fit half of it take the halves in turn
     int32_t *d_plan = nullptr; size_t d_plan_ints = 0;
-    hipEvent_t stage_ev = nullptr; bool stage_pending = false;
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};            // the last upload out of each half
+    bool stage_pending[2] = {false, false};
+    int stage_next = 0;
     float *d_part = nullptr; size_t d_part_floats = 0;
     int device = 0;                        // the device the context was created on
     char *scratch_dev = nullptr;           // that device's copy of the static workspace (tc_prefill_attn_noalloc)
@@ -192,26 +194,30 @@ int esize_of(const tc_config &c) { return c.dtype == TC_F32 ? 4 : 2; }
 // Make room for a plan of `ints` integers: the pinned staging buffer on the host and, unless the
 // plan goes to the static workspace (`fixed`), the device buffer.  The staging buffer is created
 // by tc_create with the static workspace's plan capacity, so a fixed plan never allocates.
-tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed)
+// `at`: where in the staging buffer the plan goes; `half`: whose event its upload records.  With two
+// halves the host does not wait for the previous batch's upload, only for the one before it.
+tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, int *half)
 {
-    if (ctx->stage_pending) {                       // the previous upload still reads the staging buffer
-        TC_HIP(ctx, hipEventSynchronize(ctx->stage_ev));
-        ctx->stage_pending = false;
-    }
-    if (fixed) {
-        if (ints > kScratchPlanInts || ints > ctx->h_stage_ints)
-            return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the batch's plan needs %zu integers, the fixed workspace holds %zu",
-                        ints, std::min(kScratchPlanInts, ctx->h_stage_ints));
-        return TC_OK;
-    }
-    if (ints > ctx->h_stage_ints) {
+    if (fixed && (ints > kScratchPlanInts || ints > ctx->h_stage_ints))
+        return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the batch's plan needs %zu integers, the fixed workspace holds %zu",
+                    ints, std::min(kScratchPlanInts, ctx->h_stage_ints));
+    const bool halves = 2 * ints <= ctx->h_stage_ints;
+    *half = halves ? ctx->stage_next : 0;
+    for (int k = 0; k < 2; ++k)
+        if (ctx->stage_pending[k] && (!halves || k == *half)) {      // an earlier upload still reads that part
+            TC_HIP(ctx, hipEventSynchronize(ctx->stage_ev[k]));
+            ctx->stage_pending[k] = false;
+        }
+    if (!fixed && ints > ctx->h_stage_ints) {
         if (ctx->h_stage) TC_HIP(ctx, hipHostFree(ctx->h_stage));
         ctx->h_stage = nullptr; ctx->h_stage_ints = 0;
         const size_t cap = std::max(ints * 2, size_t(1) << 16);
         TC_HIP(ctx, hipHostMalloc((void **)&ctx->h_stage, cap * sizeof(int32_t), hipHostMallocDefault));
         ctx->h_stage_ints = cap;
     }
-    if (ints > ctx->d_plan_ints) {
+    *at = ctx->h_stage + (halves ? *half * ((ctx->h_stage_ints / 2) & ~size_t(63)) : 0);
+    ctx->stage_next = 1 - *half;
+    if (!fixed && ints > ctx->d_plan_ints) {
         if (ctx->d_plan) TC_HIP(ctx, hipFree(ctx->d_plan));   // hipFree waits for work that may use it
         ctx->d_plan = nullptr; ctx->d_plan_ints = 0;
         const size_t cap = std::max(ints * 2, size_t(1) << 16);
@@ -247,7 +253,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     const size_t o_it = take(items.size() * (sizeof(AttnItem) / 4));
     const size_t o_gr = take(groups.size() * (sizeof(MergeGroup) / 4));
     const size_t o_rp = take(p.rope ? B : 0), o_rf = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
-    const size_t total = std::max(off, size_t(8));
+    const size_t total = std::max(off, size_t(8));          // (a multiple of 8: the upload moves 16 bytes at a time)
     // split-KV partials.  bf16 kernels: per (partition, group, row block) 128 rows x (128 fp16 + 2
     // floats) in fragment order, counted in floats; fp32 and decode kernels: per (partition, new
     // token, head) D + 2 floats
@@ -258,9 +264,10 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     if (fixed && part_need > kScratchPartFloats)
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the split-KV partials need %zu floats, the fixed workspace holds %zu",
                     part_need, kScratchPartFloats);
-    tc_status st = ensure_stage(ctx, total, fixed);
+    int32_t *h = nullptr;
+    int half = 0;
+    tc_status st = ensure_stage(ctx, total, fixed, &h, &half);
     if (st != TC_OK) return st;
-    int32_t *h = ctx->h_stage;
     std::memset(h, 0, total * sizeof(int32_t));
     if (B) {
         for (size_t i = 0; i < B; ++i)
@@ -287,9 +294,9 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
 
     int32_t *d_dst = fixed ? (int32_t *)ctx->scratch_dev : ctx->d_plan;
-    TC_HIP(ctx, hipMemcpyAsync(d_dst, h, total * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-    TC_HIP(ctx, hipEventRecord(ctx->stage_ev, stream));
-    ctx->stage_pending = true;
+    TC_HIP(ctx, launch_upload(d_dst, h, total, Launch{stream, nullptr, nullptr}));
+    TC_HIP(ctx, hipEventRecord(ctx->stage_ev[half], stream));
+    ctx->stage_pending[half] = true;
 
     const int32_t *d = d_dst;
     p.dev.block_table = d + o_bt; p.dev.cu_seqlens = d + o_cu; p.dev.prefix_len = d + o_pl;
@@ -418,7 +425,8 @@ tc_status tc_create(const tc_config *cfg, void *kv_pool_dev, size_t pool_bytes, 
     ctx->read_gen.assign(64, 0);
     for (auto &e : ctx->read_ring)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return TC_ERR_HIP;
-    if (hipEventCreateWithFlags(&ctx->stage_ev, hipEventDisableTiming) != hipSuccess) return TC_ERR_HIP;
+    for (auto &e : ctx->stage_ev)
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return TC_ERR_HIP;
     if (hipEventCreateWithFlags(&ctx->raw_ev, hipEventDisableTiming) != hipSuccess) return TC_ERR_HIP;
     ctx->seq.reset(ctx->first_seq, cfg->n_pool_blocks);
     *out = ctx.release();
@@ -431,7 +439,7 @@ tc_status tc_destroy(tc_ctx *ctx)
     (void)hipDeviceSynchronize();
     for (auto &s : ctx->slots) if (s.ready) (void)hipEventDestroy(s.ready);
     for (auto &e : ctx->read_ring) if (e) (void)hipEventDestroy(e);
-    if (ctx->stage_ev) (void)hipEventDestroy(ctx->stage_ev);
+    for (auto &e : ctx->stage_ev) if (e) (void)hipEventDestroy(e);
     if (ctx->raw_ev) (void)hipEventDestroy(ctx->raw_ev);
     if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     if (ctx->d_plan) (void)hipFree(ctx->d_plan);
