@@ -30,6 +30,7 @@ struct Table {
     const char *host_k = nullptr, *host_v = nullptr;
     int32_t slot = -1;
     std::vector<uint8_t> layer_loaded;
+    int32_t n_loaded = 0;                  // how many of them are
 };
 
 struct Slot {
@@ -515,6 +516,7 @@ tc_status tc_load_async(tc_ctx *ctx, const int32_t *table_ids, int32_t n, int32_
                 ctx->slots[v.slot].table = -1;
                 v.slot = -1;
                 std::fill(v.layer_loaded.begin(), v.layer_loaded.end(), 0);
+                v.n_loaded = 0;
             }
             t.slot = *ctx->free_slots.begin();
             ctx->free_slots.erase(ctx->free_slots.begin());
@@ -562,6 +564,7 @@ tc_status tc_load_async(tc_ctx *ctx, const int32_t *table_ids, int32_t n, int32_
                 ctx->raw_pending = true;
             }
             for (int x = l; x < e; ++x) t.layer_loaded[x] = 1;
+            t.n_loaded += e - l;
             l = e;
         }
     }
@@ -651,9 +654,7 @@ static tc_status stitch_common(tc_ctx *ctx, const int32_t *table_ids, const int3
             auto it = ctx->tables.find(table_ids[k]);
             if (it == ctx->tables.end()) return fail(ctx, TC_ERR_UNKNOWN_TABLE, "stitch: table %d not registered", table_ids[k]);
             const Table &t = it->second;
-            bool all = t.slot >= 0;
-            for (int l = 0; all && l < L; ++l) all = t.layer_loaded[l] != 0;
-            if (!all) return fail(ctx, TC_ERR_NOT_RESIDENT, "stitch: table %d is not device-resident", table_ids[k]);
+            if (t.slot < 0 || t.n_loaded != L) return fail(ctx, TC_ERR_NOT_RESIDENT, "stitch: table %d is not device-resident", table_ids[k]);
             segs.push_back(SegInfo{(int32_t)p, t.n_tokens, t.slot});
             p += t.n_tokens;
             if (p + suffix_len[i] > INT32_MAX / 2) return fail(ctx, TC_ERR_INVALID, "stitch: sequence too long");
@@ -758,7 +759,7 @@ static int32_t slot_block_pad(const tc_ctx *ctx, int32_t b)
     auto it = ctx->tables.find(ctx->slots[s].table);
     if (it == ctx->tables.end()) return -1;
     const Table &t = it->second;
-    for (uint8_t l : t.layer_loaded) if (!l) return -1;
+    if (t.n_loaded != ctx->cfg.n_layers) return -1;
     const int nb = (t.n_tokens + kBlockTokens - 1) / kBlockTokens;
     if (j >= nb) return -1;
     return j == nb - 1 ? nb * kBlockTokens - t.n_tokens : 0;
@@ -790,9 +791,7 @@ tc_status tc_stitch_alias(tc_ctx *ctx, const int32_t *table_ids, const int32_t *
             auto it = ctx->tables.find(table_ids[k]);
             if (it == ctx->tables.end()) return fail(ctx, TC_ERR_UNKNOWN_TABLE, "alias: table %d not registered", table_ids[k]);
             const Table &t = it->second;
-            bool all = t.slot >= 0;
-            for (int l = 0; all && l < L; ++l) all = t.layer_loaded[l] != 0;
-            if (!all) return fail(ctx, TC_ERR_NOT_RESIDENT, "alias: table %d is not device-resident", table_ids[k]);
+            if (t.slot < 0 || t.n_loaded != L) return fail(ctx, TC_ERR_NOT_RESIDENT, "alias: table %d is not device-resident", table_ids[k]);
             nb += (t.n_tokens + kBlockTokens - 1) / kBlockTokens;
             if (nb * kBlockTokens + suffix_len[i] > INT32_MAX / 2) return fail(ctx, TC_ERR_INVALID, "alias: sequence too long");
         }
@@ -1025,17 +1024,24 @@ tc_status tc_release_seqs(tc_ctx *ctx, const int32_t *block_table, int32_t max_b
     if (!ctx) return TC_ERR_INVALID;
     if (B < 0 || max_blocks < 0 || ((int64_t)B * max_blocks > 0 && !block_table))
         return fail(ctx, TC_ERR_INVALID, "release: bad arguments");
+    // Given back one by one; an entry that is not allocated (never was, or named twice) takes the ones before it back.
     const size_t n = (size_t)B * max_blocks;
-    std::set<int32_t> seen;
+    size_t given = 0;
+    auto counts = [&](int32_t b) {      // a table slot's block that a sequence aliases is not the sequence's to give
+        return b >= 0 && !(ctx->cfg.slot_layout == TC_SLOTS_BLOCKS && b < ctx->first_seq);
+    };
     for (size_t k = 0; k < n; ++k) {
         const int32_t b = block_table[k];
-        if (b < 0) continue;
-        if (ctx->cfg.slot_layout == TC_SLOTS_BLOCKS && b < ctx->first_seq) continue;   // a table slot's block, aliased
-        if (!ctx->seq.allocated(b) || !seen.insert(b).second)
+        if (!counts(b)) continue;
+        if (!ctx->seq.allocated(b)) {
+            for (size_t j = 0; j < k; ++j)
+                if (counts(block_table[j])) ctx->seq.take(block_table[j]);
             return fail(ctx, TC_ERR_INVALID, "release: %d is not an allocated sequence block", b);
+        }
+        ctx->seq.release(b);
+        ++given;
     }
-    for (int32_t b : seen) ctx->seq.release(b);
-    if (ctx->plan.valid && (!seen.empty() || !ctx->plan.alias_slots.empty()))
+    if (ctx->plan.valid && (given > 0 || !ctx->plan.alias_slots.empty()))
         ctx->plan.valid = false;               // its blocks may be handed out again
     return TC_OK;
 }
