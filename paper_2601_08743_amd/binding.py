@@ -1,4 +1,5 @@
-"""ctypes binding over libtablecache.so: argument marshalling only.
+"""ctypes binding over libtablecache.so: argument marshalling only (that of the calls made once per layer
+by a small native module, ``csrc/py_call.cpp``).
 
 Every function here has the name of the C entry point it calls (see
 include/tablecache.h for the semantics).  Device tensors are passed as torch
@@ -27,6 +28,10 @@ if not os.path.exists(LIB_PATH):
         "(or __graft_entry__.build()); there is no CPU fallback." % LIB_PATH)
 
 _lib = ctypes.CDLL(LIB_PATH)
+try:
+    from . import _py_call
+except ImportError as e:
+    raise ImportError("_py_call.so is not built (%s). Run `python -m paper_2601_08743_amd.build`." % e) from e
 
 TC_OK = 0
 TC_ERR_INVALID, TC_ERR_UNKNOWN_TABLE, TC_ERR_OOM_POOL = -1, -2, -3
@@ -97,6 +102,10 @@ for _n, (_r, _a) in _sig.items():
     getattr(_lib, _n).argtypes = _a
 
 
+_PREFILL = ctypes.cast(_lib.tc_prefill_attn, ctypes.c_void_p).value
+_PREFILL_NOALLOC = ctypes.cast(_lib.tc_prefill_attn_noalloc, ctypes.c_void_p).value
+
+
 class TcError(RuntimeError):
     def __init__(self, code: int, msg: str):
         super().__init__("tc error %d: %s" % (code, msg))
@@ -116,6 +125,9 @@ def _ptr(x) -> Optional[int]:
 
 def _i32arr(x) -> np.ndarray:
     return np.ascontiguousarray(x, dtype=np.int32)
+
+
+_py_call.set_converter(_i32arr)
 
 
 def _stream(s) -> Optional[int]:
@@ -159,6 +171,7 @@ class Context:
         if rc != TC_OK:
             raise TcError(rc, "tc_create failed")
         self._h = h
+        self._addr = h.value
         self._keep = []                           # registered host KV
 
     def _check(self, rc: int):
@@ -168,7 +181,7 @@ class Context:
     def tc_destroy(self):
         if self._h:
             _lib.tc_destroy(self._h)
-            self._h = None
+            self._h = self._addr = None
 
     def __del__(self):
         try:
@@ -236,23 +249,17 @@ class Context:
 
     def tc_prefill_attn(self, layer: int, q, k_new, v_new, out, cu_seqlens, block_table,
                         prefix_len, suffix_len, sm_scale: float, stream=None):
-        cu, bt = _i32arr(cu_seqlens), _i32arr(block_table)
-        pl, sl = _i32arr(prefix_len), _i32arr(suffix_len)
-        B = pl.size
-        max_blocks = bt.shape[1] if bt.ndim == 2 else (bt.size // B if B else 0)
-        self._check(_lib.tc_prefill_attn(self._h, layer, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                         cu.ctypes.data, bt.ctypes.data, max_blocks, pl.ctypes.data,
-                                         sl.ctypes.data, B, sm_scale, _stream(stream)))
+        rc = _py_call.prefill(_PREFILL, self._addr, layer, q, k_new, v_new, out, cu_seqlens, block_table, prefix_len,
+                              suffix_len, sm_scale, stream)
+        if rc != TC_OK:
+            self._check(rc)
 
     def tc_prefill_attn_noalloc(self, layer: int, q, k_new, v_new, out, cu_seqlens, block_table,
                                 prefix_len, suffix_len, sm_scale: float, stream=None):
-        cu, bt = _i32arr(cu_seqlens), _i32arr(block_table)
-        pl, sl = _i32arr(prefix_len), _i32arr(suffix_len)
-        B = pl.size
-        max_blocks = bt.shape[1] if bt.ndim == 2 else (bt.size // B if B else 0)
-        self._check(_lib.tc_prefill_attn_noalloc(self._h, layer, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                                 cu.ctypes.data, bt.ctypes.data, max_blocks, pl.ctypes.data,
-                                                 sl.ctypes.data, B, sm_scale, _stream(stream)))
+        rc = _py_call.prefill(_PREFILL_NOALLOC, self._addr, layer, q, k_new, v_new, out, cu_seqlens, block_table, prefix_len,
+                              suffix_len, sm_scale, stream)
+        if rc != TC_OK:
+            self._check(rc)
 
     def tc_grow_seqs(self, block_table: np.ndarray, new_len) -> np.ndarray:
         """Returns the grown block table (a copy; the argument is left alone)."""
