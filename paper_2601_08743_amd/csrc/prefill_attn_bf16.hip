@@ -413,6 +413,7 @@ __device__ __forceinline__ void store_rows(const RowState<RB> &st, const Geom &g
             // softmax average are bounded by max|v|, so fp16's 11-bit mantissa costs ~3e-5 here and
             // halves the partial traffic, the largest cost of a split launch): 512 B contiguous per
             // (row block, db, q4); a group's slot holds 4 * RB row blocks of 32 rows
+            if (ir.wave_row0 + rb * 32 >= ir.m_rows) continue;        // none of these rows exists: nothing reads them
             const int64_t slot = (int64_t)it.split * it.n_groups + it.group;
             const int blk = w * RB + rb;
             const float inv = l > 0.f ? 1.f / l : 0.f;
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(256, RB == 1 ? 2 : 1) void attn_bf16_kernel(Geom g,
                           blockIdx.x - a.n_items, threadIdx.x);
         return;
     }
-    const AttnItem it = a.items[blockIdx.x];
+    const AttnItem it = load_item(a, blockIdx.x);
     if (it.q < 0) return;                              // padding item (uniform for the work-group)
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     ItemRows<RB> ir;
@@ -896,7 +897,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
                           blockIdx.x - a.n_items, threadIdx.x);
         return;
     }
-    const AttnItem it = a.items[blockIdx.x];
+    const AttnItem it = load_item(a, blockIdx.x);
     if (it.q < 0) return;                              // padding item (uniform for the work-group)
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     ItemRows<1> ir;
@@ -930,61 +931,77 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
     }
 }
 
-// Combine the partitions of split queries.  One thread per 4 values of a group's accumulator
-// fragment: index = ((group * n_rb + row_block) * 16 + fragment) * 64 + lane, the order the
-// attention kernel stored it in, so loads are fully coalesced.  With reference maxima m_s, sums
-// l_s and normalised partial outputs O_s:  out = sum_s w_s O_s / sum_s w_s,  w_s = 2^(m_s - M) l_s.
+// Combine the partitions of split queries.  A wave takes kFrags of the 16 accumulator fragments of one
+// 32-row block of a group, in the order the attention kernel stored them (512 contiguous bytes per
+// fragment), and each row's (maximum, sum) once for all of them.  Bound: the latency of a short launch,
+// so the loads of kBatch partitions are issued before the first use; with few row blocks a wave
+// takes one fragment and up to 16 partitions at a time (one round trip), with many it takes four
+// fragments, which reads the (maximum, sum) pairs a quarter as often.  kBatch follows the batch's
+// largest partition count: what a row does not have would be loaded all the same.  With reference maxima m_s, sums
+// l_s and normalised partial outputs O_s:   out = sum_s w_s O_s / sum_s w_s,  w_s = 2^(m_s - M) l_s.
+// Measured (28 / 4 heads; in events that read 4.0 us for an empty launch): 12 queries of 3.3 k keys and 72 new
+// tokens, 2 partitions: 8.7 us, with one fragment per thread and eight partitions always 16.2 us; one query
+// of 17 new tokens, 9 partitions: 4.6 us against 5.2; one of 128, 8 partitions: 4.3 either way.
+template <int kFrags, int kBatch>
 __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, const MergeGroup *groups,
                                                          int n_groups, int n_rb)
 {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    const int lane = idx & 63, frag = (idx >> 6) & 15, gb = idx >> 10;
+    constexpr int kWgs = 4 / kFrags;                   // work-groups per row block
+    const int gb = blockIdx.x / kWgs;                  // group * n_rb + row block
+    const int frag0 = (blockIdx.x % kWgs) * 4 * kFrags + (threadIdx.x >> 6) * kFrags;
     const int group = gb / n_rb, blk = gb - group * n_rb;
-    if (group >= n_groups) return;
-    const MergeGroup mg = groups[group];
-    if (mg.n_splits <= 1) return;                      // written directly by the attention kernel
-    const int r32 = lane & 31, hh = lane >> 5;
-    const int row_m = mg.m0 + blk * 32 + r32;
-    if (row_m >= mg.S * g.G) return;
-    // partitions in chunks of 8: all loads of a chunk are issued before anything waits on them
+    typedef const __attribute__((address_space(4))) int32_t *const_ints;
+    const const_ints mg = (const_ints)(uintptr_t)(groups + group);               // (uploaded before the launch, never written)
+    const int kvh = mg[0], m0 = mg[1], n_splits = mg[2], cu = mg[3], S = mg[4];
+    if (n_splits <= 1 || m0 + blk * 32 >= S * g.G) return;      // written directly by the attention kernel; no such rows
+    const int lane = threadIdx.x & 63, r32 = lane & 31, hh = lane >> 5;
     float M = -INFINITY, l = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int64_t stride = (int64_t)n_groups * n_rb;          // (group, block) slots per partition
-    const int64_t gb0 = (int64_t)group * n_rb + blk;
-    for (int s0 = 0; s0 < mg.n_splits; s0 += 8) {
-        f16x4 v[8];
-        float2 ml[8];
+    float acc[4 * kFrags];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int s = min(s0 + k, mg.n_splits - 1);
-            const int64_t sb = (int64_t)s * stride + gb0;
-            v[k] = ((const f16x4 *)a.part_o)[(sb * 16 + frag) * 64 + lane];
+    for (int e = 0; e < 4 * kFrags; ++e) acc[e] = 0.f;
+    const int64_t stride = (int64_t)n_groups * n_rb;          // (group, block) slots per partition
+    for (int s0 = 0; s0 < n_splits; s0 += kBatch) {
+        f16x4 v[kBatch][kFrags];
+        float2 ml[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const int64_t sb = (int64_t)min(s0 + k, n_splits - 1) * stride + gb;
             ml[k] = ((const float2 *)a.part_ml)[sb * 32 + r32];
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) v[k][f] = ((const f16x4 *)a.part_o)[(sb * 16 + frag0 + f) * 64 + lane];
         }
         float Mc = M;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (s0 + k < mg.n_splits) Mc = fmaxf(Mc, ml[k].x);
-        const float resc = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mc);   // earlier chunks -> new reference
-        l *= resc; acc.x *= resc; acc.y *= resc; acc.z *= resc; acc.w *= resc;
+        for (int k = 0; k < kBatch; ++k) Mc = fmaxf(Mc, ml[k].x);        // (a partition taken twice changes no maximum)
+        const float resc = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mc);   // earlier batches -> new reference
+        l *= resc;
+#pragma unroll
+        for (int e = 0; e < 4 * kFrags; ++e) acc[e] *= resc;
         M = Mc;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (s0 + k >= mg.n_splits) continue;
-            const float wgt = (ml[k].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y;
+        for (int k = 0; k < kBatch; ++k) {
+            const bool live = s0 + k < n_splits && ml[k].x != -INFINITY;
+            const float wgt = live ? __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y : 0.f;
             l += wgt;
-            acc.x = fmaf(wgt, (float)v[k][0], acc.x); acc.y = fmaf(wgt, (float)v[k][1], acc.y);
-            acc.z = fmaf(wgt, (float)v[k][2], acc.z); acc.w = fmaf(wgt, (float)v[k][3], acc.w);
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[4 * f + e] = fmaf(wgt, (float)v[k][f][e], acc[4 * f + e]);
         }
     }
+    const int row_m = m0 + blk * 32 + r32;
+    if (row_m >= S * g.G) return;
     const float inv = 1.f / l;
     const int s_tok = row_m / g.G;
-    const int head = mg.kvh * g.G + (row_m - s_tok * g.G);
-    const int db = frag >> 2, q4 = frag & 3;
-    bf16x4 o;
-    o[0] = (__bf16)(acc.x * inv); o[1] = (__bf16)(acc.y * inv);
-    o[2] = (__bf16)(acc.z * inv); o[3] = (__bf16)(acc.w * inv);
-    *(bf16x4 *)((char *)a.out + ((int64_t)(mg.cu + s_tok) * g.Hq + head) * 256 + (32 * db + 8 * q4 + 4 * hh) * 2) = o;
+    const int head = kvh * g.G + (row_m - s_tok * g.G);
+    char *op = (char *)a.out + ((int64_t)(cu + s_tok) * g.Hq + head) * 256 + (8 * frag0 + 4 * hh) * 2;
+#pragma unroll
+    for (int f = 0; f < kFrags; ++f) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[4 * f + e] * inv);
+        *(bf16x4 *)(op + f * 16) = o;
+    }
 }
 
 template <int RB>
@@ -1020,11 +1037,17 @@ hipError_t launch_attn_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a,
 }
 
 hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup *groups, int n_groups,
-                             int row_blocks, const Launch &L)
+                             int row_blocks, int max_splits, const Launch &L)
 {
     if (n_groups == 0) return hipSuccess;
     const int n_rb = 4 * row_blocks;                   // 32-row blocks per group
-    TC_LAUNCH(merge_bf16_kernel, n_groups * n_rb * 4, 0, L, g, a, groups, n_groups, n_rb);
+    const bool few = n_groups * n_rb <= 512;
+    const int grid = few ? n_groups * n_rb * 4 : n_groups * n_rb;
+    if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4>), grid, 0, L, g, a, groups, n_groups, n_rb);
+    else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8>), grid, 0, L, g, a, groups, n_groups, n_rb);
+    else if (few) TC_LAUNCH((merge_bf16_kernel<1, 16>), grid, 0, L, g, a, groups, n_groups, n_rb);
+    else if (max_splits <= 2) TC_LAUNCH((merge_bf16_kernel<4, 2>), grid, 0, L, g, a, groups, n_groups, n_rb);
+    else TC_LAUNCH((merge_bf16_kernel<4, 4>), grid, 0, L, g, a, groups, n_groups, n_rb);
     return hipGetLastError();
 }
 

@@ -59,7 +59,7 @@ template <bool kPads>
 __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    const AttnItem it = a.items[blockIdx.x];
+    const AttnItem it = load_item(a, blockIdx.x);
     if (it.q < 0) return;                              // padding item (uniform for the work-group)
     // the XOR addressing of the K tiles needs them 256-byte aligned
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_raw;

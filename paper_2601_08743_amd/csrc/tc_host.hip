@@ -250,6 +250,15 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     const size_t bt_row = (size_t)(p.max_blocks + 3) & ~size_t(3);
     const size_t o_bt = take(B * bt_row), o_cu = take(B + 1), o_pl = take(B), o_sl = take(B);
     const size_t o_ss = take(nseg), o_sn = take(nseg), o_st = take(nseg), o_se = take(B);
+    std::vector<AppendBlk> ablk;
+    if (p.pingpong)
+        for (int i = 0; i < p.B; ++i) {
+            const int P = p.prefix_len[i], end = P + p.suffix_len[i];
+            for (int p0 = P / kBlockTokens * kBlockTokens; p.suffix_len[i] > 0 && p0 < end; p0 += kBlockTokens)
+                ablk.push_back(AppendBlk{p.block_table[(size_t)i * p.max_blocks + p0 / kBlockTokens], p.cu_seqlens[i] + p0 - P,
+                                         std::max(P - p0, 0), std::min(end - p0, (int)kBlockTokens)});
+        }
+    const size_t o_ab = take(ablk.size() * 4);
     const size_t o_sb = take(sblk.size() * 4), o_sp = take(B), o_tq = take(p.total_S);
     const size_t o_it = take(items.size() * (sizeof(AttnItem) / 4));
     const size_t o_gr = take(groups.size() * (sizeof(MergeGroup) / 4));
@@ -284,6 +293,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     for (size_t k = 0; k < nseg; ++k) {
         h[o_ss + k] = segs[k].start; h[o_sn + k] = segs[k].len; h[o_st + k] = segs[k].slot;
     }
+    if (!ablk.empty()) std::memcpy(h + o_ab, ablk.data(), ablk.size() * sizeof(AppendBlk));
     if (!sblk.empty()) std::memcpy(h + o_sb, sblk.data(), sblk.size() * sizeof(StitchBlk));
     for (int i = 0; i < p.B; ++i)
         for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) h[o_tq + n] = i;
@@ -305,6 +315,8 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.dev.seg_slot = d + o_st; p.dev.seg_end_of_q = d + o_se;
     p.dev.stitch_blk = (const StitchBlk *)(d + o_sb); p.dev.splits_of_q = d + o_sp;
     p.dev.tok_q = d + o_tq;
+    p.dev.append_blk = (const AppendBlk *)(d + o_ab);
+    p.dev.n_append_blk = (int32_t)ablk.size();
     p.dev.rope_pos0 = p.rope ? d + o_rp : nullptr;
     p.dev.rope_rev_freq = p.rope ? (const double *)(d + o_rf) : nullptr;
     p.dev.B = p.B; p.dev.max_blocks = (int32_t)bt_row; p.dev.total_S = p.total_S;
@@ -939,11 +951,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     }
     if (p.pingpong) {   // the attention launches append in extra work-groups of their own, except this kernel's,
                         // which reads the suffix from the pool: it is appended first, block by block
-        int n_blk = 0;
-        for (int i = 0; i < p.B; ++i)
-            if (p.suffix_len[i] > 0)
-                n_blk += (p.prefix_len[i] + p.suffix_len[i] + kBlockTokens - 1) / kBlockTokens - p.prefix_len[i] / kBlockTokens;
-        TC_HIP(ctx, timed_launch(ctx, 1, stream, [&](const Launch &ln) { return launch_append_blocks(ctx->geom, p.dev, layer, k_new, v_new, n_blk, ln); }));
+        TC_HIP(ctx, timed_launch(ctx, 1, stream, [&](const Launch &ln) { return launch_append_blocks(ctx->geom, p.dev, layer, k_new, v_new, ln); }));
     }
     AttnArgs a{};
     a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
@@ -961,7 +969,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     }));
     if (p.max_splits > 1)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
-            return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, ln)
+            return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
                         : launch_merge_f32(ctx->geom, p.dev, a, p.max_splits, ln);
         }));
     return TC_OK;

@@ -73,13 +73,13 @@ hipError_t launch_attn_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a,
                             const Launch &L);
 // decode_attn_bf16.hip
 hipError_t launch_append_blocks(const Geom &g, const BatchDev &b, int layer, const void *k_new, const void *v_new,
-                                int n_blocks, const Launch &L);
+                                const Launch &L);
 hipError_t launch_attn_pp_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup *groups, int n_groups,
-                             int row_blocks, const Launch &L);
+                             int row_blocks, int max_splits, const Launch &L);
 
 }  // namespace tc
