@@ -11,6 +11,7 @@
 //   seq <first> <end>               start an allocator over blocks [first, end)
 //   t <n>                           take the n lowest free blocks -> "t b0 b1 ..."
 //   f <k> b0 .. bk-1                release
+//   stage <cap> <n> then n sizes     place n plans in a staging buffer -> one line "s <at> <parts>" each
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok>"
 //                                      one line "i q kvh m0 tile_begin tile_end split n_splits group" per item,
@@ -62,6 +63,14 @@ int main()
             int64_t first, end;
             std::cin >> first >> end;
             seq.reset(first, end);
+        } else if (cmd == "stage") {
+            size_t cap, n, ints;
+            std::cin >> cap >> n;
+            for (StageHalves st; n > 0; --n) {
+                std::cin >> ints;
+                const StageHalves::Spot spot = st.place(ints, cap);
+                std::printf("s %zu %u\n", spot.at, spot.parts);
+            }
         } else if (cmd == "t") {
             size_t n;
             std::cin >> n;

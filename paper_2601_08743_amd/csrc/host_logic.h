@@ -167,6 +167,24 @@ public:
     }
 };
 
+// ------------------------------------------------------------------ plan staging
+// Where the next plan goes in a staging buffer of `cap` integers that uploads read asynchronously: plans
+// that fit a half take the halves in turn, so that the host waits for the upload before last and not
+// for the last one; a longer plan takes the whole buffer.  `parts`: the halves it covers (bit k), all of
+// whose uploads must have ended before it is written, and whose event its own upload must record.
+struct StageHalves {
+    int next = 0;
+    struct Spot { size_t at; unsigned parts; };
+    static size_t half_of(size_t cap) { return (cap / 2) & ~size_t(63); }     // (uploads move whole 16-byte chunks)
+    Spot place(size_t ints, size_t cap)
+    {
+        if (ints > half_of(cap)) return Spot{0, 3u};
+        const int k = next;
+        next = 1 - k;
+        return Spot{(size_t)k * half_of(cap), 1u << k};
+    }
+};
+
 // ------------------------------------------------------------------ the plan of one batch
 // The integer plan of one batch, host copy and layout of the device copy.
 struct Plan {

@@ -83,11 +83,11 @@ struct tc_ctx {
     hipStream_t raw_stream = nullptr;      // on this stream
     bool raw_pending = false;
     Plan plan;
-    int32_t *h_stage = nullptr; size_t h_stage_ints = 0;    // pinned; plans that fit half of it take the halves in turn
+    int32_t *h_stage = nullptr; size_t h_stage_ints = 0;    // pinned
+    StageHalves stage;
     int32_t *d_plan = nullptr; size_t d_plan_ints = 0;
-    hipEvent_t stage_ev[2] = {nullptr, nullptr};            // the last upload out of each half
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};            // the last upload out of each half of h_stage
     bool stage_pending[2] = {false, false};
-    int stage_next = 0;
     float *d_part = nullptr; size_t d_part_floats = 0;
     int device = 0;                        // the device the context was created on
     char *scratch_dev = nullptr;           // that device's copy of the static workspace (tc_prefill_attn_noalloc)
@@ -195,29 +195,34 @@ int esize_of(const tc_config &c) { return c.dtype == TC_F32 ? 4 : 2; }
 // Make room for a plan of `ints` integers: the pinned staging buffer on the host and, unless the
 // plan goes to the static workspace (`fixed`), the device buffer.  The staging buffer is created
 // by tc_create with the static workspace's plan capacity, so a fixed plan never allocates.
-// `at`: where in the staging buffer the plan goes; `half`: whose event its upload records.  With two
-// halves the host does not wait for the previous batch's upload, only for the one before it.
-tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, int *half)
+// `at`: where in the staging buffer the plan goes; `parts`: the halves of it whose events its upload records.
+tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, unsigned *parts)
 {
     if (fixed && (ints > kScratchPlanInts || ints > ctx->h_stage_ints))
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the batch's plan needs %zu integers, the fixed workspace holds %zu",
                     ints, std::min(kScratchPlanInts, ctx->h_stage_ints));
-    const bool halves = 2 * ints <= ctx->h_stage_ints;
-    *half = halves ? ctx->stage_next : 0;
-    for (int k = 0; k < 2; ++k)
-        if (ctx->stage_pending[k] && (!halves || k == *half)) {      // an earlier upload still reads that part
-            TC_HIP(ctx, hipEventSynchronize(ctx->stage_ev[k]));
-            ctx->stage_pending[k] = false;
-        }
+    auto wait_for = [&](unsigned halves) -> tc_status {          // earlier uploads that still read those halves
+        for (int k = 0; k < 2; ++k)
+            if ((halves >> k & 1) && ctx->stage_pending[k]) {
+                TC_HIP(ctx, hipEventSynchronize(ctx->stage_ev[k]));
+                ctx->stage_pending[k] = false;
+            }
+        return TC_OK;
+    };
     if (!fixed && ints > ctx->h_stage_ints) {
+        const tc_status st = wait_for(3u);
+        if (st != TC_OK) return st;
         if (ctx->h_stage) TC_HIP(ctx, hipHostFree(ctx->h_stage));
         ctx->h_stage = nullptr; ctx->h_stage_ints = 0;
         const size_t cap = std::max(ints * 2, size_t(1) << 16);
         TC_HIP(ctx, hipHostMalloc((void **)&ctx->h_stage, cap * sizeof(int32_t), hipHostMallocDefault));
         ctx->h_stage_ints = cap;
     }
-    *at = ctx->h_stage + (halves ? *half * ((ctx->h_stage_ints / 2) & ~size_t(63)) : 0);
-    ctx->stage_next = 1 - *half;
+    const StageHalves::Spot spot = ctx->stage.place(ints, ctx->h_stage_ints);
+    const tc_status st = wait_for(spot.parts);
+    if (st != TC_OK) return st;
+    *at = ctx->h_stage + spot.at;
+    *parts = spot.parts;
     if (!fixed && ints > ctx->d_plan_ints) {
         if (ctx->d_plan) TC_HIP(ctx, hipFree(ctx->d_plan));   // hipFree waits for work that may use it
         ctx->d_plan = nullptr; ctx->d_plan_ints = 0;
@@ -275,8 +280,8 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the split-KV partials need %zu floats, the fixed workspace holds %zu",
                     part_need, kScratchPartFloats);
     int32_t *h = nullptr;
-    int half = 0;
-    tc_status st = ensure_stage(ctx, total, fixed, &h, &half);
+    unsigned parts = 0;
+    tc_status st = ensure_stage(ctx, total, fixed, &h, &parts);
     if (st != TC_OK) return st;
     std::memset(h, 0, total * sizeof(int32_t));
     if (B) {
@@ -306,8 +311,11 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
 
     int32_t *d_dst = fixed ? (int32_t *)ctx->scratch_dev : ctx->d_plan;
     TC_HIP(ctx, launch_upload(d_dst, h, total, Launch{stream, nullptr, nullptr}));
-    TC_HIP(ctx, hipEventRecord(ctx->stage_ev[half], stream));
-    ctx->stage_pending[half] = true;
+    for (int k = 0; k < 2; ++k)
+        if (parts >> k & 1) {
+            TC_HIP(ctx, hipEventRecord(ctx->stage_ev[k], stream));
+            ctx->stage_pending[k] = true;
+        }
 
     const int32_t *d = d_dst;
     p.dev.block_table = d + o_bt; p.dev.cu_seqlens = d + o_cu; p.dev.prefix_len = d + o_pl;

@@ -89,6 +89,29 @@ def test_allocator_equals_the_sorted_set_model(exe):
     assert run(exe, "\n".join(script) + "\n") == want
 
 
+@pytest.mark.parametrize("cap", [1 << 20, 1 << 16, 131080, 65544])
+def test_staged_plans_share_no_memory_with_an_upload_nobody_waited_for(exe, cap):
+    """Plans longer than half the buffer between short ones, sizes at the half's edge: a plan may overlap an
+    earlier one only if it waits for one of the events that the earlier one's upload recorded."""
+    rng = np.random.default_rng(cap)
+    half = cap // 2
+    sizes = [int(x) for x in rng.choice([8, 4096, half - 64, half - 8, half, half + 8, cap - 8, cap], 300)]
+    spots = [tuple(map(int, l.split()[1:])) for l in run(exe, "stage %d %d %s\n" % (cap, len(sizes), " ".join(map(str, sizes))))]
+    assert len(spots) == len(sizes)
+    pending = {}                                 # half -> index of the plan whose upload recorded its event last
+    for i, ((at, parts), n) in enumerate(zip(spots, sizes)):
+        assert parts in (1, 2, 3) and at % 4 == 0 and at + n <= cap
+        over = {pending[k] for k in pending if parts >> k & 1}          # waited for
+        for j in set(pending.values()) - over:
+            (a, _), m = spots[j], sizes[j]
+            assert at + n <= a or a + m <= at, (i, j)
+        for k in (0, 1):
+            if parts >> k & 1:
+                pending[k] = i
+    short = [p for (_, p), n in zip(spots, sizes) if n <= 4096]
+    assert {1, 2} <= set(short)                  # and short ones do alternate
+
+
 def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128):
     lines = run(exe, "plan %d %d %d %d %d %d %d %d %s\n" % (dtype, Hq, Hkv, D, splits, rb, kernel, len(PS),
                                                           " ".join("%d %d" % ps for ps in PS)))
