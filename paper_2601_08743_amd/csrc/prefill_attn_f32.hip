@@ -198,6 +198,42 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         }
         if (more) wait_loads<kPieces>();         // V(u) has landed, K(u + 4) may be outstanding
         else wait_loads<0>();
+        // A matrix instruction multiplies a key that a row must not see by zero, which an infinity or a NaN in
+        // its value would not survive.  Units that hold such keys are looked through first, and values that are
+        // not finite are added to the rows that see them here and then taken as zero.
+        if (key0 + kF32Unit - 1 > P) {
+            float zero = 0.f;                    // stays so unless something is not finite
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const vcols vf = *(lds_cols)(uintptr_t)(v_at + (8 * (e >> 2) + (e & 3)) * (D * 4));
+#pragma unroll
+                for (int j = 0; j < kCols; ++j) zero = fmaf(vf[j], 0.f, zero);
+            }
+            if (__any(!(zero == 0.f))) {
+#pragma unroll 1
+                for (int kr = 0; kr < kF32Unit; ++kr) {
+                    float p = s[0];
+#pragma unroll
+                    for (int e = 1; e < 16; ++e) p = e == 4 * (kr >> 3) + (kr & 3) ? s[e] : p;
+                    p = __shfl(p, r32 + 32 * ((kr >> 2) & 1));
+                    const bool seen = key0 + kr <= limit;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const vcols vf = *(lds_cols)(uintptr_t)(lds_w + L::kPart + (kr * D + kCols * (8 * (e >> 2) + 4 * hh + (e & 3))) * 4);
+#pragma unroll
+                        for (int j = 0; j < kCols; ++j) o[j][e] += seen && !__builtin_isfinite(vf[j]) ? p * vf[j] : 0.f;
+                    }
+                }
+                asm volatile("" ::: "memory");
+                typedef __attribute__((address_space(3))) float *lds_float;
+#pragma unroll 1
+                for (int i = lane; i < kF32Unit * D; i += 64) {
+                    const lds_float at = (lds_float)(uintptr_t)(lds_w + L::kPart + i * 4);
+                    if (!__builtin_isfinite(*at)) *at = 0.f;
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const vcols vf = *(lds_cols)(uintptr_t)(v_at + (8 * (e >> 2) + (e & 3)) * (D * 4));

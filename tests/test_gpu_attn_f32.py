@@ -60,3 +60,30 @@ def test_edges(H, D, hq, hkv):
 def test_range_longer_than_the_block_id_table(H, D):
     """513 key tiles of prefix where a work item may have 512: cut in two although one range is asked for."""
     _run(H, D, 2, 1, [32800, 40], [[0], [1]], [3, 17], (1, 0))
+
+
+@pytest.mark.parametrize("D,splits", [(64, 1), (64, 3), (128, 1)])
+def test_values_of_later_tokens_reach_no_earlier_row(H, D, splits):
+    """An infinity and a NaN in the values of one suffix token: the rows before it are what they are
+    without it, the rows from it on are not finite in exactly those columns."""
+    cfg = W.WorkloadConfig("f", 1, 6, 2, D, "f32", 2, (1, 70), 2, (0, 2), "uniform", (1, 9), 2, 312)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = [70, 33]
+    wl.queries[:] = [np.array([0, 1], dtype=np.int32), np.array([1], dtype=np.int32)]
+    wl.suffix_len[:] = [45, 20]
+    dw = H.DeviceWorkload(wl)
+    dw.ctx.tc_set_kv_splits(splits)
+    q, k, v = wl.suffix_qkv(0)
+    ref = H.oracle_attn_layer(wl, dw.tables_np, 0, (q, k, v))
+    at = 27                                      # token 27 of the first query, columns 3 and 5 of KV head 1
+    bad = v.copy()
+    bad[at, 1, 3], bad[at, 1, 5] = np.inf, np.nan
+    bt, pl = dw.stitch()
+    got = H.out_to_f64(dw.attn_layer(0, bt, pl, qkv=(q, k, bad))[0], cfg)
+    want = np.concatenate([ref[0], ref[1]])
+    hit = np.zeros(want.shape, dtype=bool)
+    hit[at:45, 3:, 3] = hit[at:45, 3:, 5] = True
+    assert not np.isfinite(got[hit]).any()
+    assert float(np.abs(got - want)[~hit].max()) <= TOL
+    dw.ctx.tc_release_seqs(bt)
+    dw.close()
