@@ -319,9 +319,10 @@ tc_status tc_set_row_blocks(tc_ctx *ctx, int32_t row_blocks);
  * second kernel combines them and adds the new token), 4 = the kernel for long launches (256
  * rows per work-group in two groups of waves that alternate between matrix and vector work; the
  * suffix is appended to the pool by a launch of its own before attention, which then reads all
- * keys from the pool; ignored while tc_set_row_blocks forces a row count).  Results do not depend
- * on it beyond rounding.  Invalidates the cached plan.
- * tc_attn_kernel reports the kernel of the current plan (1 .. 4; 0 when no plan is cached, for
+ * keys from the pool; ignored while tc_set_row_blocks forces a row count), 5 = the kernel for short
+ * launches (32 rows per work-group, whose eight waves split the keys; ignored likewise).  Results do
+ * not depend on it beyond rounding.  Invalidates the cached plan.
+ * tc_attn_kernel reports the kernel of the current plan (1 .. 5; 0 when no plan is cached, for
  * fp32 contexts and for forced 256-row work-groups of the general kernel). */
 tc_status tc_set_attn_kernel(tc_ctx *ctx, int32_t kind);
 int32_t tc_attn_kernel(const tc_ctx *ctx);

@@ -310,7 +310,9 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 // work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
 // threads would load what nobody needs.  (Slots of partitions that the query, but not the batch, lacks
 // exist in the buffer; they are loaded and ignored.)
-template <int kGroups>
+// Without kSelf there is no new token to add and rows of one partition are left alone (they were written
+// directly): the merge of the short-launch prefill kernel's partitions.
+template <int kGroups, bool kSelf>
 __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
     constexpr int kBatch = 4, kRows = 8 / kGroups;
@@ -332,9 +334,12 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
         }
     };
     fetch(grp);
-    const uint2 q2 = *(const uint2 *)((const unsigned short *)a.q + (int64_t)row * 128 + d);
-    const uint2 k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
-    const uint2 v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
+    uint2 q2, k2, v2;
+    if (kSelf) {
+        q2 = *(const uint2 *)((const unsigned short *)a.q + (int64_t)row * 128 + d);
+        k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
+        v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
+    }
     const int ns = b.splits_of_q[b.tok_q[n]];
     float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -358,14 +363,16 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
         if (d == 0) { s_ml[slot8][0] = M; s_ml[slot8][1] = L; }
         __syncthreads();
     }
-    if (grp > 0 || want >= n_rows) return;
+    if (grp > 0 || want >= n_rows || (!kSelf && ns <= 1)) return;
     // the row's first group goes on: score of the new token against itself, then the other groups' results
-    auto lo = [](uint32_t x) { return __uint_as_float(x << 16); };
-    auto hi = [](uint32_t x) { return __uint_as_float(x & 0xffff0000u); };
-    float prod = lo(q2.x) * lo(k2.x) + hi(q2.x) * hi(k2.x) + lo(q2.y) * lo(k2.y) + hi(q2.y) * hi(k2.y);
+    if (kSelf) {
+        auto lo = [](uint32_t x) { return __uint_as_float(x << 16); };
+        auto hi = [](uint32_t x) { return __uint_as_float(x & 0xffff0000u); };
+        float prod = lo(q2.x) * lo(k2.x) + hi(q2.x) * hi(k2.x) + lo(q2.y) * lo(k2.y) + hi(q2.y) * hi(k2.y);
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1) prod += __shfl_xor(prod, off, 32);
-    fold(prod * a.scale_log2, 1.f, f32x4{lo(v2.x), hi(v2.x), lo(v2.y), hi(v2.y)});
+        for (int off = 16; off > 0; off >>= 1) prod += __shfl_xor(prod, off, 32);
+        fold(prod * a.scale_log2, 1.f, f32x4{lo(v2.x), hi(v2.x), lo(v2.y), hi(v2.y)});
+    }
 #pragma unroll
     for (int k = 1; k < kGroups; ++k) fold(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
     const float inv = 1.f / L;
@@ -392,16 +399,27 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     return hipGetLastError();
 }
 
-hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+template <bool kSelf>
+static hipError_t launch_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
     const int n_rows = b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
     if (max_splits < 1) return hipErrorInvalidValue;
-    if (max_splits <= 4) TC_LAUNCH(decode_finish_kernel<1>, (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 8) TC_LAUNCH(decode_finish_kernel<2>, (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 16) TC_LAUNCH(decode_finish_kernel<4>, (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
-    else TC_LAUNCH(decode_finish_kernel<8>, n_rows, 0, L, g, b, a, max_splits);
+    if (max_splits <= 4) TC_LAUNCH((decode_finish_kernel<1, kSelf>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH((decode_finish_kernel<2, kSelf>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH((decode_finish_kernel<4, kSelf>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH((decode_finish_kernel<8, kSelf>), n_rows, 0, L, g, b, a, max_splits);
     return hipGetLastError();
+}
+
+hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+{
+    return launch_finish<true>(g, b, a, max_splits, L);
+}
+
+hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+{
+    return launch_finish<false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

@@ -12,8 +12,9 @@
 //   t <n>                           take the n lowest free blocks -> "t b0 b1 ..."
 //   f <k> b0 .. bk-1                release
 //   stage <cap> <n> then n sizes     place n plans in a staging buffer -> one line "s <at> <parts>" each
+//   short <rows>                    rows per work item of the short-launch kernel in the plans that follow (0: without it)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
-//                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok>"
+//                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
 //                                      one line "i q kvh m0 tile_begin tile_end split n_splits group" per item,
 //                                      "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
@@ -38,6 +39,7 @@ int main()
     SeqBlocks seq;
     tc_trie *trie = nullptr;
     std::string cmd;
+    int32_t short_rows = 0;
     while (std::cin >> cmd) {
         if (cmd == "rule") {
             int policy;
@@ -88,9 +90,12 @@ int main()
                 if (seq.allocated(b)) seq.release(b);
                 else std::printf("f bad %d\n", b);
             }
+        } else if (cmd == "short") {
+            std::cin >> short_rows;
         } else if (cmd == "plan") {
             tc_config c{};
             PlanKnobs knobs;
+            knobs.short_rows = short_rows;
             int B;
             std::cin >> c.dtype >> c.n_q_heads >> c.n_kv_heads >> c.head_dim >> knobs.forced_splits >>
                 knobs.forced_row_blocks >> knobs.forced_attn_kernel >> B;
@@ -118,8 +123,8 @@ int main()
             std::vector<int32_t> splits;
             std::vector<MergeGroup> groups;
             const bool ok = plan_attention(c, knobs, p, items, splits, groups);
-            std::printf("plan %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
-                        p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0);
+            std::printf("plan %d %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
+                        p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
             for (const AttnItem &it : items)
                 std::printf("i %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
                             it.q < 0 ? -1 : it.group);

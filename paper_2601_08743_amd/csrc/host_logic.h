@@ -193,6 +193,7 @@ struct Plan {
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups; the suffix is appended first
+    bool brief = false;         // bf16, 32 rows per work-group, its waves split the keys: the short-launch kernel
     bool rope = false;          // the stitch re-encodes keys by position (Sec. 4.1.1)
     std::vector<int32_t> rope_pos0;      // [B]
     std::vector<double> rope_rev_freq;   // [D/2]
@@ -210,7 +211,8 @@ struct Plan {
 struct PlanKnobs {
     int32_t forced_splits = 0;
     int32_t forced_row_blocks = 0;
-    int32_t forced_attn_kernel = 0;   // 1 general, 2 pipelined, 3 decode (where it applies), 4 long launches
+    int32_t forced_attn_kernel = 0;   // 1 general, 2 pipelined, 3 decode (where it applies), 4 long launches, 5 short launches
+    int32_t short_rows = 0;           // rows per work item of the short-launch kernel (tc_create sets it), 0: do without that kernel
     int32_t f32_rows = 4;             // fp32: rows per work item (tc_create sets the kernel's; any other plans the same way)
 };
 
@@ -254,6 +256,60 @@ inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int k
     return best_range;
 }
 
+// The short-launch kernel (32 rows per work-group, one work-group per CU, its eight waves split the
+// range's 32-key units): the key range of a work item in key tiles, and what the launch takes, in us.  A
+// round of work-groups costs 4.4 us and 1.6 for each unit of a wave (a round trip to memory and its
+// arithmetic: the wave has one unit in flight), the merge 3.5 us and its fp32 partials, each MB of keys and
+// values 0.1 us.  Ranges are only cut where the chip has CUs to spare and a KV head has at most 512 rows (16 row
+// tiles that each fetch the keys; one query of 2.1 k + 140 tokens, 28 / 4 heads: 19.1 us in two ranges, 19.5 in
+// the pipelined kernel), so partials stay small, and more than two rounds of work-groups are left to the
+// other kernels (three: 1.04 times as fast as those, two: 1.3, one: 1.4).  Fitted to
+// 740 batches (1 .. 16 queries of 350 .. 10500 prefix and 2 .. 330 new tokens, 28 / 4, 32 / 8 and 40 / 8
+// heads) in 1 .. 9 ranges: 8 % rms.
+inline double batch_mb(const tc_config &c, const Plan &p)
+{
+    double tokens = 0;
+    for (int i = 0; i < p.B; ++i)
+        if (p.suffix_len[i] > 0) tokens += (double)p.prefix_len[i] + p.suffix_len[i];
+    return tokens * c.n_kv_heads * c.head_dim * 4e-6;
+}
+struct BriefPlan { int range = 0; double us = 1e30; };
+inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int key_tile, int max_tiles)
+{
+    const int G = c.n_q_heads / c.n_kv_heads;
+    auto tiles_of = [&](int i) { return (p.prefix_len[i] + key_tile - 1) / key_tile + (p.suffix_len[i] + key_tile - 1) / key_tile; };
+    int longest = 0;
+    for (int i = 0; i < p.B; ++i)
+        if (p.suffix_len[i] > 0) longest = std::max(longest, tiles_of(i));
+    BriefPlan best;
+    const double mb = batch_mb(c, p);
+    for (int cuts = 1; cuts <= 32; ++cuts) {
+        const int range = std::max(1, (longest + cuts - 1) / cuts);
+        if (range > max_tiles) continue;
+        int64_t n = 0;
+        double units = 0, rows_cut = 0;
+        int most = 0;
+        bool split = false, wide = false;
+        for (int i = 0; i < p.B; ++i) {
+            const int S = p.suffix_len[i];
+            if (S <= 0) continue;
+            const int tiles = tiles_of(i), ns = std::min((tiles + range - 1) / range, std::max(1, tiles / 2));
+            const int per_wave = (2 * ((tiles + ns - 1) / ns) + 7) / 8;
+            const int64_t k = (int64_t)c.n_kv_heads * ((S * G + row_tile - 1) / row_tile) * ns;
+            n += k;
+            units += (double)k * per_wave;
+            most = std::max(most, per_wave);
+            if (ns > 1) { split = true; wide = wide || S * G > 512; rows_cut += (double)S * c.n_q_heads * ns; }
+        }
+        if (n == 0 || n > 512 || (split && (n > 256 || wide))) break;          // (n grows with the cuts)
+        const double rounds = (double)((n + 255) / 256);
+        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? 3.5 + 3e-5 * rows_cut : 0.0) + 0.1 * mb;
+        if (us < best.us - 1e-9) best = BriefPlan{range, us};
+        if (range == 1) break;
+    }
+    return best;
+}
+
 // Attention work list for the batch in `p` (host arrays filled in).  Items of one
 // (query, KV head, split) read the same K/V; they are given work-group ids that are congruent
 // modulo 8 so that they land on the same XCD and share its L2 (work-groups go to the 8 XCDs
@@ -274,6 +330,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     const int KT = bf16 ? kAttnKeys : kF32Keys;
     p.decode = false;
     p.pingpong = false;
+    p.brief = false;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
     // the four waves of a work-group and over `ns` work-groups.  A work-group holds a CU (its ring of
@@ -376,14 +433,18 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // wave per SIMD) is kept as an option: it is slower until its matrix and vector work overlap
     const int rb = pp ? 2 : (bf16 && ctx->forced_row_blocks > 0) ? ctx->forced_row_blocks : 1;
     p.row_blocks = rb;
-    const int RT = bf16 ? kAttnRows * rb : ctx->f32_rows;
+    int RT = bf16 ? kAttnRows * rb : ctx->f32_rows;
     int64_t base = 0, tiles_sum = 0, n_q = 0;
-    for (int i = 0; i < p.B; ++i)
-        if (p.suffix_len[i] > 0) {
-            base += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + RT - 1) / RT);
-            tiles_sum += tiles_of(p.prefix_len[i], p.suffix_len[i]);
-            ++n_q;
-        }
+    auto count_items = [&] {
+        base = tiles_sum = n_q = 0;
+        for (int i = 0; i < p.B; ++i)
+            if (p.suffix_len[i] > 0) {
+                base += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + RT - 1) / RT);
+                tiles_sum += tiles_of(p.prefix_len[i], p.suffix_len[i]);
+                ++n_q;
+            }
+    };
+    count_items();
     // Number of key partitions: a small cost model, in units of one key tile of one work-group
     // (~1.4 us).  The work items of one (query, KV head, partition) - a bucket - go to one XCD (they
     // share its L2), so what counts is the most loaded XCD: buckets per XCD x items per bucket over
@@ -392,14 +453,14 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // work-group (co-resident work-groups overlap each other's stalls: x0.7); plus a fixed start-up
     // and epilogue cost; plus the merge: a launch and the partials written and read back at about
     // 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
-    int want = 1, f32_range = 0;
+    int want = 1, cut_range = 0;           // (cut_range: the length of a range in key tiles, where the queries are cut by that)
     if (ctx->forced_splits > 0) want = ctx->forced_splits;
-    else if (!bf16 && base > 0) f32_range = plan_f32_range(c, p, RT, KT);
+    else if (!bf16 && base > 0) cut_range = plan_f32_range(c, p, RT, KT);
     else if (base > 0) {
         const double tiles = (double)tiles_sum / (double)n_q;
         const double items_per_bucket = (double)base / (double)(n_q * c.n_kv_heads);
         const double rows = (double)p.total_S * c.n_q_heads;
-        double best = 1e30;
+        double best = 1e30, us = 0;
         for (int ns = 1; ns <= 32; ++ns) {
             if (ns > 1 && tiles / ns < 2.0) break;
             const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
@@ -407,8 +468,37 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             const double merge = ns > 1 ? 1.0 + 0.93e-4 * ns * rows : 0.0;   // fp16 partials: 264 B per row and partition
             // (two work-groups on a CU overlap each other's stalls; the long-launch kernel runs one per CU)
             const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 && !pp ? 0.7 : 1.0) + 3.0 + merge;
-            if (cost < best - 1e-9) { best = cost; want = ns; }
+            if (cost < best - 1e-9) {
+                best = cost;
+                want = ns;
+                // What such a launch takes, in us, for the comparison below only: fitted to 710 of the batches that
+                // plan_brief was fitted to (9 % rms), with the append work-groups and the traffic, which the
+                // choice between partition counts does not turn on.
+                us = 0.8 + 7.1 * per_cu + 1.44 * per_cu * (tiles / ns) * (per_cu >= 2.0 ? 0.7 : 1.0) +
+                     (ns > 1 ? 1.9 + 1e-4 * ns * rows : 0.0) + 2.2 * p.total_S / 256.0 + 0.087 * batch_mb(c, p);
+            }
         }
+        // The short-launch kernel, where it is faster by more than the two models are unsure: of the batches that they
+        // were fitted to it takes 451 of 740 and loses time in 8; over all 740 the call is 1.21 times as fast (1.24
+        // if the faster kernel were known each time).  28 / 4 heads: one query of 1.1 k + 17 tokens 10.4 us against
+        // 14.5; eight of 1 k + 17: 13 against 24; but one of 4.1 k + 128, whose rows fill 128-row tiles and
+        // whose keys 32-row tiles would read four times as often, 25 against 22.
+        if (!pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 0) {
+            const BriefPlan b = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles);
+            if (b.us < 0.85 * us) {
+                p.brief = true;
+                cut_range = b.range;
+            }
+        }
+    }
+    if (bf16 && !pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 5) {
+        p.brief = true;
+        if (ctx->forced_splits == 0) cut_range = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).range;
+        want = std::max(1, ctx->forced_splits);
+    }
+    if (p.brief) {
+        RT = ctx->short_rows;
+        count_items();
     }
     splits_of_q.assign(p.B, 1);
     p.max_splits = 1;
@@ -424,7 +514,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // last block a tile load may touch: bf16 reads only prefix blocks from the pool
         const int last_blk = std::max(0, (unified ? (P + S + kBlockTokens - 1) / kBlockTokens
                                                   : (P + kBlockTokens - 1) / kBlockTokens) - 1);
-        if (f32_range > 0) want = (n_tiles + f32_range - 1) / f32_range;
+        if (cut_range > 0) want = (n_tiles + cut_range - 1) / cut_range;
         int ns = std::min(want, ctx->forced_splits > 0 ? n_tiles : std::max(1, n_tiles / 2));
         const int cap = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : general_cap;   // block ids of a range fit LDS
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
@@ -438,7 +528,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         for (;; ++ns) {
             cut.assign(ns + 1, 0);
             const int npt = unified ? n_tiles : (P + KT - 1) / KT;
-            const int w_new = 4;
+            const int w_new = p.brief ? 1 : 4;
             const int64_t total_w = npt + (int64_t)(n_tiles - npt) * w_new;
             int t = 0;
             int64_t acc = 0;
@@ -478,9 +568,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     flat.back().m0 = mt * RT;
                     flat.back().group = n_groups + mt;
                     ++bucket.count;
-                    // (fp32: eight row tiles share their keys' way into one L2, the next eight may go to another
-                    // XCD, so that few (query, KV head) pairs still spread evenly)
-                    if (!bf16 && bucket.count == 8 && mt + 1 < n_mt) {
+                    // (32-row tiles: eight, or four, of them share their keys' way into one L2, the next may go to
+                    // another XCD, so that few (query, KV head) pairs still spread evenly)
+                    if (bucket.count == (!bf16 ? 8 : p.brief ? 4 : INT32_MAX) && mt + 1 < n_mt) {
                         buckets.push_back(bucket);
                         bucket = Bucket{(int32_t)flat.size(), 0, t1 - t0};
                     }
@@ -529,7 +619,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             ++n_real;
             fast_tiles += std::max(std::min(it.tile_end, it.P >> 6) - it.tile_begin, 0);
         }
-    p.pipelined = bf16 && rb == 1 && !pp && n_real > 0 &&
+    p.pipelined = bf16 && rb == 1 && !pp && !p.brief && n_real > 0 &&
                   (ctx->forced_attn_kernel == 1 || ctx->forced_attn_kernel == 2 ? ctx->forced_attn_kernel == 2
                                            : (n_real <= 2 * 256 || fast_tiles >= 48 * n_real));
     // every range's block ids must fit the table of the kernel that will run it

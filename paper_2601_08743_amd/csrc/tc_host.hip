@@ -270,10 +270,10 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     const size_t o_rp = take(p.rope ? B : 0), o_rf = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     const size_t total = std::max(off, size_t(8));          // (a multiple of 8: the upload moves 16 bytes at a time)
     // split-KV partials.  bf16 kernels: per (partition, group, row block) 128 rows x (128 fp16 + 2
-    // floats) in fragment order, counted in floats; fp32 and decode kernels: per (partition, new
+    // floats) in fragment order, counted in floats; fp32, decode and short-launch kernels: per (partition, new
     // token, head) D + 2 floats
     const size_t part_need = !(p.max_splits > 1 || p.decode) ? 0
-        : ctx->cfg.dtype == TC_BF16 && !p.decode
+        : ctx->cfg.dtype == TC_BF16 && !p.decode && !p.brief
             ? (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * (64 + 2)
             : (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * (ctx->cfg.head_dim + 2);
     if (fixed && part_need > kScratchPartFloats)
@@ -436,6 +436,7 @@ tc_status tc_create(const tc_config *cfg, void *kv_pool_dev, size_t pool_bytes, 
 
     ctx->rule.reset(make_rule(cfg->policy));
     ctx->knobs.f32_rows = kF32Rows;
+    ctx->knobs.short_rows = kShortRows;
 
     ctx->slots.resize(cfg->table_capacity);
     for (int s = 0; s < cfg->table_capacity; ++s) {
@@ -963,21 +964,23 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     }
     AttnArgs a{};
     a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
-    a.n_append = p.pingpong ? 0 : append_units(p.total_S, p.B, bf16 ? 1 : kF32AppendTokens); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
+    a.n_append = p.pingpong || p.brief ? 0 : append_units(p.total_S, p.B, bf16 ? 1 : kF32AppendTokens); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     a.has_pads = p.block_pad.empty() ? 0 : 1;
     a.part_o = p.part;
     a.part_ml = !p.part ? nullptr
-              : bf16 ? p.part + (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * 64
+              : bf16 && !p.brief ? p.part + (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * 64
                      : p.part + (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
     TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) {
         return p.pingpong ? launch_attn_pp_bf16(ctx->geom, p.dev, a, ln)
+             : p.brief ? launch_attn_short_bf16(ctx->geom, p.dev, a, ln)
              : bf16 ? launch_attn_bf16(ctx->geom, p.dev, a, p.row_blocks, p.pipelined, ln)
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
     if (p.max_splits > 1)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
-            return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
+            return p.brief ? launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, ln)
+                 : bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
                         : launch_merge_f32(ctx->geom, p.dev, a, p.max_splits, ln);
         }));
     return TC_OK;
@@ -1135,13 +1138,14 @@ int32_t tc_attn_kernel(const tc_ctx *ctx)
     if (!ctx || !ctx->plan.valid || ctx->cfg.dtype != TC_BF16) return 0;
     if (ctx->plan.decode) return 3;
     if (ctx->plan.pingpong) return 4;
+    if (ctx->plan.brief) return 5;
     if (ctx->plan.row_blocks != 1) return 0;
     return ctx->plan.pipelined ? 2 : 1;
 }
 
 tc_status tc_set_attn_kernel(tc_ctx *ctx, int32_t kind)
 {
-    if (!ctx || kind < 0 || kind > 4) return TC_ERR_INVALID;
+    if (!ctx || kind < 0 || kind > 5) return TC_ERR_INVALID;
     ctx->knobs.forced_attn_kernel = kind;
     ctx->plan.valid = false;
     return TC_OK;

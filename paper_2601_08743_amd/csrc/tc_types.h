@@ -13,6 +13,7 @@ constexpr int kAttnKeys = 64;        // bf16 kernel: keys per tile (4 pool block
 constexpr int kAttnMaxTiles = 256;   // bf16 kernel: key tiles per work item (block ids kept in LDS)
 constexpr int kPpMaxTiles = 1024;    // the same for the long-launch kernel, which has the LDS to spare
 constexpr int kPipeMaxTiles = 1024;  // and for the pipelined kernel (one work-group per CU)
+constexpr int kShortRows = 32;       // short-launch kernel: rows per work-group (its waves split the keys)
 constexpr int kF32Rows = 32;         // fp32 kernel: rows per work-group (its waves split the keys)
 constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
 constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item (block ids kept in LDS)

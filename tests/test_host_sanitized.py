@@ -274,6 +274,44 @@ def test_planner_random_batches(exe):
         _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
 
 
+def test_short_launch_plans(exe):
+    """What the short-launch kernel relies on: 32-row tiles, every (query, KV head, row tile) covered by
+    consecutive non-empty ranges of at most 256 key tiles; chosen by itself: at most 512 items, uncut
+    beyond 256.  Forced, it serves any batch; chosen, few tokens against few tables, neither long nor wide ones."""
+    rng = np.random.default_rng(17)
+    batches = [[(1050, 17)], [(0, 5)], [(33000, 3)], [(4086, 128)], [(60, 1), (61, 0), (0, 2)], [(24600, 512)] * 4]
+    for _ in range(60):
+        n = int(rng.integers(1, 24))
+        batches.append([(int(rng.integers(0, 12000)), int(2 ** rng.uniform(0, 8.5))) for _ in range(n)])
+    chosen = []
+    for (hq, hkv), kernel in [((28, 4), 0), ((28, 4), 5), ((40, 8), 0), ((3, 3), 5), ((96, 2), 5)]:
+        for PS in batches:
+            lines = run(exe, "short 32\nplan 1 %d %d 128 0 0 %d %d %s\n" % (hq, hkv, kernel, len(PS), " ".join("%d %d" % x for x in PS)))
+            head = list(map(int, lines[0].split()[1:]))
+            assert head[6] == 1                  # no range longer than its kernel's table
+            if kernel == 0 and (hq, hkv) == (28, 4):
+                chosen.append(head[7])
+            if head[7] == 0:
+                assert kernel == 0 or head[2]    # (a decode step)
+                continue
+            items = [tuple(map(int, l.split()[1:8])) for l in lines if l.startswith("i ")]
+            items = [x for x in items if x[0] >= 0]
+            G = hq // hkv
+            if kernel == 0:
+                assert len(items) <= 512 and (head[1] == 1 or len(items) <= 256)
+            cover = {}
+            for q, kvh, m0, tb, te, split, ns in items:
+                assert 0 < te - tb <= 256 and m0 % 32 == 0
+                cover.setdefault((q, kvh, m0), []).append((split, tb, te, ns))
+            assert set(cover) == {(q, h, m) for q, (P, S) in enumerate(PS) for h in range(hkv) for m in range(0, S * G, 32)}
+            for (q, _, _), parts in cover.items():
+                parts.sort()
+                P, S = PS[q]
+                assert [x[0] for x in parts] == list(range(parts[0][3])) and parts[0][1] == 0
+                assert all(a[2] == b[1] for a, b in zip(parts, parts[1:])) and parts[-1][2] == -(-P // 64) + -(-S // 64)
+    assert chosen[0] == 1 and chosen[3] == 0 and chosen[5] == 0
+
+
 def test_front_end_equals_the_checker(exe):
     rng = np.random.default_rng(5)
     tables, seen = {}, set()
