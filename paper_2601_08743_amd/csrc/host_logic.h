@@ -411,17 +411,22 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // ~0.85 us per 128 x 64 tile and CU): its own append launch costs ~10 us, and with 256 rows per
     // work-group a short launch would not fill the chip.  Measured: c3 (1140 items of ~24 tiles)
     // 207 + 12 us against 226 us in the general kernel, c4 775 + 14 us against 814 us in the pipelined
-    // one; c2 (17 us) and the micro-batches of the loading pipeline stay with the other kernels.
+    // one.  Since the append launch costs 7 us and not 10, shorter launches gain as well, if 256-row tiles
+    // are nearly as full as 128-row ones (54 batches estimated at 14 .. 80 us that pad by up to a fifth:
+    // 1.19 times as fast, two slower; where tiles pad by more 0.8 .. 1.2; below 14 us 0.75 .. 1.3).
     bool pp = false;
     if (bf16 && ctx->forced_row_blocks == 0) {
         if (ctx->forced_attn_kernel == 4) pp = true;
         else if (ctx->forced_attn_kernel == 0) {
-            double work = 0;
+            double work = 0, work_pp = 0;               // in 128-row tiles; the same with rows padded to this kernel's 256
             for (int i = 0; i < p.B; ++i)
-                if (p.suffix_len[i] > 0)
-                    work += (double)c.n_kv_heads * ((p.suffix_len[i] * G + kAttnRows - 1) / kAttnRows) *
-                            ((p.prefix_len[i] + p.suffix_len[i] + KT - 1) / KT);
-            pp = work * 0.85 / 256.0 >= 80.0;
+                if (p.suffix_len[i] > 0) {
+                    const double per_row_tile = (double)c.n_kv_heads * ((p.prefix_len[i] + p.suffix_len[i] + KT - 1) / KT);
+                    work += per_row_tile * ((p.suffix_len[i] * G + kAttnRows - 1) / kAttnRows);
+                    work_pp += per_row_tile * 2 * ((p.suffix_len[i] * G + 2 * kAttnRows - 1) / (2 * kAttnRows));
+                }
+            const double us = work * 0.85 / 256.0;
+            pp = us >= 80.0 || (us >= 14.0 && work_pp <= 1.2 * work);
         }
     }
     const bool unified = !bf16 || pp;
@@ -464,7 +469,10 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         for (int ns = 1; ns <= 32; ++ns) {
             if (ns > 1 && tiles / ns < 2.0) break;
             const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
-            const double per_cu = load <= 1.0 ? 1.0 : (load <= 2.0 ? 2.0 : load);
+            // (uncut items of the long-launch kernel differ in length, start longest first and end together rather
+            // than in rounds: 272 items of 16 queries, 105 us in one range each, 115 in two; cut ones are equally
+            // long: 52 x 4 items 40 us, 52 x 5 46)
+            const double per_cu = load <= 1.0 ? 1.0 : (load <= 2.0 && !(pp && ns == 1) ? 2.0 : load);
             const double merge = ns > 1 ? 1.0 + 0.93e-4 * ns * rows : 0.0;   // fp16 partials: 264 B per row and partition
             // (two work-groups on a CU overlap each other's stalls; the long-launch kernel runs one per CU)
             const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 && !pp ? 0.7 : 1.0) + 3.0 + merge;
