@@ -511,9 +511,18 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     splits_of_q.assign(p.B, 1);
     p.max_splits = 1;
     struct Bucket { int32_t first, count, tiles; };  // consecutive items of one (query, KV head, partition)
+    // (a query has no more partitions than key tiles, whatever count a caller forces)
+    auto partitions = [&](int n_tiles) {
+        const int n = cut_range > 0 ? (n_tiles + cut_range - 1) / cut_range : want;
+        return std::max(1, std::min(n, ctx->forced_splits > 0 ? n_tiles : n_tiles / 2));
+    };
+    int64_t n_flat = 0;
+    for (int i = 0; i < p.B; ++i)
+        if (p.suffix_len[i] > 0)
+            n_flat += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + RT - 1) / RT) * partitions(tiles_of(p.prefix_len[i], p.suffix_len[i]));
     std::vector<AttnItem> flat;
     std::vector<Bucket> buckets;
-    flat.reserve((size_t)std::max<int64_t>(base, 0) * (size_t)std::max(1, want));
+    flat.reserve((size_t)n_flat);
     int n_groups = 0;
     for (int i = 0; i < p.B; ++i) {
         const int S = p.suffix_len[i], P = p.prefix_len[i];
@@ -522,8 +531,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // last block a tile load may touch: bf16 reads only prefix blocks from the pool
         const int last_blk = std::max(0, (unified ? (P + S + kBlockTokens - 1) / kBlockTokens
                                                   : (P + kBlockTokens - 1) / kBlockTokens) - 1);
-        if (cut_range > 0) want = (n_tiles + cut_range - 1) / cut_range;
-        int ns = std::min(want, ctx->forced_splits > 0 ? n_tiles : std::max(1, n_tiles / 2));
+        int ns = partitions(n_tiles);
         const int cap = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : general_cap;   // block ids of a range fit LDS
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
         ns = std::max(1, std::min(ns, n_tiles));

@@ -197,6 +197,26 @@ def test_planner_partition_limit_with_forced_splits(exe):
             assert info["max_splits"] == want, (kernel, splits, info["max_splits"])
 
 
+@pytest.mark.parametrize("splits", [1000, 10 ** 6, 2 * 10 ** 9])
+@pytest.mark.parametrize("kernel,dtype", [(0, 1), (1, 1), (4, 1), (5, 1), (0, 0)])
+def test_planner_takes_any_forced_partition_count(exe, splits, kernel, dtype):
+    """tc_set_kv_splits accepts any count; more partitions than key tiles means one per key tile, and
+    the planner's memory goes by that and not by the number asked for."""
+    PS = [(2000, 128), (3000, 100)]
+    lines = run(exe, "plan %d 28 4 128 %d 0 %d 2 2000 128 3000 100\n" % (dtype, splits, kernel))
+    head = list(map(int, lines[0].split()[1:]))
+    unified = dtype == 0 or head[3]
+    want = [-(-(P + S) // 64) if unified else -(-P // 64) + -(-S // 64) for P, S in PS]
+    assert head[6] == 1 and head[1] == max(want)
+    ns = {}
+    for l in lines:
+        if l.startswith("i "):
+            q, n = (int(l.split()[k]) for k in (1, 7))
+            if q >= 0:
+                ns[q] = n
+    assert [ns[0], ns[1]] == want
+
+
 def test_planner_paper_shapes(exe):
     c4 = [(24625, 512)] * 4
     info, items = _plan(exe, 32, 8, c4)
