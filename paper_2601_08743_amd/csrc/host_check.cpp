@@ -39,7 +39,7 @@ int main()
     SeqBlocks seq;
     tc_trie *trie = nullptr;
     std::string cmd;
-    int32_t short_rows = 0;
+    int32_t short_rows = kShortRows;
     while (std::cin >> cmd) {
         if (cmd == "rule") {
             int policy;

@@ -212,8 +212,7 @@ struct PlanKnobs {
     int32_t forced_splits = 0;
     int32_t forced_row_blocks = 0;
     int32_t forced_attn_kernel = 0;   // 1 general, 2 pipelined, 3 decode (where it applies), 4 long launches, 5 short launches
-    int32_t short_rows = 0;           // rows per work item of the short-launch kernel (tc_create sets it), 0: do without that kernel
-    int32_t f32_rows = 4;             // fp32: rows per work item (tc_create sets the kernel's; any other plans the same way)
+    int32_t short_rows = kShortRows;  // rows per work item of the short-launch kernel, 0: do without that kernel
 };
 
 // fp32 batches: the key range of a work item, in key tiles.  A wave works through a quarter of its
@@ -438,7 +437,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // wave per SIMD) is kept as an option: it is slower until its matrix and vector work overlap
     const int rb = pp ? 2 : (bf16 && ctx->forced_row_blocks > 0) ? ctx->forced_row_blocks : 1;
     p.row_blocks = rb;
-    int RT = bf16 ? kAttnRows * rb : ctx->f32_rows;
+    int RT = bf16 ? kAttnRows * rb : kF32Rows;
     int64_t base = 0, tiles_sum = 0, n_q = 0;
     auto count_items = [&] {
         base = tiles_sum = n_q = 0;

@@ -435,8 +435,6 @@ tc_status tc_create(const tc_config *cfg, void *kv_pool_dev, size_t pool_bytes, 
     g.head_bytes = g.D * g.esize;
 
     ctx->rule.reset(make_rule(cfg->policy));
-    ctx->knobs.f32_rows = kF32Rows;
-    ctx->knobs.short_rows = kShortRows;
 
     ctx->slots.resize(cfg->table_capacity);
     for (int s = 0; s < cfg->table_capacity; ++s) {

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(ROOT, "paper_2601_08743_amd", "csrc")
 
 # key tiles whose block ids one work item may keep in LDS, per kernel (csrc/tc_types.h)
-CAP_GENERAL, CAP_PIPE, CAP_PP = 256, 1024, 1024
+CAP_GENERAL, CAP_PIPE, CAP_PP, CAP_F32 = 256, 1024, 1024, 512
 
 
 @pytest.fixture(scope="module")
@@ -121,7 +121,7 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128):
     assert head[0] == len(items)
     ghead = [l for l in lines if l.startswith("groups ")][0].split()
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
-    info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6],
+    info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
                 n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows])
     assert int(ghead[1]) == len(groups)
     return info, items
@@ -136,8 +136,8 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
     if info["decode"]:
         cap, rt, unified = CAP_GENERAL, None, False
     else:
-        cap = 10 ** 9 if dtype == 0 else CAP_PP if info["pingpong"] else CAP_PIPE if info["pipelined"] else CAP_GENERAL
-        rt = 4 if dtype == 0 else 128 * info["row_blocks"]
+        cap = CAP_F32 if dtype == 0 else CAP_PP if info["pingpong"] else CAP_PIPE if info["pipelined"] else CAP_GENERAL
+        rt = 32 if dtype == 0 or info["brief"] else 128 * info["row_blocks"]      # what the kernels stride their rows by
         unified = dtype == 0 or bool(info["pingpong"])
     cover = {}
     if not info["decode"] and dtype == 1:
@@ -165,6 +165,7 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
         else:
             n_tiles = -(-(P + S) // 64) if unified else -(-P // 64) + -(-S // 64)
             rows = list(range(0, S * G, rt))
+        assert {k[1:] for k in cover if k[0] == i} == {(kvh, m0) for kvh in range(Hkv) for m0 in rows}
         for kvh in range(Hkv):
             for m0 in rows:
                 parts = sorted(cover[(i, kvh, m0)])
@@ -232,6 +233,10 @@ def test_planner_paper_shapes(exe):
     info, items = _plan(exe, 28, 4, c2)
     _check_plan(info, items, 28, 4, c2)
     assert info["pipelined"] == 1 and info["max_splits"] == 8
+    for PS, chosen in (([(1050, 17)], 1), ([(1050, 17)] * 8, 1), (c2, 0), (c4, 0)):     # a short question goes to the short-launch kernel
+        info, items = _plan(exe, 28, 4, PS)
+        _check_plan(info, items, 28, 4, PS)
+        assert info["brief"] == chosen
     dec = [(5000, 1), (17, 1), (0, 1), (900, 0)]
     info, items = _plan(exe, 28, 4, dec)
     assert info["decode"] == 1
@@ -289,7 +294,7 @@ def test_planner_random_batches(exe):
                int(rng.choice([0, 1, 64, int(rng.integers(0, 600))]))) for _ in range(B)]
         dtype = int(rng.random() < 0.85)
         kw = dict(splits=int(rng.choice([0, 0, 1, 2, 5, 40])), rb=int(rng.choice([0, 0, 0, 1, 2])) if dtype else 0,
-                  kernel=int(rng.choice([0, 0, 1, 2, 3, 4])) if dtype else 0)
+                  kernel=int(rng.choice([0, 0, 1, 2, 3, 4, 5])) if dtype else 0)
         info, items = _plan(exe, Hkv * G, Hkv, PS, dtype=dtype, D=128 if dtype else 64, **kw)
         _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
 
