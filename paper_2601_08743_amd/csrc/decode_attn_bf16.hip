@@ -263,7 +263,6 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
         }
     }
     __syncthreads();
-    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     for (int idx = tid; idx < G * 32; idx += 256) {
         const int row = idx >> 5, d = 4 * (idx & 31);
         float M = -INFINITY;
@@ -281,7 +280,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
         }
-        const int64_t slot = (int64_t)it.split * n_rows + (int64_t)it.cu * g.Hq + it.kvh * G + row;
+        const int64_t slot = (int64_t)(it.part0 + it.split) * g.Hq + it.kvh * G + row;
         *(f32x4 *)(a.part_o + slot * 128 + d) = acc;
         if (d == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(M, L);
     }
@@ -308,8 +307,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 // groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
 // row of up to 4 * kGroups partitions costs one round trip - and fold their results through LDS.  A
 // work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
-// threads would load what nobody needs.  (Slots of partitions that the query, but not the batch, lacks
-// exist in the buffer; they are loaded and ignored.)
+// threads would load what nobody needs.  (Beyond a row's last partition the last one is loaded again and ignored.)
 // Without kSelf there is no new token to add and rows of one partition are left alone (they were written
 // directly): the merge of the short-launch prefill kernel's partitions.
 template <int kGroups, bool kSelf>
@@ -322,25 +320,25 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
     const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
     const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
     const int n = row / g.Hq, head = row - n * g.Hq, kvh = head / g.G;      // n: the token (queries may bring none)
+    const int slot0 = b.part_slot[n], ns = b.part_slot[n + 1] - slot0;
     float2 ml[kBatch];
     f32x4 po[kBatch];
     auto fetch = [&](int s0) {
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             if (kGroups * j >= max_splits) break;
-            const int64_t slot = (int64_t)min(s0 + kGroups * j, max_splits - 1) * n_rows + row;
+            const int64_t slot = (int64_t)(slot0 + min(s0 + kGroups * j, ns - 1)) * g.Hq + head;
             ml[j] = *(const float2 *)(a.part_ml + slot * 2);
             po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
         }
     };
-    fetch(grp);
     uint2 q2, k2, v2;
     if (kSelf) {
         q2 = *(const uint2 *)((const unsigned short *)a.q + (int64_t)row * 128 + d);
         k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
         v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
     }
-    const int ns = b.splits_of_q[b.tok_q[n]];
+    if (kSelf || ns > 0) fetch(grp);         // (a decode step has at least one partition)
     float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     auto fold = [&](float m, float l, f32x4 o) {

@@ -15,7 +15,8 @@
 //   short <rows>                    rows per work item of the short-launch kernel in the plans that follow (0: without it)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
-//                                      one line "i q kvh m0 tile_begin tile_end split n_splits group" per item,
+//                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0" per item,
+//                                      "parts <floats>" and, for kernels that keep partials by row, the tokens' first slots,
 //                                      "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
@@ -126,8 +127,16 @@ int main()
             std::printf("plan %d %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
                         p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
             for (const AttnItem &it : items)
-                std::printf("i %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
-                            it.q < 0 ? -1 : it.group);
+                std::printf("i %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
+                            it.q < 0 ? -1 : it.group, it.part0);
+            std::vector<int32_t> slots;
+            if (ok && parts_by_row(c, p)) {
+                slots.resize((size_t)p.total_S + 1);
+                fill_part_slots(p, splits, slots.data());
+            }
+            std::printf("parts %zu", part_floats(c, p));
+            for (int32_t s : slots) std::printf(" %d", s);
+            std::printf("\n");
             std::printf("groups %d %d\n", (int)groups.size(), p.n_groups);
             for (const MergeGroup &mg : groups) std::printf("g %d %d %d %d %d\n", mg.kvh, mg.m0, mg.n_splits, mg.cu, mg.S);
         } else if (cmd == "trie") {

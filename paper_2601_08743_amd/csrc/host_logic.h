@@ -190,6 +190,7 @@ struct StageHalves {
 struct Plan {
     bool valid = false;
     int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
+    int64_t n_part_slots = 0;   // kernels that keep partials by row: (suffix token, partition) pairs of the batch
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups; the suffix is appended first
@@ -330,6 +331,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.decode = false;
     p.pingpong = false;
     p.brief = false;
+    p.n_part_slots = 0;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
     // the four waves of a work-group and over `ns` work-groups.  A work-group holds a CU (its ring of
@@ -374,11 +376,14 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             ns = std::max(1, std::min(ns, std::max(n_tiles, 1)));
             splits_of_q[i] = ns;
             p.max_splits = std::max(p.max_splits, ns);
+            const int32_t part0 = (int32_t)p.n_part_slots;
+            p.n_part_slots += ns;
             const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
             const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
             for (int h = 0; h < c.n_kv_heads; ++h)
                 for (int s = 0; s < ns; ++s) {
                     AttnItem it{};
+                    it.part0 = part0;
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
                     it.split = s; it.n_splits = ns; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
@@ -523,6 +528,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     std::vector<Bucket> buckets;
     flat.reserve((size_t)n_flat);
     int n_groups = 0;
+    const bool by_row = !bf16 || p.brief;            // how this kernel keeps its partials
     for (int i = 0; i < p.B; ++i) {
         const int S = p.suffix_len[i], P = p.prefix_len[i];
         if (S <= 0) continue;
@@ -561,6 +567,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
         splits_of_q[i] = ns;
         p.max_splits = std::max(p.max_splits, ns);
+        const int32_t part0 = (int32_t)p.n_part_slots;
+        if (by_row && ns > 1) p.n_part_slots += (int64_t)S * ns;
         const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
         const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
         for (int h = 0; h < c.n_kv_heads; ++h) {
@@ -569,7 +577,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 Bucket bucket{(int32_t)flat.size(), 0, t1 - t0};
                 AttnItem proto{};                       // what the row tiles share
                 proto.q = i; proto.kvh = h; proto.tile_begin = t0; proto.tile_end = t1; proto.split = s; proto.n_splits = ns;
-                proto.P = P; proto.S = S; proto.cu = p.cu_seqlens[i];
+                proto.P = P; proto.S = S; proto.cu = p.cu_seqlens[i]; proto.part0 = part0;
                 for (int k = 0; k < 16; ++k) {
                     const int idx = std::min(t0 * (KT / kBlockTokens) + k, last_blk);
                     proto.bid[k] = bt[idx] | (pad_of ? (int32_t)((uint32_t)pad_of[idx] << kPadShift) : 0);
@@ -662,6 +670,29 @@ inline bool plan_attention(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
     return true;
 }
 
+// Split-KV partials.  The fp32, decode and short-launch kernels keep them by row: a suffix token has one slot
+// for each of its query's partitions (none where the query is not cut; a decode step always has them), a
+// slot holds D + 2 floats for each query head, and slots follow one another token by token - a batch pays
+// for the partitions that its queries have, not for its longest query's count everywhere.  The other bf16 kernels
+// keep, per (partition, group, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.
+inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode || ((c.dtype != TC_BF16 || p.brief) && p.max_splits > 1); }
 
+inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the batch's partials, in floats
+{
+    if (parts_by_row(c, p)) return (size_t)p.n_part_slots * c.n_q_heads * (c.head_dim + 2);
+    return p.max_splits > 1 ? (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * (64 + 2) : 0;
+}
+
+// The first slot of every suffix token, and the slot behind the last one ([total_S + 1]).
+inline void fill_part_slots(const Plan &p, const std::vector<int32_t> &splits_of_q, int32_t *out)
+{
+    int32_t at = 0;
+    for (int i = 0; i < p.B; ++i)
+        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) {
+            out[n] = at;
+            if (p.decode || splits_of_q[i] > 1) at += splits_of_q[i];
+        }
+    out[p.total_S] = at;
+}
 
 }  // namespace tc

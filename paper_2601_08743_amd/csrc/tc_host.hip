@@ -264,18 +264,15 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
                                          std::max(P - p0, 0), std::min(end - p0, (int)kBlockTokens)});
         }
     const size_t o_ab = take(ablk.size() * 4);
-    const size_t o_sb = take(sblk.size() * 4), o_sp = take(B), o_tq = take(p.total_S);
+    const size_t o_sb = take(sblk.size() * 4), o_tq = take(p.total_S);
+    const bool by_row = parts_by_row(ctx->cfg, p);
+    const size_t o_ps = take(by_row ? (size_t)p.total_S + 1 : 0);
     const size_t o_it = take(items.size() * (sizeof(AttnItem) / 4));
     const size_t o_gr = take(groups.size() * (sizeof(MergeGroup) / 4));
     const size_t o_rp = take(p.rope ? B : 0), o_rf = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     const size_t total = std::max(off, size_t(8));          // (a multiple of 8: the upload moves 16 bytes at a time)
-    // split-KV partials.  bf16 kernels: per (partition, group, row block) 128 rows x (128 fp16 + 2
-    // floats) in fragment order, counted in floats; fp32, decode and short-launch kernels: per (partition, new
-    // token, head) D + 2 floats
-    const size_t part_need = !(p.max_splits > 1 || p.decode) ? 0
-        : ctx->cfg.dtype == TC_BF16 && !p.decode && !p.brief
-            ? (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * (64 + 2)
-            : (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * (ctx->cfg.head_dim + 2);
+    if (p.n_part_slots > INT32_MAX) return fail(ctx, TC_ERR_CAPACITY, "attn: %lld split-KV partials", (long long)p.n_part_slots);
+    const size_t part_need = part_floats(ctx->cfg, p);
     if (fixed && part_need > kScratchPartFloats)
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the split-KV partials need %zu floats, the fixed workspace holds %zu",
                     part_need, kScratchPartFloats);
@@ -292,7 +289,6 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         std::memcpy(h + o_cu, p.cu_seqlens.data(), (B + 1) * 4);
         std::memcpy(h + o_pl, p.prefix_len.data(), B * 4);
         std::memcpy(h + o_sl, p.suffix_len.data(), B * 4);
-        std::memcpy(h + o_sp, splits_of_q.data(), B * 4);
         if (!seg_end_of_q.empty()) std::memcpy(h + o_se, seg_end_of_q.data(), B * 4);
     }
     for (size_t k = 0; k < nseg; ++k) {
@@ -302,6 +298,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     if (!sblk.empty()) std::memcpy(h + o_sb, sblk.data(), sblk.size() * sizeof(StitchBlk));
     for (int i = 0; i < p.B; ++i)
         for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) h[o_tq + n] = i;
+    if (by_row) fill_part_slots(p, splits_of_q, h + o_ps);
     if (!items.empty()) std::memcpy(h + o_it, items.data(), items.size() * sizeof(AttnItem));
     if (!groups.empty()) std::memcpy(h + o_gr, groups.data(), groups.size() * sizeof(MergeGroup));
     if (p.rope) {
@@ -321,7 +318,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.dev.block_table = d + o_bt; p.dev.cu_seqlens = d + o_cu; p.dev.prefix_len = d + o_pl;
     p.dev.suffix_len = d + o_sl; p.dev.seg_start = d + o_ss; p.dev.seg_len = d + o_sn;
     p.dev.seg_slot = d + o_st; p.dev.seg_end_of_q = d + o_se;
-    p.dev.stitch_blk = (const StitchBlk *)(d + o_sb); p.dev.splits_of_q = d + o_sp;
+    p.dev.stitch_blk = (const StitchBlk *)(d + o_sb); p.dev.part_slot = by_row ? d + o_ps : nullptr;
     p.dev.tok_q = d + o_tq;
     p.dev.append_blk = (const AppendBlk *)(d + o_ab);
     p.dev.n_append_blk = (int32_t)ablk.size();
@@ -951,7 +948,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
-        a.part_ml = p.part + (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
+        a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_decode_finish(ctx->geom, p.dev, a, p.max_splits, ln); }));
         return TC_OK;
@@ -968,7 +965,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.part_o = p.part;
     a.part_ml = !p.part ? nullptr
               : bf16 && !p.brief ? p.part + (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * 64
-                     : p.part + (size_t)p.max_splits * p.total_S * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
+                     : p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
     TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) {
         return p.pingpong ? launch_attn_pp_bf16(ctx->geom, p.dev, a, ln)
              : p.brief ? launch_attn_short_bf16(ctx->geom, p.dev, a, ln)
@@ -979,7 +976,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
             return p.brief ? launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, ln)
                  : bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
-                        : launch_merge_f32(ctx->geom, p.dev, a, p.max_splits, ln);
+                        : launch_merge_f32(ctx->geom, p.dev, a, ln);
         }));
     return TC_OK;
 }

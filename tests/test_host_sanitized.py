@@ -122,7 +122,8 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128):
     ghead = [l for l in lines if l.startswith("groups ")][0].split()
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
-                n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows])
+                n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part0=[r[8] for r in rows])
+    info["part_floats"], *info["slots"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
     assert int(ghead[1]) == len(groups)
     return info, items
 
@@ -173,6 +174,38 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
                 assert parts[0][1] == 0 and parts[-1][2] == n_tiles
                 assert all(a[2] == b[1] for a, b in zip(parts, parts[1:]))
     return max([te - tb for q, _, _, tb, te, _, _ in items if q >= 0], default=0)
+
+
+def _check_slots(info, items, Hq, D, PS):
+    """Partials kept by row: every (token, partition) of a cut query - of any query in a decode step - has a slot
+    of its own, the items write and the merge reads the same ones, and the buffer holds exactly those."""
+    ns, base = {}, np.cumsum([0] + [S for _, S in PS])
+    for it, part0 in zip(items, info["item_part0"]):
+        if it[0] >= 0:
+            ns[it[0]] = it[6]
+            if info["decode"] or it[6] > 1:
+                assert part0 == info["slots"][base[it[0]]]
+                for t in range(PS[it[0]][1]):                # where the attention kernels write
+                    assert part0 + t * it[6] + it[5] == info["slots"][base[it[0]] + t] + it[5]
+    counts = [n if info["decode"] or n > 1 else 0 for q, (_, S) in enumerate(PS) for n in [ns.get(q, 0)] * S]
+    assert info["slots"] == np.cumsum([0] + counts).tolist()
+    assert info["part_floats"] == sum(counts) * Hq * (D + 2)
+
+
+# Batches of one long sequence among short ones, which the workspace of the entry point that allocates nothing
+# (15 Mi floats of partials) holds: the long one's partition count is not everybody's.
+WORKSPACE = 15 << 20
+
+
+@pytest.mark.parametrize("Hq,Hkv,PS,kernel", [
+    (32, 1, [(45776, 1)] + [(20, 1)] * 15, "decode"), (32, 2, [(300, 1)] * 63 + [(20000, 1)], "decode"),
+    (32, 1, [(300, 1)] * 31 + [(20000, 1)], "decode"), (32, 1, [(300, 1)] * 63 + [(20000, 1)], "decode"),
+    (28, 4, [(12800, 5)] + [(200, 4)] * 3, "brief")])
+def test_partials_of_ragged_batches_stay_small(exe, Hq, Hkv, PS, kernel):
+    info, items = _plan(exe, Hq, Hkv, PS, kernel=0 if kernel == "decode" else 5, splits=0 if kernel == "decode" else 40)
+    assert info["ok"] and info[kernel]
+    _check_slots(info, items, Hq, 128, PS)
+    assert info["max_splits"] > 30 and info["part_floats"] <= WORKSPACE // 4
 
 
 def test_planner_partition_limit_with_forced_splits(exe):
@@ -297,6 +330,8 @@ def test_planner_random_batches(exe):
                   kernel=int(rng.choice([0, 0, 1, 2, 3, 4, 5])) if dtype else 0)
         info, items = _plan(exe, Hkv * G, Hkv, PS, dtype=dtype, D=128 if dtype else 64, **kw)
         _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
+        if info["slots"]:
+            _check_slots(info, items, Hkv * G, 128 if dtype else 64, PS)
 
 
 def test_short_launch_plans(exe):

@@ -91,6 +91,49 @@ def test_noalloc_other_kernels():
     dw.close()
 
 
+def _ragged(H, dtype, hq, hkv, D, lens, suffix, kernel, splits=0):
+    """One query per table, through both entry points; returns the partition count."""
+    cfg = W.WorkloadConfig("n", 1, hq, hkv, D, dtype, len(lens), (1, max(lens)), len(lens), (1, 1), "uniform", (1, 9), len(lens), 317)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = lens
+    wl.queries[:] = [np.array([i], dtype=np.int32) for i in range(len(lens))]
+    wl.suffix_len[:] = suffix
+    dw = H.DeviceWorkload(wl)
+    dw.ctx.tc_set_kv_splits(splits)
+    if kernel == 5:
+        dw.ctx.tc_set_attn_kernel(5)
+    bt, pl = dw.stitch()
+    out, qkv = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_attn_kernel() == kernel
+    n, got = dw.ctx.tc_kv_splits(), torch.full_like(out, float("nan"))
+    dw.ctx.tc_prefill_attn_noalloc(0, *(H.to_dev(x, cfg) for x in qkv), got, wl.cu_seqlens, bt, pl, wl.suffix_len, wl.sm_scale)
+    torch.cuda.synchronize()
+    assert dw.ctx.tc_attn_kernel() == kernel and dw.ctx.tc_kv_splits() == n
+    assert torch.isfinite(out.float()).all() and torch.equal(out, got)
+    ref = H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+    g64 = H.out_to_f64(got, cfg)
+    err = max(float(np.abs(g64[int(wl.cu_seqlens[i]):int(wl.cu_seqlens[i + 1])] - r).max()) for i, r in ref.items() if r.size)
+    assert err <= (1e-5 if dtype == "f32" else 2.2e-2), err      # as the kernels' own tests: fp32 sums; 8-bit weights and outputs, |v| < 5.5
+    dw.close()
+    return n
+
+
+def test_noalloc_ragged_decode():
+    """One long sequence among short ones: its many key ranges are its own, the others have one or two (all of them
+    as often as the longest would be 20.9 M floats of partials where the workspace has 15.7 M)."""
+    import harness as H
+    assert _ragged(H, "bf16", 32, 1, 128, [20000] + [300] * 31, [1] * 32, 3) > 100
+
+
+def test_noalloc_short_launch_and_fp32():
+    """Kernels that keep their partials by row: queries in one range (written directly) among cut ones, a query without
+    new tokens."""
+    import harness as H
+    assert _ragged(H, "bf16", 28, 4, 128, [3000, 40, 700, 1500], [5, 3, 0, 20], 5, splits=9) == 9
+    assert _ragged(H, "f32", 8, 2, 64, [2100, 30, 500, 900], [23, 1, 0, 40], 0) > 1
+    assert _ragged(H, "f32", 32, 8, 128, [7744, 2119], [23, 220], 0) >= 1
+
+
 def test_noalloc_refuses_what_does_not_fit():
     """A batch whose partials exceed the fixed workspace is refused with TC_ERR_CAPACITY and
     enqueues nothing; the allocating entry point still serves it."""
