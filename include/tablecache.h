@@ -256,9 +256,11 @@ tc_status tc_prefill_attn(tc_ctx *ctx, int32_t layer, const void *q, const void 
  * tc_prefill_attn puts them in buffers it allocates and grows on demand; this entry point puts them
  * in a fixed 64 MiB workspace that the library's code object carries (4 MiB plan, 60 MiB partials;
  * one copy per GPU, held until the process ends) and calls no hipMalloc, hipFree or other allocating
- * routine.  A batch whose plan or partials do not fit is refused with TC_ERR_CAPACITY and nothing
- * is enqueued (for scale: c2 needs 0.1 MiB + 7.6 MiB, a c5 micro-batch of 8 queries 0.5 + 21.6 MiB;
- * c3 and c4 run unsplit and need no partials).
+ * routine.  A batch that does not fit as tc_prefill_attn would plan it is planned for the least space
+ * (fewer or no partitions; the results then differ from tc_prefill_attn's by rounding); one that
+ * does not fit even so - its work items alone, or the partitions that tc_set_kv_splits forces - is
+ * refused with TC_ERR_CAPACITY and nothing is enqueued (for scale: c2 needs 0.03 MiB + 7.2 MiB, a c5
+ * micro-batch of 8 queries up to 0.1 + 37 MiB; c3 and c4 run unsplit and need no partials).
  * Every call re-plans from its integer arguments unless they equal those of the previous call
  * through this entry point (a batch stitched by tc_stitch_kv is planned again here, once).
  * All contexts on one GPU share that GPU's workspace, which keeps the last call's contents (nothing

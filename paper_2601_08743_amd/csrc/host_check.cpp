@@ -13,10 +13,11 @@
 //   f <k> b0 .. bk-1                release
 //   stage <cap> <n> then n sizes     place n plans in a staging buffer -> one line "s <at> <parts>" each
 //   short <rows>                    rows per work item of the short-launch kernel in the plans that follow (0: without it)
+//   within <ints> <floats>          plan for a workspace of that many integers and floats of partials (0 0: as much as it takes)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
 //                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0" per item,
-//                                      "parts <floats>" and, for kernels that keep partials by row, the tokens' first slots,
+//                                      "ints <size of the device copy> <compact>", "parts <floats>" and, for kernels that keep partials by row, the tokens' first slots,
 //                                      "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
@@ -41,6 +42,7 @@ int main()
     tc_trie *trie = nullptr;
     std::string cmd;
     int32_t short_rows = kShortRows;
+    size_t max_ints = 0, max_floats = 0;
     while (std::cin >> cmd) {
         if (cmd == "rule") {
             int policy;
@@ -93,6 +95,8 @@ int main()
             }
         } else if (cmd == "short") {
             std::cin >> short_rows;
+        } else if (cmd == "within") {
+            std::cin >> max_ints >> max_floats;
         } else if (cmd == "plan") {
             tc_config c{};
             PlanKnobs knobs;
@@ -123,7 +127,8 @@ int main()
             std::vector<AttnItem> items;
             std::vector<int32_t> splits;
             std::vector<MergeGroup> groups;
-            const bool ok = plan_attention(c, knobs, p, items, splits, groups);
+            const bool ok = max_ints ? plan_attention_within(c, knobs, p, items, splits, groups, max_ints, max_floats)
+                                     : plan_attention(c, knobs, p, items, splits, groups);
             std::printf("plan %d %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
                         p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
             for (const AttnItem &it : items)
@@ -134,6 +139,7 @@ int main()
                 slots.resize((size_t)p.total_S + 1);
                 fill_part_slots(p, splits, slots.data());
             }
+            std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, append_blocks(p).size(), items.size(), groups.size()).total, p.compact ? 1 : 0);
             std::printf("parts %zu", part_floats(c, p));
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");

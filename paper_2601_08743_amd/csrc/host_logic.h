@@ -190,10 +190,12 @@ struct StageHalves {
 struct Plan {
     bool valid = false;
     int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
+    int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
     int64_t n_part_slots = 0;   // kernels that keep partials by row: (suffix token, partition) pairs of the batch
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups; the suffix is appended first
+    bool compact = false;       // planned for the least space (a batch that did not fit the static workspace otherwise)
     bool brief = false;         // bf16, 32 rows per work-group, its waves split the keys: the short-launch kernel
     bool rope = false;          // the stitch re-encodes keys by position (Sec. 4.1.1)
     std::vector<int32_t> rope_pos0;      // [B]
@@ -214,6 +216,11 @@ struct PlanKnobs {
     int32_t forced_row_blocks = 0;
     int32_t forced_attn_kernel = 0;   // 1 general, 2 pipelined, 3 decode (where it applies), 4 long launches, 5 short launches
     int32_t short_rows = kShortRows;  // rows per work item of the short-launch kernel, 0: do without that kernel
+    // For callers whose workspace is fixed: floats there are for partials (0: as many as it takes), and whether to
+    // plan for the least space - one partition where a kernel can, no kernel that needs more than the general one
+    // unless its launch is long.
+    size_t part_cap = 0;
+    bool compact = false;
 };
 
 // fp32 batches: the key range of a work item, in key tiles.  A wave works through a quarter of its
@@ -223,7 +230,7 @@ struct PlanKnobs {
 // a launch takes is its full rounds plus the last one, however few items that holds: ranges are cut
 // so that the rounds come out full.  The merge costs a launch of ~2.5 us and its traffic.
 // Measured (8 queries, 23 k keys, 8 / 2 heads of 64): 102 us against 118..127 us for one or two ranges a query.
-inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int key_tile)
+inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
 {
     const int G = c.n_q_heads / c.n_kv_heads;
     const double unit_us = 1.9 * c.head_dim / 64.0;
@@ -247,6 +254,7 @@ inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int k
             item = std::max(item, per_wave);
             if (ns > 1) partial_rows += (double)S * c.n_q_heads * ns;
         }
+        if (part_cap > 0 && partial_rows * (c.head_dim + 2) > (double)part_cap) continue;
         const int64_t rest = n % 512;
         const double us = unit_us * ((double)(n / 512) * 2.0 * (units / (double)n) + (rest == 0 ? 0.0 : rest <= 256 ? 1.25 * item : 2.0 * item)) +
                           (partial_rows > 0 ? 2.5 + 2e-6 * partial_rows * c.head_dim : 0.0);
@@ -332,6 +340,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = false;
     p.brief = false;
     p.n_part_slots = 0;
+    p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
     // the four waves of a work-group and over `ns` work-groups.  A work-group holds a CU (its ring of
@@ -354,7 +363,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             return n;
         };
         int L = kAttnMaxTiles;
-        if (items_at(L) <= kCus) {                      // one round is possible: the shortest ranges that still fit it
+        if (!ctx->compact && items_at(L) <= kCus) {                      // one round is possible: the shortest ranges that still fit it
             int lo = kMinRange, hi = kAttnMaxTiles;     // items_at is non-increasing in L
             while (lo < hi) {
                 const int mid = (lo + hi) / 2;
@@ -430,7 +439,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     work_pp += per_row_tile * 2 * ((p.suffix_len[i] * G + 2 * kAttnRows - 1) / (2 * kAttnRows));
                 }
             const double us = work * 0.85 / 256.0;
-            pp = us >= 80.0 || (us >= 14.0 && work_pp <= 1.2 * work);
+            pp = us >= 80.0 || (!ctx->compact && us >= 14.0 && work_pp <= 1.2 * work);
         }
     }
     const bool unified = !bf16 || pp;
@@ -464,7 +473,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
     int want = 1, cut_range = 0;           // (cut_range: the length of a range in key tiles, where the queries are cut by that)
     if (ctx->forced_splits > 0) want = ctx->forced_splits;
-    else if (!bf16 && base > 0) cut_range = plan_f32_range(c, p, RT, KT);
+    else if (ctx->compact) want = 1;
+    else if (!bf16 && base > 0) cut_range = plan_f32_range(c, p, RT, KT, ctx->part_cap);
     else if (base > 0) {
         const double tiles = (double)tiles_sum / (double)n_q;
         const double items_per_bucket = (double)base / (double)(n_q * c.n_kv_heads);
@@ -472,6 +482,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         double best = 1e30, us = 0;
         for (int ns = 1; ns <= 32; ++ns) {
             if (ns > 1 && tiles / ns < 2.0) break;
+            if (ns > 1 && ctx->part_cap > 0 && (double)ns * base * RT * (64 + 2) > (double)ctx->part_cap) break;
             const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
             // (uncut items of the long-launch kernel differ in length, start longest first and end together rather
             // than in rounds: 272 items of 16 queries, 105 us in one range each, 115 in two; cut ones are equally
@@ -505,7 +516,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     }
     if (bf16 && !pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 5) {
         p.brief = true;
-        if (ctx->forced_splits == 0) cut_range = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).range;
+        if (ctx->forced_splits == 0 && !ctx->compact) cut_range = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).range;
         want = std::max(1, ctx->forced_splits);
     }
     if (p.brief) {
@@ -537,7 +548,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         const int last_blk = std::max(0, (unified ? (P + S + kBlockTokens - 1) / kBlockTokens
                                                   : (P + kBlockTokens - 1) / kBlockTokens) - 1);
         int ns = partitions(n_tiles);
-        const int cap = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : general_cap;   // block ids of a range fit LDS
+        // block ids of a range fit LDS (the fp32 kernel can fetch those that do not from memory, which is slower)
+        const int cap = !bf16 ? (ctx->compact ? n_tiles : kF32MaxTiles) : pp ? kPpMaxTiles : general_cap;
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
         ns = std::max(1, std::min(ns, n_tiles));
         const int n_mt = (S * G + RT - 1) / RT;
@@ -646,10 +658,11 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                   (ctx->forced_attn_kernel == 1 || ctx->forced_attn_kernel == 2 ? ctx->forced_attn_kernel == 2
                                            : (n_real <= 2 * 256 || fast_tiles >= 48 * n_real));
     // every range's block ids must fit the table of the kernel that will run it
-    const int limit = !bf16 ? kF32MaxTiles : pp ? kPpMaxTiles : p.pipelined ? kPipeMaxTiles : kAttnMaxTiles;
+    const int limit = !bf16 ? (ctx->compact ? INT32_MAX : kF32MaxTiles) : pp ? kPpMaxTiles : p.pipelined ? kPipeMaxTiles : kAttnMaxTiles;
+    p.longest_range = 0;
     for (const AttnItem &it : items)
-        if (it.q >= 0 && it.tile_end - it.tile_begin > limit) return false;
-    return true;
+        if (it.q >= 0) p.longest_range = std::max(p.longest_range, it.tile_end - it.tile_begin);
+    return p.longest_range <= limit;
 }
 
 // Attention work list of the batch in `p`.  The general kernel keeps the block ids of at most
@@ -693,6 +706,70 @@ inline void fill_part_slots(const Plan &p, const std::vector<int32_t> &splits_of
             if (p.decode || splits_of_q[i] > 1) at += splits_of_q[i];
         }
     out[p.total_S] = at;
+}
+
+// The blocks that take suffix tokens, for the long-launch kernel's append.
+inline std::vector<AppendBlk> append_blocks(const Plan &p)
+{
+    std::vector<AppendBlk> out;
+    for (int i = 0; p.pingpong && i < p.B; ++i) {
+        const int P = p.prefix_len[i], end = P + p.suffix_len[i];
+        for (int p0 = P / kBlockTokens * kBlockTokens; p.suffix_len[i] > 0 && p0 < end; p0 += kBlockTokens)
+            out.push_back(AppendBlk{p.block_table[(size_t)i * p.max_blocks + p0 / kBlockTokens], p.cu_seqlens[i] + p0 - P,
+                                    std::max(P - p0, 0), std::min(end - p0, (int)kBlockTokens)});
+    }
+    return out;
+}
+
+// Where the parts of a plan stand in its device copy, in integers; only what the batch's kernels read
+// is there (`n_*`: how many of each).
+struct PlanLayout {
+    size_t bt_row = 0;                     // integers per row of the block table
+    size_t block_table, cu, prefix, suffix, tok_q, part_slot, append, items, groups;
+    size_t seg_start, seg_len, seg_slot, stitch, rope_pos0, rope_freq;
+    size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
+    bool lengths = false, tokens = false, by_row = false, merge_groups = false;
+};
+inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_append, size_t n_items,
+                              size_t n_groups)
+{
+    PlanLayout l;
+    const size_t B = p.B;
+    auto take = [&](size_t n) { const size_t o = l.total; l.total += (n + 7) & ~size_t(7); return o; };
+    l.tokens = !p.decode && !p.pingpong && !p.brief;             // appended token by token, in extra work-groups
+    l.lengths = l.tokens || n_stitch > 0;
+    l.by_row = parts_by_row(c, p);
+    l.merge_groups = p.max_splits > 1 && !l.by_row;
+    // rows are padded to whole 16-byte chunks: the decode and short-launch kernels fetch them so, the long-launch
+    // kernel where it can
+    l.bt_row = p.compact && !p.decode && !p.brief ? (size_t)p.max_blocks : (size_t)(p.max_blocks + 3) & ~size_t(3);
+    l.block_table = take(B * l.bt_row);
+    l.prefix = take(l.lengths ? B : 0);
+    l.cu = take(l.tokens ? B + 1 : 0); l.suffix = take(l.tokens ? B : 0); l.tok_q = take(l.tokens ? p.total_S : 0);
+    l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
+    l.append = take(n_append * (sizeof(AppendBlk) / 4));
+    l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
+    l.part_slot = take(l.by_row ? (size_t)p.total_S + 1 : 0);
+    l.items = take(n_items * (sizeof(AttnItem) / 4));
+    l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
+    l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
+    l.total = std::max(l.total, size_t(8));
+    return l;
+}
+
+// The plan of a batch for a workspace of `max_ints` integers and `max_floats` floats of partials: the fastest
+// one if it fits, else the one that takes the least space (which may still not fit: the caller looks).
+inline bool plan_attention_within(const tc_config &c, const PlanKnobs &knobs, Plan &p, std::vector<AttnItem> &items,
+                                  std::vector<int32_t> &splits_of_q, std::vector<MergeGroup> &groups, size_t max_ints,
+                                  size_t max_floats)
+{
+    PlanKnobs k = knobs;
+    k.part_cap = max_floats;
+    if (!plan_attention(c, k, p, items, splits_of_q, groups)) return false;
+    if (part_floats(c, p) <= max_floats &&
+        plan_layout(c, p, 0, 0, append_blocks(p).size(), items.size(), groups.size()).total <= max_ints) return true;
+    k.compact = true;
+    return plan_attention(c, k, p, items, splits_of_q, groups);
 }
 
 }  // namespace tc

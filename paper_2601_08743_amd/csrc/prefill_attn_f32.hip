@@ -41,7 +41,9 @@ struct F32Lds {
     static constexpr int kRow = D + 4;                             // padded row of the final exchange (floats)
 };
 
-template <int D>
+// kLong: some range of the batch has more key tiles than the table in LDS has block ids for; the planner makes such
+// ranges only for a workspace that has no room for the partials of shorter ones.
+template <int D, bool kLong>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     typedef F32Lds<D> L;
@@ -76,14 +78,21 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
     const int last_key = P + (min(it.m0 + kF32Rows, n_rows) - 1) / G;
     const int u_end = min(it.tile_end * (kF32Keys / kF32Unit), last_key / kF32Unit + 1);
 
-    // block ids of the range's prefix part
+    // block ids of the range's prefix part, as many as the table in LDS holds
+    constexpr int kIds = kF32MaxTiles * (kF32Keys / kBlockTokens);
     const int blk0 = it.tile_begin * (kF32Keys / kBlockTokens);
+    const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks + blk0;
     {
         const int n_pblk = (P + kBlockTokens - 1) >> 4;
-        const int n = min(it.tile_end * (kF32Keys / kBlockTokens), n_pblk) - blk0;
-        const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks + blk0;
+        const int n_range = min(it.tile_end * (kF32Keys / kBlockTokens), n_pblk) - blk0, n = kLong ? min(n_range, kIds) : n_range;
         for (int idx = tid; idx < n; idx += 256) s_bid[idx] = bt[idx];
     }
+    // block `idx` of the range, the same for the whole wave (by a scalar load where LDS does not have it: a vector
+    // load would have to wait for the tile loads in flight)
+    typedef const __attribute__((address_space(4))) int32_t *const_ints;
+    auto block_id = [&](int idx) {
+        return !kLong || idx < kIds ? __builtin_amdgcn_readfirstlane(s_bid[idx]) : ((const_ints)(uintptr_t)bt)[idx];
+    };
     // Q^T fragments (B operand): lane (row r32, half hh) holds q[row][hh * D/2 ..]
     float qf[D / 2];
     {
@@ -116,7 +125,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         if (key0 + kF32Unit <= P) {              // two whole blocks of the pool
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const char *src = pool_l + (int64_t)__builtin_amdgcn_readfirstlane(s_bid[2 * u + j - blk0]) * g.block_bytes + (is_v ? v_half : 0);
+                const char *src = pool_l + (int64_t)block_id(2 * u + j - blk0) * g.block_bytes + (is_v ? v_half : 0);
 #pragma unroll
                 for (int i = 0; i < kPieces / 2; ++i) {
                     const int r = i * kRowsPer + l_row;
@@ -124,13 +133,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
                 }
             }
         } else {                                 // the end of the prefix and / or suffix tokens
+            const int id0 = key0 < P ? block_id(2 * u - blk0) : 0, id1 = key0 + kBlockTokens < P ? block_id(2 * u + 1 - blk0) : 0;
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
                 const int r = i * kRowsPer + l_row;
                 const int key = key0 + r;
                 const int st = min(max(key - P, 0), S - 1);
                 const char *src = (is_v ? new_v : new_k) + (int64_t)st * g.row_bytes;
-                if (key < P) src = pool_l + (int64_t)s_bid[(key >> 4) - blk0] * g.block_bytes + (is_v ? v_half : 0) + (key & 15) * (D * 4);
+                if (key < P) src = pool_l + (int64_t)(r < kBlockTokens ? id0 : id1) * g.block_bytes + (is_v ? v_half : 0) + (key & 15) * (D * 4);
                 load_to_lds_each(dst + i * 1024, src + (is_v ? l_chunk : l_chunk ^ (r & 15)) * 16);
             }
         }
@@ -293,23 +303,24 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
     }
 }
 
+template <int D, bool kLong>
+static hipError_t launch_attn(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
+{
+    static PerDeviceOnce configured;
+    const hipError_t e = configured.run([] {
+        return hipFuncSetAttribute((const void *)attn_f32_kernel<D, kLong>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<D>::kBytes);
+    });
+    if (e != hipSuccess) return e;
+    TC_LAUNCH((attn_f32_kernel<D, kLong>), a.n_items + a.n_append, F32Lds<D>::kBytes, L, g, b, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
     if (a.n_items + a.n_append == 0) return hipSuccess;
-    static PerDeviceOnce configured;
-    const hipError_t e = configured.run([] {
-        const hipError_t e64 = hipFuncSetAttribute((const void *)attn_f32_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<64>::kBytes);
-        if (e64 != hipSuccess) return e64;
-        return hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<128>::kBytes);
-    });
-    if (e != hipSuccess) return e;
-    if (g.D == 64)
-        TC_LAUNCH(attn_f32_kernel<64>, a.n_items + a.n_append, F32Lds<64>::kBytes, L, g, b, a);
-    else if (g.D == 128)
-        TC_LAUNCH(attn_f32_kernel<128>, a.n_items + a.n_append, F32Lds<128>::kBytes, L, g, b, a);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (g.D == 64) return a.long_ranges ? launch_attn<64, true>(g, b, a, L) : launch_attn<64, false>(g, b, a, L);
+    if (g.D == 128) return a.long_ranges ? launch_attn<128, true>(g, b, a, L) : launch_attn<128, false>(g, b, a, L);
+    return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------------------------------ merge

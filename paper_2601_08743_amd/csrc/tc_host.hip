@@ -45,8 +45,6 @@ struct Slot {
     bool reader_pending = false;           // read the slot through an aliasing sequence, not yet ordered
 };
 
-inline size_t align8(size_t n) { return (n + 7) & ~size_t(7); }
-
 // ------------------------------------------------------------------ workspace of tc_prefill_attn_noalloc
 // The entry point that allocates nothing keeps what tc_prefill_attn keeps in hipMalloc'ed buffers -
 // the batch's integer plan and the split-KV partials - in this array, which the code object brings
@@ -239,39 +237,20 @@ struct SegInfo { int32_t start, len, slot; };
 // `fixed`: the device copy and the partials go to the static workspace; nothing is allocated, and a
 // batch that does not fit it is refused.
 tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
-                      const std::vector<int32_t> &seg_end_of_q, const std::vector<StitchBlk> &sblk,
-                      hipStream_t stream, bool fixed = false)
+                      const std::vector<StitchBlk> &sblk, hipStream_t stream, bool fixed = false)
 {
     std::vector<AttnItem> items;
     std::vector<int32_t> splits_of_q;
     std::vector<MergeGroup> groups;
-    if (!plan_attention(ctx->cfg, ctx->knobs, p, items, splits_of_q, groups))
+    if (!(fixed ? plan_attention_within(ctx->cfg, ctx->knobs, p, items, splits_of_q, groups, kScratchPlanInts, kScratchPartFloats)
+                : plan_attention(ctx->cfg, ctx->knobs, p, items, splits_of_q, groups)))
         return fail(ctx, TC_ERR_INVALID, "attn: a work item's key range exceeds its kernel's block-id table");
 
     const size_t B = p.B, nseg = segs.size();
-    size_t off = 0;
-    auto take = [&](size_t n) { size_t o = off; off += align8(n); return o; };
-    // rows of the device's block table are padded to whole 16-byte chunks (the decode kernel fetches them so)
-    const size_t bt_row = (size_t)(p.max_blocks + 3) & ~size_t(3);
-    const size_t o_bt = take(B * bt_row), o_cu = take(B + 1), o_pl = take(B), o_sl = take(B);
-    const size_t o_ss = take(nseg), o_sn = take(nseg), o_st = take(nseg), o_se = take(B);
-    std::vector<AppendBlk> ablk;
-    if (p.pingpong)
-        for (int i = 0; i < p.B; ++i) {
-            const int P = p.prefix_len[i], end = P + p.suffix_len[i];
-            for (int p0 = P / kBlockTokens * kBlockTokens; p.suffix_len[i] > 0 && p0 < end; p0 += kBlockTokens)
-                ablk.push_back(AppendBlk{p.block_table[(size_t)i * p.max_blocks + p0 / kBlockTokens], p.cu_seqlens[i] + p0 - P,
-                                         std::max(P - p0, 0), std::min(end - p0, (int)kBlockTokens)});
-        }
-    const size_t o_ab = take(ablk.size() * 4);
-    const size_t o_sb = take(sblk.size() * 4), o_tq = take(p.total_S);
-    const bool by_row = parts_by_row(ctx->cfg, p);
-    const size_t o_ps = take(by_row ? (size_t)p.total_S + 1 : 0);
-    const size_t o_it = take(items.size() * (sizeof(AttnItem) / 4));
-    const size_t o_gr = take(groups.size() * (sizeof(MergeGroup) / 4));
-    const size_t o_rp = take(p.rope ? B : 0), o_rf = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
-    const size_t total = std::max(off, size_t(8));          // (a multiple of 8: the upload moves 16 bytes at a time)
-    if (p.n_part_slots > INT32_MAX) return fail(ctx, TC_ERR_CAPACITY, "attn: %lld split-KV partials", (long long)p.n_part_slots);
+    const std::vector<AppendBlk> ablk = append_blocks(p);
+    const PlanLayout at = plan_layout(ctx->cfg, p, nseg, sblk.size(), ablk.size(), items.size(), groups.size());
+    const size_t total = at.total;
+    if (p.n_part_slots > INT32_MAX) return fail(ctx, fixed ? TC_ERR_CAPACITY : TC_ERR_HIP, "attn: %lld split-KV partials", (long long)p.n_part_slots);
     const size_t part_need = part_floats(ctx->cfg, p);
     if (fixed && part_need > kScratchPartFloats)
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the split-KV partials need %zu floats, the fixed workspace holds %zu",
@@ -281,30 +260,26 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     tc_status st = ensure_stage(ctx, total, fixed, &h, &parts);
     if (st != TC_OK) return st;
     std::memset(h, 0, total * sizeof(int32_t));
-    if (B) {
-        for (size_t i = 0; i < B; ++i)
-            std::memcpy(h + o_bt + i * bt_row, p.block_table.data() + i * p.max_blocks, (size_t)p.max_blocks * 4);
-        for (size_t k = 0; k < p.block_pad.size(); ++k)
-            if (p.block_pad[k]) h[o_bt + k / p.max_blocks * bt_row + k % p.max_blocks] |= (int32_t)((uint32_t)p.block_pad[k] << kPadShift);
-        std::memcpy(h + o_cu, p.cu_seqlens.data(), (B + 1) * 4);
-        std::memcpy(h + o_pl, p.prefix_len.data(), B * 4);
-        std::memcpy(h + o_sl, p.suffix_len.data(), B * 4);
-        if (!seg_end_of_q.empty()) std::memcpy(h + o_se, seg_end_of_q.data(), B * 4);
-    }
+    for (size_t i = 0; i < B; ++i)
+        if (p.max_blocks) std::memcpy(h + at.block_table + i * at.bt_row, p.block_table.data() + i * p.max_blocks, (size_t)p.max_blocks * 4);
+    for (size_t k = 0; k < p.block_pad.size(); ++k)
+        if (p.block_pad[k]) h[at.block_table + k / p.max_blocks * at.bt_row + k % p.max_blocks] |= (int32_t)((uint32_t)p.block_pad[k] << kPadShift);
+    auto put = [&](size_t o, const auto &v, bool want = true) { if (want && !v.empty()) std::memcpy(h + o, v.data(), v.size() * sizeof(v[0])); };
+    put(at.prefix, p.prefix_len, at.lengths);
+    put(at.cu, p.cu_seqlens, at.tokens);
+    put(at.suffix, p.suffix_len, at.tokens);
+    for (int i = 0; at.tokens && i < p.B; ++i)
+        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) h[at.tok_q + n] = i;
     for (size_t k = 0; k < nseg; ++k) {
-        h[o_ss + k] = segs[k].start; h[o_sn + k] = segs[k].len; h[o_st + k] = segs[k].slot;
+        h[at.seg_start + k] = segs[k].start; h[at.seg_len + k] = segs[k].len; h[at.seg_slot + k] = segs[k].slot;
     }
-    if (!ablk.empty()) std::memcpy(h + o_ab, ablk.data(), ablk.size() * sizeof(AppendBlk));
-    if (!sblk.empty()) std::memcpy(h + o_sb, sblk.data(), sblk.size() * sizeof(StitchBlk));
-    for (int i = 0; i < p.B; ++i)
-        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) h[o_tq + n] = i;
-    if (by_row) fill_part_slots(p, splits_of_q, h + o_ps);
-    if (!items.empty()) std::memcpy(h + o_it, items.data(), items.size() * sizeof(AttnItem));
-    if (!groups.empty()) std::memcpy(h + o_gr, groups.data(), groups.size() * sizeof(MergeGroup));
-    if (p.rope) {
-        if (B) std::memcpy(h + o_rp, p.rope_pos0.data(), B * 4);
-        std::memcpy(h + o_rf, p.rope_rev_freq.data(), p.rope_rev_freq.size() * sizeof(double));
-    }
+    put(at.append, ablk);
+    put(at.stitch, sblk);
+    if (at.by_row) fill_part_slots(p, splits_of_q, h + at.part_slot);
+    put(at.items, items);
+    put(at.groups, groups, at.merge_groups);
+    put(at.rope_pos0, p.rope_pos0, p.rope);
+    put(at.rope_freq, p.rope_rev_freq, p.rope);
 
     int32_t *d_dst = fixed ? (int32_t *)ctx->scratch_dev : ctx->d_plan;
     TC_HIP(ctx, launch_upload(d_dst, h, total, Launch{stream, nullptr, nullptr}));
@@ -315,20 +290,24 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         }
 
     const int32_t *d = d_dst;
-    p.dev.block_table = d + o_bt; p.dev.cu_seqlens = d + o_cu; p.dev.prefix_len = d + o_pl;
-    p.dev.suffix_len = d + o_sl; p.dev.seg_start = d + o_ss; p.dev.seg_len = d + o_sn;
-    p.dev.seg_slot = d + o_st; p.dev.seg_end_of_q = d + o_se;
-    p.dev.stitch_blk = (const StitchBlk *)(d + o_sb); p.dev.part_slot = by_row ? d + o_ps : nullptr;
-    p.dev.tok_q = d + o_tq;
-    p.dev.append_blk = (const AppendBlk *)(d + o_ab);
+    p.dev = BatchDev{};
+    p.dev.block_table = d + at.block_table;
+    if (at.lengths) p.dev.prefix_len = d + at.prefix;
+    if (at.tokens) {
+        p.dev.cu_seqlens = d + at.cu; p.dev.suffix_len = d + at.suffix; p.dev.tok_q = d + at.tok_q;
+    }
+    p.dev.seg_start = d + at.seg_start; p.dev.seg_len = d + at.seg_len; p.dev.seg_slot = d + at.seg_slot;
+    p.dev.stitch_blk = (const StitchBlk *)(d + at.stitch);
+    if (at.by_row) p.dev.part_slot = d + at.part_slot;
+    p.dev.append_blk = (const AppendBlk *)(d + at.append);
     p.dev.n_append_blk = (int32_t)ablk.size();
-    p.dev.rope_pos0 = p.rope ? d + o_rp : nullptr;
-    p.dev.rope_rev_freq = p.rope ? (const double *)(d + o_rf) : nullptr;
-    p.dev.B = p.B; p.dev.max_blocks = (int32_t)bt_row; p.dev.total_S = p.total_S;
+    p.dev.rope_pos0 = p.rope ? d + at.rope_pos0 : nullptr;
+    p.dev.rope_rev_freq = p.rope ? (const double *)(d + at.rope_freq) : nullptr;
+    p.dev.B = p.B; p.dev.max_blocks = (int32_t)at.bt_row; p.dev.total_S = p.total_S;
     p.dev.n_stitch_blk = (int32_t)sblk.size();
     p.n_stitch_blk = (int32_t)sblk.size();
-    p.items_dev = (const AttnItem *)(d + o_it);
-    p.groups_dev = (const MergeGroup *)(d + o_gr);
+    p.items_dev = (const AttnItem *)(d + at.items);
+    p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
     p.fixed = fixed;
     p.part = nullptr;
@@ -718,7 +697,7 @@ static tc_status stitch_common(tc_ctx *ctx, const int32_t *table_ids, const int3
             }
         }
     }
-    tc_status st = upload_plan(ctx, p, segs, seg_end_of_q, sblk, stream);
+    tc_status st = upload_plan(ctx, p, segs, sblk, stream);
     if (st != TC_OK) return st;               // nothing allocated yet
 
     // ---- commit: take the blocks, order the gather after the loads it reads, launch
@@ -847,7 +826,7 @@ tc_status tc_stitch_alias(tc_ctx *ctx, const int32_t *table_ids, const int32_t *
         for (int j = 0; j < n_suf[i]; ++j, ++next_free, ++at) p.block_table[at] = *next_free;
     }
     p.alias_slots.assign(used_slots.begin(), used_slots.end());
-    tc_status st = upload_plan(ctx, p, {}, {}, {}, stream);
+    tc_status st = upload_plan(ctx, p, {}, {}, stream);
     if (st != TC_OK) return st;               // nothing allocated yet
 
     // ---- commit: take the suffix blocks; whatever follows on `stream` comes after the loads it reads
@@ -923,7 +902,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         p.cu_seqlens.assign(cu_seqlens, cu_seqlens + B + 1);
         p.prefix_len.assign(prefix_len, prefix_len + B);
         p.suffix_len.assign(suffix_len, suffix_len + B);
-        tc_status st = upload_plan(ctx, p, {}, {}, {}, stream, fixed);
+        tc_status st = upload_plan(ctx, p, {}, {}, stream, fixed);
         if (st != TC_OK) return st;
         for (int32_t sidx : p.alias_slots) {        // the launches come after the loads of what they read
             Slot &sl = ctx->slots[sidx];
@@ -962,6 +941,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.n_append = p.pingpong || p.brief ? 0 : append_units(p.total_S, p.B, bf16 ? 1 : kF32AppendTokens); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     a.has_pads = p.block_pad.empty() ? 0 : 1;
+    a.long_ranges = p.longest_range > kF32MaxTiles ? 1 : 0;
     a.part_o = p.part;
     a.part_ml = !p.part ? nullptr
               : bf16 && !p.brief ? p.part + (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * 64

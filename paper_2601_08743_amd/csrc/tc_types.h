@@ -16,7 +16,7 @@ constexpr int kPipeMaxTiles = 1024;  // and for the pipelined kernel (one work-g
 constexpr int kShortRows = 32;       // short-launch kernel: rows per work-group (its waves split the keys)
 constexpr int kF32Rows = 32;         // fp32 kernel: rows per work-group (its waves split the keys)
 constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
-constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item (block ids kept in LDS)
+constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item whose block ids are kept in LDS (those of longer ranges are fetched one by one)
 constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
@@ -59,7 +59,8 @@ struct AppendBlk {
     int32_t phys, row0, t_begin, t_end;
 };
 
-// Device-side view of the current batch (all arrays int32, one upload per batch).
+// Device-side view of the current batch (all arrays int32, one upload per batch; those that the batch's kernels do
+// not read are null).
 struct BatchDev {
     const int32_t *block_table;   // [B][max_blocks], max_blocks here a multiple of 4
     const int32_t *cu_seqlens;    // [B+1]
@@ -68,7 +69,6 @@ struct BatchDev {
     const int32_t *seg_start;     // [n_seg] logical start of segment within its query
     const int32_t *seg_len;       // [n_seg]
     const int32_t *seg_slot;      // [n_seg] table slot holding the segment's table
-    const int32_t *seg_end_of_q;  // [B] one past the last segment index of query q
     const StitchBlk *stitch_blk;  // [n_stitch_blk]
     const AppendBlk *append_blk;  // [n_append_blk] (batches whose suffix is appended by a launch of its own, else none)
     const int32_t *part_slot;     // [sum S + 1] first partial slot of each suffix token (kernels that keep partials by row, else null)
@@ -117,6 +117,7 @@ struct AttnArgs {
     int32_t layer;
     int32_t n_items;
     int32_t n_append;    // append units run by the attention launch, 0 = none
+    int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };
 

@@ -112,8 +112,8 @@ def test_staged_plans_share_no_memory_with_an_upload_nobody_waited_for(exe, cap)
     assert {1, 2} <= set(short)                  # and short ones do alternate
 
 
-def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128):
-    lines = run(exe, "plan %d %d %d %d %d %d %d %d %s\n" % (dtype, Hq, Hkv, D, splits, rb, kernel, len(PS),
+def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0, 0)):
+    lines = run(exe, "within %d %d\n" % within + "plan %d %d %d %d %d %d %d %d %s\n" % (dtype, Hq, Hkv, D, splits, rb, kernel, len(PS),
                                                           " ".join("%d %d" % ps for ps in PS)))
     head = list(map(int, lines[0].split()[1:]))
     rows = [tuple(map(int, l.split()[1:])) for l in lines[1:] if l.startswith("i ")]
@@ -123,6 +123,7 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128):
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
                 n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part0=[r[8] for r in rows])
+    info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
     info["part_floats"], *info["slots"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
     assert int(ghead[1]) == len(groups)
     return info, items
@@ -137,7 +138,7 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
     if info["decode"]:
         cap, rt, unified = CAP_GENERAL, None, False
     else:
-        cap = CAP_F32 if dtype == 0 else CAP_PP if info["pingpong"] else CAP_PIPE if info["pipelined"] else CAP_GENERAL
+        cap = (10 ** 9 if info["compact"] else CAP_F32) if dtype == 0 else CAP_PP if info["pingpong"] else CAP_PIPE if info["pipelined"] else CAP_GENERAL
         rt = 32 if dtype == 0 or info["brief"] else 128 * info["row_blocks"]      # what the kernels stride their rows by
         unified = dtype == 0 or bool(info["pingpong"])
     cover = {}
@@ -206,6 +207,43 @@ def test_partials_of_ragged_batches_stay_small(exe, Hq, Hkv, PS, kernel):
     assert info["ok"] and info[kernel]
     _check_slots(info, items, Hq, 128, PS)
     assert info["max_splits"] > 30 and info["part_floats"] <= WORKSPACE // 4
+
+
+PLAN_INTS = 1 << 20                          # and of its plan
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,PS", [(32, 8, 128, [(7744, 23), (2119, 220)]), (8, 2, 128, [(15727, 652), (284, 992)]),
+                                         (32, 8, 128, [(6000, 500)] * 3 + [(8000, 8)]), (8, 2, 64, [(20000, 1000)] * 6)])
+def test_fp32_ranges_go_by_the_workspace(exe, Hq, Hkv, D, PS):
+    """Where the partials of the fastest plan do not fit, a plan with fewer partitions whose partials do."""
+    free, _ = _plan(exe, Hq, Hkv, PS, dtype=0, D=D)
+    info, items = _plan(exe, Hq, Hkv, PS, dtype=0, D=D, within=(PLAN_INTS, WORKSPACE))
+    _check_plan(info, items, Hq, Hkv, PS, dtype=0)
+    assert not info["compact"] and info["ints"] <= PLAN_INTS and info["part_floats"] <= WORKSPACE
+    assert info["max_splits"] == free["max_splits"] if free["part_floats"] <= WORKSPACE else info["max_splits"] < free["max_splits"]
+
+
+def test_plan_of_least_space(exe):
+    """What a fixed workspace cannot hold as planned for speed is planned for the least space: fp32 in one range
+    however long (one partition never needs partials), no padded block table, no short-launch or extra partitions."""
+    PS = [(40000, 2000), (50, 3)]                # 656 key tiles; two partitions would be 2000 x 32 x 2 rows of 130 floats = 16.6 M
+    info, items = _plan(exe, 32, 8, PS, dtype=0, within=(PLAN_INTS, WORKSPACE))
+    assert _check_plan(info, items, 32, 8, PS, dtype=0) == 657 and info["compact"] and info["max_splits"] == 1 and info["part_floats"] == 0
+    PS = [(4992, 8)] * 30 + [(5008, 0)] * 3265   # 313 blocks a row, 316 padded: 3295 of those and the plan exceed 1 Mi integers
+    free, _ = _plan(exe, 28, 4, PS)
+    info, items = _plan(exe, 28, 4, PS, within=(PLAN_INTS, WORKSPACE))
+    _check_plan(info, items, 28, 4, PS)
+    assert free["brief"] and free["ints"] > PLAN_INTS and info["compact"] and info["ints"] <= PLAN_INTS
+    # nothing of one partition and few rows is refused, whatever its shape
+    rng = np.random.default_rng(23)
+    for _ in range(60):
+        dtype, Hkv, G = int(rng.random() < 0.5), int(rng.choice([1, 2, 8])), int(rng.choice([1, 4, 7, 32]))
+        PS = [(int(2 ** rng.uniform(0, 16)), int(2 ** rng.uniform(0, 10))) for _ in range(int(rng.integers(1, 9)))]
+        info, items = _plan(exe, Hkv * G, Hkv, PS, dtype=dtype, within=(PLAN_INTS, WORKSPACE))
+        _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
+        rows = sum(S for _, S in PS) * Hkv * G
+        if (rows <= 1e5 and dtype == 0) or rows <= 2e4:
+            assert info["ints"] <= PLAN_INTS and info["part_floats"] <= WORKSPACE, (dtype, Hkv, G, PS)
 
 
 def test_planner_partition_limit_with_forced_splits(exe):

@@ -134,6 +134,31 @@ def test_noalloc_short_launch_and_fp32():
     assert _ragged(H, "f32", 32, 8, 128, [7744, 2119], [23, 220], 0) >= 1
 
 
+def test_noalloc_range_longer_than_the_block_id_table():
+    """fp32, 563 key tiles where the kernel keeps the block ids of 512: the partials of two ranges (16.6 M floats) do not fit,
+    so the entry point that allocates nothing runs it in one.  Against the other one's two ranges, every row."""
+    import harness as H
+    cfg = W.WorkloadConfig("n", 1, 32, 1, 128, "f32", 2, (1, 34000), 2, (1, 1), "uniform", (1, 9), 2, 318)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = [34000, 70]
+    wl.queries[:] = [np.array([0], dtype=np.int32), np.array([1], dtype=np.int32)]
+    wl.suffix_len[:] = [2000, 5]
+    dw = H.DeviceWorkload(wl)
+    bt, pl = dw.stitch()
+    dw.ctx.tc_set_kv_splits(1)                   # (the kernel's block-id table still cuts it in two)
+    out, qkv = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_kv_splits() == 2
+    got = torch.full_like(out, float("nan"))
+    dw.ctx.tc_prefill_attn_noalloc(0, *(H.to_dev(x, cfg) for x in qkv), got, wl.cu_seqlens, bt, pl, wl.suffix_len, wl.sm_scale)
+    torch.cuda.synchronize()
+    assert dw.ctx.tc_kv_splits() == 1
+    assert torch.isfinite(out).all()
+    # the same sums in another order, each within 1e-5 of the exact value (as in the kernel's own tests; the rows of the first
+    # query average 34 k values and are far closer)
+    assert float((out - got)[:2000].abs().max()) <= 1e-5 and torch.equal(out[2000:], got[2000:])
+    dw.close()
+
+
 def test_noalloc_refuses_what_does_not_fit():
     """A batch whose partials exceed the fixed workspace is refused with TC_ERR_CAPACITY and
     enqueues nothing; the allocating entry point still serves it."""
