@@ -980,13 +980,20 @@ __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, con
         M = Mc;
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            const bool live = s0 + k < n_splits && ml[k].x != -INFINITY;
-            const float wgt = live ? __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y : 0.f;
+            // beyond the last partition stands the last one again: a weight of zero, and no values, for its infinities
+            // times zero would be NaN (two words a fragment)
+            const bool there = s0 + k < n_splits;
+            const float wgt = there && ml[k].x != -INFINITY ? __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y : 0.f;
             l += wgt;
 #pragma unroll
-            for (int f = 0; f < kFrags; ++f)
+            for (int f = 0; f < kFrags; ++f) {
+                union { f16x4 h; uint32_t w[2]; } x;
+                x.h = v[k][f];
+                x.w[0] = there ? x.w[0] : 0u;
+                x.w[1] = there ? x.w[1] : 0u;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[4 * f + e] = fmaf(wgt, (float)v[k][f][e], acc[4 * f + e]);
+                for (int e = 0; e < 4; ++e) acc[4 * f + e] = fmaf(wgt, (float)x.h[e], acc[4 * f + e]);
+            }
         }
     }
     const int row_m = m0 + blk * 32 + r32;

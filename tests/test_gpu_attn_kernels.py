@@ -346,3 +346,41 @@ def test_repeated_launches_are_bit_identical(H, heads):
             sl = slice(int(wl.cu_seqlens[i]), int(wl.cu_seqlens[i + 1]))
             assert np.abs(got[sl] - r).max() <= TOL, (kind, P[i], S[i])
         dw.close()
+
+
+def _one_query(H, dtype, hq, hkv, D, n_tokens, suffix, edit):
+    """One query over one table of n_tokens whose K and V `edit` has changed, on the device."""
+    cfg = W.WorkloadConfig("e", 1, hq, hkv, D, dtype, 1, (n_tokens, n_tokens), 1, (1, 1), "uniform", (suffix, suffix), 1, 319)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = n_tokens
+    wl.suffix_len[:] = suffix
+    k, v = wl.table_kv(0)
+    k, v = (torch.from_numpy(np.ascontiguousarray(x)) for x in (k, v))
+    if dtype == "bf16":
+        k, v = k.view(torch.bfloat16), v.view(torch.bfloat16)
+    edit(k, v)                                   # [1][n][Hkv][D]
+    dw = H.DeviceWorkload(wl, tables=[])
+    hk, hv = k.pin_memory(), v.pin_memory()
+    dw.ctx.tc_register_table_kv(0, n_tokens, hk, hv)
+    dw.ctx.tc_load_async([0], 0, 1, None)
+    torch.cuda.synchronize()
+    return wl, dw, (hk, hv)
+
+
+@pytest.mark.parametrize("kernel,splits", [(1, 2), (1, 3), (1, 5), (1, 9), (2, 3), (4, 3), (5, 3)])
+def test_infinite_values_stay_infinite_through_the_merge(H, kernel, splits):
+    """A column of the table's values is +infinity: so is that column of every row that has a part in it, for any number of
+    partitions (the merges load partitions several at a time, the last one more than once), and no other column."""
+    def edit(k, v):
+        v[0, :, 1, 7] = float("inf")
+    wl, dw, keep = _one_query(H, "bf16", 14, 2, 128, 64 * 12, 40, edit)      # whole key tiles: no masked key has such a value
+    dw.ctx.tc_set_attn_kernel(kernel)
+    dw.ctx.tc_set_kv_splits(splits)
+    bt, pl = dw.stitch()
+    out, _ = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_attn_kernel() == kernel and dw.ctx.tc_kv_splits() >= min(splits, 3)
+    o = out.float()
+    assert torch.isposinf(o[:, 7:, 7]).all()
+    o[:, 7:, 7] = 0
+    assert torch.isfinite(o).all()
+    dw.close()
