@@ -342,9 +342,10 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
     float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     auto fold = [&](float m, float l, f32x4 o) {
-        if (m == -INFINITY) return;
         const float Mn = fmaxf(M, m);
-        const float r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn), wgt = __builtin_amdgcn_exp2f(m - Mn);
+        const float r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+        // (no maximum: no key for this row - l and o are 0 - or only scores that are NaN - so are they, and so is the row)
+        const float wgt = m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - Mn);
         L = L * r + l * wgt;
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = acc[e] * r + o[e] * wgt;

@@ -367,8 +367,10 @@ __global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, Attn
         M = Mc;
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            if (s0 + j >= ns || ml[j].x == -INFINITY) continue;
-            const float wgt = exp2f(ml[j].x - M);
+            if (s0 + j >= ns) break;
+            // a partition without a maximum saw no key of this row (sum and output are 0) or only scores that are NaN
+            // (so are they, and so is the row)
+            const float wgt = ml[j].x == -INFINITY ? 1.f : exp2f(ml[j].x - M);
             den = fmaf(wgt, ml[j].y, den);
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, po[j][e], acc[e]);

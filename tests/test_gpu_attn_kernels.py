@@ -384,3 +384,21 @@ def test_infinite_values_stay_infinite_through_the_merge(H, kernel, splits):
     o[:, 7:, 7] = 0
     assert torch.isfinite(o).all()
     dw.close()
+
+
+@pytest.mark.parametrize("dtype,kernel", [("f32", 0), ("bf16", 1), ("bf16", 5), ("bf16", 3)])
+def test_keys_that_are_not_numbers_are_not_dropped(H, dtype, kernel):
+    """The keys of a whole partition are NaN: the rows that see them are NaN, as in one partition, and not what they
+    would be without those keys."""
+    def edit(k, v):
+        k[0, :192, 1] = float("nan")
+    wl, dw, keep = _one_query(H, dtype, 14, 2, 128, 64 * 6, 1 if kernel == 3 else 20, edit)
+    dw.ctx.tc_set_attn_kernel(kernel)
+    for splits in (1, 3, 6):
+        dw.ctx.tc_set_kv_splits(splits)
+        bt, pl = dw.stitch()
+        out, _ = dw.attn_layer(0, bt, pl)
+        assert dw.ctx.tc_attn_kernel() == kernel and dw.ctx.tc_kv_splits() == splits
+        assert torch.isnan(out[:, 7:]).all() and torch.isfinite(out[:, :7].float()).all()
+        dw.ctx.tc_release_seqs(bt)
+    dw.close()
