@@ -55,6 +55,10 @@ constexpr size_t kScratchPlanInts = size_t(1) << 20;
 constexpr size_t kScratchPartFloats = size_t(15) << 20;
 constexpr size_t kScratchBytes = (kScratchPlanInts + kScratchPartFloats) * 4;
 constexpr int kMaxDevices = 64;
+// Plans are uploaded by a kernel that reads the pinned staging buffer, whose halves are written again and again:
+// it must not find an earlier plan in a GPU cache.  Named here because the default follows the environment
+// (HIP_HOST_COHERENT).
+constexpr unsigned kStagingFlags = hipHostMallocCoherent;
 std::mutex g_scratch_mutex;
 char *g_scratch_ptr[kMaxDevices];                   // device address of `scratch` on each device, once resolved
 
@@ -213,7 +217,7 @@ tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, unsig
         if (ctx->h_stage) TC_HIP(ctx, hipHostFree(ctx->h_stage));
         ctx->h_stage = nullptr; ctx->h_stage_ints = 0;
         const size_t cap = std::max(ints * 2, size_t(1) << 16);
-        TC_HIP(ctx, hipHostMalloc((void **)&ctx->h_stage, cap * sizeof(int32_t), hipHostMallocDefault));
+        TC_HIP(ctx, hipHostMalloc((void **)&ctx->h_stage, cap * sizeof(int32_t), kStagingFlags));
         ctx->h_stage_ints = cap;
     }
     const StageHalves::Spot spot = ctx->stage.place(ints, ctx->h_stage_ints);
@@ -384,7 +388,7 @@ tc_status tc_create(const tc_config *cfg, void *kv_pool_dev, size_t pool_bytes, 
         ctx->scratch_dev = g_scratch_ptr[ctx->device];
     }
     // pinned staging for plan uploads, sized so that a plan bound for the static workspace always fits
-    if (hipHostMalloc((void **)&ctx->h_stage, kScratchPlanInts * sizeof(int32_t), hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void **)&ctx->h_stage, kScratchPlanInts * sizeof(int32_t), kStagingFlags) != hipSuccess)
         return TC_ERR_HIP;
     ctx->h_stage_ints = kScratchPlanInts;
     ctx->slot_blocks = (cfg->max_table_tokens + kBlockTokens - 1) / kBlockTokens;

@@ -112,6 +112,17 @@ def test_staged_plans_share_no_memory_with_an_upload_nobody_waited_for(exe, cap)
     assert {1, 2} <= set(short)                  # and short ones do alternate
 
 
+def test_staging_memory_names_its_coherence():
+    """A kernel reads the pinned staging buffer, so what it may keep of it in a cache is not left to the environment
+    (hipHostMallocDefault follows HIP_HOST_COHERENT)."""
+    import re
+    with open(os.path.join(CSRC, "tc_host.hip")) as f:
+        src = f.read()
+    flags = re.findall(r"hipHostMalloc\([^;]*, (\w+)\)", src)
+    assert len(flags) == src.count("hipHostMalloc(") and set(flags) == {"kStagingFlags"}
+    assert re.search(r"kStagingFlags = hipHostMallocCoherent;", src)
+
+
 def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0, 0)):
     lines = run(exe, "within %d %d\n" % within + "plan %d %d %d %d %d %d %d %d %s\n" % (dtype, Hq, Hkv, D, splits, rb, kernel, len(PS),
                                                           " ".join("%d %d" % ps for ps in PS)))
