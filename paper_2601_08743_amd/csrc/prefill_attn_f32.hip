@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, Attn
         M = Mc;
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            if (s0 + j >= ns) break;
+            if (s0 + j >= ns) continue;
             // a partition without a maximum saw no key of this row (sum and output are 0) or only scores that are NaN
             // (so are they, and so is the row)
             const float wgt = ml[j].x == -INFINITY ? 1.f : exp2f(ml[j].x - M);
