@@ -307,10 +307,11 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 // groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
 // row of up to 4 * kGroups partitions costs one round trip - and fold their results through LDS.  A
 // work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
-// threads would load what nobody needs.  (Beyond a row's last partition the last one is loaded again and ignored.)
+// threads would load what nobody needs.  (Slots beyond a row's last partition are loaded and ignored; with evenly
+// spaced slots, kEven, nothing waits for the number of partitions before the loads.)
 // Without kSelf there is no new token to add and rows of one partition are left alone (they were written
 // directly): the merge of the short-launch prefill kernel's partitions.
-template <int kGroups, bool kSelf>
+template <int kGroups, bool kSelf, bool kEven>
 __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
     constexpr int kBatch = 4, kRows = 8 / kGroups;
@@ -320,14 +321,14 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
     const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
     const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
     const int n = row / g.Hq, head = row - n * g.Hq, kvh = head / g.G;      // n: the token (queries may bring none)
-    const int slot0 = b.part_slot[n], ns = b.part_slot[n + 1] - slot0;
+    const PartSlots slots = part_slots<kEven>(b, n);
     float2 ml[kBatch];
     f32x4 po[kBatch];
     auto fetch = [&](int s0) {
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             if (kGroups * j >= max_splits) break;
-            const int64_t slot = (int64_t)(slot0 + min(s0 + kGroups * j, ns - 1)) * g.Hq + head;
+            const int64_t slot = (int64_t)min(slots.first + s0 + kGroups * j, slots.last) * g.Hq + head;
             ml[j] = *(const float2 *)(a.part_ml + slot * 2);
             po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
         }
@@ -338,7 +339,8 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
         k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
         v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
     }
-    if (kSelf || ns > 0) fetch(grp);         // (a decode step has at least one partition)
+    if (kEven || kSelf || slots.count > 0) fetch(grp);       // (a decode step has at least one partition)
+    const int ns = slots.count;
     float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     auto fold = [&](float m, float l, f32x4 o) {
@@ -398,27 +400,27 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     return hipGetLastError();
 }
 
-template <bool kSelf>
+template <bool kSelf, bool kEven>
 static hipError_t launch_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
     const int n_rows = b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
-    if (max_splits < 1) return hipErrorInvalidValue;
-    if (max_splits <= 4) TC_LAUNCH((decode_finish_kernel<1, kSelf>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 8) TC_LAUNCH((decode_finish_kernel<2, kSelf>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 16) TC_LAUNCH((decode_finish_kernel<4, kSelf>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
-    else TC_LAUNCH((decode_finish_kernel<8, kSelf>), n_rows, 0, L, g, b, a, max_splits);
+    if (max_splits < 1 || !b.part_tab) return hipErrorInvalidValue;
+    if (max_splits <= 4) TC_LAUNCH((decode_finish_kernel<1, kSelf, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH((decode_finish_kernel<2, kSelf, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH((decode_finish_kernel<4, kSelf, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH((decode_finish_kernel<8, kSelf, kEven>), n_rows, 0, L, g, b, a, max_splits);
     return hipGetLastError();
 }
 
 hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
-    return launch_finish<true>(g, b, a, max_splits, L);
+    return b.part_stride > 0 ? launch_finish<true, true>(g, b, a, max_splits, L) : launch_finish<true, false>(g, b, a, max_splits, L);
 }
 
 hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
-    return launch_finish<false>(g, b, a, max_splits, L);
+    return b.part_stride > 0 ? launch_finish<false, true>(g, b, a, max_splits, L) : launch_finish<false, false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

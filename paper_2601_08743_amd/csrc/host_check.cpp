@@ -16,8 +16,8 @@
 //   within <ints> <floats>          plan for a workspace of that many integers and floats of partials (0 0: as much as it takes)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
-//                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0" per item,
-//                                      "ints <size of the device copy> <compact>", "parts <floats>" and, for kernels that keep partials by row, the tokens' first slots,
+//                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0 part_stride" per item,
+//                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, for kernels that keep partials by row, their table,
 //                                      "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
@@ -132,15 +132,15 @@ int main()
             std::printf("plan %d %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
                         p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
             for (const AttnItem &it : items)
-                std::printf("i %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
-                            it.q < 0 ? -1 : it.group, it.part0);
+                std::printf("i %d %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
+                            it.q < 0 ? -1 : it.group, it.part0, it.part_stride);
             std::vector<int32_t> slots;
             if (ok && parts_by_row(c, p)) {
-                slots.resize((size_t)p.total_S + 1);
-                fill_part_slots(p, splits, slots.data());
+                slots.resize(part_tab_ints(p));
+                fill_part_tab(p, splits, slots.data());
             }
             std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, append_blocks(p).size(), items.size(), groups.size()).total, p.compact ? 1 : 0);
-            std::printf("parts %zu", part_floats(c, p));
+            std::printf("parts %zu %d", part_floats(c, p), p.part_stride);
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");
             std::printf("groups %d %d\n", (int)groups.size(), p.n_groups);

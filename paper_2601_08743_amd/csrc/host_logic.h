@@ -191,7 +191,8 @@ struct Plan {
     bool valid = false;
     int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
     int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
-    int64_t n_part_slots = 0;   // kernels that keep partials by row: (suffix token, partition) pairs of the batch
+    int64_t n_part_slots = 0;   // kernels that keep partials by row: slots of the batch
+    int32_t part_stride = 0;    // and slots from token to token, 0: packed
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups; the suffix is appended first
@@ -318,6 +319,36 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
     return best;
 }
 
+// Where the split-KV partials of the fp32, decode and short-launch kernels stand.  They are kept by row: a slot, D + 2
+// floats for each query head, for every (suffix token, partition).  Where the queries have about as many
+// partitions each, every token has as many slots as the most it could need, so that the merge knows them without a
+// look into a table; where that would be more than twice the slots needed, or more than the workspace holds,
+// they are packed - a batch pays for the partitions that its queries have, not for its longest query's count
+// everywhere - and a query in one range has none (a decode step always has them).  Decode steps of one table each, 8 us
+// with the finish: 0.3 us less than packed.
+// (The other bf16 kernels keep, per (partition, group, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.)
+inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, const std::vector<int32_t> &splits_of_q,
+                           std::vector<AttnItem> &items)
+{
+    const int64_t even = (int64_t)p.max_splits * p.total_S;       // (n_part_slots: packed, so far)
+    if (!knobs.compact && even <= 2 * p.n_part_slots &&
+        (knobs.part_cap == 0 || (size_t)even * c.n_q_heads * (c.head_dim + 2) <= knobs.part_cap)) {
+        p.part_stride = p.max_splits;
+        p.n_part_slots = even;
+    }
+    std::vector<int64_t> first(p.B);
+    int64_t at = 0;
+    for (int i = 0; i < p.B; ++i) {
+        first[i] = p.part_stride ? (int64_t)p.cu_seqlens[i] * p.part_stride : at;
+        if (p.decode || splits_of_q[i] > 1) at += (int64_t)p.suffix_len[i] * splits_of_q[i];
+    }
+    for (AttnItem &it : items)
+        if (it.q >= 0) {
+            it.part0 = (int32_t)first[it.q];
+            it.part_stride = p.part_stride ? p.part_stride : it.n_splits;
+        }
+}
+
 // Attention work list for the batch in `p` (host arrays filled in).  Items of one
 // (query, KV head, split) read the same K/V; they are given work-group ids that are congruent
 // modulo 8 so that they land on the same XCD and share its L2 (work-groups go to the 8 XCDs
@@ -340,6 +371,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = false;
     p.brief = false;
     p.n_part_slots = 0;
+    p.part_stride = 0;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
@@ -385,14 +417,12 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             ns = std::max(1, std::min(ns, std::max(n_tiles, 1)));
             splits_of_q[i] = ns;
             p.max_splits = std::max(p.max_splits, ns);
-            const int32_t part0 = (int32_t)p.n_part_slots;
             p.n_part_slots += ns;
             const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
             const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
             for (int h = 0; h < c.n_kv_heads; ++h)
                 for (int s = 0; s < ns; ++s) {
                     AttnItem it{};
-                    it.part0 = part0;
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
                     it.split = s; it.n_splits = ns; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
@@ -412,6 +442,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
         p.decode = true;
+        place_partials(c, knobs, p, splits_of_q, items);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -579,7 +610,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
         splits_of_q[i] = ns;
         p.max_splits = std::max(p.max_splits, ns);
-        const int32_t part0 = (int32_t)p.n_part_slots;
         if (by_row && ns > 1) p.n_part_slots += (int64_t)S * ns;
         const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
         const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
@@ -589,7 +619,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 Bucket bucket{(int32_t)flat.size(), 0, t1 - t0};
                 AttnItem proto{};                       // what the row tiles share
                 proto.q = i; proto.kvh = h; proto.tile_begin = t0; proto.tile_end = t1; proto.split = s; proto.n_splits = ns;
-                proto.P = P; proto.S = S; proto.cu = p.cu_seqlens[i]; proto.part0 = part0;
+                proto.P = P; proto.S = S; proto.cu = p.cu_seqlens[i];
                 for (int k = 0; k < 16; ++k) {
                     const int idx = std::min(t0 * (KT / kBlockTokens) + k, last_blk);
                     proto.bid[k] = bt[idx] | (pad_of ? (int32_t)((uint32_t)pad_of[idx] << kPadShift) : 0);
@@ -644,6 +674,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
     while (!items.empty() && items.back().q < 0) items.pop_back();
     p.n_items = (int32_t)items.size();
+    if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one
     // work-group per CU: nothing hides a work-group's start-up and drain.  It wins when a launch is a
     // single round of work-groups or when they are long; many short ones (measured: 1140 work-groups
@@ -683,11 +714,6 @@ inline bool plan_attention(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
     return true;
 }
 
-// Split-KV partials.  The fp32, decode and short-launch kernels keep them by row: a suffix token has one slot
-// for each of its query's partitions (none where the query is not cut; a decode step always has them), a
-// slot holds D + 2 floats for each query head, and slots follow one another token by token - a batch pays
-// for the partitions that its queries have, not for its longest query's count everywhere.  The other bf16 kernels
-// keep, per (partition, group, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.
 inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode || ((c.dtype != TC_BF16 || p.brief) && p.max_splits > 1); }
 
 inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the batch's partials, in floats
@@ -696,16 +722,16 @@ inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the 
     return p.max_splits > 1 ? (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * (64 + 2) : 0;
 }
 
-// The first slot of every suffix token, and the slot behind the last one ([total_S + 1]).
-inline void fill_part_slots(const Plan &p, const std::vector<int32_t> &splits_of_q, int32_t *out)
+// BatchDev::part_tab
+inline size_t part_tab_ints(const Plan &p) { return (size_t)p.total_S + (p.part_stride == 0); }
+inline void fill_part_tab(const Plan &p, const std::vector<int32_t> &splits_of_q, int32_t *out)
 {
     int32_t at = 0;
-    for (int i = 0; i < p.B; ++i)
-        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n) {
-            out[n] = at;
-            if (p.decode || splits_of_q[i] > 1) at += splits_of_q[i];
-        }
-    out[p.total_S] = at;
+    for (int i = 0; i < p.B; ++i) {
+        const int32_t count = p.decode || splits_of_q[i] > 1 ? splits_of_q[i] : 0;
+        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += count) out[n] = p.part_stride ? count : at;
+    }
+    if (!p.part_stride) out[p.total_S] = at;
 }
 
 // The blocks that take suffix tokens, for the long-launch kernel's append.
@@ -725,7 +751,7 @@ inline std::vector<AppendBlk> append_blocks(const Plan &p)
 // is there (`n_*`: how many of each).
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
-    size_t block_table, cu, prefix, suffix, tok_q, part_slot, append, items, groups;
+    size_t block_table, cu, prefix, suffix, tok_q, part_tab, append, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
     bool lengths = false, tokens = false, by_row = false, merge_groups = false;
@@ -749,7 +775,7 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
     l.append = take(n_append * (sizeof(AppendBlk) / 4));
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
-    l.part_slot = take(l.by_row ? (size_t)p.total_S + 1 : 0);
+    l.part_tab = take(l.by_row ? part_tab_ints(p) : 0);
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
     l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);

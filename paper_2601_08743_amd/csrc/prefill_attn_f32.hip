@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
             for (int e = 0; e < 4; ++e) acc[e] *= inv;
             *(f32x4 *)((float *)a.out + orow * D + 4 * d4) = acc;
         } else {
-            const int64_t prow = (int64_t)(it.part0 + tok * it.n_splits + it.split) * g.Hq + it.kvh * G + (mr - tok * G);
+            const int64_t prow = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + it.kvh * G + (mr - tok * G);
             *(f32x4 *)(a.part_o + prow * D + 4 * d4) = acc;
             if (d4 == 0) { a.part_ml[prow * 2] = M; a.part_ml[prow * 2 + 1] = sum; }
         }
@@ -327,10 +327,10 @@ hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, 
 // Combine split-KV partials of one output row: with reference maxima m_s (log2 units), sums l_s
 // and unnormalised partial outputs O_s:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // D/4 threads per (suffix token, head) row, four columns each.  Bound: the latency of the loads of a
-// short launch - where the token's slots are, then the slots - so those of eight partitions are issued
-// before the first use (beyond the last one the last one again, ignored).
+// short launch, so those of eight partitions are issued before the first use, and (kEven) before it is known how
+// many there are (slots beyond a token's last partition are loaded and ignored).
 // Measured (2 queries, 9 k keys, 2 + 59 tokens, 20 partitions): 5.3 us; one partition after the other 18.4 us.
-template <int D>
+template <int D, bool kEven>
 __global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     constexpr int kThreads = D / 4;
@@ -340,19 +340,21 @@ __global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, Attn
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     if (row >= n_rows) return;
     const int n = (int)(row / g.Hq), head = (int)(row - (int64_t)n * g.Hq);
-    const int slot0 = b.part_slot[n], ns = b.part_slot[n + 1] - slot0;
-    if (ns <= 1) return;                         // written directly by the attention kernel
+    const PartSlots slots = part_slots<kEven>(b, n);
+    if (!kEven && slots.count <= 1) return;      // written directly by the attention kernel
     float2 ml[kBatch];
     f32x4 po[kBatch];
     auto fetch = [&](int s0) {
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const int64_t slot = (int64_t)(slot0 + min(s0 + j, ns - 1)) * g.Hq + head;
+            const int64_t slot = (int64_t)min(slots.first + s0 + j, slots.last) * g.Hq + head;
             ml[j] = *(const float2 *)(a.part_ml + slot * 2);
             po[j] = *(const f32x4 *)(a.part_o + slot * D + d);
         }
     };
     fetch(0);
+    const int ns = slots.count;
+    if (kEven && ns <= 1) return;
     float M = -INFINITY, den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < ns; s0 += kBatch) {
@@ -386,15 +388,15 @@ hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a,
 {
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
-    if (!b.part_slot) return hipErrorInvalidValue;
+    if (!b.part_tab) return hipErrorInvalidValue;
     const int per = 256 / (g.D / 4);
     const int grid = (int)((n_rows + per - 1) / per);
-    if (g.D == 64)
-        TC_LAUNCH(merge_f32_kernel<64>, grid, 0, L, g, b, a);
-    else if (g.D == 128)
-        TC_LAUNCH(merge_f32_kernel<128>, grid, 0, L, g, b, a);
-    else
-        return hipErrorInvalidValue;
+    const bool even = b.part_stride > 0;
+    if (g.D == 64 && even) TC_LAUNCH((merge_f32_kernel<64, true>), grid, 0, L, g, b, a);
+    else if (g.D == 64) TC_LAUNCH((merge_f32_kernel<64, false>), grid, 0, L, g, b, a);
+    else if (g.D == 128 && even) TC_LAUNCH((merge_f32_kernel<128, true>), grid, 0, L, g, b, a);
+    else if (g.D == 128) TC_LAUNCH((merge_f32_kernel<128, false>), grid, 0, L, g, b, a);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom 
             }
             *(uint2 *)((unsigned short *)a.out + orow * 128 + 4 * ch) = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
         } else {
-            const int64_t slot = (int64_t)(it.part0 + tok * it.n_splits + it.split) * g.Hq + it.kvh * G + (m - tok * G);
+            const int64_t slot = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + it.kvh * G + (m - tok * G);
             *(f32x4 *)(a.part_o + slot * 128 + 4 * ch) = acc;
             if (ch == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(M, L);
         }

@@ -279,7 +279,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     put(at.append, ablk);
     put(at.stitch, sblk);
-    if (at.by_row) fill_part_slots(p, splits_of_q, h + at.part_slot);
+    if (at.by_row) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
     put(at.groups, groups, at.merge_groups);
     put(at.rope_pos0, p.rope_pos0, p.rope);
@@ -302,7 +302,10 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     p.dev.seg_start = d + at.seg_start; p.dev.seg_len = d + at.seg_len; p.dev.seg_slot = d + at.seg_slot;
     p.dev.stitch_blk = (const StitchBlk *)(d + at.stitch);
-    if (at.by_row) p.dev.part_slot = d + at.part_slot;
+    if (at.by_row) {
+        p.dev.part_tab = d + at.part_tab;
+        p.dev.part_stride = p.part_stride;
+    }
     p.dev.append_blk = (const AppendBlk *)(d + at.append);
     p.dev.n_append_blk = (int32_t)ablk.size();
     p.dev.rope_pos0 = p.rope ? d + at.rope_pos0 : nullptr;

@@ -71,7 +71,9 @@ struct BatchDev {
     const int32_t *seg_slot;      // [n_seg] table slot holding the segment's table
     const StitchBlk *stitch_blk;  // [n_stitch_blk]
     const AppendBlk *append_blk;  // [n_append_blk] (batches whose suffix is appended by a launch of its own, else none)
-    const int32_t *part_slot;     // [sum S + 1] first partial slot of each suffix token (kernels that keep partials by row, else null)
+    const int32_t *part_tab;      // kernels that keep partials by row (else null): [sum S] partitions of each suffix token where
+                                  // slots are evenly spaced, [sum S + 1] first slot of each where they are packed
+    int32_t part_stride;          // slots from token to token, 0: packed
     const int32_t *tok_q;         // [sum S] query index of each suffix token
     const int32_t *rope_pos0;     // [B] position of each query's first schema token (re-encoding stitch), else null
     const double *rope_rev_freq;  // [D/2] theta^(-2i/D) / (2 pi): revolutions per position step, else null
@@ -95,8 +97,8 @@ struct AttnItem {
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
-    int32_t part0;       // kernels that keep partials by row: slot of the query's first token and partition
-    int32_t rsv;
+    int32_t part0;       // kernels that keep partials by row: slot of the query's first token and partition,
+    int32_t part_stride; // and slots from token to token
 };
 static_assert(sizeof(AttnItem) == 128, "AttnItem layout");
 

@@ -133,9 +133,9 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0,
     ghead = [l for l in lines if l.startswith("groups ")][0].split()
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
-                n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part0=[r[8] for r in rows])
+                n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
     info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
-    info["part_floats"], *info["slots"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
+    info["part_floats"], info["part_stride"], *info["part_tab"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
     assert int(ghead[1]) == len(groups)
     return info, items
 
@@ -190,18 +190,24 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
 
 def _check_slots(info, items, Hq, D, PS):
     """Partials kept by row: every (token, partition) of a cut query - of any query in a decode step - has a slot
-    of its own, the items write and the merge reads the same ones, and the buffer holds exactly those."""
+    of its own inside the buffer, and the items write where the merge, going by its table, reads."""
     ns, base = {}, np.cumsum([0] + [S for _, S in PS])
-    for it, part0 in zip(items, info["item_part0"]):
+    for it in items:
         if it[0] >= 0:
             ns[it[0]] = it[6]
-            if info["decode"] or it[6] > 1:
-                assert part0 == info["slots"][base[it[0]]]
-                for t in range(PS[it[0]][1]):                # where the attention kernels write
-                    assert part0 + t * it[6] + it[5] == info["slots"][base[it[0]] + t] + it[5]
     counts = [n if info["decode"] or n > 1 else 0 for q, (_, S) in enumerate(PS) for n in [ns.get(q, 0)] * S]
-    assert info["slots"] == np.cumsum([0] + counts).tolist()
-    assert info["part_floats"] == sum(counts) * Hq * (D + 2)
+    if info["part_stride"]:                      # evenly spaced
+        assert info["part_tab"] == counts and info["part_stride"] == info["max_splits"]
+        first, n_slots = [n * info["part_stride"] for n in range(len(counts))], len(counts) * info["part_stride"]
+        assert n_slots <= 2 * sum(counts)
+    else:
+        assert info["part_tab"] == np.cumsum([0] + counts).tolist()
+        first, n_slots = info["part_tab"][:-1], sum(counts)
+    assert info["part_floats"] == n_slots * Hq * (D + 2)
+    for it, (part0, stride) in zip(items, info["item_part"]):
+        if it[0] >= 0 and (info["decode"] or it[6] > 1):
+            for t in range(PS[it[0]][1]):
+                assert part0 + t * stride + it[5] == first[base[it[0]] + t] + it[5] < n_slots
 
 
 # Batches of one long sequence among short ones, which the workspace of the entry point that allocates nothing
@@ -379,7 +385,7 @@ def test_planner_random_batches(exe):
                   kernel=int(rng.choice([0, 0, 1, 2, 3, 4, 5])) if dtype else 0)
         info, items = _plan(exe, Hkv * G, Hkv, PS, dtype=dtype, D=128 if dtype else 64, **kw)
         _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
-        if info["slots"]:
+        if info["part_tab"]:
             _check_slots(info, items, Hkv * G, 128 if dtype else 64, PS)
 
 
