@@ -12,7 +12,10 @@
 // all arrive by LDS-direct loads that the wave counts itself, the ids of a wave's first two units come
 // with the work item, and so the first keys are requested one scalar fetch after the kernel starts.
 // Units of 32 keys rather than 64 halve both the shortest useful range (a sequence of 4 k tokens
-// makes 132 work-groups instead of 44) and what a wave loses when a range does not divide by four.
+// makes 132 work-groups instead of 44) and what a wave loses when a range does not divide by four.  A
+// wave works on two units at a time where it has them: over tables that many sequences read in place the keys come
+// from the L2 and what counts is the wave's own work, of which one maximum, one vote and two waits for each
+// unit were 6 % (47 sequences of 9.1 k tokens, 32 / 8 heads: 159 us in single units, 151 with the 64-key tiles, 134 so).
 //
 // At the end the four waves' (max, sum, O) are combined through LDS and the work-group writes one
 // partial per row; a second kernel combines the key partitions of a query, adds the new token itself
@@ -28,6 +31,8 @@
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
+
+#include <type_traits>
 
 namespace tc {
 
@@ -165,54 +170,72 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
         const uint32_t kb = lds_w + r32 * 256 + ((hh ^ (r32 & 15)) << 4);
         const uint32_t vb = lds_w + kDecPart + r32 * 32 + hh * 16;
 
-        // K(k), V(k), K(k+1), V(k+1) are in flight when unit k starts; its operands are read into
-        // registers and their place in the ring is requested again for unit k + 2.  Loads complete
-        // in the order issued, so a wait that leaves N younger ones outstanding has everything
-        // older in LDS.
-        // The entries of unit k + 3 are read from LDS while unit k is worked on.
-        int2 e_now = e_first, e_next = e_second, e_read = n_mine > 2 ? read_entries(2) : make_int2(0, 0);
-        for (int k = 0; k < n_mine; ++k) {
-            const int left = n_mine - 1 - k;
-            const int2 e_load = make_int2(__builtin_amdgcn_readfirstlane(e_read.x), __builtin_amdgcn_readfirstlane(e_read.y));
-            if (left >= 3) e_read = read_entries(k + 3);
-            const uint32_t slot = (uint32_t)(k & 1) * kDecSlot;
-            if (left >= 1) wait_loads<24>();
+        // Two units at a time (64 keys: one maximum, one vote on the rescale, two waits), a last odd one by itself.
+        // The ring holds both; K of the next two is requested as soon as these two's K fragments are in registers,
+        // V likewise.  Loads complete in the order issued, so a wait that leaves N younger ones outstanding has
+        // everything older in LDS.
+        int2 e0 = e_first, e1 = e_second;              // block-table entries of the units at work
+        auto step = [&](auto pair_c, int k) {
+            constexpr int N = decltype(pair_c)::value; // units: k .. k + N - 1, k even: unit k + u stands in slot u
+            const int left = n_mine - k - N;           // and how many follow
+            // (for the first pair K and V were requested unit by unit: only V of the second may be outstanding)
+            if (N == 2 && k > 0) wait_loads<16>();
             else wait_loads<8>();
-            bf16x8 kf[8];
+            int2 n0 = make_int2(0, 0), n1 = n0;
+            if (left >= 1) n0 = read_entries(k + N);
+            if (left >= 2) n1 = read_entries(k + N + 1);
+            bf16x8 kf[8 * N];
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) kf[ks] = *(lds_frag)(uintptr_t)((kb + slot) ^ (ks << 5));
+            for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                for (int u = 0; u < N; ++u) kf[N * ks + u] = *(lds_frag)(uintptr_t)((kb + u * kDecSlot) ^ (ks << 5));
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // K area read out
-            if (left >= 2) issue_k(k + 2, e_load);
-            f32x16 s;
+            n0 = make_int2(__builtin_amdgcn_readfirstlane(n0.x), __builtin_amdgcn_readfirstlane(n0.y));
+            n1 = make_int2(__builtin_amdgcn_readfirstlane(n1.x), __builtin_amdgcn_readfirstlane(n1.y));
+            if (left >= 1) issue_k(k + N, n0);
+            if (left >= 2) issue_k(k + N + 1, n1);
+            f32x16 s[N];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[e] = 0.f;
+            for (int u = 0; u < N; ++u)
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
-            if (left >= 2) wait_loads<24>();
-            else if (left == 1) wait_loads<16>();
+                for (int e = 0; e < 16; ++e) s[u][e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                for (int u = 0; u < N; ++u) s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[N * ks + u], qf[ks], s[u], 0, 0, 0);
+            if (left >= 2) wait_loads<16>();
+            else if (left == 1) wait_loads<8>();
             else wait_loads<0>();
-            bf16x8 vf[8];                              // V^T fragments: in registers before the softmax starts
+            bf16x8 vf[8 * N];                          // V^T fragments: in registers before the softmax starts
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
+            for (int u = 0; u < N; ++u)
 #pragma unroll
-                for (int db = 0; db < 4; ++db) vf[4 * kk + db] = *(lds_frag)(uintptr_t)(vb + slot + kk * kDecHeadBlk + db * 1024);
+                for (int j = 0; j < 8; ++j)
+                    vf[8 * u + j] = *(lds_frag)(uintptr_t)(vb + u * kDecSlot + (j >> 2) * kDecHeadBlk + (j & 3) * 1024);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // V area read out
-            if (left >= 2) issue_v(k + 2, e_load);
+            if (left >= 1) issue_v(k + N, n0);
+            if (left >= 2) issue_v(k + N + 1, n1);
             // positions that hold no key: beyond the end of the sequence, and the unused tail of a
             // table block read in place (its count rides in the block-table entry)
-            const int key0 = (u_begin + w + 4 * k) * kDecUnit;
-            const int pad0 = entry_pad(e_now.x), pad1 = entry_pad(e_now.y);
-            if ((pad0 | pad1) != 0 || key0 + kDecUnit > P) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int in_blk = 8 * ((e >> 2) & 1) + 4 * hh + (e & 3);
-                    const int key = key0 + 8 * (e >> 2) + 4 * hh + (e & 3);
-                    s[e] = (key >= P || in_blk >= kBlockTokens - (e < 8 ? pad0 : pad1)) ? -INFINITY : s[e];
+            for (int u = 0; u < N; ++u) {
+                const int key0 = (u_begin + w + 4 * (k + u)) * kDecUnit;
+                const int2 e_u = u ? e1 : e0;
+                const int pad0 = entry_pad(e_u.x), pad1 = entry_pad(e_u.y);
+                if ((pad0 | pad1) != 0 || key0 + kDecUnit > P) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int in_blk = 8 * ((e >> 2) & 1) + 4 * hh + (e & 3);
+                        const int key = key0 + 8 * (e >> 2) + 4 * hh + (e & 3);
+                        s[u][e] = (key >= P || in_blk >= kBlockTokens - (e < 8 ? pad0 : pad1)) ? -INFINITY : s[u][e];
+                    }
                 }
             }
-            float mx = s[0];
+            float mx = s[0][0];
 #pragma unroll
-            for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+            for (int u = 0; u < N; ++u)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[u][e]);
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float mxs = mx * c;
             if (__any(mxs > m_run + kDecRescale)) {    // also taken while m_run is still -inf
@@ -227,21 +250,29 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
             }
             const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c, neg_m));
-                l_lane += s[e];
-            }
+            for (int u = 0; u < N; ++u)
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                bf16x8 pf;
+                for (int e = 0; e < 16; ++e) {
+                    s[u][e] = __builtin_amdgcn_exp2f(fmaf(s[u][e], c, neg_m));
+                    l_lane += s[u][e];
+                }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (__bf16)s[8 * kk + e];
+            for (int u = 0; u < N; ++u)
 #pragma unroll
-                for (int db = 0; db < 4; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * kk + db], pf, o[db], 0, 0, 0);
-            }
-            e_now = e_next;
-            e_next = e_load;
-        }
+                for (int kk = 0; kk < 2; ++kk) {
+                    bf16x8 pf;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pf[e] = (__bf16)s[u][8 * kk + e];
+#pragma unroll
+                    for (int db = 0; db < 4; ++db)
+                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[8 * u + 4 * kk + db], pf, o[db], 0, 0, 0);
+                }
+            e0 = n0;
+            e1 = n1;
+        };
+        int k = 0;
+        for (; k + 1 < n_mine; k += 2) step(std::integral_constant<int, 2>{}, k);
+        if (k < n_mine) step(std::integral_constant<int, 1>{}, k);
     }
 
     // ---- combine the four waves: each writes (max, sum) per row and O as padded rows of floats into

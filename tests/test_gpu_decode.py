@@ -274,3 +274,29 @@ def test_decode_batch_c3_shape(H):
             assert np.abs(outs[0][n:n + 1] - ref).max() <= 1e-2, (layer, i)
     dw.ctx.tc_release_seqs(bt)
     dw.close()
+
+
+@pytest.mark.parametrize("alias", [False, True])
+@pytest.mark.parametrize("hq,hkv,splits", [(28, 4, 1), (8, 8, 1), (32, 1, 2)])
+def test_units_per_wave(hq, hkv, splits, alias):
+    """Ranges that give the waves none, one, two (a pair), three (a pair and a single one) and more units of 32 keys each, the
+    last unit whole, one key long and one key short, blocks with unused tails among them, in one batch."""
+    import harness as H
+    lens = [1, 31, 32, 33, 127, 128, 129, 160, 255, 256, 257, 383, 385, 511, 513, 640, 769, 1025]
+    cfg = W.WorkloadConfig("d", 1, hq, hkv, 128, "bf16", len(lens), (1, max(lens)), len(lens) + 2, (1, 1), "uniform", (1, 1),
+                           len(lens), 321)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = lens
+    wl.queries[:] = [np.array([i], dtype=np.int32) for i in range(len(lens))] + [np.array([17, 3, 16], dtype=np.int32), np.array([], dtype=np.int32)]
+    wl.suffix_len[:] = 1
+    dw = H.DeviceWorkload(wl, slot_layout=1 if alias else 0, seq_blocks=sum(-(-n // 16) + 2 for n in lens) + 140)
+    dw.ctx.tc_set_kv_splits(splits)
+    bt, pl = dw.alias() if alias else dw.stitch()
+    out, qkv = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_attn_kernel() == 3
+    got, ref = H.out_to_f64(out, cfg), H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+    for i, r in ref.items():
+        # weights and outputs of 8 bits (2^-9 relative each), |v| < 5.5, weights that sum to 1
+        assert float(np.abs(got[i:i + 1] - r).max()) <= 2.2e-2, i
+    dw.ctx.tc_release_seqs(bt)
+    dw.close()
