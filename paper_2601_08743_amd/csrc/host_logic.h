@@ -452,25 +452,28 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // the alternating-groups bf16 kernel reads the suffix from the pool as well (it is appended by a
     // launch of its own first), so it, too, sees one paged sequence
     // It is chosen for long launches (estimated from the row tiles x key tiles of the batch at
-    // ~0.85 us per 128 x 64 tile and CU): its own append launch costs ~10 us, and with 256 rows per
+    // ~0.85 us per 128 x 64 tile and CU): its append launch costs 7 us, and with 256 rows per
     // work-group a short launch would not fill the chip.  Measured: c3 (1140 items of ~24 tiles)
-    // 207 + 12 us against 226 us in the general kernel, c4 775 + 14 us against 814 us in the pipelined
-    // one.  Since the append launch costs 7 us and not 10, shorter launches gain as well, if 256-row tiles
-    // are nearly as full as 128-row ones (54 batches estimated at 14 .. 80 us that pad by up to a fifth:
-    // 1.19 times as fast, two slower; where tiles pad by more 0.8 .. 1.2; below 14 us 0.75 .. 1.3).
+    // 171 + 7 us against 226 us in the general kernel, c4 688 + 9 us against 814 us in the pipelined
+    // one.  Between 14 and 80 us it gains if its 256-row tiles are nearly as full as 128-row ones.  The line is
+    // at 6 / 5, included, because five 128-row tiles that make three of 256 rows (40 / 8 heads, 128 new tokens: the
+    // micro-batches of a cold cache) still gain: 40 of those 1.085 times as fast as in the other kernels, two of
+    // them 5 % slower (192 ragged items, the longest of which outlasts the rest); of 320 drawn batches of
+    // every kind none is slower by more than 3 % than with 80 us as the only line.  Where tiles pad by more
+    // it is 0.8 .. 1.2 times as fast, below 14 us 0.75 .. 1.3.
     bool pp = false;
     if (bf16 && ctx->forced_row_blocks == 0) {
         if (ctx->forced_attn_kernel == 4) pp = true;
         else if (ctx->forced_attn_kernel == 0) {
-            double work = 0, work_pp = 0;               // in 128-row tiles; the same with rows padded to this kernel's 256
+            int64_t work = 0, work_pp = 0;              // in 128-row tiles; the same with rows padded to this kernel's 256
             for (int i = 0; i < p.B; ++i)
                 if (p.suffix_len[i] > 0) {
-                    const double per_row_tile = (double)c.n_kv_heads * ((p.prefix_len[i] + p.suffix_len[i] + KT - 1) / KT);
-                    work += per_row_tile * ((p.suffix_len[i] * G + kAttnRows - 1) / kAttnRows);
-                    work_pp += per_row_tile * 2 * ((p.suffix_len[i] * G + 2 * kAttnRows - 1) / (2 * kAttnRows));
+                    const int64_t per_row_tile = (int64_t)c.n_kv_heads * (((int64_t)p.prefix_len[i] + p.suffix_len[i] + KT - 1) / KT);
+                    work += per_row_tile * (((int64_t)p.suffix_len[i] * G + kAttnRows - 1) / kAttnRows);
+                    work_pp += per_row_tile * 2 * (((int64_t)p.suffix_len[i] * G + 2 * kAttnRows - 1) / (2 * kAttnRows));
                 }
-            const double us = work * 0.85 / 256.0;
-            pp = us >= 80.0 || (!ctx->compact && us >= 14.0 && work_pp <= 1.2 * work);
+            const double us = (double)work * 0.85 / 256.0;
+            pp = us >= 80.0 || (!ctx->compact && us >= 14.0 && 5 * work_pp <= 6 * work);
         }
     }
     const bool unified = !bf16 || pp;

@@ -331,6 +331,16 @@ def test_planner_paper_shapes(exe):
     _check_plan(info, items, 28, 4, dec)
 
 
+def test_long_launch_kernel_up_to_a_fifth_of_padding(exe):
+    """Launches of 14 .. 80 us go to the long-launch kernel if 256-row tiles make at most 6 / 5 of the rows of 128-row tiles,
+    the limit itself (five 128-row tiles, three of 256 rows) included."""
+    at = [(3000 + 17 * i, 128) for i in range(8)]           # 40 / 8 heads: 640 rows a KV head
+    for PS, want in ((at, 1), (at + [(3000, 25)], 0), (at[:1], 0), ([(3000, 51)] * 8, 1)):
+        info, items = _plan(exe, 40, 8, PS)
+        _check_plan(info, items, 40, 8, PS)
+        assert info["pingpong"] == want, PS
+
+
 def test_decode_ranges_make_one_round_of_even_work_groups(exe):
     """A decode step is planned for one round of work-groups on the 256 CUs, all about equally long:
     the paper-shaped batches come out as at most 256 items, none longer than the shortest common
