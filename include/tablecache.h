@@ -229,6 +229,10 @@ tc_status tc_stitch_kv_rope(tc_ctx *ctx, const int32_t *table_ids, const int32_t
  *   out = softmax_j( sm_scale * q . k_j ) v_j   over j in [0, P_i) U [P_i, P_i + r].
  *   q, out            DEVICE [sum S][Hq][D]      (16-byte aligned)
  *   k_new, v_new      DEVICE [sum S][Hkv][D]     (16-byte aligned)
+ * In bf16 contexts values must be finite where some row of the query does not see them: the matrix
+ * cores multiply a masked key's value by a weight of zero, so an infinity or a NaN in a suffix token's
+ * value may turn the query's earlier rows into NaN, and which of them depends on the kernel that the
+ * batch gets.  In fp32 contexts such a value reaches only the rows that see it.
  *   cu_seqlens        HOST [B+1], cu_seqlens[i+1]-cu_seqlens[i] == suffix_len[i]
  *   block_table       HOST [B][max_blocks]
  *   prefix_len, suffix_len   HOST [B]

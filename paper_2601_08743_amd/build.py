@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtablecache.so")
 PY_CALL = os.path.join(HERE, "_py_call.so")
 SOURCES = ["tc_host.hip", "kv_stitch.hip", "prefill_attn_bf16.hip", "prefill_attn_f32.hip", "decode_attn_bf16.hip", "prefill_attn_pp_bf16.hip",
-           "prefill_attn_short_bf16.hip",           "frontend.hip"]
+           "prefill_attn_short_bf16.hip", "frontend.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 instructions
          "-Wno-unused-command-line-argument"]

@@ -11,7 +11,6 @@
 #include <cstdint>
 #include <cstring>
 #include <list>
-#include <set>
 #include <unordered_map>
 #include <vector>
 

@@ -11,6 +11,10 @@
 // costs is that 32 rows, not 128, share a key tile on its way from the L2, which is why it is only
 // chosen where a launch is one or two rounds of work-groups.
 //
+// Masked keys get a weight of zero, and their values are multiplied by it: as in the other bf16 kernels those
+// have to be finite.  (So are the zeros and the suffix values that the tail of the prefix's last block holds before
+// and after the append of the same launch, which may run beside a tile's loads.)
+//
 // Measured per layer, merge included where there is one, against the pipelined or general kernel: 28 / 4
 // heads, one query of 1.1 k prefix and 17 new tokens 10.3 us (14.9); thirteen of 4 k and 3 .. 6 tokens 27.1
 // (35.4); 40 / 8 heads, eight of 350 and 40 tokens 17.7 (28.3), sixteen of 1 k and 2 tokens 16.2 (36.0), four of

@@ -357,10 +357,10 @@ def test_decode_ranges_make_one_round_of_even_work_groups(exe):
         real = [it for it in items if it[0] >= 0]
         tiles = [-(-P // 64) for P, _ in PS]
         assert len(real) <= 256, (name, len(real))
-        # no shorter common range length would have fitted the 256 CUs (or the floor of six tiles was hit)
+        # no shorter common range length would have fitted the 256 CUs (or the floor of two tiles was hit)
         L = longest
         fits = lambda L: sum(Hkv * max(1, -(-t // L)) for t in tiles) <= 256
-        assert fits(L) and (L <= 6 or not fits(L - 1)), (name, L)
+        assert fits(L) and (L <= 2 or not fits(L - 1)), (name, L)
         per_q = {}
         for q, kvh, m0, tb, te, split, ns in real:
             per_q[q] = ns
@@ -370,6 +370,10 @@ def test_decode_ranges_make_one_round_of_even_work_groups(exe):
         assert lens == sorted(lens, reverse=True), "longest items first"
         print("%s decode: %d items, ranges of %d..%d key tiles, %d..%d ranges per sequence" % (
             name, len(real), min(lens), max(lens), min(per_q.values()), max(per_q.values())))
+    # short sequences: ranges of two tiles, a unit for each wave, and a lone odd tile
+    info, items = _plan(exe, 28, 4, [(64 * 9, 1), (64 * 4 - 1, 1)])
+    assert _check_plan(info, items, 28, 4, [(64 * 9, 1), (64 * 4 - 1, 1)]) == 2
+    assert sorted({(q, te - tb) for q, _, _, tb, te, _, _ in items}) == [(0, 1), (0, 2), (1, 2)]
     # more (query, KV head) pairs than CUs: one range each, several rounds
     PS = [(3000 + 17 * i, 1) for i in range(100)]
     info, items = _plan(exe, 28, 4, PS)
