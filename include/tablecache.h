@@ -268,7 +268,7 @@ tc_status tc_prefill_attn(tc_ctx *ctx, int32_t layer, const void *q, const void 
  * Every call re-plans from its integer arguments unless they equal those of the previous call
  * through this entry point (a batch stitched by tc_stitch_kv is planned again here, once).
  * All contexts on one GPU share that GPU's workspace, which keeps the last call's contents (nothing
- * in it has to start at zero: every partial a merge reads was written by the attention launch
+ * in it has to start at zero: every partial a merge uses was written by the attention launch
  * before it): calls through this entry point that overlap on one GPU - different streams, different
  * contexts - race; keep them on one stream or order them with events.
  * Errors: as tc_prefill_attn, plus TC_ERR_CAPACITY.

@@ -319,7 +319,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.fixed = fixed;
     p.part = nullptr;
     if (fixed) {
-        // nothing in the partials has to start at zero: every slot a merge reads was written by the
+        // nothing in the partials has to start at zero: every slot a merge uses was written by the
         // attention launch before it
         if (part_need) p.part = (float *)(ctx->scratch_dev + kScratchPlanInts * 4);
     } else if (part_need) {
