@@ -159,6 +159,35 @@ def test_noalloc_range_longer_than_the_block_id_table():
     dw.close()
 
 
+def test_noalloc_plan_of_least_space():
+    """3302 rows of 313 block ids: with the rows padded to 316 and short-launch items the plan has more integers than the workspace
+    (1 Mi), so the 30 queries that bring tokens go through another kernel, over unpadded (odd) table rows."""
+    import harness as H
+    n, total, blocks = 30, 3302, 313
+    cfg = W.WorkloadConfig("n", 1, 4, 1, 128, "bf16", 1, (4992, 4992), n, (1, 1), "uniform", (8, 8), 1, 322)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = 4992
+    wl.queries[:] = [np.array([0], dtype=np.int32)] * n
+    wl.suffix_len[:] = 8
+    dw = H.DeviceWorkload(wl)
+    bt, pl = dw.stitch(max_blocks=blocks)
+    out, qkv = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_attn_kernel() == 5
+    idle = total - n                             # queries without new tokens, over the first one's blocks
+    bt, pl = np.concatenate([bt, np.repeat(bt[:1], idle, axis=0)]), np.concatenate([pl, np.full(idle, 5000, dtype=np.int32)])
+    sl = np.concatenate([wl.suffix_len, np.zeros(idle, dtype=np.int32)]).astype(np.int32)
+    cu = np.concatenate([[0], np.cumsum(sl)]).astype(np.int32)
+    got = torch.full_like(out, float("nan"))
+    dw.ctx.tc_prefill_attn_noalloc(0, *(H.to_dev(x, cfg) for x in qkv), got, cu, bt, pl, sl, wl.sm_scale)
+    torch.cuda.synchronize()
+    assert dw.ctx.tc_attn_kernel() in (1, 2) and dw.ctx.tc_kv_splits() == 1
+    ref = H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+    for o in (out, got):
+        g64 = H.out_to_f64(o, cfg)
+        assert max(float(np.abs(g64[8 * i:8 * i + 8] - r).max()) for i, r in ref.items()) <= 1e-2
+    dw.close()
+
+
 def test_noalloc_refuses_what_does_not_fit():
     """A batch whose partials exceed the fixed workspace is refused with TC_ERR_CAPACITY and
     enqueues nothing; the allocating entry point still serves it."""
