@@ -17,17 +17,18 @@
 // from the L2 and what counts is the wave's own work, of which one maximum, one vote and two waits for each
 // unit were 6 % (47 sequences of 9.1 k tokens, 32 / 8 heads: 159 us in single units, 151 with the 64-key tiles, 134 so).
 //
-// At the end the four waves' (max, sum, O) are combined through LDS and the work-group writes one
-// partial per row; a second kernel combines the key partitions of a query, adds the new token itself
-// (its key and value come from k_new / v_new: one dot product and one scaled row per head) and
-// writes the output.  The new token's K/V are appended to the pool by the first key range of each
-// (query, KV head): extra work-groups for it, as in prefill, would each wait for a CU's LDS.
+// At the end the four waves' (max, sum, O) are combined through LDS.  A work-group that has all the keys of its (query, KV
+// head) adds the new token itself (its key and value come from k_new / v_new: one dot product and one scaled row per
+// head) and writes the output; one of several stores one partial per row, and the last of them to end combines them
+// (arrive.h).  The new token's K/V are appended to the pool by the first key range of each (query, KV head): extra
+// work-groups for it, as in prefill, would each wait for a CU's LDS.
 //
-// Measured per launch (28 / 4 heads unless said): one sequence of 4.2 k tokens, 8.6 MB: 6.2 us, with 64-key
-// tiles, block ids behind a barrier and ranges of six tiles 8.8 us (an empty launch reads 4.0 us in the same
-// events); 13 sequences of 0.6 k, 40 / 8 heads: 12.5 against 17.7 us, of which the append work-groups that
-// waited for a CU were 4; 32 sequences, 142 MB: 31.4 against 32.6 us; four of 25 k, 32 / 8 heads, 412 MB:
-// 63.5 against 67.9 us = 6.5 TB/s.
+// Measured, a layer of a token step (28 / 4 heads unless said; in parentheses with a second launch that combined the
+// partials): one sequence of 200 tokens 5.3 us (7.5), of 4.2 k in 33 ranges 8.9 (10.0), of 14.4 k 12.5 (14.3); eight of 2.4 k 12.7
+// (14.3); 32 sequences, 142 MB: 32.4 (33.7); four of 25 k, 32 / 8 heads, 412 MB: 65.0 (67.1) = 6.3 TB/s.  Where the 8.9 us
+// go: 1.3 between two launches, 0.45 to the work item, 1.0 to the first keys, 1.5 for the unit, 0.5 to combine the waves, 0.3
+// to store, 0.8 to count in, 2 to fold 33 partials (118 KB) on one CU and 0.1 to write.
+#include "arrive.h"
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
@@ -50,6 +51,40 @@ constexpr int kDecIds = kDecQ + 32 * 256;            // block ids of the range, 
 constexpr int kDecLds = kDecIds + kAttnMaxTiles * (kAttnKeys / kBlockTokens) * 4 + 256;    // + alignment slack
 constexpr int kDecRow = 132;                         // padded row of the final exchange (floats)
 constexpr float kDecRescale = 8.f;
+
+// Four columns of the new token's key and value and of one head's query row.
+struct SelfRaw { uint2 q, k, v; };
+__device__ __forceinline__ SelfRaw load_self(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d)
+{
+    const int64_t kv = ((int64_t)it.cu * g.Hkv + it.kvh) * 128 + d;
+    return SelfRaw{*(const uint2 *)((const unsigned short *)a.q + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d),
+                *(const uint2 *)((const unsigned short *)a.k_new + kv), *(const uint2 *)((const unsigned short *)a.v_new + kv)};
+}
+
+// The new token's score against itself and its value (32 neighbouring threads, four columns each).
+struct Self { float score; f32x4 v; };
+__device__ __forceinline__ Self score_self(const SelfRaw &s, float scale_log2)
+{
+    auto lo = [](uint32_t u) { return __uint_as_float(u << 16); };
+    auto hi = [](uint32_t u) { return __uint_as_float(u & 0xffff0000u); };
+    const float prod = sum32(lo(s.q.x) * lo(s.k.x) + hi(s.q.x) * hi(s.k.x) + lo(s.q.y) * lo(s.k.y) + hi(s.q.y) * hi(s.k.y));
+    return Self{prod * scale_log2, {lo(s.v.x), hi(s.v.x), lo(s.v.y), hi(s.v.y)}};
+}
+
+// The new token joins the row's keys, and the row is written.
+__device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d, const Self &s, RowSum x)
+{
+    x.add(s.score, 1.f, s.v);
+    const float inv = 1.f / x.L;
+    unsigned short r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const __bf16 y = (__bf16)(x.acc[e] * inv);
+        r[e] = *(const unsigned short *)&y;
+    }
+    *(uint2 *)((unsigned short *)a.out + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d) =
+        make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
+}
 
 __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchDev b, AttnArgs a)
 {
@@ -86,15 +121,18 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
     };
     // K of a unit: two blocks as four 1 KB pieces of four rows each (chunk c of row r at chunk
     // position c ^ r); V verbatim; 8 load instructions per operand
-    const int k_off0 = (lane >> 4) * 256;
+    uint32_t k_off[4], v_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        k_off[i] = (lane >> 4) * 256 + (((lane & 15) ^ (4 * i + (lane >> 4))) * 16);
+        v_off[i] = lane * 16;
+    }
     auto issue_k = [&](int k, int2 e) {
         const uint32_t dst = lds_w + (k & 1) * kDecSlot;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const char *src = pool_l + (int64_t)entry_bid(j ? e.y : e.x) * bb;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                load_to_lds(dst + j * 4096 + i * 1024, src, k_off0 + i * 1024 + (((lane & 15) ^ (4 * i + (lane >> 4))) * 16));
+            load4_to_lds(dst + j * 4096, src, k_off);
         }
     };
     auto issue_v = [&](int k, int2 e) {
@@ -102,8 +140,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const char *src = pool_l + (int64_t)entry_bid(j ? e.y : e.x) * bb + v_half;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) load_to_lds(dst + j * 4096 + i * 1024, src + i * 1024, lane * 16);
+            load4_to_lds(dst + j * 4096, src, v_off);
         }
     };
 
@@ -111,7 +148,10 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
     // loads are issued here, ahead of the counted ones, the stores come at the very end (a store counts
     // as an outstanding memory operation).  Behind the token the block is zero, as after every append.
     // K: thread -> 16 bytes of one token row.  V^T: thread d -> the 16 tokens of row d, merged.
+    // (The new token's own key and value, and the query row that meets them, are needed last of all: requested here, too.)
     const bool appends = it.split == 0;
+    const int slot8 = tid >> 5, d4 = 4 * (tid & 31);   // at the end: eight groups of 32 threads, four columns each
+    const SelfRaw self_raw = load_self(g, a, it, min(slot8, G - 1), d4);
     const int t_new = P & 15;
     char *k_dst = nullptr, *v_dst = nullptr;
     uint4 k_put = make_uint4(0, 0, 0, 0), v_old0 = k_put, v_old1 = k_put;
@@ -294,8 +334,12 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
         }
     }
     __syncthreads();
+    const Self self = score_self(self_raw, c);
+    const int64_t first_slot = (int64_t)it.part0 * g.Hq + (int64_t)it.kvh * G * it.n_splits;
+    const uint32_t n_slots = (uint32_t)(it.n_splits * G);
+    const SharedPart part_o(a.part_o + first_slot * 128, n_slots * 512), part_ml(a.part_ml + first_slot * 2, n_slots * 8);
     for (int idx = tid; idx < G * 32; idx += 256) {
-        const int row = idx >> 5, d = 4 * (idx & 31);
+        const int row = idx >> 5, d = d4;
         float M = -INFINITY;
 #pragma unroll
         for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * kDecWave))[32 * kDecRow + 2 * row]);
@@ -311,9 +355,34 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
         }
-        const int64_t slot = (int64_t)(it.part0 + it.split) * g.Hq + it.kvh * G + row;
-        *(f32x4 *)(a.part_o + slot * 128 + d) = acc;
-        if (d == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(M, L);
+        if (it.n_splits == 1) {
+            finish_row(g, a, it, row, d, row == slot8 ? self : score_self(load_self(g, a, it, row, d), c), RowSum{M, L, acc});
+        } else {
+            const uint32_t off = (uint32_t)(it.split * G + row);
+            part_o.put4(off * 512 + d * 4, acc);
+            if (d == 0) part_ml.put2(off * 8, M, L);
+        }
+    }
+    if (it.n_splits > 1 && last_to_arrive(a.arrivals + it.group * kArrivalStride, it.n_splits, (int32_t *)(lds + kDecIds))) {
+        // a row to 32 threads; of up to four rows two such groups take every other partition each
+        const bool two = G <= 4;
+        float *s_w = (float *)lds + 8 * kDecRow + slot8 * kFoldBatch;
+        for (int r0 = 0; r0 < G; r0 += 8) {
+            const int row = two ? slot8 & 3 : r0 + slot8, half = two ? slot8 >> 2 : 0;
+            RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
+            if (row < G) x = fold_partials(part_o, part_ml, row, G, it.n_splits, half, two ? 2 : 1, tid & 31, s_w);
+            if (two) {
+                float *sx = (float *)lds + slot8 * kDecRow;
+                *(f32x4 *)(sx + d4) = x.acc;
+                if (d4 == 0) { sx[128] = x.M; sx[129] = x.L; }
+                __syncthreads();
+                const float *other = (const float *)lds + (slot8 | 4) * kDecRow;
+                if (half == 0) x.add(other[128], other[129], *(const f32x4 *)(other + d4));
+            }
+            if (row < G && half == 0) {
+                finish_row(g, a, it, row, d4, row == slot8 ? self : score_self(load_self(g, a, it, row, d4), c), x);
+            }
+        }
     }
     if (appends) {
         if ((tid >> 4) >= t_new) *(uint4 *)k_dst = k_put;
@@ -333,17 +402,15 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
     }
 }
 
-// Combine the key partitions of an output row (token, head), add the new token itself, normalise, write
-// bf16.  Bound by the latency of its loads, so all of them are issued before the first use: kGroups
-// groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
+// Combine the partitions of an output row (token, head) of the short-launch prefill kernel, normalise, write bf16.
+// Bound by the latency of its loads, so all of them are issued before the first use: kGroups groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
 // row of up to 4 * kGroups partitions costs one round trip - and fold their results through LDS.  A
 // work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
 // threads would load what nobody needs.  (Slots beyond a row's last partition are loaded and ignored; with evenly
-// spaced slots, kEven, nothing waits for the number of partitions before the loads.)
-// Without kSelf there is no new token to add and rows of one partition are left alone (they were written
-// directly): the merge of the short-launch prefill kernel's partitions.
-template <int kGroups, bool kSelf, bool kEven>
-__global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
+// spaced slots, kEven, nothing waits for the number of partitions before the loads.)  Rows of one partition are left
+// alone: they were written directly.
+template <int kGroups, bool kEven>
+__global__ __launch_bounds__(256) void merge_rows_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
     constexpr int kBatch = 4, kRows = 8 / kGroups;
     __shared__ float s_acc[8][132], s_ml[8][2];
@@ -351,7 +418,7 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
     const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
-    const int n = row / g.Hq, head = row - n * g.Hq, kvh = head / g.G;      // n: the token (queries may bring none)
+    const int n = row / g.Hq, head = row - n * g.Hq;      // n: the token (queries may bring none)
     const PartSlots slots = part_slots<kEven>(b, n);
     float2 ml[kBatch];
     f32x4 po[kBatch];
@@ -364,55 +431,30 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(Geom g, BatchDev b, 
             po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
         }
     };
-    uint2 q2, k2, v2;
-    if (kSelf) {
-        q2 = *(const uint2 *)((const unsigned short *)a.q + (int64_t)row * 128 + d);
-        k2 = *(const uint2 *)((const unsigned short *)a.k_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
-        v2 = *(const uint2 *)((const unsigned short *)a.v_new + ((int64_t)n * g.Hkv + kvh) * 128 + d);
-    }
-    if (kEven || kSelf || slots.count > 0) fetch(grp);       // (a decode step has at least one partition)
+    if (kEven || slots.count > 0) fetch(grp);
     const int ns = slots.count;
-    float M = -INFINITY, L = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    auto fold = [&](float m, float l, f32x4 o) {
-        const float Mn = fmaxf(M, m);
-        const float r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
-        // (no maximum: no key for this row - l and o are 0 - or only scores that are NaN - so are they, and so is the row)
-        const float wgt = m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - Mn);
-        L = L * r + l * wgt;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = acc[e] * r + o[e] * wgt;
-        M = Mn;
-    };
+    RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
     for (int s0 = grp; s0 < ns; s0 += kGroups * kBatch) {
         if (s0 > grp) fetch(s0);
 #pragma unroll
         for (int j = 0; j < kBatch; ++j)
-            if (s0 + kGroups * j < ns) fold(ml[j].x, ml[j].y, po[j]);
+            if (s0 + kGroups * j < ns) x.add(ml[j].x, ml[j].y, po[j]);
     }
     if (kGroups > 1) {
-        *(f32x4 *)&s_acc[slot8][d] = acc;
-        if (d == 0) { s_ml[slot8][0] = M; s_ml[slot8][1] = L; }
+        *(f32x4 *)&s_acc[slot8][d] = x.acc;
+        if (d == 0) { s_ml[slot8][0] = x.M; s_ml[slot8][1] = x.L; }
         __syncthreads();
     }
-    if (grp > 0 || want >= n_rows || (!kSelf && ns <= 1)) return;
-    // the row's first group goes on: score of the new token against itself, then the other groups' results
-    if (kSelf) {
-        auto lo = [](uint32_t x) { return __uint_as_float(x << 16); };
-        auto hi = [](uint32_t x) { return __uint_as_float(x & 0xffff0000u); };
-        float prod = lo(q2.x) * lo(k2.x) + hi(q2.x) * hi(k2.x) + lo(q2.y) * lo(k2.y) + hi(q2.y) * hi(k2.y);
+    if (grp > 0 || want >= n_rows || ns <= 1) return;
+    // the row's first group goes on: the other groups' results
 #pragma unroll
-        for (int off = 16; off > 0; off >>= 1) prod += __shfl_xor(prod, off, 32);
-        fold(prod * a.scale_log2, 1.f, f32x4{lo(v2.x), hi(v2.x), lo(v2.y), hi(v2.y)});
-    }
-#pragma unroll
-    for (int k = 1; k < kGroups; ++k) fold(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
-    const float inv = 1.f / L;
+    for (int k = 1; k < kGroups; ++k) x.add(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
+    const float inv = 1.f / x.L;
     unsigned short r[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const __bf16 x = (__bf16)(acc[e] * inv);
-        r[e] = *(const unsigned short *)&x;
+        const __bf16 y = (__bf16)(x.acc[e] * inv);
+        r[e] = *(const unsigned short *)&y;
     }
     *(uint2 *)((unsigned short *)a.out + (int64_t)row * 128 + d) =
         make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
@@ -431,27 +473,22 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     return hipGetLastError();
 }
 
-template <bool kSelf, bool kEven>
-static hipError_t launch_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+template <bool kEven>
+static hipError_t launch_merge_rows(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
     const int n_rows = b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
     if (max_splits < 1 || !b.part_tab) return hipErrorInvalidValue;
-    if (max_splits <= 4) TC_LAUNCH((decode_finish_kernel<1, kSelf, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 8) TC_LAUNCH((decode_finish_kernel<2, kSelf, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 16) TC_LAUNCH((decode_finish_kernel<4, kSelf, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
-    else TC_LAUNCH((decode_finish_kernel<8, kSelf, kEven>), n_rows, 0, L, g, b, a, max_splits);
+    if (max_splits <= 4) TC_LAUNCH((merge_rows_kernel<1, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH((merge_rows_kernel<2, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH((merge_rows_kernel<4, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH((merge_rows_kernel<8, kEven>), n_rows, 0, L, g, b, a, max_splits);
     return hipGetLastError();
-}
-
-hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
-{
-    return b.part_stride > 0 ? launch_finish<true, true>(g, b, a, max_splits, L) : launch_finish<true, false>(g, b, a, max_splits, L);
 }
 
 hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
-    return b.part_stride > 0 ? launch_finish<false, true>(g, b, a, max_splits, L) : launch_finish<false, false>(g, b, a, max_splits, L);
+    return b.part_stride > 0 ? launch_merge_rows<true>(g, b, a, max_splits, L) : launch_merge_rows<false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

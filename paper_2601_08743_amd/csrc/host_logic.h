@@ -208,6 +208,7 @@ struct Plan {
     BatchDev dev{};
     const AttnItem *items_dev = nullptr;
     const MergeGroup *groups_dev = nullptr;
+    int32_t *arrivals_dev = nullptr;
 };
 
 // What a caller may force about the attention launch (tc_set_kv_splits and friends); 0 = automatic.
@@ -393,6 +394,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 if (p.suffix_len[i] > 0) n += (int64_t)c.n_kv_heads * std::max(1, (tiles_of_q(i) + L - 1) / L);
             return n;
         };
+        int longest = 0;
+        for (int i = 0; i < p.B; ++i)
+            if (p.suffix_len[i] > 0) longest = std::max(longest, tiles_of_q(i));
         int L = kAttnMaxTiles;
         if (!ctx->compact && items_at(L) <= kCus) {                      // one round is possible: the shortest ranges that still fit it
             int lo = kMinRange, hi = kAttnMaxTiles;     // items_at is non-increasing in L
@@ -402,11 +406,20 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 else lo = mid + 1;
             }
             L = lo;
+            // The last work-group of a (query, KV head) folds the partials of all of them: 36 in one round of loads, each
+            // one more 0.07 us, against 0.65 us for each unit more that a wave takes.  At least two thirds of the
+            // work-groups stay, for the loads that they have in flight.  (One sequence, 28 / 4 heads, us a launch: 7.2 k tokens in
+            // 57 ranges of two tiles 10.4, 38 of three 9.4; 14.4 k in 57 of four 14.1, 38 of six 12.5.)
+            auto cost = [&](int l) { return 0.65 * ((l + 1) / 2) + 0.07 * std::max((longest + l - 1) / l - 36, 0); };
+            for (int l = lo + 1; l <= std::min(lo * 3 / 2, kAttnMaxTiles); ++l)
+                if (cost(l) < cost(L) - 1e-9) L = l;
+            // Up to six tiles - three units a wave - one range needs no partials and no arrival (one sequence of 200 tokens
+            // 5.3 us against 7.0 in two ranges; of 500, eight tiles, 7.2 against 6.9 in four).
+            if (longest <= 6) L = std::max(L, longest);
         }
         splits_of_q.assign(p.B, 1);
         p.max_splits = 1;
-        items.clear();
-        groups.clear();
+        p.n_groups = 0;
         for (int i = 0; i < p.B; ++i) {
             if (p.suffix_len[i] <= 0) continue;
             const int P = p.prefix_len[i];
@@ -424,7 +437,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     AttnItem it{};
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
-                    it.split = s; it.n_splits = ns; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
+                    it.split = s; it.n_splits = ns; it.group = p.n_groups + h; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
                     it.append_bid = bt[P / kBlockTokens];
                     for (int k = 0; k < 16; ++k) {          // entries of the range's first units, clamped to the prefix
                         const int idx = std::min(it.tile_begin * (KT / kBlockTokens) + k, std::max((P + kBlockTokens - 1) / kBlockTokens - 1, 0));
@@ -432,11 +445,11 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     }
                     items.push_back(it);
                 }
+            p.n_groups += c.n_kv_heads;
         }
         std::stable_sort(items.begin(), items.end(), [](const AttnItem &x, const AttnItem &y) {
             return x.tile_end - x.tile_begin > y.tile_end - y.tile_begin;
         });
-        p.n_groups = 0;
         p.row_blocks = 1;
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
@@ -754,7 +767,7 @@ inline std::vector<AppendBlk> append_blocks(const Plan &p)
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
     size_t block_table, cu, prefix, suffix, tok_q, part_tab, append, items, groups;
-    size_t seg_start, seg_len, seg_slot, stitch, rope_pos0, rope_freq;
+    size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
     bool lengths = false, tokens = false, by_row = false, merge_groups = false;
 };
@@ -777,9 +790,10 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
     l.append = take(n_append * (sizeof(AppendBlk) / 4));
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
-    l.part_tab = take(l.by_row ? part_tab_ints(p) : 0);
+    l.part_tab = take(l.by_row && !p.decode ? part_tab_ints(p) : 0);   // (the decode kernel's partials come with its items)
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
+    l.arrivals = take(p.decode ? (size_t)p.n_groups * kArrivalStride : 0);
     l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     l.total = std::max(l.total, size_t(8));
     return l;

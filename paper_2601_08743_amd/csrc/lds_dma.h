@@ -34,6 +34,22 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds_dst, const char *base, 
                  : "s"(__builtin_amdgcn_readfirstlane(lds_dst)), "v"(voff), "s"(sb) : "memory");
 }
 
+// Four such loads of neighbouring 1 KB pieces: lane l's 16 bytes of piece i come from base + off[i] + 1024 i and go to
+// lds_dst + 1024 i + 16 l.  (The instruction's offset moves both addresses, so one M0 and one base serve the four: four
+// instructions and three moves in place of some thirty, which a wave alone on its SIMD feels - see the decode kernel.)
+__device__ __forceinline__ void load4_to_lds(uint32_t lds_dst, const char *base, const uint32_t (&off)[4])
+{
+    const uint64_t b64 = (uint64_t)(uintptr_t)base;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b64), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
+    const uint64_t sb = ((uint64_t)hi << 32) | lo;
+    uint64_t sb_copy;
+    asm volatile("s_mov_b64 %0, %6\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0\n\t"
+                 "global_load_lds_dwordx4 %3, %0 offset:1024\n\tglobal_load_lds_dwordx4 %4, %0 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %5, %0 offset:3072"
+                 : "=&s"(sb_copy)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_dst)), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sb) : "memory");
+}
+
 // 16 bytes per lane, each from an address of its own (for rows that come from different buffers).
 __device__ __forceinline__ void load_to_lds_each(uint32_t lds_dst, const char *src)
 {

@@ -279,7 +279,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     put(at.append, ablk);
     put(at.stitch, sblk);
-    if (at.by_row) fill_part_tab(p, splits_of_q, h + at.part_tab);
+    if (at.by_row && !p.decode) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
     put(at.groups, groups, at.merge_groups);
     put(at.rope_pos0, p.rope_pos0, p.rope);
@@ -302,7 +302,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     p.dev.seg_start = d + at.seg_start; p.dev.seg_len = d + at.seg_len; p.dev.seg_slot = d + at.seg_slot;
     p.dev.stitch_blk = (const StitchBlk *)(d + at.stitch);
-    if (at.by_row) {
+    if (at.by_row && !p.decode) {
         p.dev.part_tab = d + at.part_tab;
         p.dev.part_stride = p.part_stride;
     }
@@ -314,6 +314,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.dev.n_stitch_blk = (int32_t)sblk.size();
     p.n_stitch_blk = (int32_t)sblk.size();
     p.items_dev = (const AttnItem *)(d + at.items);
+    p.arrivals_dev = d_dst + at.arrivals;
     p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
     p.fixed = fixed;
@@ -934,9 +935,9 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
+        a.arrivals = p.arrivals_dev;
         a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
-        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_decode_finish(ctx->geom, p.dev, a, p.max_splits, ln); }));
         return TC_OK;
     }
     if (p.pingpong) {   // the attention launches append in extra work-groups of their own, except this kernel's,

@@ -88,7 +88,6 @@ hipError_t launch_append_blocks(const Geom &g, const BatchDev &b, int layer, con
                                 const Launch &L);
 hipError_t launch_attn_pp_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
-hipError_t launch_decode_finish(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_attn_short_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);

@@ -19,6 +19,8 @@ constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
 constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item whose block ids are kept in LDS (those of longer ranges are fetched one by one)
 constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
+constexpr int kArrivalStride = 32;   // integers from one arrival counter to the next: a cache line each
+
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
 // ids): the low 27 bits are the block id; the bits above count the unused token positions at the
 // end of the block (0..15).  Only blocks of a table slot that a sequence aliases have any: a table
@@ -91,7 +93,7 @@ struct AttnItem {
     int32_t tile_end;    // one past the last key tile
     int32_t split;       // which partition this is (0 when n_splits == 1)
     int32_t n_splits;    // partitions of this query
-    int32_t group;       // index of the (query, KV head, row tile): partial slots and arrival counter
+    int32_t group;       // index of the (query, KV head, row tile): partial slots, arrival counter
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
     int32_t n_groups;    // total number of groups in the batch
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
@@ -120,6 +122,7 @@ struct AttnArgs {
     int32_t n_items;
     int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
+    int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };
 

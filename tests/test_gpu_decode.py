@@ -300,3 +300,35 @@ def test_units_per_wave(hq, hkv, splits, alias):
         assert float(np.abs(got[i:i + 1] - r).max()) <= 2.2e-2, i
     dw.ctx.tc_release_seqs(bt)
     dw.close()
+
+
+@pytest.mark.parametrize("G", [1, 3, 4, 5, 7, 8, 11])
+def test_decode_partials_folded_by_the_last_work_group(H, G):
+    """One range (no partials), and partition counts around the fold's batches (12, 36 and a second round), for head groups
+    that take the fold's threads two to a row, one to a row and more than once around; every count twice, so that the
+    arrival counters are found at zero again, and once more after a step of another plan."""
+    cfg = W.WorkloadConfig(name="decfold", n_layers=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=128, dtype="bf16", n_tables=8,
+                           table_len=(640, 640), batch=2, tables_per_query=(8, 8), choice="uniform", suffix_len=(1, 1),
+                           capacity=8, seed=407)
+    wl = W.make_workload(cfg)
+    c = wl.cfg
+    dw = H.DeviceWorkload(wl)
+    ref, worst = None, 0.0
+    for splits in (1, 2, 12, 13, 24, 36, 37, 75, 0):
+        dw.ctx.tc_set_kv_splits(splits)
+        bt, pl = dw.stitch()
+        got = []
+        for _ in range(2):
+            out, qkv = dw.attn_layer(0, bt, pl)
+            assert dw.ctx.tc_attn_kernel() == 3
+            got.append(out)
+        assert splits == 0 or dw.ctx.tc_kv_splits() == splits
+        assert torch.equal(got[0], got[1])
+        if ref is None:
+            ref = H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+        worst = max(worst, max(float(np.abs(H.out_to_f64(got[0], c)[int(wl.cu_seqlens[i]):int(wl.cu_seqlens[i + 1])] - r).max())
+                               for i, r in ref.items()))
+        dw.ctx.tc_release_seqs(bt)
+    dw.close()
+    # averages of thousands of N(0, 1) values: 2^-9 of a weight and of the output's ~0.05, as in the tests above
+    assert worst <= 1e-2, worst
