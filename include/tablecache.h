@@ -321,11 +321,9 @@ tc_status tc_set_row_blocks(tc_ctx *ctx, int32_t row_blocks);
  * running-maximum softmax, two work-groups per CU), 2 = the pipelined kernel (128 rows,
  * direct-to-LDS K/V, fixed softmax reference with overflow fallback, one work-group per CU),
  * 3 = as 0 (the decode kernels serve batches in which no query brings more than one new token,
- * unless another kernel is forced: the keys of a KV head are split over waves and work-groups, a
- * second kernel combines them and adds the new token), 4 = the kernel for long launches (256
- * rows per work-group in two groups of waves that alternate between matrix and vector work; the
- * suffix is appended to the pool by a launch of its own before attention, which then reads all
- * keys from the pool; ignored while tc_set_row_blocks forces a row count), 5 = the kernel for short
+ * unless another kernel is forced: the keys of a KV head are split over waves and work-groups, the
+ * last of which to end combines them), 4 = the kernel for long launches (256
+ * rows per work-group in two groups of waves that alternate between matrix and vector work; ignored while tc_set_row_blocks forces a row count), 5 = the kernel for short
  * launches (32 rows per work-group, whose eight waves split the keys; ignored likewise).  Results do
  * not depend on it beyond rounding.  Invalidates the cached plan.
  * tc_attn_kernel reports the kernel of the current plan (1 .. 5; 0 when no plan is cached, for
@@ -336,7 +334,7 @@ int32_t tc_attn_kernel(const tc_ctx *ctx);
 /*
  * Measurement support.  With profiling on, every kernel the library launches carries two HIP
  * events that receive the begin and end timestamps of its own dispatch on the stream it is launched
- * on (no extra packets between kernels).  tc_profile_read waits for them and returns, per kernel kind (0 stitch, 1 append, 2 attention, 3 split-KV merge), the summed
+ * on (no extra packets between kernels).  tc_profile_read waits for them and returns, per kernel kind (0 stitch, 1 append where it is a launch of its own (no kernel's is), 2 attention, 3 split-KV merge), the summed
  * elapsed milliseconds and the number of launches since the previous read.
  *   ms_out HOST double[4], count_out HOST int64_t[4].
  */

@@ -139,7 +139,7 @@ int main()
                 slots.resize(part_tab_ints(p));
                 fill_part_tab(p, splits, slots.data());
             }
-            std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, append_blocks(p).size(), items.size(), groups.size()).total, p.compact ? 1 : 0);
+            std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, items.size(), groups.size()).total, p.compact ? 1 : 0);
             std::printf("parts %zu %d", part_floats(c, p), p.part_stride);
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");

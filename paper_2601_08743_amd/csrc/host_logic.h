@@ -194,7 +194,7 @@ struct Plan {
     int32_t part_stride = 0;    // and slots from token to token, 0: packed
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
-    bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups; the suffix is appended first
+    bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups
     bool compact = false;       // planned for the least space (a batch that did not fit the static workspace otherwise)
     bool brief = false;         // bf16, 32 rows per work-group, its waves split the keys: the short-launch kernel
     bool rope = false;          // the stitch re-encodes keys by position (Sec. 4.1.1)
@@ -461,8 +461,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     }
     // key tiles of a query.  bf16 kernel: the tiles of the prefix (from the pool), then the tiles of
     // the suffix (from k_new / v_new); fp32 kernel: one paged sequence of P + S keys
-    // the alternating-groups bf16 kernel reads the suffix from the pool as well (it is appended by a
-    // launch of its own first), so it, too, sees one paged sequence
+    // the alternating-groups bf16 kernel, too, sees one sequence of P + S keys
     // It is chosen for long launches (estimated from the row tiles x key tiles of the batch at
     // ~0.85 us per 128 x 64 tile and CU): its append launch costs 7 us, and with 256 rows per
     // work-group a short launch would not fill the chip.  Measured: c3 (1140 items of ~24 tiles)
@@ -749,29 +748,16 @@ inline void fill_part_tab(const Plan &p, const std::vector<int32_t> &splits_of_q
     if (!p.part_stride) out[p.total_S] = at;
 }
 
-// The blocks that take suffix tokens, for the long-launch kernel's append.
-inline std::vector<AppendBlk> append_blocks(const Plan &p)
-{
-    std::vector<AppendBlk> out;
-    for (int i = 0; p.pingpong && i < p.B; ++i) {
-        const int P = p.prefix_len[i], end = P + p.suffix_len[i];
-        for (int p0 = P / kBlockTokens * kBlockTokens; p.suffix_len[i] > 0 && p0 < end; p0 += kBlockTokens)
-            out.push_back(AppendBlk{p.block_table[(size_t)i * p.max_blocks + p0 / kBlockTokens], p.cu_seqlens[i] + p0 - P,
-                                    std::max(P - p0, 0), std::min(end - p0, (int)kBlockTokens)});
-    }
-    return out;
-}
-
 // Where the parts of a plan stand in its device copy, in integers; only what the batch's kernels read
 // is there (`n_*`: how many of each).
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
-    size_t block_table, cu, prefix, suffix, tok_q, part_tab, append, items, groups;
+    size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
     bool lengths = false, tokens = false, by_row = false, merge_groups = false;
 };
-inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_append, size_t n_items,
+inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
                               size_t n_groups)
 {
     PlanLayout l;
@@ -788,7 +774,6 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.prefix = take(l.lengths ? B : 0);
     l.cu = take(l.tokens ? B + 1 : 0); l.suffix = take(l.tokens ? B : 0); l.tok_q = take(l.tokens ? p.total_S : 0);
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
-    l.append = take(n_append * (sizeof(AppendBlk) / 4));
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
     l.part_tab = take(l.by_row && !p.decode ? part_tab_ints(p) : 0);   // (the decode kernel's partials come with its items)
     l.items = take(n_items * (sizeof(AttnItem) / 4));
@@ -809,7 +794,7 @@ inline bool plan_attention_within(const tc_config &c, const PlanKnobs &knobs, Pl
     k.part_cap = max_floats;
     if (!plan_attention(c, k, p, items, splits_of_q, groups)) return false;
     if (part_floats(c, p) <= max_floats &&
-        plan_layout(c, p, 0, 0, append_blocks(p).size(), items.size(), groups.size()).total <= max_ints) return true;
+        plan_layout(c, p, 0, 0, items.size(), groups.size()).total <= max_ints) return true;
     k.compact = true;
     return plan_attention(c, k, p, items, splits_of_q, groups);
 }

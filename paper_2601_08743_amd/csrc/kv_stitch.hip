@@ -33,16 +33,10 @@ __device__ __forceinline__ uint4 keep_if(uint4 v, bool keep)        // v, or zer
 // issued before the first store, so that a thread has 128 bytes in flight instead of 16.
 constexpr int kCopyBatch = 4;
 
-// Where token t of a block comes from: byte offset of its row, -1: no such token.  From a table in LDS, or
-// (rows of k_new / v_new follow one another) computed.
+// Where token t of a block comes from: byte offset of its row, -1: no such token.
 struct ListedRows {
     const int64_t *off;
     __device__ __forceinline__ int64_t operator()(int t) const { return off[t]; }
-};
-struct ConsecutiveRows {
-    int64_t first;                                 // of token 0, also where the block does not take it from here
-    int32_t row_bytes, t_begin, t_end;
-    __device__ __forceinline__ int64_t operator()(int t) const { return t >= t_begin && t < t_end ? first + (int64_t)t * row_bytes : -1; }
 };
 
 // K chunk c of the destination, in address order: consecutive threads write consecutive 16 bytes
@@ -77,37 +71,19 @@ __device__ __forceinline__ int64_t v_plain_offset(const Geom &g, int c)
 }
 
 // second half of the transposing path: out chunk oc = (h, d, half): 8 tokens of one (h, d)
-// t_first > 0: tokens below t_first keep what the block already holds: `old` brings the block's
-// chunks (chunk tid + 256 k in old[k]), read by the caller before anything else so that the read is
-// not one more round trip at the end; they are merged and written back.
-constexpr int kOldChunks = 8;                  // covers Hkv * D * 2 <= 2048 chunks; beyond that the chunk is read here
-__device__ __forceinline__ void store_v_transposed(const Geom &g, const uint4 *lds, char *vdst, int tid, int t_first = 0,
-                                                   const uint4 *old_pre = nullptr)
+__device__ __forceinline__ void store_v_transposed(const Geom &g, const uint4 *lds, char *vdst, int tid)
 {
     const unsigned short *l16 = (const unsigned short *)lds;
     const int row_elems = g.row_bytes >> 1;
     const int n_out = g.Hkv * g.D * 2;
-    for (int k = 0; tid + 256 * k < n_out; ++k) {
-        const int oc = tid + 256 * k;
+    for (int oc = tid; oc < n_out; oc += 256) {
         const int half = oc & 1;
         const int hd = oc >> 1;                // h * D + d
-        uint4 old = make_uint4(0, 0, 0, 0);
-        if (t_first > 0) {
-            if (old_pre && k < kOldChunks) {
-                // (selected, not indexed, so that the array stays in registers)
-#pragma unroll
-                for (int q = 0; q < kOldChunks; ++q) if (q == k) old = old_pre[q];
-            } else {
-                old = *(const uint4 *)(vdst + ((int64_t)oc << 4));
-            }
-        }
-        const unsigned o32[4] = {old.x, old.y, old.z, old.w};
         unsigned short e[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int t = (k & 3) | ((k & 4) << 1) | (half << 2);
-            const unsigned short fresh = l16[t * row_elems + hd];
-            e[k] = t >= t_first ? fresh : (unsigned short)(o32[k >> 1] >> (16 * (k & 1)));
+            e[k] = l16[t * row_elems + hd];
         }
         uint4 v;
         v.x = e[0] | ((unsigned)e[1] << 16);
@@ -146,17 +122,9 @@ __device__ __forceinline__ void copy_block_v(const Geom &g, const char *v_src, c
 // Keys and values of one block together.
 template <bool kTransposeV, typename Rows>
 __device__ __forceinline__ void copy_block_kv(const Geom &g, const char *k_src, const char *v_src, const Rows &rows,
-                                              char *dst, char *vdst, uint4 *lds, int tid, int t_first = 0)
+                                              char *dst, char *vdst, uint4 *lds, int tid)
 {
     const int n_chunks = kBlockTokens * (g.row_bytes >> 4);
-    const int cpr = g.row_bytes >> 4, cph = g.head_bytes >> 4;
-    uint4 old_v[kOldChunks];
-    if (kTransposeV && t_first > 0) {              // the shared block's values, on their way while the rows are fetched
-        const int n_out = g.Hkv * g.D * 2;
-#pragma unroll
-        for (int k = 0; k < kOldChunks; ++k)
-            old_v[k] = *(const uint4 *)(vdst + ((int64_t)min(tid + 256 * k, n_out - 1) << 4));
-    }
     for (int c0 = tid; c0 < n_chunks; c0 += 256 * kCopyBatch) {
         uint4 kk[kCopyBatch], vv[kCopyBatch];
         bool kok[kCopyBatch], vok[kCopyBatch];
@@ -167,20 +135,19 @@ __device__ __forceinline__ void copy_block_kv(const Geom &g, const char *k_src, 
 #pragma unroll
         for (int j = 0; j < kCopyBatch; ++j) {
             const int c = c0 + 256 * j;
-            // (K chunk c belongs to token (c / cph) % 16, V chunk c to token c / cpr)
-            if (c < n_chunks && (c / cph) % kBlockTokens >= t_first) *(uint4 *)(dst + ((int64_t)c << 4)) = keep_if(kk[j], kok[j]);
+            if (c < n_chunks) *(uint4 *)(dst + ((int64_t)c << 4)) = keep_if(kk[j], kok[j]);
         }
 #pragma unroll
         for (int j = 0; j < kCopyBatch; ++j) {
             const int c = c0 + 256 * j;
             if (c >= n_chunks) continue;
             if (kTransposeV) lds[c] = keep_if(vv[j], vok[j]);
-            else if (c / cpr >= t_first) *(uint4 *)(vdst + v_plain_offset(g, c)) = keep_if(vv[j], vok[j]);
+            else *(uint4 *)(vdst + v_plain_offset(g, c)) = keep_if(vv[j], vok[j]);
         }
     }
     if (kTransposeV) {
         __syncthreads();
-        store_v_transposed(g, lds, vdst, tid, t_first, old_v);
+        store_v_transposed(g, lds, vdst, tid);
     }
 }
 
@@ -397,37 +364,6 @@ hipError_t launch_stitch(const Geom &g, const BatchDev &b, int l0, int l1, bool 
         if (rope) TC_LAUNCH((stitch_kernel<false, true>), grid, cs_bytes, L, g, b, l0);
         else TC_LAUNCH((stitch_kernel<false, false>), grid, 0, L, g, b, l0);
     }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------ append
-// Append by blocks, for launches that must have the suffix in the pool before attention starts:
-// one work-group per sequence block that holds suffix tokens (the plan lists them: which block, which
-// rows of k_new / v_new).  A block that lies wholly behind the prefix is written like a stitched
-// block (zeros behind the end of the sequence); in the one block a query may share with its prefix the
-// prefix tokens stay (keys: their rows are skipped; transposed values: 16 bytes read, merged, written
-// back).
-// Bound: latency - one scalar fetch, the rows, the transpose, the stores.  Measured (an empty launch reads
-// 4.0 us): 32 queries, 5.2 k tokens: 6.9 us; with the block looked for in the queries' lengths by every
-// work-group 10.4 us.
-__global__ __launch_bounds__(256) void append_blocks_kernel(Geom g, BatchDev b, int layer,
-                                                            const char *k_new, const char *v_new)
-{
-    extern __shared__ uint4 lds[];
-    typedef const __attribute__((address_space(4))) int32_t *const_ints;
-    const const_ints e = (const_ints)(uintptr_t)(b.append_blk + blockIdx.x);     // (uploaded before the launch, never written)
-    const AppendBlk ab{e[0], e[1], e[2], e[3]};
-    char *dst = g.pool + (int64_t)layer * g.layer_stride + (int64_t)ab.phys * g.block_bytes;
-    copy_block_kv<true>(g, k_new, v_new, ConsecutiveRows{(int64_t)ab.row0 * g.row_bytes, g.row_bytes, ab.t_begin, ab.t_end},
-                        dst, dst + (g.block_bytes >> 1), lds, threadIdx.x, ab.t_begin);
-}
-
-hipError_t launch_append_blocks(const Geom &g, const BatchDev &b, int layer, const void *k_new, const void *v_new,
-                                const Launch &L)
-{
-    if (b.n_append_blk == 0) return hipSuccess;
-    if (g.esize != 2) return hipErrorInvalidValue;
-    TC_LAUNCH(append_blocks_kernel, b.n_append_blk, kBlockTokens * g.row_bytes, L, g, b, layer, (const char *)k_new, (const char *)v_new);
     return hipGetLastError();
 }
 

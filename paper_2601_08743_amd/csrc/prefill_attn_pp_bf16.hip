@@ -15,9 +15,10 @@
 // reads; V(t): mask, running maximum, exponentials, row sums, weights packed to bf16.  While one
 // wave of a SIMD feeds the matrix core the other one runs its softmax.
 //
-// All keys come from the pool: the suffix is appended by a launch of its own BEFORE this kernel
-// (a few microseconds, which is why this kernel is for long launches), so a query is one paged
-// sequence of P + S keys, tiles of 64, and row (token s, head) sees keys 0 .. P + s.  Tiles travel
+// A query is one sequence of P + S keys, tiles of 64, and row (token s, head) sees keys 0 .. P + s: the prefix from the
+// pool, the suffix from k_new / v_new.  The launch appends the suffix to the pool itself, at the end of a row tile's first
+// key range (a launch of its own ahead of this one was 5 .. 10 us; in here it is about one for
+// an item, and less where the launch has more than one round).  Tiles travel
 // global -> LDS directly (global_load_lds_dwordx4), two tiles ahead: a ring of three K buffers
 // (rows of 256 B, 16-byte chunks XOR-swizzled by row as in the other kernels) and four V buffers;
 // each wave brings 1/8 of a tile and waits for its own part before the barrier that publishes it.
@@ -25,6 +26,7 @@
 // Rows: work-group rows m0 .. m0+255 of the (query, KV head) row space (row = token * G + head in
 // group); wave w owns rows m0 + 32 w ...  Partials of split queries use the layout of the other
 // bf16 kernels with eight 32-row blocks per group, which the merge kernel takes as a parameter.
+#include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
 
@@ -38,7 +40,8 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kPpTile = kAttnKeys * 256;             // 16 KB: a K tile (64 rows of 256 B) or a V tile (4 x 4 KB)
 constexpr int kPpKBufs = 3, kPpVBufs = 4;
 constexpr int kPpV = kPpKBufs * kPpTile;             // V ring behind the K ring
-constexpr int kPpBid = kPpV + kPpVBufs * kPpTile;    // block-table entries of the item's key range
+constexpr int kPpNew = kPpV + kPpVBufs * kPpTile;    // new value rows of the block that a query shares with its prefix
+constexpr int kPpBid = kPpNew + kBlockTokens * 256;  // block-table entries of the item's key range
 constexpr int kPpLds = kPpBid + kPpMaxTiles * 4 * 4 + 256;   // + slack to align the rings to 256 B
 constexpr int kPpRing = 5;                           // operand fragments in flight: reads run kPpRing - 1 matrix instructions ahead
 constexpr float kPpRescale = 8.f;                    // log2 units: rescale O only when the maximum grew by more
@@ -93,10 +96,16 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qp + ks * 32);
     }
+    // ---- the blocks that this wave appends (see below): ab0, ab0 + 8, .. below ab1
+    const int blk0 = P >> 4, n_blk = ((P + S + kBlockTokens - 1) >> 4) - blk0, n_rt = (m_rows + 255) >> 8, rt = it.m0 >> 8;
+    const int ab0 = blk0 + (int)((int64_t)n_blk * rt / n_rt) + w, ab1 = it.split == 0 ? blk0 + (int)((int64_t)n_blk * (rt + 1) / n_rt) : 0;
+    const int32_t *bt_q = b.block_table + (int64_t)it.q * b.max_blocks;
+    int ap_bid = ab0 < ab1 ? bt_q[ab0] : 0;
+
     // ---- block-table entries of the range -> LDS (past the sequence: its last block, masked)
     {
         const int last_blk = max(((P + S + kBlockTokens - 1) >> 4) - 1, 0);
-        const int32_t *bt = b.block_table + (int64_t)it.q * b.max_blocks;
+        const int32_t *bt = bt_q;
         // (whole tiles below the sequence's last block go four entries per access where the table row
         // is 16-byte aligned; the rest entry by entry, clamped)
         const int32_t *src = bt + it.tile_begin * 4;
@@ -105,6 +114,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
         for (int idx = n_wide * 4 + tid; idx < n * 4; idx += 512) s_bid[idx] = bt[min(it.tile_begin * 4 + idx, last_blk)];
     }
     __syncthreads();
+    ap_bid = __builtin_amdgcn_readfirstlane(ap_bid);
 
     // ---- loads: wave w brings two of the four 1 KB pieces of block (w / 2) of a tile, K and V
     const char *pool_l = g.pool + (int64_t)a.layer * g.layer_stride + (int64_t)it.kvh * 4096;
@@ -112,24 +122,80 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
     const uint32_t v_half = (uint32_t)(g.block_bytes >> 1);
     // (the block id of the tile after the one being requested is read from LDS right behind the
     // loads and used by the next call, so that no call waits for an LDS round trip)
+    // Blocks that hold suffix tokens are not in the pool yet (this launch appends them, see below): their rows
+    // come from k_new / v_new.  K rows go where a block's go.  V rows go, as they are, to the piece of LDS that this wave is
+    // to fill (its 64 columns of 16 tokens, 2 KB) and are turned there before the tile is published; of the one block
+    // that a query shares with its prefix, the pool's V goes there and the new rows to a place of their own.
+    // Tokens behind the sequence's end repeat the last one: masked, like the zeros they are in the pool.
+    const int j_blk = w >> 1, i0 = 2 * (w & 1);
+    const char *new_k = (const char *)a.k_new + ((int64_t)it.cu * g.Hkv + it.kvh) * 256;
+    const char *new_v = (const char *)a.v_new + ((int64_t)it.cu * g.Hkv + it.kvh) * 256;
+    const uint32_t lds_new = lds0 + kPpNew + (w & 1) * 2048;
+    auto block_pos = [&](int t) { return (it.tile_begin + t) * kAttnKeys + kBlockTokens * j_blk; };
     int bid_next = s_bid[w >> 1];                      // tile 0 (never used when the range is empty)
-    auto issue_tile = [&](int t) {                     // 4 load instructions; t = 0, 1, 2, .. in order
-        const int j = w >> 1, i0 = 2 * (w & 1);
+    // (`all_pool`: known to hold no suffix token)
+    auto issue_tile = [&](int t, bool all_pool) {      // 4 load instructions (6 for a shared block); t = 0, 1, 2, .. in order
+        const int p0 = block_pos(t);
         const char *src = pool_l + (int64_t)entry_bid(__builtin_amdgcn_readfirstlane(bid_next)) * bb;
-        const uint32_t kd = lds0 + (t % kPpKBufs) * kPpTile + j * 4096;
-        const uint32_t vd = lds0 + kPpV + (t % kPpVBufs) * kPpTile + j * 4096;
+        const uint32_t kd = lds0 + (t % kPpKBufs) * kPpTile + j_blk * 4096;
+        const uint32_t vd = lds0 + kPpV + (t % kPpVBufs) * kPpTile + j_blk * 4096;
+        if (!all_pool && p0 + kBlockTokens > P) {
 #pragma unroll
-        for (int i = i0; i < i0 + 2; ++i) {
-            const int rb = 4 * i + (lane >> 4);       // row of the block; chunk c of row r goes to position c ^ r
-            load_to_lds(kd + i * 1024, src, rb * 256 + (((lane & 15) ^ rb) * 16));
+            for (int i = i0; i < i0 + 2; ++i) {
+                const int rb = 4 * i + (lane >> 4), c16 = ((lane & 15) ^ rb) * 16, tok = p0 + rb - P;
+                load_to_lds_each(kd + i * 1024, tok < 0 ? src + rb * 256 + c16 : new_k + (int64_t)min(tok, S - 1) * g.row_bytes + c16);
+            }
+            const bool shared = p0 < P;
+            if (shared)
+#pragma unroll
+                for (int i = i0; i < i0 + 2; ++i)
+                    load_to_lds(vd + i * 1024, src + v_half + i * 1024, (2 * (lane & 31) + (lane >> 5)) * 16);
+            const uint32_t rows = shared ? lds_new : vd + i0 * 1024;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int tok = min(max(p0 + 8 * i + (lane >> 3) - P, 0), S - 1);
+                load_to_lds_each(rows + i * 1024, new_v + (int64_t)tok * g.row_bytes + (w & 1) * 128 + (lane & 7) * 16);
+            }
+        } else {
+#pragma unroll
+            for (int i = i0; i < i0 + 2; ++i) {
+                const int rb = 4 * i + (lane >> 4);       // row of the block; chunk c of row r goes to position c ^ r
+                load_to_lds(kd + i * 1024, src, rb * 256 + (((lane & 15) ^ rb) * 16));
+            }
+#pragma unroll
+            for (int i = i0; i < i0 + 2; ++i)               // V chunks in operand order (see v_off)
+                load_to_lds(vd + i * 1024, src + v_half + i * 1024, (2 * (lane & 31) + (lane >> 5)) * 16);
         }
-#pragma unroll
-        for (int i = i0; i < i0 + 2; ++i)               // V chunks in operand order (see v_off)
-            load_to_lds(vd + i * 1024, src + v_half + i * 1024, (2 * (lane & 31) + (lane >> 5)) * 16);
-        bid_next = s_bid[min(t + 1, n - 1) * 4 + j];
+        bid_next = s_bid[min(t + 1, n - 1) * 4 + j_blk];
     };
-    if (0 < n) issue_tile(0);
-    if (1 < n) issue_tile(1);
+    // A tile's V rows that came from v_new, transposed inside this wave's piece: lane -> one column's 16 tokens.
+    auto turn_new = [&](int t) {
+        const int p0 = block_pos(t);
+        if (p0 + kBlockTokens <= P) return;
+        char *piece = lds_raw + pad + kPpV + (t % kPpVBufs) * kPpTile + j_blk * 4096 + i0 * 1024;
+        const unsigned short *rows = (const unsigned short *)(p0 < P ? lds_raw + pad + kPpNew + (w & 1) * 2048 : piece) + lane;
+        uint32_t x[kBlockTokens];
+#pragma unroll
+        for (int tok = 0; tok < kBlockTokens; ++tok) x[tok] = rows[tok * 64];
+        uint4 *chunk = (uint4 *)(piece + (lane >> 5) * 1024 + (lane & 31) * 16);    // positions 0 .. 7, and 512 bytes on 8 .. 15
+        uint32_t out[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) out[p] = x[vperm(2 * p)] | (x[vperm(2 * p + 1)] << 16);
+        if (p0 < P) {
+            const int t_new = P - p0;
+            const uint4 o0 = chunk[0], o1 = chunk[32];
+            const uint32_t old[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const uint32_t keep = (vperm(2 * p) < t_new ? 0xffffu : 0u) | (vperm(2 * p + 1) < t_new ? 0xffff0000u : 0u);
+                out[p] = (old[p] & keep) | (out[p] & ~keep);
+            }
+        }
+        chunk[0] = make_uint4(out[0], out[1], out[2], out[3]);
+        chunk[32] = make_uint4(out[4], out[5], out[6], out[7]);
+    };
+    if (0 < n) issue_tile(0, false);
+    if (1 < n) issue_tile(1, false);
 
     // ---- state
     f32x16 o[4], sacc[2];         // sacc: scores of the tile between its M and V phase
@@ -268,17 +334,40 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
         for (int j = 0; j < kPpRing - 1; ++j) vpre[j] = *(lds_frag)(uintptr_t)(vb + j * 1024);
         if (kPads) e4_next = *(const int4 *)&s_bid[min(t + 1, n - 1) * 4];
     };
-    // the wave's own part of tile t must have landed before the barrier that lets the first wave
-    // read it; the tile issued after it may still be in flight
+    // the wave's own part of tile t must have landed - and be turned - before the barrier that lets the first wave
+    // read it; of tile 0, the tile issued after it may still be in flight
     auto wait_tile = [&](int t) {
+        if (t >= n) return;
         if (t + 1 < n) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        turn_new(t);
     };
+    auto wait_all = [&](int t) {                       // (nothing younger has been requested)
+        if (t >= n) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        turn_new(t);
+    };
+
+    // ---- The item of a row tile's first key range also appends: its share of the blocks that take suffix tokens, one block
+    // at a time per wave.  The rows of a wave's first block are requested when tile n + 1 would be, into the buffers that
+    // tiles n and n + 1 would take, and so are there at the end.
+    const int ap_k = ((n + grp) % kPpKBufs) * kPpTile + (w & 3) * 4096, ap_v = kPpV + ((n + grp) % kPpVBufs) * kPpTile + (w & 3) * 4096;
+    auto fetch_block = [&](int blk) {                  // rows of 256 B, as they are
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t row = (int64_t)min(max(blk * kBlockTokens + 4 * i + (lane >> 4) - P, 0), S - 1) * g.row_bytes + (lane & 15) * 16;
+            load_to_lds_each(lds0 + ap_k + i * 1024, new_k + row);
+            load_to_lds_each(lds0 + ap_v + i * 1024, new_v + row);
+        }
+    };
+    if (n == 0 && ab0 < ab1) fetch_block(ab0);
 
     // ---- intervals (barrier to barrier).  Group A does M(t) in interval 2t and V(t) in 2t+1, group B
     // one interval later: both run the same loop, B behind one extra barrier at the start and A
-    // through one at the end.  Tile t is first read in interval 2t (A's M(t)): A's waves make sure of
-    // their part at the end of their V(t-1), B's at the end of their M(t-1).  Tile t+2 is requested at
+    // through one at the end.  Tile t is first read in interval 2t (A's M(t)): B's waves make sure of
+    // their part at the end of their M(t-1), A's of a tile of prefix tokens at the end of their V(t-1), and of one whose
+    // values have to be turned where B's do, for the matrix phase is the one with time to spare (turned at the end of
+    // V(t-1): 16 queries of 2.4 k + 116 tokens 97 us a layer, 95 so).  Tile t+2 is requested at
     // the start of a wave's V(t) (A: interval 2t+1, B: 2t+2); the buffers it goes to were last read in
     // interval 2t-1.
     // A wave none of whose 32 rows exists (the row space of a (query, KV head) rarely fills its last
@@ -286,46 +375,56 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
     // nor softmax phase: on a chip whose clock is set by its power budget, work not done is time
     // gained by the others.  (Kept apart from the loop below, which compiles to worse code with a
     // test around its phases.)
-    if (__builtin_amdgcn_readfirstlane((int)(it.m0 + w * 32 >= m_rows))) {
+    const int n_pool = min(n, (P >> 6) - it.tile_begin);       // tiles of prefix tokens only
+    const bool idle = __builtin_amdgcn_readfirstlane((int)(it.m0 + w * 32 >= m_rows));
+    if (idle) {
         if (n > 0) {
             wait_tile(0);
             __syncthreads();
             if (grp) __syncthreads();
-            if (grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            wait_all(1);
             __syncthreads();
-            if (2 < n) issue_tile(2);
-            if (!grp) wait_tile(1);
+            if (2 < n) issue_tile(2, false);
+            if (n == 1 && ab0 < ab1) fetch_block(ab0);
             __syncthreads();
             for (int t = 1; t < n; ++t) {
-                if (grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                wait_all(t + 1);
                 __syncthreads();
-                if (t + 2 < n) issue_tile(t + 2);
-                if (!grp) wait_tile(t + 1);
-                __syncthreads();
+                if (t + 2 < n) issue_tile(t + 2, false);
+                if (t + 1 == n && ab0 < ab1) fetch_block(ab0);
+                    __syncthreads();
             }
             __syncthreads();
             if (!grp) __syncthreads();
         }
-        return;
-    }
-    if (n > 0) {
+    } else if (n > 0) {
         wait_tile(0);
         __syncthreads();                               // tile 0 visible
         if (grp) __syncthreads();
         m_phase(0, true, false);
-        if (grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // tile 1 (B has requested nothing younger)
+        wait_all(1);
         __syncthreads();
-        if (2 < n) issue_tile(2);
+        if (2 < n) issue_tile(2, false);
+        if (n == 1 && ab0 < ab1) fetch_block(ab0);
         v_phase(0);
-        if (!grp) wait_tile(1);
         __syncthreads();
-        for (int t = 1; t < n; ++t) {
+        int t = 1;
+        for (; t + 2 < n_pool; ++t) {                  // the same with nothing but the pool's tiles to bring
             m_phase(t, true, true);
-            if (grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // tile t+1
+            if (grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (t + 2 < n) issue_tile(t + 2);          // in the softmax phase, which has the time to spare
+            issue_tile(t + 2, true);                   // in the softmax phase, which has the time to spare
             v_phase(t);
-            if (!grp) wait_tile(t + 1);
+            if (!grp) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            __syncthreads();
+        }
+        for (; t < n; ++t) {
+            m_phase(t, true, true);
+            wait_all(t + 1);
+            __syncthreads();
+            if (t + 2 < n) issue_tile(t + 2, false);
+            if (t + 1 == n && ab0 < ab1) fetch_block(ab0);
+            v_phase(t);
             __syncthreads();
         }
         m_phase(n, false, true);                       // PV of the last tile
@@ -333,9 +432,57 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
         if (!grp) __syncthreads();
     }
 
+    for (int blk = ab0; blk < ab1; blk += 8) {
+        if (blk != ab0) {
+            ap_bid = bt_q[blk];
+            fetch_block(blk);
+        }
+        const int t_new = max(P - blk * kBlockTokens, 0), t_end = P + S - blk * kBlockTokens;   // its tokens t_new .. t_end - 1, behind them zeros
+        char *kd = const_cast<char *>(pool_l) + (int64_t)entry_bid(__builtin_amdgcn_readfirstlane(ap_bid)) * bb;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const char *krows = lds_raw + pad + ap_k;
+        const unsigned short *vrows = (const unsigned short *)(lds_raw + pad + ap_v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = 4 * i + (lane >> 4);
+            uint4 x = *(const uint4 *)(krows + t * 256 + (lane & 15) * 16);
+            if (t >= t_end) x = make_uint4(0, 0, 0, 0);
+            if (t >= t_new) *(uint4 *)(kd + t * 256 + (lane & 15) * 16) = x;
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int d = lane + 64 * half;
+            uint32_t x[kBlockTokens];
+#pragma unroll
+            for (int t = 0; t < kBlockTokens; ++t) x[t] = t < t_end ? vrows[t * 128 + d] : 0u;
+            char *vd = kd + v_half + d * 32;
+            if (t_new == 0) {
+                uint32_t out[8];
+#pragma unroll
+                for (int p = 0; p < 8; ++p) out[p] = x[vperm(2 * p)] | (x[vperm(2 * p + 1)] << 16);
+                *(uint4 *)vd = make_uint4(out[0], out[1], out[2], out[3]);
+                *(uint4 *)(vd + 16) = make_uint4(out[4], out[5], out[6], out[7]);
+            } else {                                   // (the prefix's tokens are being read by this launch: not written, not even as they are)
+#pragma unroll
+                for (int t = 0; t < kBlockTokens; t += 4) {           // four tokens are eight bytes
+                    unsigned short *at = (unsigned short *)vd + vperm(t);
+                    if (t >= t_new) {
+                        *(uint2 *)at = make_uint2(x[t] | (x[t + 1] << 16), x[t + 2] | (x[t + 3] << 16));
+                    } else {
+#pragma unroll
+                        for (int e = 1; e < 4; ++e)
+                            if (t + e >= t_new) at[e] = (unsigned short)x[t + e];
+                    }
+                }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // read out, should another block follow
+    }
+
     // ---- final normalisation and store: the output rows, or (split queries) this partition's partial
     const float l = l_lane + __shfl_xor(l_lane, 32);
-    if (it.n_splits > 1) {
+    if (idle) {
+    } else if (it.n_splits > 1) {
         const int64_t slot = (int64_t)it.split * it.n_groups + it.group;
         const float inv = l > 0.f ? 1.f / l : 0.f;
         f16x4 *po = (f16x4 *)a.part_o + ((slot * 8 + w) * 16) * 64 + lane;
@@ -355,21 +502,20 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
             ml[1] = l;
             __builtin_nontemporal_store(ml, &((f32x2 *)a.part_ml)[(slot * 8 + w) * 32 + r32]);
         }
-        return;
+    } else if (valid) {
+        const int64_t row = (int64_t)(it.cu + s_tok) * g.Hq + head;
+        const float inv = 1.f / l;
+        char *op = (char *)a.out + row * 256 + hh * 8;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                bf16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[db][4 * q4 + e] * inv);
+                *(bf16x4 *)(op + (32 * db + 8 * q4) * 2) = v;
+            }
     }
-    if (!valid) return;
-    const int64_t row = (int64_t)(it.cu + s_tok) * g.Hq + head;
-    const float inv = 1.f / l;
-    char *op = (char *)a.out + row * 256 + hh * 8;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[db][4 * q4 + e] * inv);
-            *(bf16x4 *)(op + (32 * db + 8 * q4) * 2) = v;
-        }
 }
 
 hipError_t launch_attn_pp_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)

@@ -251,8 +251,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         return fail(ctx, TC_ERR_INVALID, "attn: a work item's key range exceeds its kernel's block-id table");
 
     const size_t B = p.B, nseg = segs.size();
-    const std::vector<AppendBlk> ablk = append_blocks(p);
-    const PlanLayout at = plan_layout(ctx->cfg, p, nseg, sblk.size(), ablk.size(), items.size(), groups.size());
+    const PlanLayout at = plan_layout(ctx->cfg, p, nseg, sblk.size(), items.size(), groups.size());
     const size_t total = at.total;
     if (p.n_part_slots > INT32_MAX) return fail(ctx, fixed ? TC_ERR_CAPACITY : TC_ERR_HIP, "attn: %lld split-KV partials", (long long)p.n_part_slots);
     const size_t part_need = part_floats(ctx->cfg, p);
@@ -277,7 +276,6 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     for (size_t k = 0; k < nseg; ++k) {
         h[at.seg_start + k] = segs[k].start; h[at.seg_len + k] = segs[k].len; h[at.seg_slot + k] = segs[k].slot;
     }
-    put(at.append, ablk);
     put(at.stitch, sblk);
     if (at.by_row && !p.decode) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
@@ -306,8 +304,6 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         p.dev.part_tab = d + at.part_tab;
         p.dev.part_stride = p.part_stride;
     }
-    p.dev.append_blk = (const AppendBlk *)(d + at.append);
-    p.dev.n_append_blk = (int32_t)ablk.size();
     p.dev.rope_pos0 = p.rope ? d + at.rope_pos0 : nullptr;
     p.dev.rope_rev_freq = p.rope ? (const double *)(d + at.rope_freq) : nullptr;
     p.dev.B = p.B; p.dev.max_blocks = (int32_t)at.bt_row; p.dev.total_S = p.total_S;
@@ -939,10 +935,6 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
         return TC_OK;
-    }
-    if (p.pingpong) {   // the attention launches append in extra work-groups of their own, except this kernel's,
-                        // which reads the suffix from the pool: it is appended first, block by block
-        TC_HIP(ctx, timed_launch(ctx, 1, stream, [&](const Launch &ln) { return launch_append_blocks(ctx->geom, p.dev, layer, k_new, v_new, ln); }));
     }
     AttnArgs a{};
     a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;

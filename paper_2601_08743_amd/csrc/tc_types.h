@@ -55,12 +55,6 @@ struct StitchBlk {
     int32_t q;         // query index in the batch
 };
 
-// One sequence block that takes suffix tokens: its positions [t_begin, t_end) come from rows
-// row0 + t_begin .. of k_new / v_new (row0, where position 0 would come from, may be negative).
-struct AppendBlk {
-    int32_t phys, row0, t_begin, t_end;
-};
-
 // Device-side view of the current batch (all arrays int32, one upload per batch; those that the batch's kernels do
 // not read are null).
 struct BatchDev {
@@ -72,14 +66,13 @@ struct BatchDev {
     const int32_t *seg_len;       // [n_seg]
     const int32_t *seg_slot;      // [n_seg] table slot holding the segment's table
     const StitchBlk *stitch_blk;  // [n_stitch_blk]
-    const AppendBlk *append_blk;  // [n_append_blk] (batches whose suffix is appended by a launch of its own, else none)
     const int32_t *part_tab;      // kernels that keep partials by row (else null): [sum S] partitions of each suffix token where
                                   // slots are evenly spaced, [sum S + 1] first slot of each where they are packed
     int32_t part_stride;          // slots from token to token, 0: packed
     const int32_t *tok_q;         // [sum S] query index of each suffix token
     const int32_t *rope_pos0;     // [B] position of each query's first schema token (re-encoding stitch), else null
     const double *rope_rev_freq;  // [D/2] theta^(-2i/D) / (2 pi): revolutions per position step, else null
-    int32_t B, max_blocks, total_S, n_stitch_blk, n_append_blk;
+    int32_t B, max_blocks, total_S, n_stitch_blk;
 };
 
 // One unit of attention work: a tile of rows of one (query, KV head) against a range of key tiles.
