@@ -190,7 +190,7 @@ struct Plan {
     bool valid = false;
     int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
     int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
-    int64_t n_part_slots = 0;   // kernels that keep partials by row: slots of the batch
+    int64_t n_part_slots = 0;   // partial slots of the batch: by (token, partition) in kernels that keep them by row, else by (row tile, partition)
     int32_t part_stride = 0;    // and slots from token to token, 0: packed
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
@@ -319,6 +319,115 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
     return best;
 }
 
+// The general and the pipelined kernel (128 rows per work-group; `row_tile` 256 with two row blocks per wave): the number of
+// key partitions, by a small cost model in units of one key tile of one work-group
+// (~1.4 us).  The work items of one (query, KV head, partition) - a bucket - go to one XCD (they
+// share its L2), so what counts is the most loaded XCD: buckets per XCD x items per bucket over
+// its 32 CUs gives the work-groups per CU (a whole number while the chip is not full: 35 items
+// on an XCD mean 3 CUs run two and the launch takes as long as with 64); times the key tiles per
+// work-group (co-resident work-groups overlap each other's stalls: x0.7); plus a fixed start-up
+// and epilogue cost; plus the merge: a launch and the partials written and read back at about
+// 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
+struct GeneralPlan { int splits = 1; double us = 1e30; };
+inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
+{
+    const int G = c.n_q_heads / c.n_kv_heads;
+    int64_t base = 0, tiles_sum = 0, n_q = 0;
+    for (int i = 0; i < p.B; ++i)
+        if (p.suffix_len[i] > 0) {
+            base += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + row_tile - 1) / row_tile);
+            tiles_sum += (p.prefix_len[i] + key_tile - 1) / key_tile + (p.suffix_len[i] + key_tile - 1) / key_tile;
+            ++n_q;
+        }
+    GeneralPlan out;
+    if (base == 0) return out;
+    const double tiles = (double)tiles_sum / (double)n_q;
+    const double items_per_bucket = (double)base / (double)(n_q * c.n_kv_heads);
+    const double rows = (double)p.total_S * c.n_q_heads;
+    double best = 1e30;
+    for (int ns = 1; ns <= 32; ++ns) {
+        if (ns > 1 && tiles / ns < 2.0) break;
+        if (ns > 1 && part_cap > 0 && (double)ns * base * row_tile * (64 + 2) > (double)part_cap) break;
+        const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
+        const double per_cu = load <= 1.0 ? 1.0 : load <= 2.0 ? 2.0 : load;
+        const double merge = ns > 1 ? 1.0 + 0.93e-4 * ns * rows : 0.0;   // fp16 partials: 264 B per row and partition
+        const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 ? 0.7 : 1.0) + 3.0 + merge;
+        if (cost < best - 1e-9) {
+            best = cost;
+            out.splits = ns;
+            // What such a launch takes, in us, for the comparisons with the other kernels only: fitted to 710 of the batches
+            // that plan_brief was fitted to (9 % rms), with the append work-groups and the traffic, which the
+            // choice between partition counts does not turn on.
+            out.us = 0.8 + 7.1 * per_cu + 1.44 * per_cu * (tiles / ns) * (per_cu >= 2.0 ? 0.7 : 1.0) +
+                     (ns > 1 ? 1.9 + 1e-4 * ns * rows : 0.0) + 2.2 * p.total_S / 256.0 + 0.087 * batch_mb(c, p);
+        }
+    }
+    return out;
+}
+
+// The long-launch kernel (one work-group of 256 rows per CU): the key range of a work item in key tiles, and what the launch
+// takes, in us.  Its items go out longest first to whichever CU is free, so the launch lasts as long as that placement of
+// them on 256 CUs: each item 7.8 us and 1.32 a key tile, where some query is cut 1.8 us and its partials for the
+// merge, and 3.0 for the launch.  One range length for the batch: a long query is cut into more than a short one.
+// Tried are lengths from the longest query's down to an eleventh of it.
+// Fitted to 90 batches (1 .. 36 queries of 0.2 .. 18 k prefix and 24 .. 512 new tokens, 28 / 4, 32 / 8 and 40 / 8 heads) at 9 .. 13
+// lengths each: 8 % rms, and of the lengths tried the choice is within 0.3 % of the fastest on average, 8 % at worst.
+// (With one partition count for all, taken from a batch's mean length: 11 % behind it; micro-batches of eight queries of
+// 1 .. 5 k + 128 tokens, 40 / 8 heads, 100 .. 107 us against 80 .. 90.)
+struct LongPlan { int range = 0; double us = 1e30; };
+inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
+{
+    constexpr int kCus = 256;
+    constexpr int64_t kItem = 780, kTile = 132;          // 1/100 us
+    const int G = c.n_q_heads / c.n_kv_heads;
+    struct Query { int tiles; int64_t count, rows; };
+    std::vector<Query> queries;
+    int longest = 0;
+    for (int i = 0; i < p.B; ++i) {
+        const int64_t S = p.suffix_len[i];
+        if (S <= 0) continue;
+        queries.push_back(Query{(int)(((int64_t)p.prefix_len[i] + S + key_tile - 1) / key_tile), c.n_kv_heads * ((S * G + row_tile - 1) / row_tile), S * c.n_q_heads});
+        longest = std::max(longest, queries.back().tiles);
+    }
+    LongPlan best;
+    double uncut = 0.0;                                  // with no query cut: left for 5 % or more, which the fit resolves
+    std::vector<std::pair<int, int64_t>> parts;         // (key tiles, how many items)
+    std::vector<std::pair<int64_t, int64_t>> cus;       // (when free, how many), the first free last
+    int last = 0;
+    for (const int tenths : {10, 12, 14, 16, 18, 20, 25, 30, 40, 50, 60, 80, 110}) {
+        const int range = std::max(2, (longest * 10 + tenths - 1) / tenths);
+        if (range == last) continue;
+        last = range;
+        parts.clear();
+        int64_t cut_rows = 0, cut_tiles = 0, total = 0;
+        for (const Query &q : queries) {
+            const int ns = std::max(1, std::min((q.tiles + range - 1) / range, q.tiles / 2)), len = q.tiles / ns, more = q.tiles % ns;
+            if (more) parts.push_back({len + 1, more * q.count});
+            parts.push_back({len, (ns - more) * q.count});
+            total += q.count * (ns * kItem + q.tiles * kTile);
+            if (ns > 1) { cut_rows += q.rows * ns; cut_tiles += q.count * ns; }
+        }
+        if (part_cap > 0 && (double)cut_tiles * row_tile * (64 + 2) > (double)part_cap) continue;
+        const double merge = cut_rows > 0 ? 1.8 + 0.74e-4 * (double)cut_rows : 0.0;
+        std::sort(parts.begin(), parts.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+        if (3.0 + merge + 0.01 * (double)std::max(total / kCus, kItem + parts[0].first * kTile) >= (uncut > 0.0 ? std::min(best.us, 0.95 * uncut) : best.us)) continue;
+        cus.assign(1, {0, kCus});
+        for (auto [len, count] : parts)
+            while (count > 0) {
+                const int64_t free_at = cus.back().first, n = std::min(count, cus.back().second), end = free_at + kItem + len * kTile;
+                if ((cus.back().second -= n) == 0) cus.pop_back();
+                const auto at = std::lower_bound(cus.begin(), cus.end(), end, [](const auto &x, int64_t t) { return x.first > t; });
+                if (at != cus.end() && at->first == end) at->second += n;
+                else cus.insert(at, {end, n});
+                count -= n;
+            }
+        const double us = 3.0 + merge + 0.01 * (double)cus.front().first;
+        if (us < best.us - 1e-9 && (uncut == 0.0 || us < 0.95 * uncut)) best = LongPlan{range, us};
+        if (cut_rows == 0 && uncut == 0.0) uncut = us;
+    }
+    return best;
+}
+
 // Where the split-KV partials of the fp32, decode and short-launch kernels stand.  They are kept by row: a slot, D + 2
 // floats for each query head, for every (suffix token, partition).  Where the queries have about as many
 // partitions each, every token has as many slots as the most it could need, so that the merge knows them without a
@@ -326,7 +435,7 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
 // they are packed - a batch pays for the partitions that its queries have, not for its longest query's count
 // everywhere - and a query in one range has none (a decode step always has them).  Decode steps of one table each, 8 us
 // with the finish: 0.3 us less than packed.
-// (The other bf16 kernels keep, per (partition, group, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.)
+// (The other bf16 kernels keep, per (cut row tile, partition, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.)
 inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, const std::vector<int32_t> &splits_of_q,
                            std::vector<AttnItem> &items)
 {
@@ -462,16 +571,15 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // key tiles of a query.  bf16 kernel: the tiles of the prefix (from the pool), then the tiles of
     // the suffix (from k_new / v_new); fp32 kernel: one paged sequence of P + S keys
     // the alternating-groups bf16 kernel, too, sees one sequence of P + S keys
-    // It is chosen for long launches (estimated from the row tiles x key tiles of the batch at
-    // ~0.85 us per 128 x 64 tile and CU): its append launch costs 7 us, and with 256 rows per
-    // work-group a short launch would not fill the chip.  Measured: c3 (1140 items of ~24 tiles)
-    // 171 + 7 us against 226 us in the general kernel, c4 688 + 9 us against 814 us in the pipelined
-    // one.  Between 14 and 80 us it gains if its 256-row tiles are nearly as full as 128-row ones.  The line is
-    // at 6 / 5, included, because five 128-row tiles that make three of 256 rows (40 / 8 heads, 128 new tokens: the
-    // micro-batches of a cold cache) still gain: 40 of those 1.085 times as fast as in the other kernels, two of
-    // them 5 % slower (192 ragged items, the longest of which outlasts the rest); of 320 drawn batches of
-    // every kind none is slower by more than 3 % than with 80 us as the only line.  Where tiles pad by more
-    // it is 0.8 .. 1.2 times as fast, below 14 us 0.75 .. 1.3.
+    // It is chosen for launches of 14 us or more (estimated from the row tiles x key tiles of the batch at ~0.85 us
+    // per 128 x 64 tile and CU) if its 256-row tiles are nearly as full as 128-row ones, of 80 us or more whatever
+    // they are.  Measured: c3 (1140 items of ~24 tiles) 171 us against 226 us in the general kernel, c4 688 against 814 us in
+    // the pipelined one.  The line is at 6 / 5, included, because five 128-row tiles that make three of 256 rows (40 / 8 heads,
+    // 128 new tokens: the micro-batches of a cold cache) gain: 40 of those 1.085 times as fast as in the other kernels with
+    // one partition count for all their queries, and another 1.1 .. 1.35 with plan_long's.
+    // Shorter launches take it where plan_long puts it 15 % below both of the others' models, 25 % where rows are padded by more
+    // than that: on average 1.2 times as fast, a few 4 .. 7 % slower; one query of 4.6 k + 128 tokens, 40 / 8 heads, 25 us
+    // against 33.
     bool pp = false;
     if (bf16 && ctx->forced_row_blocks == 0) {
         if (ctx->forced_attn_kernel == 4) pp = true;
@@ -485,6 +593,11 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 }
             const double us = (double)work * 0.85 / 256.0;
             pp = us >= 80.0 || (!ctx->compact && us >= 14.0 && 5 * work_pp <= 6 * work);
+            if (!pp && !ctx->compact && us >= 4.0 && us < 14.0) {
+                double others = plan_general(c, p, kAttnRows, KT, ctx->part_cap).us;
+                if (ctx->short_rows > 0) others = std::min(others, plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).us);
+                pp = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap).us < (5 * work_pp <= 6 * work ? 0.85 : 0.75) * others;
+            }
         }
     }
     const bool unified = !bf16 || pp;
@@ -497,55 +610,15 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     const int rb = pp ? 2 : (bf16 && ctx->forced_row_blocks > 0) ? ctx->forced_row_blocks : 1;
     p.row_blocks = rb;
     int RT = bf16 ? kAttnRows * rb : kF32Rows;
-    int64_t base = 0, tiles_sum = 0, n_q = 0;
-    auto count_items = [&] {
-        base = tiles_sum = n_q = 0;
-        for (int i = 0; i < p.B; ++i)
-            if (p.suffix_len[i] > 0) {
-                base += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + RT - 1) / RT);
-                tiles_sum += tiles_of(p.prefix_len[i], p.suffix_len[i]);
-                ++n_q;
-            }
-    };
-    count_items();
-    // Number of key partitions: a small cost model, in units of one key tile of one work-group
-    // (~1.4 us).  The work items of one (query, KV head, partition) - a bucket - go to one XCD (they
-    // share its L2), so what counts is the most loaded XCD: buckets per XCD x items per bucket over
-    // its 32 CUs gives the work-groups per CU (a whole number while the chip is not full: 35 items
-    // on an XCD mean 3 CUs run two and the launch takes as long as with 64); times the key tiles per
-    // work-group (co-resident work-groups overlap each other's stalls: x0.7); plus a fixed start-up
-    // and epilogue cost; plus the merge: a launch and the partials written and read back at about
-    // 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
+    const bool any = p.total_S > 0;
     int want = 1, cut_range = 0;           // (cut_range: the length of a range in key tiles, where the queries are cut by that)
     if (ctx->forced_splits > 0) want = ctx->forced_splits;
     else if (ctx->compact) want = 1;
-    else if (!bf16 && base > 0) cut_range = plan_f32_range(c, p, RT, KT, ctx->part_cap);
-    else if (base > 0) {
-        const double tiles = (double)tiles_sum / (double)n_q;
-        const double items_per_bucket = (double)base / (double)(n_q * c.n_kv_heads);
-        const double rows = (double)p.total_S * c.n_q_heads;
-        double best = 1e30, us = 0;
-        for (int ns = 1; ns <= 32; ++ns) {
-            if (ns > 1 && tiles / ns < 2.0) break;
-            if (ns > 1 && ctx->part_cap > 0 && (double)ns * base * RT * (64 + 2) > (double)ctx->part_cap) break;
-            const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
-            // (uncut items of the long-launch kernel differ in length, start longest first and end together rather
-            // than in rounds: 272 items of 16 queries, 105 us in one range each, 115 in two; cut ones are equally
-            // long: 52 x 4 items 40 us, 52 x 5 46)
-            const double per_cu = load <= 1.0 ? 1.0 : (load <= 2.0 && !(pp && ns == 1) ? 2.0 : load);
-            const double merge = ns > 1 ? 1.0 + 0.93e-4 * ns * rows : 0.0;   // fp16 partials: 264 B per row and partition
-            // (two work-groups on a CU overlap each other's stalls; the long-launch kernel runs one per CU)
-            const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 && !pp ? 0.7 : 1.0) + 3.0 + merge;
-            if (cost < best - 1e-9) {
-                best = cost;
-                want = ns;
-                // What such a launch takes, in us, for the comparison below only: fitted to 710 of the batches that
-                // plan_brief was fitted to (9 % rms), with the append work-groups and the traffic, which the
-                // choice between partition counts does not turn on.
-                us = 0.8 + 7.1 * per_cu + 1.44 * per_cu * (tiles / ns) * (per_cu >= 2.0 ? 0.7 : 1.0) +
-                     (ns > 1 ? 1.9 + 1e-4 * ns * rows : 0.0) + 2.2 * p.total_S / 256.0 + 0.087 * batch_mb(c, p);
-            }
-        }
+    else if (!bf16 && any) cut_range = plan_f32_range(c, p, RT, KT, ctx->part_cap);
+    else if (pp && any) cut_range = plan_long(c, p, RT, KT, ctx->part_cap).range;
+    else if (any) {
+        const GeneralPlan general = plan_general(c, p, RT, KT, ctx->part_cap);
+        want = general.splits;
         // The short-launch kernel, where it is faster by more than the two models are unsure: of the batches that they
         // were fitted to it takes 451 of 740 and loses time in 8; over all 740 the call is 1.21 times as fast (1.24
         // if the faster kernel were known each time).  28 / 4 heads: one query of 1.1 k + 17 tokens 10.4 us against
@@ -553,7 +626,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // whose keys 32-row tiles would read four times as often, 25 against 22.
         if (!pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 0) {
             const BriefPlan b = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles);
-            if (b.us < 0.85 * us) {
+            if (b.us < 0.85 * general.us) {
                 p.brief = true;
                 cut_range = b.range;
             }
@@ -566,7 +639,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     }
     if (p.brief) {
         RT = ctx->short_rows;
-        count_items();
     }
     splits_of_q.assign(p.B, 1);
     p.max_splits = 1;
@@ -646,6 +718,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     flat.push_back(proto);
                     flat.back().m0 = mt * RT;
                     flat.back().group = n_groups + mt;
+                    if (!by_row && ns > 1) flat.back().part0 = (int32_t)(p.n_part_slots + (int64_t)mt * ns);
                     ++bucket.count;
                     // (32-row tiles: eight, or four, of them share their keys' way into one L2, the next may go to
                     // another XCD, so that few (query, KV head) pairs still spread evenly)
@@ -656,8 +729,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 }
                 buckets.push_back(bucket);
             }
-            for (int mt = 0; mt < n_mt; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, {0, 0, 0}});
+            for (int mt = 0; mt < n_mt; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, (int32_t)(p.n_part_slots + (int64_t)mt * ns), {0, 0}});
             n_groups += n_mt;
+            if (!by_row && ns > 1) p.n_part_slots += (int64_t)n_mt * ns;
         }
     }
     p.n_groups = n_groups;
@@ -684,7 +758,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         for (int32_t j = 0; j < buckets[k].count; ++j) {
             AttnItem &it = items[(size_t)at[xcd_of[k]]++ * 8 + xcd_of[k]];
             it = flat[buckets[k].first + j];
-            it.n_groups = n_groups;
         }
     while (!items.empty() && items.back().q < 0) items.pop_back();
     p.n_items = (int32_t)items.size();
@@ -733,7 +806,7 @@ inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode ||
 inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the batch's partials, in floats
 {
     if (parts_by_row(c, p)) return (size_t)p.n_part_slots * c.n_q_heads * (c.head_dim + 2);
-    return p.max_splits > 1 ? (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * (64 + 2) : 0;
+    return (size_t)p.n_part_slots * p.row_blocks * kAttnRows * (64 + 2);
 }
 
 // BatchDev::part_tab

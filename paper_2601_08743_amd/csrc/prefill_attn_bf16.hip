@@ -414,7 +414,7 @@ __device__ __forceinline__ void store_rows(const RowState<RB> &st, const Geom &g
             // halves the partial traffic, the largest cost of a split launch): 512 B contiguous per
             // (row block, db, q4); a group's slot holds 4 * RB row blocks of 32 rows
             if (ir.wave_row0 + rb * 32 >= ir.m_rows) continue;        // none of these rows exists: nothing reads them
-            const int64_t slot = (int64_t)it.split * it.n_groups + it.group;
+            const int64_t slot = (int64_t)it.part0 + it.split;
             const int blk = w * RB + rb;
             const float inv = l > 0.f ? 1.f / l : 0.f;
             f16x4 *po = (f16x4 *)a.part_o + ((slot * (4 * RB) + blk) * 16) * 64 + lane;
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
 // of 17 new tokens, 9 partitions: 4.6 us against 5.2; one of 128, 8 partitions: 4.3 either way.
 template <int kFrags, int kBatch>
 __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, const MergeGroup *groups,
-                                                         int n_groups, int n_rb)
+                                                         int n_rb)
 {
     constexpr int kWgs = 4 / kFrags;                   // work-groups per row block
     const int gb = blockIdx.x / kWgs;                  // group * n_rb + row block
@@ -952,20 +952,19 @@ __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, con
     const int group = gb / n_rb, blk = gb - group * n_rb;
     typedef const __attribute__((address_space(4))) int32_t *const_ints;
     const const_ints mg = (const_ints)(uintptr_t)(groups + group);               // (uploaded before the launch, never written)
-    const int kvh = mg[0], m0 = mg[1], n_splits = mg[2], cu = mg[3], S = mg[4];
+    const int kvh = mg[0], m0 = mg[1], n_splits = mg[2], cu = mg[3], S = mg[4], part0 = mg[5];
     if (n_splits <= 1 || m0 + blk * 32 >= S * g.G) return;      // written directly by the attention kernel; no such rows
     const int lane = threadIdx.x & 63, r32 = lane & 31, hh = lane >> 5;
     float M = -INFINITY, l = 0.f;
     float acc[4 * kFrags];
 #pragma unroll
     for (int e = 0; e < 4 * kFrags; ++e) acc[e] = 0.f;
-    const int64_t stride = (int64_t)n_groups * n_rb;          // (group, block) slots per partition
     for (int s0 = 0; s0 < n_splits; s0 += kBatch) {
         f16x4 v[kBatch][kFrags];
         float2 ml[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            const int64_t sb = (int64_t)min(s0 + k, n_splits - 1) * stride + gb;
+            const int64_t sb = (int64_t)(part0 + min(s0 + k, n_splits - 1)) * n_rb + blk;
             ml[k] = ((const float2 *)a.part_ml)[sb * 32 + r32];
 #pragma unroll
             for (int f = 0; f < kFrags; ++f) v[k][f] = ((const f16x4 *)a.part_o)[(sb * 16 + frag0 + f) * 64 + lane];
@@ -1050,11 +1049,11 @@ hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup 
     const int n_rb = 4 * row_blocks;                   // 32-row blocks per group
     const bool few = n_groups * n_rb <= 512;
     const int grid = few ? n_groups * n_rb * 4 : n_groups * n_rb;
-    if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4>), grid, 0, L, g, a, groups, n_groups, n_rb);
-    else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8>), grid, 0, L, g, a, groups, n_groups, n_rb);
-    else if (few) TC_LAUNCH((merge_bf16_kernel<1, 16>), grid, 0, L, g, a, groups, n_groups, n_rb);
-    else if (max_splits <= 2) TC_LAUNCH((merge_bf16_kernel<4, 2>), grid, 0, L, g, a, groups, n_groups, n_rb);
-    else TC_LAUNCH((merge_bf16_kernel<4, 4>), grid, 0, L, g, a, groups, n_groups, n_rb);
+    if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4>), grid, 0, L, g, a, groups, n_rb);
+    else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8>), grid, 0, L, g, a, groups, n_rb);
+    else if (few) TC_LAUNCH((merge_bf16_kernel<1, 16>), grid, 0, L, g, a, groups, n_rb);
+    else if (max_splits <= 2) TC_LAUNCH((merge_bf16_kernel<4, 2>), grid, 0, L, g, a, groups, n_rb);
+    else TC_LAUNCH((merge_bf16_kernel<4, 4>), grid, 0, L, g, a, groups, n_rb);
     return hipGetLastError();
 }
 

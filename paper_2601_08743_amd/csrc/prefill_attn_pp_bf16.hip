@@ -483,7 +483,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
     const float l = l_lane + __shfl_xor(l_lane, 32);
     if (idle) {
     } else if (it.n_splits > 1) {
-        const int64_t slot = (int64_t)it.split * it.n_groups + it.group;
+        const int64_t slot = (int64_t)it.part0 + it.split;
         const float inv = l > 0.f ? 1.f / l : 0.f;
         f16x4 *po = (f16x4 *)a.part_o + ((slot * 8 + w) * 16) * 64 + lane;
 #pragma unroll

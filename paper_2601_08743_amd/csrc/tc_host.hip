@@ -944,7 +944,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.long_ranges = p.longest_range > kF32MaxTiles ? 1 : 0;
     a.part_o = p.part;
     a.part_ml = !p.part ? nullptr
-              : bf16 && !p.brief ? p.part + (size_t)p.max_splits * p.n_groups * p.row_blocks * kAttnRows * 64
+              : bf16 && !p.brief ? p.part + (size_t)p.n_part_slots * p.row_blocks * kAttnRows * 64
                      : p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
     TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) {
         return p.pingpong ? launch_attn_pp_bf16(ctx->geom, p.dev, a, ln)

@@ -86,20 +86,20 @@ struct AttnItem {
     int32_t tile_end;    // one past the last key tile
     int32_t split;       // which partition this is (0 when n_splits == 1)
     int32_t n_splits;    // partitions of this query
-    int32_t group;       // index of the (query, KV head, row tile): partial slots, arrival counter
+    int32_t group;       // index of the (query, KV head, row tile); decode steps: arrival counter
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
-    int32_t n_groups;    // total number of groups in the batch
+    int32_t spare;       // (to 128 bytes)
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
-    int32_t part0;       // kernels that keep partials by row: slot of the query's first token and partition,
+    int32_t part0;       // first partial slot: of the query's first token (kernels that keep partials by row), else of the row tile,
     int32_t part_stride; // and slots from token to token
 };
 static_assert(sizeof(AttnItem) == 128, "AttnItem layout");
 
 // A (query, KV head, row tile) whose partitions the bf16 merge kernel combines.
 struct MergeGroup {
-    int32_t kvh, m0, n_splits, cu, S, pad[3];
+    int32_t kvh, m0, n_splits, cu, S, part0, pad[2];
 };
 
 struct AttnArgs {
