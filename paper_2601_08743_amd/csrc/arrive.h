@@ -31,7 +31,8 @@ typedef float part_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kDeviceScope = 16;                     // sc1, in the buffer instructions' cache policy
 
-// Memory that work-groups of one launch share: `bytes` from `base` on (reads beyond them give zero, stores nothing).
+// Memory that work-groups of one launch share: `bytes` (at most 2 GiB) from `base` on.  Reads beyond them give zero: the whole
+// offset is in the vector register, for the hardware does not check the scalar one.
 struct SharedPart {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ SharedPart(float *base, uint32_t bytes) : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000)) {}
@@ -46,9 +47,9 @@ struct SharedPart {
         const u32x2 v = {__float_as_uint(x), __float_as_uint(y)};
         __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kDeviceScope);
     }
-    __device__ __forceinline__ part_f32x4 get4(uint32_t off, uint32_t uniform) const
+    __device__ __forceinline__ part_f32x4 get4(uint32_t off) const
     {
-        return __builtin_bit_cast(part_f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, uniform, kDeviceScope));
+        return __builtin_bit_cast(part_f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kDeviceScope));
     }
     __device__ __forceinline__ float2 get2(uint32_t off) const
     {
@@ -107,8 +108,8 @@ __device__ __forceinline__ float sum32(float x) { return reduce32(x, [](float a,
 
 // Partials `first`, first + step, .. of the `n` of a row, folded by 32 neighbouring threads of a wave (lane: 0 .. 31), four
 // columns each; row r's partial s stands in slot s * rows + r.  What this takes is the latency of its own instructions - a wave
-// alone on its SIMD - and one round trip, so: up to 36 partials are requested at once, by loads that differ in a scalar
-// offset only and read zeros beyond the group's last; their weights come from one lane each and go around through LDS, where
+// alone on its SIMD - and one round trip, so: up to 36 partials are requested at once, and slots
+// beyond the group's last read as zeros; their weights come from one lane each and go around through LDS, where
 // one shuffle and one branch a partial took three times as long (17 partials: 3.4 -> 1.3 us).
 constexpr int kFoldBatch = 36, kFoldGroup = 12;
 __device__ __forceinline__ RowSum fold_partials(const SharedPart &po, const SharedPart &pml, int row, int rows, int n, int first, int step, int lane, float *s_w)
@@ -123,7 +124,7 @@ __device__ __forceinline__ RowSum fold_partials(const SharedPart &po, const Shar
         part_f32x4 o[kFoldBatch];
         auto fetch = [&](int j0) {
 #pragma unroll
-            for (int j = j0; j < j0 + kFoldGroup; ++j) o[j] = po.get4(o_at, j * o_step);
+            for (int j = j0; j < j0 + kFoldGroup; ++j) o[j] = po.get4(o_at + j * o_step);
         };
         auto use = [&](int j0) {
             part_f32x4 w[kFoldGroup / 4];
