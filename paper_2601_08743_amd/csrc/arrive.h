@@ -90,19 +90,27 @@ struct RowSum {
     }
 };
 
-// Over 32 neighbouring lanes (half a wave): every lane's value exchanged with DPP inside rows of 16 lanes, then the two rows.
+constexpr uint32_t kNowhere = 0x80000000u;            // an offset beyond any SharedPart: reads as zero
+
+// Over 16 neighbouring lanes, every lane's value exchanged with DPP; over 32, the two rows of 16 as well.
 template <typename F>
-__device__ __forceinline__ float reduce32(float x, F op)
+__device__ __forceinline__ float reduce16(float x, F op)
 {
     auto dpp = [](float v, auto ctrl) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false)); };
     x = op(x, dpp(x, std::integral_constant<int, 0xb1>{}));      // lane ^ 1
     x = op(x, dpp(x, std::integral_constant<int, 0x4e>{}));      // lane ^ 2
     x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));     // mirrored in each eight
-    x = op(x, dpp(x, std::integral_constant<int, 0x140>{}));     // mirrored in each sixteen
-    const unsigned u = __float_as_uint(x);
+    return op(x, dpp(x, std::integral_constant<int, 0x140>{}));  // mirrored in the sixteen
+}
+template <typename F>
+__device__ __forceinline__ float reduce32(float x, F op)
+{
+    const unsigned u = __float_as_uint(reduce16(x, op));
     const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+__device__ __forceinline__ float max16(float x) { return reduce16(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float sum16(float x) { return reduce16(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float max32(float x) { return reduce32(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float sum32(float x) { return reduce32(x, [](float a, float b) { return a + b; }); }
 

@@ -363,7 +363,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
             if (d == 0) part_ml.put2(off * 8, M, L);
         }
     }
-    if (it.n_splits > 1 && last_to_arrive(a.arrivals + it.group * kArrivalStride, it.n_splits, (int32_t *)(lds + kDecIds))) {
+    if (it.n_splits > 1 && last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, it.n_splits, (int32_t *)(lds + kDecIds))) {
         // a row to 32 threads; of up to four rows two such groups take every other partition each
         const bool two = G <= 4;
         float *s_w = (float *)lds + 8 * kDecRow + slot8 * kFoldBatch;
@@ -402,64 +402,6 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
     }
 }
 
-// Combine the partitions of an output row (token, head) of the short-launch prefill kernel, normalise, write bf16.
-// Bound by the latency of its loads, so all of them are issued before the first use: kGroups groups of 32 threads (four columns each) take every kGroups-th partition of a row, four at a time - a
-// row of up to 4 * kGroups partitions costs one round trip - and fold their results through LDS.  A
-// work-group does 8 / kGroups rows: with eight groups for rows of one or two partitions most
-// threads would load what nobody needs.  (Slots beyond a row's last partition are loaded and ignored; with evenly
-// spaced slots, kEven, nothing waits for the number of partitions before the loads.)  Rows of one partition are left
-// alone: they were written directly.
-template <int kGroups, bool kEven>
-__global__ __launch_bounds__(256) void merge_rows_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
-{
-    constexpr int kBatch = 4, kRows = 8 / kGroups;
-    __shared__ float s_acc[8][132], s_ml[8][2];
-    const int tid = threadIdx.x, slot8 = tid >> 5, grp = slot8 % kGroups, d = 4 * (tid & 31);
-    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
-    const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
-    const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
-    const int n = row / g.Hq, head = row - n * g.Hq;      // n: the token (queries may bring none)
-    const PartSlots slots = part_slots<kEven>(b, n);
-    float2 ml[kBatch];
-    f32x4 po[kBatch];
-    auto fetch = [&](int s0) {
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (kGroups * j >= max_splits) break;
-            const int64_t slot = (int64_t)min(slots.first + s0 + kGroups * j, slots.last) * g.Hq + head;
-            ml[j] = *(const float2 *)(a.part_ml + slot * 2);
-            po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
-        }
-    };
-    if (kEven || slots.count > 0) fetch(grp);
-    const int ns = slots.count;
-    RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
-    for (int s0 = grp; s0 < ns; s0 += kGroups * kBatch) {
-        if (s0 > grp) fetch(s0);
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j)
-            if (s0 + kGroups * j < ns) x.add(ml[j].x, ml[j].y, po[j]);
-    }
-    if (kGroups > 1) {
-        *(f32x4 *)&s_acc[slot8][d] = x.acc;
-        if (d == 0) { s_ml[slot8][0] = x.M; s_ml[slot8][1] = x.L; }
-        __syncthreads();
-    }
-    if (grp > 0 || want >= n_rows || ns <= 1) return;
-    // the row's first group goes on: the other groups' results
-#pragma unroll
-    for (int k = 1; k < kGroups; ++k) x.add(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
-    const float inv = 1.f / x.L;
-    unsigned short r[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const __bf16 y = (__bf16)(x.acc[e] * inv);
-        r[e] = *(const unsigned short *)&y;
-    }
-    *(uint2 *)((unsigned short *)a.out + (int64_t)row * 128 + d) =
-        make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
-}
-
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
     if (a.n_items == 0) return hipSuccess;
@@ -471,24 +413,6 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     if (e != hipSuccess) return e;
     TC_LAUNCH(decode_attn_bf16_kernel, a.n_items, kDecLds, L, g, b, a);
     return hipGetLastError();
-}
-
-template <bool kEven>
-static hipError_t launch_merge_rows(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
-{
-    const int n_rows = b.total_S * g.Hq;
-    if (n_rows == 0) return hipSuccess;
-    if (max_splits < 1 || !b.part_tab) return hipErrorInvalidValue;
-    if (max_splits <= 4) TC_LAUNCH((merge_rows_kernel<1, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 8) TC_LAUNCH((merge_rows_kernel<2, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 16) TC_LAUNCH((merge_rows_kernel<4, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
-    else TC_LAUNCH((merge_rows_kernel<8, kEven>), n_rows, 0, L, g, b, a, max_splits);
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
-{
-    return b.part_stride > 0 ? launch_merge_rows<true>(g, b, a, max_splits, L) : launch_merge_rows<false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

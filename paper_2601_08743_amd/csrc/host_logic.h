@@ -188,7 +188,7 @@ struct StageHalves {
 // The integer plan of one batch, host copy and layout of the device copy.
 struct Plan {
     bool valid = false;
-    int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
+    int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, n_arrivals = 0, row_blocks = 1;
     int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
     int64_t n_part_slots = 0;   // partial slots of the batch: by (token, partition) in kernels that keep them by row, else by (row tile, partition)
     int32_t part_stride = 0;    // and slots from token to token, 0: packed
@@ -209,6 +209,7 @@ struct Plan {
     const AttnItem *items_dev = nullptr;
     const MergeGroup *groups_dev = nullptr;
     int32_t *arrivals_dev = nullptr;
+    int32_t arrival_stride = 0;
 };
 
 // What a caller may force about the attention launch (tc_set_kv_splits and friends); 0 = automatic.
@@ -268,9 +269,10 @@ inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int k
 // The short-launch kernel (32 rows per work-group, one work-group per CU, its eight waves split the
 // range's 32-key units): the key range of a work item in key tiles, and what the launch takes, in us.  A
 // round of work-groups costs 4.4 us and 1.6 for each unit of a wave (a round trip to memory and its
-// arithmetic: the wave has one unit in flight), the merge 3.5 us and its fp32 partials, each MB of keys and
-// values 0.1 us.  Ranges are only cut where the chip has CUs to spare and a KV head has at most 512 rows (16 row
-// tiles that each fetch the keys; one query of 2.1 k + 140 tokens, 28 / 4 heads: 19.1 us in two ranges, 19.5 in
+// arithmetic: the wave has one unit in flight), combining the ranges of a query 3.5 us and 1.7 more for each eight
+// of them (a round of loads; one query of 1.5 k + 17 tokens, 28 / 4 heads: 10.4 us in 7 ranges, 10.5 in 8, 11.6 in 10; when a launch
+// of its own combined them 12.0), each MB of keys and values 0.1 us.  Ranges are only cut where the chip has CUs to
+// spare and a KV head has at most 512 rows (16 row tiles that each fetch the keys; one query of 2.1 k + 140 tokens, 28 / 4 heads: 19.1 us in two ranges, 19.5 in
 // the pipelined kernel), so partials stay small, and more than two rounds of work-groups are left to the
 // other kernels (three: 1.04 times as fast as those, two: 1.3, one: 1.4).  Fitted to
 // 740 batches (1 .. 16 queries of 350 .. 10500 prefix and 2 .. 330 new tokens, 28 / 4, 32 / 8 and 40 / 8
@@ -296,8 +298,8 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
         const int range = std::max(1, (longest + cuts - 1) / cuts);
         if (range > max_tiles) continue;
         int64_t n = 0;
-        double units = 0, rows_cut = 0;
-        int most = 0;
+        double units = 0;
+        int most = 0, most_ns = 1;
         bool split = false, wide = false;
         for (int i = 0; i < p.B; ++i) {
             const int S = p.suffix_len[i];
@@ -308,11 +310,12 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
             n += k;
             units += (double)k * per_wave;
             most = std::max(most, per_wave);
-            if (ns > 1) { split = true; wide = wide || S * G > 512; rows_cut += (double)S * c.n_q_heads * ns; }
+            most_ns = std::max(most_ns, ns);
+            if (ns > 1) { split = true; wide = wide || S * G > 512; }
         }
         if (n == 0 || n > 512 || (split && (n > 256 || wide))) break;          // (n grows with the cuts)
         const double rounds = (double)((n + 255) / 256);
-        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? 3.5 + 3e-5 * rows_cut : 0.0) + 0.1 * mb;
+        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? 3.5 + 1.7 * ((most_ns - 1) / 8) : 0.0) + 0.1 * mb;
         if (us < best.us - 1e-9) best = BriefPlan{range, us};
         if (range == 1) break;
     }
@@ -480,6 +483,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = false;
     p.brief = false;
     p.n_part_slots = 0;
+    p.n_groups = p.n_arrivals = 0;
     p.part_stride = 0;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
@@ -528,7 +532,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
         splits_of_q.assign(p.B, 1);
         p.max_splits = 1;
-        p.n_groups = 0;
         for (int i = 0; i < p.B; ++i) {
             if (p.suffix_len[i] <= 0) continue;
             const int P = p.prefix_len[i];
@@ -546,7 +549,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     AttnItem it{};
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
-                    it.split = s; it.n_splits = ns; it.group = p.n_groups + h; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
+                    it.split = s; it.n_splits = ns; it.arrival = p.n_arrivals + h; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
                     it.append_bid = bt[P / kBlockTokens];
                     for (int k = 0; k < 16; ++k) {          // entries of the range's first units, clamped to the prefix
                         const int idx = std::min(it.tile_begin * (KT / kBlockTokens) + k, std::max((P + kBlockTokens - 1) / kBlockTokens - 1, 0));
@@ -554,7 +557,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     }
                     items.push_back(it);
                 }
-            p.n_groups += c.n_kv_heads;
+            if (ns > 1) p.n_arrivals += c.n_kv_heads;
         }
         std::stable_sort(items.begin(), items.end(), [](const AttnItem &x, const AttnItem &y) {
             return x.tile_end - x.tile_begin > y.tile_end - y.tile_begin;
@@ -668,6 +671,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // block ids of a range fit LDS (the fp32 kernel can fetch those that do not from memory, which is slower)
         const int cap = !bf16 ? (ctx->compact ? n_tiles : kF32MaxTiles) : pp ? kPpMaxTiles : general_cap;
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
+        // (the short-launch kernel addresses the partials of a row tile's tokens, up to 33, with 31 bits)
+        if (p.brief) ns = (int)std::min<int64_t>(ns, ((int64_t)1 << 31) / (33 * 512 * (int64_t)c.n_q_heads) - 1);
         ns = std::max(1, std::min(ns, n_tiles));
         const int n_mt = (S * G + RT - 1) / RT;
         // Partition boundaries.  A suffix tile of the bf16 kernel costs about 4 prefix tiles (its V
@@ -718,6 +723,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     flat.push_back(proto);
                     flat.back().m0 = mt * RT;
                     flat.back().group = n_groups + mt;
+                    if (p.brief && ns > 1) flat.back().arrival = p.n_arrivals + mt;
                     if (!by_row && ns > 1) flat.back().part0 = (int32_t)(p.n_part_slots + (int64_t)mt * ns);
                     ++bucket.count;
                     // (32-row tiles: eight, or four, of them share their keys' way into one L2, the next may go to
@@ -731,6 +737,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             }
             for (int mt = 0; mt < n_mt; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, (int32_t)(p.n_part_slots + (int64_t)mt * ns), {0, 0}});
             n_groups += n_mt;
+            if (p.brief && ns > 1) p.n_arrivals += n_mt;
             if (!by_row && ns > 1) p.n_part_slots += (int64_t)n_mt * ns;
         }
     }
@@ -821,6 +828,8 @@ inline void fill_part_tab(const Plan &p, const std::vector<int32_t> &splits_of_q
     if (!p.part_stride) out[p.total_S] = at;
 }
 
+constexpr size_t kBigPlanInts = size_t(1) << 18;    // 1 MiB: in larger plans the arrival counters stand closer together
+
 // Where the parts of a plan stand in its device copy, in integers; only what the batch's kernels read
 // is there (`n_*`: how many of each).
 struct PlanLayout {
@@ -828,7 +837,8 @@ struct PlanLayout {
     size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
-    bool lengths = false, tokens = false, by_row = false, merge_groups = false;
+    bool lengths = false, tokens = false, part_tab_read = false, merge_groups = false;
+    int arrival_stride = kArrivalStride;
 };
 inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
                               size_t n_groups)
@@ -838,8 +848,8 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     auto take = [&](size_t n) { const size_t o = l.total; l.total += (n + 7) & ~size_t(7); return o; };
     l.tokens = !p.decode && !p.pingpong && !p.brief;             // appended token by token, in extra work-groups
     l.lengths = l.tokens || n_stitch > 0;
-    l.by_row = parts_by_row(c, p);
-    l.merge_groups = p.max_splits > 1 && !l.by_row;
+    l.part_tab_read = c.dtype != TC_BF16 && p.max_splits > 1;    // (the decode and short-launch kernels' partials come with their items)
+    l.merge_groups = p.max_splits > 1 && !parts_by_row(c, p);
     // rows are padded to whole 16-byte chunks: the decode and short-launch kernels fetch them so, the long-launch
     // kernel where it can
     l.bt_row = p.compact && !p.decode && !p.brief ? (size_t)p.max_blocks : (size_t)(p.max_blocks + 3) & ~size_t(3);
@@ -848,10 +858,11 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.cu = take(l.tokens ? B + 1 : 0); l.suffix = take(l.tokens ? B : 0); l.tok_q = take(l.tokens ? p.total_S : 0);
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
-    l.part_tab = take(l.by_row && !p.decode ? part_tab_ints(p) : 0);   // (the decode kernel's partials come with its items)
+    l.part_tab = take(l.part_tab_read ? part_tab_ints(p) : 0);
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
-    l.arrivals = take(p.decode ? (size_t)p.n_groups * kArrivalStride : 0);
+    if (l.total + (size_t)p.n_arrivals * kArrivalStride > kBigPlanInts) l.arrival_stride = kArrivalStrideBig;
+    l.arrivals = take((size_t)p.n_arrivals * l.arrival_stride);
     l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     l.total = std::max(l.total, size_t(8));
     return l;

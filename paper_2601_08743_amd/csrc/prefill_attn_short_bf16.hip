@@ -7,7 +7,7 @@
 // and its EIGHT waves split the keys: wave w takes the 32-key units w, w + 8, ... of the range, streams
 // each straight into its own LDS area and keeps its own running maximum, sum and output, so there is no
 // barrier before the waves are combined at the end.  A prefix of a thousand tokens is four or five units
-// per wave, needs no second launch, and two waves on a SIMD cover each other's round trips.  What it
+// per wave, needs no cut, and two waves on a SIMD cover each other's round trips.  What it
 // costs is that 32 rows, not 128, share a key tile on its way from the L2, which is why it is only
 // chosen where a launch is one or two rounds of work-groups.
 //
@@ -15,10 +15,15 @@
 // have to be finite.  (So are the zeros and the suffix values that the tail of the prefix's last block holds before
 // and after the append of the same launch, which may run beside a tile's loads.)
 //
-// Measured per layer, merge included where there is one, against the pipelined or general kernel: 28 / 4
+// Where a query is cut all the same, the last of a row tile's ranges to end combines their partials (16 KB each) in the same
+// launch (arrive.h).  A launch of its own for that: one query of 1.5 k + 17 tokens, 28 / 4 heads, in 7 ranges 11.8 us a layer,
+// so 10.2; 28 layers of a short question 362 us, so 340.
+//
+// Measured per layer, against the pipelined or general kernel, partials combined by a launch of its own: 28 / 4
 // heads, one query of 1.1 k prefix and 17 new tokens 10.3 us (14.9); thirteen of 4 k and 3 .. 6 tokens 27.1
 // (35.4); 40 / 8 heads, eight of 350 and 40 tokens 17.7 (28.3), sixteen of 1 k and 2 tokens 16.2 (36.0), four of
 // 1 k and 40 tokens 14.4 (24.0).
+#include "arrive.h"
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
@@ -39,7 +44,23 @@ constexpr int kShIds = kShQ + kShortRows * 256;      // block ids of the range, 
 constexpr int kShMl = kShIds + kAttnMaxTiles * (kAttnKeys / kBlockTokens) * 4;     // (maximum, sum) per wave and row
 constexpr int kShLds = kShMl + kShWaves * kShortRows * 8 + 256;                    // + alignment slack
 constexpr float kShRescale = 8.f;
+constexpr int kShFold = 8;                           // partials of a row requested at once (a lane of 16 each, and one to spare)
 
+// Four columns of an output row.
+__device__ __forceinline__ void write_part(const AttnArgs &a, int64_t row, int ch, f32x4 acc, float l)
+{
+    const float inv = 1.f / l;
+    unsigned short r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const __bf16 x = (__bf16)(acc[e] * inv);
+        r[e] = *(const unsigned short *)&x;
+    }
+    *(uint2 *)((unsigned short *)a.out + row * 128 + 4 * ch) = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
+}
+
+// kCut: some query of the batch is in several ranges.  (With their end compiled in, batches without any paid 0.1 us for it.)
+template <bool kCut>
 __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -299,45 +320,94 @@ __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom 
         if (hh == 0) *(float2 *)(lds + kShMl + (w * kShortRows + r32) * 8) = make_float2(m_run, l_row);
     }
     __syncthreads();
-#pragma unroll
-    for (int idx = tid; idx < kShortRows * 32; idx += 64 * kShWaves) {
-        const int row = idx >> 5, ch = idx & 31;
-        const int m = it.m0 + row;
-        if (m > m_last) continue;
+    const int tok0 = it.m0 / G;
+    auto fold_waves = [&](int row, int ch) {           // four columns of a row of this range
         float2 ml[kShWaves];
-        float M = -INFINITY;
+        RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int k = 0; k < kShWaves; ++k) {
             ml[k] = *(const float2 *)(lds + kShMl + (k * kShortRows + row) * 8);
-            M = fmaxf(M, ml[k].x);
+            x.M = fmaxf(x.M, ml[k].x);
         }
-        float L = 0.f;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < kShWaves; ++k) {
-            const float wgt = (ml[k].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - M);
-            L += wgt * ml[k].y;
+            const float wgt = (ml[k].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - x.M);
+            x.L += wgt * ml[k].y;
             const f32x4 v = *(const f32x4 *)(lds + k * kShWave + row * 512 + ((ch ^ row) << 4));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
+            for (int e = 0; e < 4; ++e) x.acc[e] += wgt * v[e];
         }
-        const int tok = m / G;
-        const int64_t orow = (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (m - tok * G);
-        if (it.n_splits == 1) {
-            const float inv = 1.f / L;
-            unsigned short r[4];
+        return x;
+    };
+    const int ch = tid & 31;
+    if (!kCut || it.n_splits == 1) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const __bf16 x = (__bf16)(acc[e] * inv);
-                r[e] = *(const unsigned short *)&x;
+        for (int j = 0; j < 2; ++j) {
+            const int row = (tid >> 5) + 16 * j, m = it.m0 + row;
+            if (m > m_last) continue;
+            const RowSum x = fold_waves(row, ch);
+            const int tok = m / G;
+            write_part(a, (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (m - tok * G), ch, x.acc, x.L);
+        }
+    } else {
+        // A range of several: the last work-group of the row tile to end combines them (arrive.h).  32 threads take two rows
+        // at a time, four columns each; lanes 0 .. 15 and 16 .. 31 bring their weights.
+        const int64_t first_slot = ((int64_t)it.part0 + (int64_t)tok0 * it.part_stride) * g.Hq + it.kvh * G;
+        const uint32_t n_slots = (uint32_t)min((int64_t)(m_last / G - tok0 + 1) * it.part_stride * g.Hq, (int64_t)0x3fffff);
+        const SharedPart part_o(a.part_o + first_slot * 128, n_slots * 512), part_ml(a.part_ml + first_slot * 2, n_slots * 8);
+        const int ns = it.n_splits;
+        const uint32_t step = (uint32_t)g.Hq * 512;
+        uint32_t slot[2];
+        int64_t orow[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = (tid >> 5) + 16 * j, m = min(it.m0 + row, m_last), tok = m / G;
+            slot[j] = (uint32_t)((tok - tok0) * it.part_stride * g.Hq + m - tok * G);
+            orow[j] = (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (m - tok * G);
+            if (it.m0 + row > m_last) continue;
+            const RowSum x = fold_waves(row, ch);
+            part_o.put4(slot[j] * 512 + it.split * step + ch * 16, x.acc);
+            if (ch == 0) part_ml.put2(slot[j] * 8 + it.split * (step >> 6), x.M, x.L);
+        }
+        const uint32_t ml_at = (ch < 16 ? slot[0] : slot[1]) * 8 + (ch & 15) * (step >> 6);
+        float *s_w = (float *)(lds + kShMl) + (tid >> 5) * 32;
+        if (last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, ns, (int32_t *)(lds + kShIds))) {
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            float M = -INFINITY, l_lane = 0.f;         // of the lane's row
+            for (int s0 = 0; s0 < ns; s0 += kShFold) {
+                const bool there = (ch & 15) < min(ns - s0, kShFold);
+                const float2 ml = part_ml.get2(there ? ml_at + s0 * (step >> 6) : kNowhere);
+                f32x4 o[kShFold][2];
+#pragma unroll
+                for (int k = 0; k < kShFold; ++k)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) o[k][j] = part_o.get4(s0 + k < ns ? slot[j] * 512 + ch * 16 + (s0 + k) * step : kNowhere);
+                const float m = there ? ml.x : -INFINITY;
+                const float Mn = fmaxf(M, max16(m)), r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+                const float w = m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - Mn);     // (no maximum: its sums are 0, or NaN and so is the row)
+                l_lane = l_lane * r + w * ml.y;
+                M = Mn;
+                s_w[ch] = (ch & 15) == kShFold ? r : w;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    f32x4 wj[kShFold / 4 + 1];
+#pragma unroll
+                    for (int k = 0; k < kShFold / 4 + 1; ++k) wj[k] = *(const f32x4 *)(s_w + 16 * j + 4 * k);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[j][e] *= wj[kShFold / 4][0];
+#pragma unroll
+                    for (int k = 0; k < kShFold; ++k)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[j][e] += wj[k >> 2][k & 3] * o[k][j][e];
+                }
             }
-            *(uint2 *)((unsigned short *)a.out + orow * 128 + 4 * ch) = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
-        } else {
-            const int64_t slot = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + it.kvh * G + (m - tok * G);
-            *(f32x4 *)(a.part_o + slot * 128 + 4 * ch) = acc;
-            if (ch == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(M, L);
+            s_w[ch] = sum16(l_lane);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (it.m0 + (tid >> 5) + 16 * j <= m_last) write_part(a, orow[j], ch, acc[j], s_w[16 * j]);
         }
     }
+
     for (int idx = tid; idx < n_append; idx += 64 * kShWaves) {
         if (idx != tid) put = fetch_new(idx);
         const int t = (P + a_begin + (idx >> 4)) & 15, ch = idx & 15;
@@ -356,10 +426,14 @@ hipError_t launch_attn_short_bf16(const Geom &g, const BatchDev &b, const AttnAr
     if (g.D != 128 || g.esize != 2) return hipErrorInvalidValue;
     static PerDeviceOnce configured;
     const hipError_t e = configured.run([] {
-        return hipFuncSetAttribute((const void *)attn_bf16_short_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
+        const hipError_t e0 = hipFuncSetAttribute((const void *)attn_bf16_short_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
+        return e0 != hipSuccess ? e0 : hipFuncSetAttribute((const void *)attn_bf16_short_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
     });
     if (e != hipSuccess) return e;
-    hipExtLaunchKernelGGL(attn_bf16_short_kernel, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a);
+    if (a.part_o)
+        hipExtLaunchKernelGGL(attn_bf16_short_kernel<true>, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a);
+    else
+        hipExtLaunchKernelGGL(attn_bf16_short_kernel<false>, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a);
     return hipGetLastError();
 }
 

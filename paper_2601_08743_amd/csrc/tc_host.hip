@@ -277,7 +277,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         h[at.seg_start + k] = segs[k].start; h[at.seg_len + k] = segs[k].len; h[at.seg_slot + k] = segs[k].slot;
     }
     put(at.stitch, sblk);
-    if (at.by_row && !p.decode) fill_part_tab(p, splits_of_q, h + at.part_tab);
+    if (at.part_tab_read) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
     put(at.groups, groups, at.merge_groups);
     put(at.rope_pos0, p.rope_pos0, p.rope);
@@ -300,7 +300,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     p.dev.seg_start = d + at.seg_start; p.dev.seg_len = d + at.seg_len; p.dev.seg_slot = d + at.seg_slot;
     p.dev.stitch_blk = (const StitchBlk *)(d + at.stitch);
-    if (at.by_row && !p.decode) {
+    if (at.part_tab_read) {
         p.dev.part_tab = d + at.part_tab;
         p.dev.part_stride = p.part_stride;
     }
@@ -311,6 +311,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.n_stitch_blk = (int32_t)sblk.size();
     p.items_dev = (const AttnItem *)(d + at.items);
     p.arrivals_dev = d_dst + at.arrivals;
+    p.arrival_stride = at.arrival_stride;
     p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
     p.fixed = fixed;
@@ -931,7 +932,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
-        a.arrivals = p.arrivals_dev;
+        a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
         a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
         return TC_OK;
@@ -943,6 +944,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.has_pads = p.block_pad.empty() ? 0 : 1;
     a.long_ranges = p.longest_range > kF32MaxTiles ? 1 : 0;
     a.part_o = p.part;
+    a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
     a.part_ml = !p.part ? nullptr
               : bf16 && !p.brief ? p.part + (size_t)p.n_part_slots * p.row_blocks * kAttnRows * 64
                      : p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
@@ -952,10 +954,9 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
              : bf16 ? launch_attn_bf16(ctx->geom, p.dev, a, p.row_blocks, p.pipelined, ln)
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
-    if (p.max_splits > 1)
+    if (p.max_splits > 1 && !p.brief)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
-            return p.brief ? launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, ln)
-                 : bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
+            return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
                         : launch_merge_f32(ctx->geom, p.dev, a, ln);
         }));
     return TC_OK;

@@ -19,7 +19,7 @@ constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
 constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item whose block ids are kept in LDS (those of longer ranges are fetched one by one)
 constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
-constexpr int kArrivalStride = 32;   // integers from one arrival counter to the next: a cache line each
+constexpr int kArrivalStride = 32, kArrivalStrideBig = 8;   // integers from one arrival counter to the next: a cache line each, in large plans a quarter of one
 
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
 // ids): the low 27 bits are the block id; the bits above count the unused token positions at the
@@ -86,9 +86,9 @@ struct AttnItem {
     int32_t tile_end;    // one past the last key tile
     int32_t split;       // which partition this is (0 when n_splits == 1)
     int32_t n_splits;    // partitions of this query
-    int32_t group;       // index of the (query, KV head, row tile); decode steps: arrival counter
+    int32_t group;       // index of the (query, KV head, row tile)
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
-    int32_t spare;       // (to 128 bytes)
+    int32_t arrival;     // which counter the work-groups of this group count themselves in at (decode and short-launch kernel, several partitions)
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
@@ -116,6 +116,7 @@ struct AttnArgs {
     int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
     int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches
+    int32_t arrival_stride;
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };
 
