@@ -191,7 +191,6 @@ struct Plan {
     int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, n_arrivals = 0, row_blocks = 1;
     int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
     int64_t n_part_slots = 0;   // partial slots of the batch: by (token, partition) in kernels that keep them by row, else by (row tile, partition)
-    int32_t part_stride = 0;    // and slots from token to token, 0: packed
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups
@@ -432,32 +431,21 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
 }
 
 // Where the split-KV partials of the fp32, decode and short-launch kernels stand.  They are kept by row: a slot, D + 2
-// floats for each query head, for every (suffix token, partition).  Where the queries have about as many
-// partitions each, every token has as many slots as the most it could need, so that the merge knows them without a
-// look into a table; where that would be more than twice the slots needed, or more than the workspace holds,
-// they are packed - a batch pays for the partitions that its queries have, not for its longest query's count
-// everywhere - and a query in one range has none (a decode step always has them).  Decode steps of one table each, 8 us
-// with the finish: 0.3 us less than packed.
+// floats for each query head, for every (suffix token, partition), packed: a batch pays for the partitions that its
+// queries have, not for its longest query's count everywhere, and a query in one range has none.
 // (The other bf16 kernels keep, per (cut row tile, partition, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.)
-inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, const std::vector<int32_t> &splits_of_q,
-                           std::vector<AttnItem> &items)
+inline void place_partials(Plan &p, const std::vector<int32_t> &splits_of_q, std::vector<AttnItem> &items)
 {
-    const int64_t even = (int64_t)p.max_splits * p.total_S;       // (n_part_slots: packed, so far)
-    if (!knobs.compact && even <= 2 * p.n_part_slots &&
-        (knobs.part_cap == 0 || (size_t)even * c.n_q_heads * (c.head_dim + 2) <= knobs.part_cap)) {
-        p.part_stride = p.max_splits;
-        p.n_part_slots = even;
-    }
     std::vector<int64_t> first(p.B);
     int64_t at = 0;
     for (int i = 0; i < p.B; ++i) {
-        first[i] = p.part_stride ? (int64_t)p.cu_seqlens[i] * p.part_stride : at;
+        first[i] = at;
         if (p.decode || splits_of_q[i] > 1) at += (int64_t)p.suffix_len[i] * splits_of_q[i];
     }
     for (AttnItem &it : items)
         if (it.q >= 0) {
             it.part0 = (int32_t)first[it.q];
-            it.part_stride = p.part_stride ? p.part_stride : it.n_splits;
+            it.part_stride = it.n_splits;
         }
 }
 
@@ -484,7 +472,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.brief = false;
     p.n_part_slots = 0;
     p.n_groups = p.n_arrivals = 0;
-    p.part_stride = 0;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
@@ -566,7 +553,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
         p.decode = true;
-        place_partials(c, knobs, p, splits_of_q, items);
+        place_partials(p, splits_of_q, items);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -671,8 +658,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // block ids of a range fit LDS (the fp32 kernel can fetch those that do not from memory, which is slower)
         const int cap = !bf16 ? (ctx->compact ? n_tiles : kF32MaxTiles) : pp ? kPpMaxTiles : general_cap;
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
-        // (the short-launch kernel addresses the partials of a row tile's tokens, up to 33, with 31 bits)
-        if (p.brief) ns = (int)std::min<int64_t>(ns, ((int64_t)1 << 31) / (33 * 512 * (int64_t)c.n_q_heads) - 1);
+        // (the partials by row of a row tile's tokens, up to 33, are addressed with 31 bits)
+        if (by_row) ns = (int)std::min<int64_t>(ns, ((int64_t)1 << 31) / (33 * 512 * (int64_t)c.n_q_heads) - 1);
         ns = std::max(1, std::min(ns, n_tiles));
         const int n_mt = (S * G + RT - 1) / RT;
         // Partition boundaries.  A suffix tile of the bf16 kernel costs about 4 prefix tiles (its V
@@ -723,7 +710,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     flat.push_back(proto);
                     flat.back().m0 = mt * RT;
                     flat.back().group = n_groups + mt;
-                    if (p.brief && ns > 1) flat.back().arrival = p.n_arrivals + mt;
+                    if (by_row && ns > 1) flat.back().arrival = p.n_arrivals + mt;
                     if (!by_row && ns > 1) flat.back().part0 = (int32_t)(p.n_part_slots + (int64_t)mt * ns);
                     ++bucket.count;
                     // (32-row tiles: eight, or four, of them share their keys' way into one L2, the next may go to
@@ -737,7 +724,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             }
             for (int mt = 0; mt < n_mt; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, (int32_t)(p.n_part_slots + (int64_t)mt * ns), {0, 0}});
             n_groups += n_mt;
-            if (p.brief && ns > 1) p.n_arrivals += n_mt;
+            if (by_row && ns > 1) p.n_arrivals += n_mt;
             if (!by_row && ns > 1) p.n_part_slots += (int64_t)n_mt * ns;
         }
     }
@@ -768,7 +755,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
     while (!items.empty() && items.back().q < 0) items.pop_back();
     p.n_items = (int32_t)items.size();
-    if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
+    if (by_row && p.max_splits > 1) place_partials(p, splits_of_q, items);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one
     // work-group per CU: nothing hides a work-group's start-up and drain.  It wins when a launch is a
     // single round of work-groups or when they are long; many short ones (measured: 1140 work-groups
@@ -816,28 +803,16 @@ inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the 
     return (size_t)p.n_part_slots * p.row_blocks * kAttnRows * (64 + 2);
 }
 
-// BatchDev::part_tab
-inline size_t part_tab_ints(const Plan &p) { return (size_t)p.total_S + (p.part_stride == 0); }
-inline void fill_part_tab(const Plan &p, const std::vector<int32_t> &splits_of_q, int32_t *out)
-{
-    int32_t at = 0;
-    for (int i = 0; i < p.B; ++i) {
-        const int32_t count = p.decode || splits_of_q[i] > 1 ? splits_of_q[i] : 0;
-        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += count) out[n] = p.part_stride ? count : at;
-    }
-    if (!p.part_stride) out[p.total_S] = at;
-}
-
 constexpr size_t kBigPlanInts = size_t(1) << 18;    // 1 MiB: in larger plans the arrival counters stand closer together
 
 // Where the parts of a plan stand in its device copy, in integers; only what the batch's kernels read
 // is there (`n_*`: how many of each).
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
-    size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
+    size_t block_table, cu, prefix, suffix, tok_q, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
-    bool lengths = false, tokens = false, part_tab_read = false, merge_groups = false;
+    bool lengths = false, tokens = false, merge_groups = false;
     int arrival_stride = kArrivalStride;
 };
 inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
@@ -848,7 +823,6 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     auto take = [&](size_t n) { const size_t o = l.total; l.total += (n + 7) & ~size_t(7); return o; };
     l.tokens = !p.decode && !p.pingpong && !p.brief;             // appended token by token, in extra work-groups
     l.lengths = l.tokens || n_stitch > 0;
-    l.part_tab_read = c.dtype != TC_BF16 && p.max_splits > 1;    // (the decode and short-launch kernels' partials come with their items)
     l.merge_groups = p.max_splits > 1 && !parts_by_row(c, p);
     // rows are padded to whole 16-byte chunks: the decode and short-launch kernels fetch them so, the long-launch
     // kernel where it can
@@ -858,7 +832,6 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.cu = take(l.tokens ? B + 1 : 0); l.suffix = take(l.tokens ? B : 0); l.tok_q = take(l.tokens ? p.total_S : 0);
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
-    l.part_tab = take(l.part_tab_read ? part_tab_ints(p) : 0);
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
     if (l.total + (size_t)p.n_arrivals * kArrivalStride > kBigPlanInts) l.arrival_stride = kArrivalStrideBig;

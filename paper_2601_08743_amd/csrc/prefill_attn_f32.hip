@@ -17,10 +17,14 @@
 // O^T += V^T . P^T for the key pair that its two lane halves stand for; V is read from its token rows
 // D/32 neighbouring columns at a time.
 //
-// Measured (8 queries, 23 k prefix and 1.4 k suffix tokens, 8 query / 2 KV heads of 64: 8.3 GFLOP): 102 us
-// + 4.5 us merge; one wave per row with v_fma_f32, keys from LDS one float at a time, values straight from
-// the pool, took 1049 us.  A batch long enough to drown its edges runs at 112 TFLOP/s (a 4096^3 library
-// product: 140).  One query of 731 + 64 tokens: 11 + 4.5 us, before 28 + 4 us and an append launch.
+// A query in several ranges: the last of a row tile's ranges to end combines their partials (arrive.h).
+//
+// Measured (8 queries, 23 k prefix and 1.4 k suffix tokens, 8 query / 2 KV heads of 64: 8.3 GFLOP): 109 us a layer with
+// the ranges combined (110 with a launch of its own for that: 102 + 4.5 us and the gap between them); one wave per row
+// with v_fma_f32, keys from LDS one float at a time, values straight from the pool, took 1049 us.  A batch long enough
+// to drown its edges runs at 112 TFLOP/s (a 4096^3 library product: 140).  A whole pass over one query of 731 + 64 tokens:
+// 30.5 us with two launches, 29.1 with one.
+#include "arrive.h"
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
@@ -269,12 +273,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         if (hh == 0) { wo[32 * L::kRow + 2 * r32] = m_run; wo[32 * L::kRow + 2 * r32 + 1] = l_row_sum; }
     }
     __syncthreads();
-#pragma unroll 2
-    for (int idx = tid; idx < kF32Rows * kChunks; idx += 256) {
-        const int r = idx / kChunks, d4 = idx - r * kChunks;
-        const int mr = it.m0 + r;
-        if (mr >= n_rows) continue;
-        float M = -INFINITY, sum = 0.f;
+    constexpr int kPass = 256 / kChunks, kPasses = kF32Rows / kPass;      // rows at a time
+    const int r0 = tid / kChunks, d4 = tid % kChunks;
+    auto fold_waves = [&](int r, float &M, float &sum) {                // four columns of a row of this range
+        M = -INFINITY;
+        sum = 0.f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * L::kWave))[32 * L::kRow + 2 * r]);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -288,19 +291,87 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, v[e], acc[e]);
         }
-        const int tok = mr / G;
-        const int64_t orow = (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (mr - tok * G);
-        if (it.n_splits == 1) {
-            const float inv = 1.f / sum;
+        return acc;
+    };
+    auto write = [&](int mr, f32x4 acc, float sum) {
+        const float inv = 1.f / sum;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] *= inv;
-            *(f32x4 *)((float *)a.out + orow * D + 4 * d4) = acc;
-        } else {
-            const int64_t prow = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + it.kvh * G + (mr - tok * G);
-            *(f32x4 *)(a.part_o + prow * D + 4 * d4) = acc;
-            if (d4 == 0) { a.part_ml[prow * 2] = M; a.part_ml[prow * 2 + 1] = sum; }
+        for (int e = 0; e < 4; ++e) acc[e] *= inv;
+        const int tok = mr / G;
+        *(f32x4 *)((float *)a.out + ((int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (mr - tok * G)) * D + 4 * d4) = acc;
+    };
+    if (it.n_splits == 1) {
+#pragma unroll 2
+        for (int r = r0; r < kF32Rows; r += kPass) {
+            if (it.m0 + r >= n_rows) continue;
+            float M, sum;
+            const f32x4 acc = fold_waves(r, M, sum);
+            write(it.m0 + r, acc, sum);
+        }
+        return;
+    }
+
+    // ---- a range of several: its partial, and by the last work-group of the row tile to end the rows from all of them (arrive.h):
+    // with reference maxima m_s (log2 units), sums l_s and unnormalised outputs O_s, sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+    // All of a thread's rows at a time, four partials a round trip.
+    const int tok0 = it.m0 / G, m_last = min(it.m0 + kF32Rows, n_rows) - 1, ns = it.n_splits;
+    const int64_t first_slot = ((int64_t)it.part0 + (int64_t)tok0 * it.part_stride) * g.Hq + it.kvh * G;
+    const uint32_t n_slots = (uint32_t)min((int64_t)(m_last / G - tok0 + 1) * it.part_stride * g.Hq, (int64_t)(0x7fffffff / (D * 4)));
+    const SharedPart part_o(a.part_o + first_slot * D, n_slots * (D * 4)), part_ml(a.part_ml + first_slot * 2, n_slots * 8);
+    uint32_t slot[kPasses];
+#pragma unroll
+    for (int j = 0; j < kPasses; ++j) {
+        const int r = r0 + j * kPass, mr = min(it.m0 + r, m_last), tok = mr / G;
+        slot[j] = (uint32_t)((tok - tok0) * it.part_stride * g.Hq + mr - tok * G);
+        if (it.m0 + r > m_last) continue;
+        float M, sum;
+        const f32x4 acc = fold_waves(r, M, sum);
+        const uint32_t at = slot[j] + it.split * g.Hq;
+        part_o.put4(at * (D * 4) + d4 * 16, acc);
+        if (d4 == 0) part_ml.put2(at * 8, M, sum);
+    }
+    if (!last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, ns, s_bid)) return;
+    constexpr int kBatch = 4;
+    float M[kPasses], den[kPasses];
+    f32x4 acc[kPasses];
+#pragma unroll
+    for (int j = 0; j < kPasses; ++j) { M[j] = -INFINITY; den[j] = 0.f; acc[j] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int s0 = 0; s0 < ns; s0 += kBatch) {
+        float2 ml[kPasses][kBatch];
+        f32x4 po[kPasses][kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+            for (int j = 0; j < kPasses; ++j) {
+                const uint32_t at = slot[j] + (s0 + k) * g.Hq;
+                ml[j][k] = part_ml.get2(s0 + k < ns ? at * 8 : kNowhere);
+                po[j][k] = part_o.get4(s0 + k < ns ? at * (D * 4) + d4 * 16 : kNowhere);
+            }
+#pragma unroll
+        for (int j = 0; j < kPasses; ++j) {
+            float Mc = M[j];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) Mc = s0 + k < ns ? fmaxf(Mc, ml[j][k].x) : Mc;
+            const float r = M[j] == -INFINITY ? 0.f : exp2f(M[j] - Mc);
+            den[j] *= r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[j][e] *= r;
+            M[j] = Mc;
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                if (s0 + k >= ns) continue;
+                // a partition without a maximum saw no key of this row (sum and output are 0) or only scores that are NaN
+                // (so are they, and so is the row)
+                const float wgt = ml[j][k].x == -INFINITY ? 1.f : exp2f(ml[j][k].x - Mc);
+                den[j] = fmaf(wgt, ml[j][k].y, den[j]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(wgt, po[j][k][e], acc[j][e]);
+            }
         }
     }
+#pragma unroll
+    for (int j = 0; j < kPasses; ++j)
+        if (it.m0 + r0 + j * kPass <= m_last) write(it.m0 + r0 + j * kPass, acc[j], den[j]);
 }
 
 template <int D, bool kLong>
@@ -321,83 +392,6 @@ hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, 
     if (g.D == 64) return a.long_ranges ? launch_attn<64, true>(g, b, a, L) : launch_attn<64, false>(g, b, a, L);
     if (g.D == 128) return a.long_ranges ? launch_attn<128, true>(g, b, a, L) : launch_attn<128, false>(g, b, a, L);
     return hipErrorInvalidValue;
-}
-
-// ------------------------------------------------------------------------------------ merge
-// Combine split-KV partials of one output row: with reference maxima m_s (log2 units), sums l_s
-// and unnormalised partial outputs O_s:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// D/4 threads per (suffix token, head) row, four columns each.  Bound: the latency of the loads of a
-// short launch, so those of eight partitions are issued before the first use, and (kEven) before it is known how
-// many there are (slots beyond a token's last partition are loaded and ignored).
-// Measured (2 queries, 9 k keys, 2 + 59 tokens, 20 partitions): 5.3 us; one partition after the other 18.4 us.
-template <int D, bool kEven>
-__global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, AttnArgs a)
-{
-    constexpr int kThreads = D / 4;
-    constexpr int kBatch = 8;
-    const int64_t row = (int64_t)blockIdx.x * (256 / kThreads) + threadIdx.x / kThreads;
-    const int d = 4 * (threadIdx.x % kThreads);
-    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
-    if (row >= n_rows) return;
-    const int n = (int)(row / g.Hq), head = (int)(row - (int64_t)n * g.Hq);
-    const PartSlots slots = part_slots<kEven>(b, n);
-    if (!kEven && slots.count <= 1) return;      // written directly by the attention kernel
-    float2 ml[kBatch];
-    f32x4 po[kBatch];
-    auto fetch = [&](int s0) {
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int64_t slot = (int64_t)min(slots.first + s0 + j, slots.last) * g.Hq + head;
-            ml[j] = *(const float2 *)(a.part_ml + slot * 2);
-            po[j] = *(const f32x4 *)(a.part_o + slot * D + d);
-        }
-    };
-    fetch(0);
-    const int ns = slots.count;
-    if (kEven && ns <= 1) return;
-    float M = -INFINITY, den = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < ns; s0 += kBatch) {
-        if (s0 > 0) fetch(s0);
-        float Mc = M;
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) Mc = s0 + j < ns ? fmaxf(Mc, ml[j].x) : Mc;
-        const float r = M == -INFINITY ? 0.f : exp2f(M - Mc);
-        den *= r;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] *= r;
-        M = Mc;
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (s0 + j >= ns) continue;
-            // a partition without a maximum saw no key of this row (sum and output are 0) or only scores that are NaN
-            // (so are they, and so is the row)
-            const float wgt = ml[j].x == -INFINITY ? 1.f : exp2f(ml[j].x - M);
-            den = fmaf(wgt, ml[j].y, den);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, po[j][e], acc[e]);
-        }
-    }
-    const float inv = 1.f / den;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] *= inv;
-    *(f32x4 *)((float *)a.out + row * D + d) = acc;
-}
-
-hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
-{
-    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
-    if (n_rows == 0) return hipSuccess;
-    if (!b.part_tab) return hipErrorInvalidValue;
-    const int per = 256 / (g.D / 4);
-    const int grid = (int)((n_rows + per - 1) / per);
-    const bool even = b.part_stride > 0;
-    if (g.D == 64 && even) TC_LAUNCH((merge_f32_kernel<64, true>), grid, 0, L, g, b, a);
-    else if (g.D == 64) TC_LAUNCH((merge_f32_kernel<64, false>), grid, 0, L, g, b, a);
-    else if (g.D == 128 && even) TC_LAUNCH((merge_f32_kernel<128, true>), grid, 0, L, g, b, a);
-    else if (g.D == 128) TC_LAUNCH((merge_f32_kernel<128, false>), grid, 0, L, g, b, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
 }
 
 }  // namespace tc

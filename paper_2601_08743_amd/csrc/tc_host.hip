@@ -277,7 +277,6 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         h[at.seg_start + k] = segs[k].start; h[at.seg_len + k] = segs[k].len; h[at.seg_slot + k] = segs[k].slot;
     }
     put(at.stitch, sblk);
-    if (at.part_tab_read) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
     put(at.groups, groups, at.merge_groups);
     put(at.rope_pos0, p.rope_pos0, p.rope);
@@ -300,10 +299,6 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     }
     p.dev.seg_start = d + at.seg_start; p.dev.seg_len = d + at.seg_len; p.dev.seg_slot = d + at.seg_slot;
     p.dev.stitch_blk = (const StitchBlk *)(d + at.stitch);
-    if (at.part_tab_read) {
-        p.dev.part_tab = d + at.part_tab;
-        p.dev.part_stride = p.part_stride;
-    }
     p.dev.rope_pos0 = p.rope ? d + at.rope_pos0 : nullptr;
     p.dev.rope_rev_freq = p.rope ? (const double *)(d + at.rope_freq) : nullptr;
     p.dev.B = p.B; p.dev.max_blocks = (int32_t)at.bt_row; p.dev.total_S = p.total_S;
@@ -954,10 +949,9 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
              : bf16 ? launch_attn_bf16(ctx->geom, p.dev, a, p.row_blocks, p.pipelined, ln)
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
-    if (p.max_splits > 1 && !p.brief)
+    if (p.groups_dev)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
-            return bf16 ? launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln)
-                        : launch_merge_f32(ctx->geom, p.dev, a, ln);
+            return launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln);
         }));
     return TC_OK;
 }

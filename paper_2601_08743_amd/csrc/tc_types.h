@@ -66,9 +66,6 @@ struct BatchDev {
     const int32_t *seg_len;       // [n_seg]
     const int32_t *seg_slot;      // [n_seg] table slot holding the segment's table
     const StitchBlk *stitch_blk;  // [n_stitch_blk]
-    const int32_t *part_tab;      // kernels that keep partials by row (else null): [sum S] partitions of each suffix token where
-                                  // slots are evenly spaced, [sum S + 1] first slot of each where they are packed
-    int32_t part_stride;          // slots from token to token, 0: packed
     const int32_t *tok_q;         // [sum S] query index of each suffix token
     const int32_t *rope_pos0;     // [B] position of each query's first schema token (re-encoding stitch), else null
     const double *rope_rev_freq;  // [D/2] theta^(-2i/D) / (2 pi): revolutions per position step, else null
@@ -88,7 +85,7 @@ struct AttnItem {
     int32_t n_splits;    // partitions of this query
     int32_t group;       // index of the (query, KV head, row tile)
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
-    int32_t arrival;     // which counter the work-groups of this group count themselves in at (decode and short-launch kernel, several partitions)
+    int32_t arrival;     // which counter the work-groups of this group count themselves in at (kernels that keep partials by row, several partitions)
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
