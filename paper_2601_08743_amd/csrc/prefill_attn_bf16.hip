@@ -1047,7 +1047,9 @@ hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup 
 {
     if (n_groups == 0) return hipSuccess;
     const int n_rb = 4 * row_blocks;                   // 32-row blocks per group
-    const bool few = n_groups * n_rb <= 512;
+    // (a CU's worth of row blocks each: with 416 of them, four partitions, four re-encoded queries take 42.7 us a layer with
+    // one fragment a wave, 41.7 with four; with 1536 one fragment is 5 % of the whole layer slower)
+    const bool few = n_groups * n_rb <= 256;
     const int grid = few ? n_groups * n_rb * 4 : n_groups * n_rb;
     if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4>), grid, 0, L, g, a, groups, n_rb);
     else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8>), grid, 0, L, g, a, groups, n_rb);
