@@ -139,22 +139,30 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
         const char *src = pool_l + (int64_t)entry_bid(__builtin_amdgcn_readfirstlane(bid_next)) * bb;
         const uint32_t kd = lds0 + (t % kPpKBufs) * kPpTile + j_blk * 4096;
         const uint32_t vd = lds0 + kPpV + (t % kPpVBufs) * kPpTile + j_blk * 4096;
-        if (!all_pool && p0 + kBlockTokens > P) {
+        if (!all_pool && p0 >= P) {
+            const int t0 = min(p0 - P, S - 1), t_last = S - 1 - t0;       // the block's first token, and how many the suffix has behind it
+            const char *k_rows = new_k + (int64_t)t0 * g.row_bytes, *v_rows = new_v + (int64_t)t0 * g.row_bytes + (w & 1) * 128;
+#pragma unroll
+            for (int i = i0; i < i0 + 2; ++i) {
+                const int rb = 4 * i + (lane >> 4);
+                load_to_lds(kd + i * 1024, k_rows, min(rb, t_last) * g.row_bytes + (((lane & 15) ^ rb) * 16));
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                load_to_lds(vd + (i0 + i) * 1024, v_rows, min(8 * i + (lane >> 3), t_last) * g.row_bytes + (lane & 7) * 16);
+        } else if (!all_pool && p0 + kBlockTokens > P) {
 #pragma unroll
             for (int i = i0; i < i0 + 2; ++i) {
                 const int rb = 4 * i + (lane >> 4), c16 = ((lane & 15) ^ rb) * 16, tok = p0 + rb - P;
                 load_to_lds_each(kd + i * 1024, tok < 0 ? src + rb * 256 + c16 : new_k + (int64_t)min(tok, S - 1) * g.row_bytes + c16);
             }
-            const bool shared = p0 < P;
-            if (shared)
 #pragma unroll
-                for (int i = i0; i < i0 + 2; ++i)
-                    load_to_lds(vd + i * 1024, src + v_half + i * 1024, (2 * (lane & 31) + (lane >> 5)) * 16);
-            const uint32_t rows = shared ? lds_new : vd + i0 * 1024;
+            for (int i = i0; i < i0 + 2; ++i)
+                load_to_lds(vd + i * 1024, src + v_half + i * 1024, (2 * (lane & 31) + (lane >> 5)) * 16);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int tok = min(max(p0 + 8 * i + (lane >> 3) - P, 0), S - 1);
-                load_to_lds_each(rows + i * 1024, new_v + (int64_t)tok * g.row_bytes + (w & 1) * 128 + (lane & 7) * 16);
+                load_to_lds_each(lds_new + i * 1024, new_v + (int64_t)tok * g.row_bytes + (w & 1) * 128 + (lane & 7) * 16);
             }
         } else {
 #pragma unroll
