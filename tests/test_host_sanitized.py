@@ -469,3 +469,30 @@ def test_front_end_equals_the_checker(exe):
         got = [tuple(map(int, l.split()[1:])) for l in out[at + 1:at + 1 + len(steps)]]
         assert got == [tuple(st) for st in steps]
         at += 1 + len(steps)
+
+
+def test_long_launch_ranges_go_by_each_query(exe):
+    """One range length for the batch: a query has as many ranges as it takes, so long ones have more; batches that a cut
+    does not promise 5 % stay whole; and the items placed longest first on 256 CUs end no later than uncut."""
+    def ends(items):                                     # 7.8 us an item, 1.32 a key tile
+        free = [0.0] * 256
+        import heapq
+        for n in sorted((it[4] - it[3] for it in items if it[0] >= 0), reverse=True):
+            heapq.heapreplace(free, free[0] + 7.8 + 1.32 * n)
+        return max(free)
+
+    rng = np.random.default_rng(29)
+    ragged = 0
+    for _ in range(40):
+        PS = [(int(rng.integers(200, 5000)), 128) for _ in range(int(rng.integers(2, 12)))]
+        info, items = _plan(exe, 40, 8, PS, kernel=4)
+        _check_plan(info, items, 40, 8, PS)
+        whole, uncut = _plan(exe, 40, 8, PS, kernel=4, splits=1)
+        ns = {it[0]: it[6] for it in items if it[0] >= 0}
+        order = sorted(ns, key=lambda q: PS[q][0])
+        assert all(ns[a] <= ns[b] for a, b in zip(order, order[1:]))
+        assert ends(items) <= ends(uncut) + 1e-6
+        ragged += len(set(ns.values())) > 1
+    assert ragged >= 10
+    info, items = _plan(exe, 28, 4, [(1500, 250)] * 60, kernel=4)      # many even items: nothing to gain
+    assert info["max_splits"] == 1
