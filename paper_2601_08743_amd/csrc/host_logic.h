@@ -194,6 +194,7 @@ struct Plan {
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups
+    bool part_f32 = false;      // partials in fragment order are fp32 (the long-launch kernel's, by a rule of the planner), else fp16
     bool compact = false;       // planned for the least space (a batch that did not fit the static workspace otherwise)
     bool brief = false;         // bf16, 32 rows per work-group, its waves split the keys: the short-launch kernel
     bool rope = false;          // the stitch re-encodes keys by position (Sec. 4.1.1)
@@ -330,15 +331,18 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
 // work-group (co-resident work-groups overlap each other's stalls: x0.7); plus a fixed start-up
 // and epilogue cost; plus the merge: a launch and the partials written and read back at about
 // 4 TB/s.  Fitted to split-count sweeps and per-work-group traces on c2, c3 and c5-sized batches.
+// `long_launch`: the same question for the long-launch kernel (one work-group per CU; uncut items differ in length, start
+// longest first and end together rather than in rounds), which goes by plan_long but by this for the type of its partials.
 struct GeneralPlan { int splits = 1; double us = 1e30; };
-inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
+inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap, bool long_launch = false)
 {
     const int G = c.n_q_heads / c.n_kv_heads;
     int64_t base = 0, tiles_sum = 0, n_q = 0;
     for (int i = 0; i < p.B; ++i)
         if (p.suffix_len[i] > 0) {
             base += (int64_t)c.n_kv_heads * ((p.suffix_len[i] * G + row_tile - 1) / row_tile);
-            tiles_sum += (p.prefix_len[i] + key_tile - 1) / key_tile + (p.suffix_len[i] + key_tile - 1) / key_tile;
+            tiles_sum += long_launch ? ((int64_t)p.prefix_len[i] + p.suffix_len[i] + key_tile - 1) / key_tile
+                                     : (p.prefix_len[i] + key_tile - 1) / key_tile + (p.suffix_len[i] + key_tile - 1) / key_tile;
             ++n_q;
         }
     GeneralPlan out;
@@ -351,9 +355,9 @@ inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile,
         if (ns > 1 && tiles / ns < 2.0) break;
         if (ns > 1 && part_cap > 0 && (double)ns * base * row_tile * (64 + 2) > (double)part_cap) break;
         const double load = std::ceil((double)n_q * c.n_kv_heads * ns / 8.0) * items_per_bucket / 32.0;
-        const double per_cu = load <= 1.0 ? 1.0 : load <= 2.0 ? 2.0 : load;
+        const double per_cu = load <= 1.0 ? 1.0 : load <= 2.0 && !(long_launch && ns == 1) ? 2.0 : load;
         const double merge = ns > 1 ? 1.0 + 0.93e-4 * ns * rows : 0.0;   // fp16 partials: 264 B per row and partition
-        const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 ? 0.7 : 1.0) + 3.0 + merge;
+        const double cost = per_cu * (tiles / ns) * (per_cu >= 2.0 && !long_launch ? 0.7 : 1.0) + 3.0 + merge;
         if (cost < best - 1e-9) {
             best = cost;
             out.splits = ns;
@@ -377,7 +381,7 @@ inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile,
 // (With one partition count for all, taken from a batch's mean length: 11 % behind it; micro-batches of eight queries of
 // 1 .. 5 k + 128 tokens, 40 / 8 heads, 100 .. 107 us against 80 .. 90.)
 struct LongPlan { int range = 0; double us = 1e30; };
-inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
+inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap, bool part_f32)
 {
     constexpr int kCus = 256;
     constexpr int64_t kItem = 780, kTile = 132;          // 1/100 us
@@ -409,8 +413,8 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
             total += q.count * (ns * kItem + q.tiles * kTile);
             if (ns > 1) { cut_rows += q.rows * ns; cut_tiles += q.count * ns; }
         }
-        if (part_cap > 0 && (double)cut_tiles * row_tile * (64 + 2) > (double)part_cap) continue;
-        const double merge = cut_rows > 0 ? 1.8 + 0.74e-4 * (double)cut_rows : 0.0;
+        if (part_cap > 0 && (double)cut_tiles * row_tile * ((part_f32 ? 128 : 64) + 2) > (double)part_cap) continue;
+        const double merge = cut_rows > 0 ? 1.8 + (part_f32 ? 1.45e-4 : 0.74e-4) * (double)cut_rows : 0.0;
         std::sort(parts.begin(), parts.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
         if (3.0 + merge + 0.01 * (double)std::max(total / kCus, kItem + parts[0].first * kTile) >= (uncut > 0.0 ? std::min(best.us, 0.95 * uncut) : best.us)) continue;
         cus.assign(1, {0, kCus});
@@ -433,7 +437,8 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
 // Where the split-KV partials of the fp32, decode and short-launch kernels stand.  They are kept by row: a slot, D + 2
 // floats for each query head, for every (suffix token, partition), packed: a batch pays for the partitions that its
 // queries have, not for its longest query's count everywhere, and a query in one range has none.
-// (The other bf16 kernels keep, per (cut row tile, partition, row block), 128 rows x (128 fp16 + 2 floats) in fragment order.)
+// (The other bf16 kernels keep, per (cut row tile, partition, row block), 128 rows x (128 fp16 + 2 floats)
+// in fragment order, or 128 fp32.)
 inline void place_partials(Plan &p, const std::vector<int32_t> &splits_of_q, std::vector<AttnItem> &items)
 {
     std::vector<int64_t> first(p.B);
@@ -468,7 +473,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     const bool bf16 = c.dtype == TC_BF16;
     const int KT = bf16 ? kAttnKeys : kF32Keys;
     p.decode = false;
-    p.pingpong = false;
+    p.pingpong = p.part_f32 = false;
     p.brief = false;
     p.n_part_slots = 0;
     p.n_groups = p.n_arrivals = 0;
@@ -567,10 +572,24 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // the pipelined one.  The line is at 6 / 5, included, because five 128-row tiles that make three of 256 rows (40 / 8 heads,
     // 128 new tokens: the micro-batches of a cold cache) gain: 40 of those 1.085 times as fast as in the other kernels with
     // one partition count for all their queries, and another 1.1 .. 1.35 with plan_long's.
-    // Shorter launches take it where plan_long puts it 15 % below both of the others' models, 25 % where rows are padded by more
-    // than that: on average 1.2 times as fast, a few 4 .. 7 % slower; one query of 4.6 k + 128 tokens, 40 / 8 heads, 25 us
-    // against 33.
-    bool pp = false;
+    // Shorter launches take it where plan_long puts it 15 % below the general and the pipelined kernel's model, 25 % where rows
+    // are padded by more than that; what the short-launch kernel would take stays there, whose softmax weights, over eight
+    // times as many key ranges, and partials lose less to rounding.
+    //
+    // The type of its partials (`wide`: fp32).  This kernel cuts queries that the others, or one partition count for the batch,
+    // leave whole: those stay in fp32 to the end.  Where the batch's queries would be cut with fp16 partials in any case, they
+    // are fp16 here as well: fp32 ones are twice the traffic (70 batches of 14 .. 300 us, 60 of 4 .. 14 us: 2.5 % slower on
+    // average, 17 % at most, with fp32 in all of them).
+    bool pp = false, wide = false;
+    const bool any = p.total_S > 0, free_cut = any && !ctx->compact && ctx->forced_splits == 0;
+    GeneralPlan general;
+    BriefPlan brief;
+    LongPlan lng;
+    auto plan_others = [&] {
+        general = plan_general(c, p, kAttnRows, KT, ctx->part_cap);
+        if (ctx->short_rows > 0) brief = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles);
+    };
+    auto brief_wins = [&] { return brief.us < 0.85 * general.us; };      // (by more than the two models are unsure)
     if (bf16 && ctx->forced_row_blocks == 0) {
         if (ctx->forced_attn_kernel == 4) pp = true;
         else if (ctx->forced_attn_kernel == 0) {
@@ -584,14 +603,22 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             const double us = (double)work * 0.85 / 256.0;
             pp = us >= 80.0 || (!ctx->compact && us >= 14.0 && 5 * work_pp <= 6 * work);
             if (!pp && !ctx->compact && us >= 4.0 && us < 14.0) {
-                double others = plan_general(c, p, kAttnRows, KT, ctx->part_cap).us;
-                if (ctx->short_rows > 0) others = std::min(others, plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).us);
-                pp = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap).us < (5 * work_pp <= 6 * work ? 0.85 : 0.75) * others;
+                plan_others();
+                if (!brief_wins()) {
+                    wide = free_cut && general.splits == 1;
+                    lng = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap, wide);
+                    pp = lng.us < (5 * work_pp <= 6 * work ? 0.85 : 0.75) * std::min(general.us, brief.us);
+                }
             }
+        }
+        if (pp && free_cut && lng.range == 0) {
+            wide = plan_general(c, p, 2 * kAttnRows, KT, ctx->part_cap, true).splits == 1;
+            lng = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap, wide);
         }
     }
     const bool unified = !bf16 || pp;
     p.pingpong = pp;
+    p.part_f32 = pp && wide;
     auto tiles_of = [&](int P, int S) {
         return unified ? (P + S + KT - 1) / KT : (P + KT - 1) / KT + (S + KT - 1) / KT;
     };
@@ -600,31 +627,28 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     const int rb = pp ? 2 : (bf16 && ctx->forced_row_blocks > 0) ? ctx->forced_row_blocks : 1;
     p.row_blocks = rb;
     int RT = bf16 ? kAttnRows * rb : kF32Rows;
-    const bool any = p.total_S > 0;
     int want = 1, cut_range = 0;           // (cut_range: the length of a range in key tiles, where the queries are cut by that)
     if (ctx->forced_splits > 0) want = ctx->forced_splits;
     else if (ctx->compact) want = 1;
     else if (!bf16 && any) cut_range = plan_f32_range(c, p, RT, KT, ctx->part_cap);
-    else if (pp && any) cut_range = plan_long(c, p, RT, KT, ctx->part_cap).range;
+    else if (pp && any) cut_range = lng.range;
     else if (any) {
-        const GeneralPlan general = plan_general(c, p, RT, KT, ctx->part_cap);
+        if (rb != 1) general = plan_general(c, p, RT, KT, ctx->part_cap);
+        else if (general.us == GeneralPlan{}.us) plan_others();
         want = general.splits;
         // The short-launch kernel, where it is faster by more than the two models are unsure: of the batches that they
         // were fitted to it takes 451 of 740 and loses time in 8; over all 740 the call is 1.21 times as fast (1.24
         // if the faster kernel were known each time).  28 / 4 heads: one query of 1.1 k + 17 tokens 10.4 us against
         // 14.5; eight of 1 k + 17: 13 against 24; but one of 4.1 k + 128, whose rows fill 128-row tiles and
         // whose keys 32-row tiles would read four times as often, 25 against 22.
-        if (!pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 0) {
-            const BriefPlan b = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles);
-            if (b.us < 0.85 * general.us) {
-                p.brief = true;
-                cut_range = b.range;
-            }
+        if (ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 0 && brief_wins()) {
+            p.brief = true;
+            cut_range = brief.range;
         }
     }
     if (bf16 && !pp && ctx->short_rows > 0 && ctx->forced_row_blocks == 0 && ctx->forced_attn_kernel == 5) {
         p.brief = true;
-        if (ctx->forced_splits == 0 && !ctx->compact) cut_range = plan_brief(c, p, ctx->short_rows, KT, kAttnMaxTiles).range;
+        if (ctx->forced_splits == 0 && !ctx->compact) cut_range = brief.range;
         want = std::max(1, ctx->forced_splits);
     }
     if (p.brief) {
@@ -797,10 +821,12 @@ inline bool plan_attention(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
 
 inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode || ((c.dtype != TC_BF16 || p.brief) && p.max_splits > 1); }
 
+inline int part_row_floats(const Plan &p) { return p.part_f32 ? 128 : 64; }      // a row's partial in fragment order, without its (maximum, sum)
+
 inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the batch's partials, in floats
 {
     if (parts_by_row(c, p)) return (size_t)p.n_part_slots * c.n_q_heads * (c.head_dim + 2);
-    return (size_t)p.n_part_slots * p.row_blocks * kAttnRows * (64 + 2);
+    return (size_t)p.n_part_slots * p.row_blocks * kAttnRows * (part_row_floats(p) + 2);
 }
 
 constexpr size_t kBigPlanInts = size_t(1) << 18;    // 1 MiB: in larger plans the arrival counters stand closer together

@@ -40,6 +40,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kKRow = 272;                       // LDS bytes per K row: 256 + 16 pad (conflict-free b128 reads)
 constexpr int kHeadBlk = 4096;                   // bytes of one head's K (or V) in one block: 16 * 128 * 2
@@ -933,7 +934,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
 
 // Combine the partitions of split queries.  A wave takes kFrags of the 16 accumulator fragments of one
 // 32-row block of a group, in the order the attention kernel stored them (512 contiguous bytes per
-// fragment), and each row's (maximum, sum) once for all of them.  Bound: the latency of a short launch,
+// fp16 fragment, 1 KB per fp32 one), and each row's (maximum, sum) once for all of them.  Bound: the latency of a short launch,
 // so the loads of kBatch partitions are issued before the first use; with few row blocks a wave
 // takes one fragment and up to 16 partitions at a time (one round trip), with many it takes four
 // fragments, which reads the (maximum, sum) pairs a quarter as often.  kBatch follows the batch's
@@ -942,7 +943,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_pipe_kernel(Geom g, BatchDev
 // Measured (28 / 4 heads; in events that read 4.0 us for an empty launch): 12 queries of 3.3 k keys and 72 new
 // tokens, 2 partitions: 8.7 us, with one fragment per thread and eight partitions always 16.2 us; one query
 // of 17 new tokens, 9 partitions: 4.6 us against 5.2; one of 128, 8 partitions: 4.3 either way.
-template <int kFrags, int kBatch>
+template <int kFrags, int kBatch, typename Frag>
 __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, const MergeGroup *groups,
                                                          int n_rb)
 {
@@ -960,14 +961,14 @@ __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, con
 #pragma unroll
     for (int e = 0; e < 4 * kFrags; ++e) acc[e] = 0.f;
     for (int s0 = 0; s0 < n_splits; s0 += kBatch) {
-        f16x4 v[kBatch][kFrags];
+        Frag v[kBatch][kFrags];
         float2 ml[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int64_t sb = (int64_t)(part0 + min(s0 + k, n_splits - 1)) * n_rb + blk;
             ml[k] = ((const float2 *)a.part_ml)[sb * 32 + r32];
 #pragma unroll
-            for (int f = 0; f < kFrags; ++f) v[k][f] = ((const f16x4 *)a.part_o)[(sb * 16 + frag0 + f) * 64 + lane];
+            for (int f = 0; f < kFrags; ++f) v[k][f] = ((const Frag *)a.part_o)[(sb * 16 + frag0 + f) * 64 + lane];
         }
         float Mc = M;
 #pragma unroll
@@ -980,16 +981,16 @@ __global__ __launch_bounds__(256) void merge_bf16_kernel(Geom g, AttnArgs a, con
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             // beyond the last partition stands the last one again: a weight of zero, and no values, for its infinities
-            // times zero would be NaN (two words a fragment)
+            // times zero would be NaN (selected word by word)
             const bool there = s0 + k < n_splits;
             const float wgt = there && ml[k].x != -INFINITY ? __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y : 0.f;
             l += wgt;
 #pragma unroll
             for (int f = 0; f < kFrags; ++f) {
-                union { f16x4 h; uint32_t w[2]; } x;
+                union { Frag h; uint32_t w[sizeof(Frag) / 4]; } x;
                 x.h = v[k][f];
-                x.w[0] = there ? x.w[0] : 0u;
-                x.w[1] = there ? x.w[1] : 0u;
+#pragma unroll
+                for (unsigned i = 0; i < sizeof(Frag) / 4; ++i) x.w[i] = there ? x.w[i] : 0u;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[4 * f + e] = fmaf(wgt, (float)x.h[e], acc[4 * f + e]);
             }
@@ -1051,11 +1052,16 @@ hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup 
     // one fragment a wave, 41.7 with four; with 1536 one fragment is 5 % of the whole layer slower)
     const bool few = n_groups * n_rb <= 256;
     const int grid = few ? n_groups * n_rb * 4 : n_groups * n_rb;
-    if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4>), grid, 0, L, g, a, groups, n_rb);
-    else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8>), grid, 0, L, g, a, groups, n_rb);
-    else if (few) TC_LAUNCH((merge_bf16_kernel<1, 16>), grid, 0, L, g, a, groups, n_rb);
-    else if (max_splits <= 2) TC_LAUNCH((merge_bf16_kernel<4, 2>), grid, 0, L, g, a, groups, n_rb);
-    else TC_LAUNCH((merge_bf16_kernel<4, 4>), grid, 0, L, g, a, groups, n_rb);
+    auto launch = [&](auto frag) {
+        typedef decltype(frag) Frag;
+        if (few && max_splits <= 4) TC_LAUNCH((merge_bf16_kernel<1, 4, Frag>), grid, 0, L, g, a, groups, n_rb);
+        else if (few && max_splits <= 8) TC_LAUNCH((merge_bf16_kernel<1, 8, Frag>), grid, 0, L, g, a, groups, n_rb);
+        else if (few) TC_LAUNCH((merge_bf16_kernel<1, 16, Frag>), grid, 0, L, g, a, groups, n_rb);
+        else if (max_splits <= 2) TC_LAUNCH((merge_bf16_kernel<4, 2, Frag>), grid, 0, L, g, a, groups, n_rb);
+        else TC_LAUNCH((merge_bf16_kernel<4, 4, Frag>), grid, 0, L, g, a, groups, n_rb);
+    };
+    if (a.part_f32) launch(f32x4{});
+    else launch(f16x4{});
     return hipGetLastError();
 }
 

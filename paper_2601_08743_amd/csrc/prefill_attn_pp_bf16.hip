@@ -25,7 +25,8 @@
 //
 // Rows: work-group rows m0 .. m0+255 of the (query, KV head) row space (row = token * G + head in
 // group); wave w owns rows m0 + 32 w ...  Partials of split queries use the layout of the other
-// bf16 kernels with eight 32-row blocks per group, which the merge kernel takes as a parameter.
+// bf16 kernels with eight 32-row blocks per group, which the merge kernel takes as a parameter.  Where a
+// query would not be cut without this kernel they are fp32 (the planner's rule), else fp16 like the others'.
 #include "kv_append.h"
 #include "lds_dma.h"
 #include "tc_internal.h"
@@ -36,6 +37,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPpTile = kAttnKeys * 256;             // 16 KB: a K tile (64 rows of 256 B) or a V tile (4 x 4 KB)
 constexpr int kPpKBufs = 3, kPpVBufs = 4;
@@ -493,16 +495,21 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_pp_kernel(Geom g, BatchDev b
     } else if (it.n_splits > 1) {
         const int64_t slot = (int64_t)it.part0 + it.split;
         const float inv = l > 0.f ? 1.f / l : 0.f;
-        f16x4 *po = (f16x4 *)a.part_o + ((slot * 8 + w) * 16) * 64 + lane;
+        auto put = [&](auto frag) {
+            typedef decltype(frag) Frag;
+            Frag *po = (Frag *)a.part_o + ((slot * 8 + w) * 16) * 64 + lane;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                f16x4 v;
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x4 v;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (_Float16)(o[db][4 * q4 + e] * inv);
-                __builtin_nontemporal_store(v, &po[(db * 4 + q4) * 64]);
-            }
+                    for (int e = 0; e < 4; ++e) v[e] = o[db][4 * q4 + e] * inv;
+                    __builtin_nontemporal_store(__builtin_convertvector(v, Frag), &po[(db * 4 + q4) * 64]);
+                }
+        };
+        if (a.part_f32) put(f32x4{});
+        else put(f16x4{});
         if (hh == 0) {
             typedef float f32x2 __attribute__((ext_vector_type(2)));
             f32x2 ml;

@@ -937,11 +937,12 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.n_append = p.pingpong || p.brief ? 0 : append_units(p.total_S, p.B, bf16 ? 1 : kF32AppendTokens); a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     a.has_pads = p.block_pad.empty() ? 0 : 1;
+    a.part_f32 = p.part_f32 ? 1 : 0;
     a.long_ranges = p.longest_range > kF32MaxTiles ? 1 : 0;
     a.part_o = p.part;
     a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
     a.part_ml = !p.part ? nullptr
-              : bf16 && !p.brief ? p.part + (size_t)p.n_part_slots * p.row_blocks * kAttnRows * 64
+              : bf16 && !p.brief ? p.part + (size_t)p.n_part_slots * p.row_blocks * kAttnRows * part_row_floats(p)
                      : p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
     TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) {
         return p.pingpong ? launch_attn_pp_bf16(ctx->geom, p.dev, a, ln)

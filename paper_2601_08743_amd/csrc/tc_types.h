@@ -114,6 +114,7 @@ struct AttnArgs {
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
     int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches
     int32_t arrival_stride;
+    int32_t part_f32;    // partials in fragment order are fp32 (else fp16)
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };
 

@@ -59,3 +59,33 @@ def test_suffix_from_the_new_rows(H, hq, hkv, alias):
                 assert not have[n:].any()
         dw.ctx.tc_release_seqs(bt)
     dw.close()
+
+
+@pytest.mark.parametrize("lens,suffix,cut", [([1400, 2600, 900, 2100], [128, 128, 128, 128], True), ([700, 700, 700, 700], [128] * 4, False)])
+def test_values_beyond_fp16(H, lens, suffix, cut):
+    """Values times 2^30 (exact in bf16): rows that average far above 65504, which a partial of a query that is only cut
+    here must hold - with the scale taken out they are what they are without it."""
+    def times_2_30(a):                               # bf16 bits: the exponent 30 more (zeros stay)
+        return np.where(a.view(np.uint16) & 0x7f80, a.view(np.uint16) + (30 << 7), a.view(np.uint16)).astype(np.uint16).view(a.dtype)
+
+    cfg = W.WorkloadConfig("v", 1, 40, 8, 128, "bf16", len(lens), (1, max(lens)), 8, (1, 2), "uniform", (1, 9), len(lens), 331)
+    wl = W.make_workload(cfg)
+    wl.table_len[:] = lens
+    wl.queries[:] = [np.array(q, dtype=np.int32) for q in ([0], [1], [2], [1, 3], [0, 1], [3, 3], [1, 1], [2])]
+    wl.suffix_len[:] = 2 * suffix
+    plain = wl.table_kv
+    wl.table_kv = lambda t: (plain(t)[0], times_2_30(plain(t)[1]))
+    q, k, v = wl.suffix_qkv(0)
+    dw = H.DeviceWorkload(wl)
+    bt, pl = dw.stitch()
+    dw.ctx.tc_set_attn_kernel(4)
+    if not cut:
+        dw.ctx.tc_set_kv_splits(1)
+    out, qkv = dw.attn_layer(0, bt, pl, qkv=(q, k, times_2_30(v)))
+    assert dw.ctx.tc_attn_kernel() == 4 and (dw.ctx.tc_kv_splits() > 1) == cut
+    got, ref = H.out_to_f64(out, cfg) * 2.0 ** -30, H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+    for i, r in ref.items():
+        err = float(np.abs(got[int(wl.cu_seqlens[i]):int(wl.cu_seqlens[i + 1])] - r * 2.0 ** -30).max())
+        assert err <= TOL, (i, err)
+    dw.ctx.tc_release_seqs(bt)
+    dw.close()

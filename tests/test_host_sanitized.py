@@ -134,6 +134,7 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0,
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
                 n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
+    info["part_f32"] = int([l for l in lines if l.startswith("part_f32")][0].split()[1])
     info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
     info["part_floats"], info["part_stride"], *info["part_tab"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
     assert int(ghead[1]) == len(groups)
@@ -401,6 +402,26 @@ def test_planner_random_batches(exe):
         _check_plan(info, items, Hkv * G, Hkv, PS, dtype=dtype)
         if info["part_tab"]:
             _check_slots(info, items, Hkv * G, 128 if dtype else 64, PS)
+
+
+RAGGED = [(P, 128) for P in (1400, 2600, 900, 5200, 2000, 3100, 4300, 700)]
+
+
+def test_partials_of_queries_cut_by_the_long_launch_kernel_alone_are_fp32(exe):
+    """What one partition count for the batch, or the kernel that would take it otherwise, leaves whole is fp32 to the end:
+    fp32 partials where the long-launch kernel cuts it.  Batches whose queries are cut with fp16 partials either way keep those, forced
+    counts and plans of least space too, and what the short-launch kernel would take stays there."""
+    for Hq, Hkv, PS, kw, cut, f32 in (
+            (40, 8, RAGGED, {}, 1, 1), (40, 8, RAGGED, dict(kernel=4), 1, 1), (40, 8, RAGGED, dict(kernel=4, splits=3), 1, 0),
+            (40, 8, RAGGED, dict(within=(1 << 30, 1 << 22)), 1, 1), (32, 8, [(70000, 200)] * 4, dict(within=(1 << 30, 4456448)), 1, 0),
+            (28, 4, [(1727, 100), (4048, 160), (3773, 48), (2584, 90)], {}, 1, 0), (40, 8, [(4600, 128)], {}, 1, 0)):
+        info, items = _plan(exe, Hq, Hkv, PS, **kw)
+        _check_plan(info, items, Hq, Hkv, PS)
+        assert info["pingpong"] and (info["max_splits"] > 1, info["part_f32"]) == (bool(cut), f32), (PS, kw)
+        slots = sum(1 for it in items if it[0] >= 0 and it[6] > 1)
+        assert info["part_floats"] == slots * 256 * ((128 if f32 else 64) + 2) <= kw.get("within", (0, 1 << 62))[1]
+    info, items = _plan(exe, 40, 8, [(809, 100), (809, 160)])
+    assert info["brief"] and info["max_splits"] == 1
 
 
 def test_short_launch_plans(exe):
