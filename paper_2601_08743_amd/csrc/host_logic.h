@@ -372,35 +372,40 @@ inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile,
 }
 
 // The long-launch kernel (one work-group of 256 rows per CU): the key range of a work item in key tiles, and what the launch
-// takes, in us.  Its items go out longest first to whichever CU is free, so the launch lasts as long as that placement of
-// them on 256 CUs: each item 7.8 us and 1.32 a key tile, where some query is cut 1.8 us and its partials for the
-// merge, and 3.0 for the launch.  One range length for the batch: a long query is cut into more than a short one.
-// Tried are lengths from the longest query's down to an eleventh of it.
-// Fitted to 90 batches (1 .. 36 queries of 0.2 .. 18 k prefix and 24 .. 512 new tokens, 28 / 4, 32 / 8 and 40 / 8 heads) at 9 .. 13
-// lengths each: 8 % rms, and of the lengths tried the choice is within 0.3 % of the fastest on average, 8 % at worst.
-// (With one partition count for all, taken from a batch's mean length: 11 % behind it; micro-batches of eight queries of
-// 1 .. 5 k + 128 tokens, 40 / 8 heads, 100 .. 107 us against 80 .. 90.)
+// takes, in us.  The row tiles of one (query, KV head, range) - a bucket - go to one XCD, the longest first to whichever has the
+// least work, and there to whichever CU is free, so the launch lasts as long as that placement of them on 8 x 32 CUs: each item
+// 7.8 us and 1.32 a key tile, where some query is cut 1.8 us and its partials for the merge, and 3.0 for the launch.  One range length
+// for the batch: a long query is cut into more than a short one.  Tried are lengths from the longest query's down to a
+// twenty-eighth of it.
+// Fitted to 90 batches, and held against 150 others (1 .. 32 queries of 0.1 .. 18 k prefix and 2 .. 512 new tokens, 28 / 4, 32 / 8 and
+// 40 / 8 heads) at up to 16 lengths each, with fp16 and with fp32 partials: 7.7 % rms, and of the lengths tried the choice is
+// within 0.6 % of the fastest on average, 12 % at worst.  (Placed on 256 CUs alike: 1.3 %, and 40 % at worst - one query of 4.4 k
+// + 400 tokens, 28 / 4 heads, in five ranges: 20 buckets of 11 items put 33 on some XCD, 59.8 us against 42.0 in four; with one
+// partition count for all, taken from a batch's mean length: 11 % behind it.)
 struct LongPlan { int range = 0; double us = 1e30; };
 inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap, bool part_f32)
 {
-    constexpr int kCus = 256;
+    constexpr int kCus = 256, kXcds = 8;
     constexpr int64_t kItem = 780, kTile = 132;          // 1/100 us
     const int G = c.n_q_heads / c.n_kv_heads;
-    struct Query { int tiles; int64_t count, rows; };
+    struct Query { int tiles; int64_t row_tiles, rows; };
     std::vector<Query> queries;
     int longest = 0;
     for (int i = 0; i < p.B; ++i) {
         const int64_t S = p.suffix_len[i];
         if (S <= 0) continue;
-        queries.push_back(Query{(int)(((int64_t)p.prefix_len[i] + S + key_tile - 1) / key_tile), c.n_kv_heads * ((S * G + row_tile - 1) / row_tile), S * c.n_q_heads});
+        queries.push_back(Query{(int)(((int64_t)p.prefix_len[i] + S + key_tile - 1) / key_tile), (S * G + row_tile - 1) / row_tile, S * c.n_q_heads});
         longest = std::max(longest, queries.back().tiles);
     }
     LongPlan best;
     double uncut = 0.0;                                  // with no query cut: left for 5 % or more, which the fit resolves
-    std::vector<std::pair<int, int64_t>> parts;         // (key tiles, how many items)
-    std::vector<std::pair<int64_t, int64_t>> cus;       // (when free, how many), the first free last
+    struct Part { int tiles; int64_t row_tiles, buckets; };
+    std::vector<Part> parts;
+    struct Xcd { int64_t load; std::vector<std::pair<int64_t, int64_t>> cus; } xcds[kXcds];      // (when free, how many), the first free last
+    // (the buckets of a query's KV heads are alike: they go to as many XCDs, which then are, too, and one stands for them)
+    const int alike = c.n_kv_heads % 8 == 0 ? 8 : c.n_kv_heads % 4 == 0 ? 4 : c.n_kv_heads % 2 == 0 ? 2 : 1;
     int last = 0;
-    for (const int tenths : {10, 12, 14, 16, 18, 20, 25, 30, 40, 50, 60, 80, 110}) {
+    for (const int tenths : {10, 12, 14, 16, 18, 20, 25, 30, 40, 50, 60, 80, 110, 150, 200, 280}) {
         const int range = std::max(2, (longest * 10 + tenths - 1) / tenths);
         if (range == last) continue;
         last = range;
@@ -408,26 +413,34 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
         int64_t cut_rows = 0, cut_tiles = 0, total = 0;
         for (const Query &q : queries) {
             const int ns = std::max(1, std::min((q.tiles + range - 1) / range, q.tiles / 2)), len = q.tiles / ns, more = q.tiles % ns;
-            if (more) parts.push_back({len + 1, more * q.count});
-            parts.push_back({len, (ns - more) * q.count});
-            total += q.count * (ns * kItem + q.tiles * kTile);
-            if (ns > 1) { cut_rows += q.rows * ns; cut_tiles += q.count * ns; }
+            if (more) parts.push_back({len + 1, q.row_tiles, (int64_t)more * c.n_kv_heads});
+            parts.push_back({len, q.row_tiles, (int64_t)(ns - more) * c.n_kv_heads});
+            total += q.row_tiles * c.n_kv_heads * (ns * kItem + q.tiles * kTile);
+            if (ns > 1) { cut_rows += q.rows * ns; cut_tiles += q.row_tiles * c.n_kv_heads * ns; }
         }
         if (part_cap > 0 && (double)cut_tiles * row_tile * ((part_f32 ? 128 : 64) + 2) > (double)part_cap) continue;
         const double merge = cut_rows > 0 ? 1.8 + (part_f32 ? 1.45e-4 : 0.74e-4) * (double)cut_rows : 0.0;
-        std::sort(parts.begin(), parts.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-        if (3.0 + merge + 0.01 * (double)std::max(total / kCus, kItem + parts[0].first * kTile) >= (uncut > 0.0 ? std::min(best.us, 0.95 * uncut) : best.us)) continue;
-        cus.assign(1, {0, kCus});
-        for (auto [len, count] : parts)
-            while (count > 0) {
-                const int64_t free_at = cus.back().first, n = std::min(count, cus.back().second), end = free_at + kItem + len * kTile;
-                if ((cus.back().second -= n) == 0) cus.pop_back();
-                const auto at = std::lower_bound(cus.begin(), cus.end(), end, [](const auto &x, int64_t t) { return x.first > t; });
-                if (at != cus.end() && at->first == end) at->second += n;
-                else cus.insert(at, {end, n});
-                count -= n;
+        std::stable_sort(parts.begin(), parts.end(), [](const Part &x, const Part &y) { return x.tiles > y.tiles; });
+        if (3.0 + merge + 0.01 * (double)std::max(total / kCus, kItem + parts[0].tiles * kTile) >= (uncut > 0.0 ? std::min(best.us, 0.95 * uncut) : best.us)) continue;
+        for (Xcd &x : xcds) { x.load = 0; x.cus.assign(1, {0, kCus / kXcds}); }
+        for (const Part &part : parts)
+            for (int64_t k = 0; k < part.buckets; k += alike) {
+                Xcd *x = &xcds[0];
+                for (Xcd *y = x + 1; y < xcds + kXcds / alike; ++y) if (y->load < x->load) x = y;
+                x->load += (part.tiles + 3) * part.row_tiles;
+                for (int64_t count = part.row_tiles; count > 0;) {
+                    auto &cus = x->cus;
+                    const int64_t free_at = cus.back().first, n = std::min(count, cus.back().second), end = free_at + kItem + part.tiles * kTile;
+                    if ((cus.back().second -= n) == 0) cus.pop_back();
+                    const auto at = std::lower_bound(cus.begin(), cus.end(), end, [](const auto &c0, int64_t t) { return c0.first > t; });
+                    if (at != cus.end() && at->first == end) at->second += n;
+                    else cus.insert(at, {end, n});
+                    count -= n;
+                }
             }
-        const double us = 3.0 + merge + 0.01 * (double)cus.front().first;
+        int64_t ends = 0;
+        for (Xcd *x = xcds; x < xcds + kXcds / alike; ++x) ends = std::max(ends, x->cus.front().first);
+        const double us = 3.0 + merge + 0.01 * (double)ends;
         if (us < best.us - 1e-9 && (uncut == 0.0 || us < 0.95 * uncut)) best = LongPlan{range, us};
         if (cut_rows == 0 && uncut == 0.0) uncut = us;
     }

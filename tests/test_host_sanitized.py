@@ -517,3 +517,27 @@ def test_long_launch_ranges_go_by_each_query(exe):
     assert ragged >= 10
     info, items = _plan(exe, 28, 4, [(1500, 250)] * 60, kernel=4)      # many even items: nothing to gain
     assert info["max_splits"] == 1
+
+
+@pytest.mark.parametrize("Hq,Hkv,PS", [(28, 4, [(4400, 400)]), (28, 4, [(3500, 370)]), (32, 8, [(5000, 500)]), (12, 1, [(9000, 300)] * 3)])
+def test_long_launch_ranges_go_by_the_chiplets(exe, Hq, Hkv, PS):
+    """The row tiles of a (query, KV head, range) stay on one of the eight XCDs (work-group id mod 8), 32 CUs each: of the
+    equal range counts, the chosen one is as good as any by the placement that the launch will have - 7.8 us an item and 1.32 a key
+    tile - to the 10 % that a range length in tenths, and a merge that grows with the count, may differ."""
+    import heapq
+
+    def ends(items):
+        last = 0.0
+        for x in range(8):
+            free = [0.0] * 32
+            for it in items[x::8]:
+                if it[0] >= 0:
+                    heapq.heapreplace(free, free[0] + 7.8 + 1.32 * (it[4] - it[3]))
+            last = max(last, max(free))
+        return last
+
+    info, items = _plan(exe, Hq, Hkv, PS, kernel=4)
+    _check_plan(info, items, Hq, Hkv, PS)
+    assert info["max_splits"] > 1
+    others = [ends(_plan(exe, Hq, Hkv, PS, kernel=4, splits=ns)[1]) for ns in range(1, 13)]
+    assert ends(items) <= 1.1 * min(others) + 3.0, (info["max_splits"], ends(items), others)
