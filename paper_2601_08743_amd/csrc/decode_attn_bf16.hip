@@ -71,10 +71,9 @@ __device__ __forceinline__ Self score_self(const SelfRaw &s, float scale_log2)
     return Self{prod * scale_log2, {lo(s.v.x), hi(s.v.x), lo(s.v.y), hi(s.v.y)}};
 }
 
-// The new token joins the row's keys, and the row is written.
-__device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d, const Self &s, RowSum x)
+// Four columns of an output row.
+__device__ __forceinline__ void write_row(unsigned short *out, const RowSum &x)
 {
-    x.add(s.score, 1.f, s.v);
     const float inv = 1.f / x.L;
     unsigned short r[4];
 #pragma unroll
@@ -82,8 +81,14 @@ __device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, con
         const __bf16 y = (__bf16)(x.acc[e] * inv);
         r[e] = *(const unsigned short *)&y;
     }
-    *(uint2 *)((unsigned short *)a.out + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d) =
-        make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
+    *(uint2 *)out = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
+}
+
+// The new token joins the row's keys, and the row is written.
+__device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d, const Self &s, RowSum x)
+{
+    x.add(s.score, 1.f, s.v);
+    write_row((unsigned short *)a.out + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d, x);
 }
 
 __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchDev b, AttnArgs a)
@@ -413,6 +418,71 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     if (e != hipSuccess) return e;
     TC_LAUNCH(decode_attn_bf16_kernel, a.n_items, kDecLds, L, g, b, a);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------ merge
+// Partials by row combined by a launch of its own, where one CU would take longer over a row tile's than that: 32 threads, four
+// columns each, per (suffix token, query head) row and group of partitions; a row's kGroups groups take every kGroups-th
+// partition and are combined through LDS.  Bound: the latency of the loads of a short launch, so those of four partitions are issued
+// before the first use, and (kEven) before it is known how many there are.
+template <int kGroups, bool kEven>
+__global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
+{
+    constexpr int kBatch = 4, kRows = 8 / kGroups;
+    __shared__ float s_acc[8][132], s_ml[8][2];
+    const int tid = threadIdx.x, slot8 = tid >> 5, grp = slot8 % kGroups, d = 4 * (tid & 31);
+    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
+    const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
+    const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
+    const int n = row / g.Hq, head = row - n * g.Hq;
+    const PartSlots slots = part_slots<kEven>(b, n);
+    float2 ml[kBatch];
+    f32x4 po[kBatch];
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (kGroups * j >= max_splits) break;
+            const int64_t slot = (int64_t)min(slots.first + s0 + kGroups * j, slots.last) * g.Hq + head;
+            ml[j] = *(const float2 *)(a.part_ml + slot * 2);
+            po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
+        }
+    };
+    if (kEven || slots.count > 0) fetch(grp);
+    const int ns = slots.count;
+    RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
+    for (int s0 = grp; s0 < ns; s0 += kGroups * kBatch) {
+        if (s0 > grp) fetch(s0);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (s0 + kGroups * j < ns) x.add(ml[j].x, ml[j].y, po[j]);
+    }
+    if (kGroups > 1) {
+        *(f32x4 *)&s_acc[slot8][d] = x.acc;
+        if (d == 0) { s_ml[slot8][0] = x.M; s_ml[slot8][1] = x.L; }
+        __syncthreads();
+    }
+    if (grp > 0 || want >= n_rows || ns <= 1) return;          // (a row in one range was written by the attention kernel)
+#pragma unroll
+    for (int k = 1; k < kGroups; ++k) x.add(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
+    write_row((unsigned short *)a.out + (int64_t)row * 128 + d, x);
+}
+
+template <bool kEven>
+static hipError_t launch_merge_rows(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+{
+    const int n_rows = b.total_S * g.Hq;
+    if (n_rows == 0) return hipSuccess;
+    if (max_splits < 1 || !b.part_tab) return hipErrorInvalidValue;
+    if (max_splits <= 4) TC_LAUNCH((merge_rows_bf16_kernel<1, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH((merge_rows_bf16_kernel<2, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH((merge_rows_bf16_kernel<4, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH((merge_rows_bf16_kernel<8, kEven>), n_rows, 0, L, g, b, a, max_splits);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+{
+    return b.part_stride > 0 ? launch_merge_rows<true>(g, b, a, max_splits, L) : launch_merge_rows<false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

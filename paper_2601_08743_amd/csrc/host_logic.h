@@ -194,6 +194,8 @@ struct Plan {
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups
+    int32_t part_stride = 0;    // kernels that keep partials by row: slots from token to token, 0: packed
+    bool fold = false;          // partials by row are combined inside the launch that makes them (else by one of its own)
     bool part_f32 = false;      // partials in fragment order are fp32 (the long-launch kernel's, by a rule of the planner), else fp16
     bool compact = false;       // planned for the least space (a batch that did not fit the static workspace otherwise)
     bool brief = false;         // bf16, 32 rows per work-group, its waves split the keys: the short-launch kernel
@@ -269,14 +271,14 @@ inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int k
 // The short-launch kernel (32 rows per work-group, one work-group per CU, its eight waves split the
 // range's 32-key units): the key range of a work item in key tiles, and what the launch takes, in us.  A
 // round of work-groups costs 4.4 us and 1.6 for each unit of a wave (a round trip to memory and its
-// arithmetic: the wave has one unit in flight), combining the ranges of a query 3.5 us and 1.7 more for each eight
-// of them (a round of loads; one query of 1.5 k + 17 tokens, 28 / 4 heads: 10.4 us in 7 ranges, 10.5 in 8, 11.6 in 10; when a launch
-// of its own combined them 12.0), each MB of keys and values 0.1 us.  Ranges are only cut where the chip has CUs to
-// spare and a KV head has at most 512 rows (16 row tiles that each fetch the keys; one query of 2.1 k + 140 tokens, 28 / 4 heads: 19.1 us in two ranges, 19.5 in
+// arithmetic: the wave has one unit in flight), the merge 3.5 us and its fp32 partials, each MB of keys and
+// values 0.1 us.  Ranges are only cut where the chip has CUs to spare and a KV head has at most 512 rows (16 row
+// tiles that each fetch the keys; one query of 2.1 k + 140 tokens, 28 / 4 heads: 19.1 us in two ranges, 19.5 in
 // the pipelined kernel), so partials stay small, and more than two rounds of work-groups are left to the
 // other kernels (three: 1.04 times as fast as those, two: 1.3, one: 1.4).  Fitted to
 // 740 batches (1 .. 16 queries of 350 .. 10500 prefix and 2 .. 330 new tokens, 28 / 4, 32 / 8 and 40 / 8
-// heads) in 1 .. 9 ranges: 8 % rms.
+// heads) in 1 .. 9 ranges, all merged by a launch of its own: 8 % rms.  Up to eight ranges are combined without one, which
+// saves 0.2 .. 1 us (0.4 here).
 inline double batch_mb(const tc_config &c, const Plan &p)
 {
     double tokens = 0;
@@ -298,7 +300,7 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
         const int range = std::max(1, (longest + cuts - 1) / cuts);
         if (range > max_tiles) continue;
         int64_t n = 0;
-        double units = 0;
+        double units = 0, rows_cut = 0;
         int most = 0, most_ns = 1;
         bool split = false, wide = false;
         for (int i = 0; i < p.B; ++i) {
@@ -311,11 +313,11 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
             units += (double)k * per_wave;
             most = std::max(most, per_wave);
             most_ns = std::max(most_ns, ns);
-            if (ns > 1) { split = true; wide = wide || S * G > 512; }
+            if (ns > 1) { split = true; wide = wide || S * G > 512; rows_cut += (double)S * c.n_q_heads * ns; }
         }
         if (n == 0 || n > 512 || (split && (n > 256 || wide))) break;          // (n grows with the cuts)
         const double rounds = (double)((n + 255) / 256);
-        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? 3.5 + 1.7 * ((most_ns - 1) / 8) : 0.0) + 0.1 * mb;
+        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? (most_ns <= kShortFold ? 3.1 : 3.5) + 3e-5 * rows_cut : 0.0) + 0.1 * mb;
         if (us < best.us - 1e-9) best = BriefPlan{range, us};
         if (range == 1) break;
     }
@@ -450,20 +452,30 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
 // Where the split-KV partials of the fp32, decode and short-launch kernels stand.  They are kept by row: a slot, D + 2
 // floats for each query head, for every (suffix token, partition), packed: a batch pays for the partitions that its
 // queries have, not for its longest query's count everywhere, and a query in one range has none.
+// Where a launch of its own combines them and the queries have about as many partitions each, every token has as many slots as
+// the most it could need instead, so that the merge knows them without a look into a table (0.3 us); where that would be more than
+// twice the slots needed, or more than the workspace holds, they are packed there as well.
 // (The other bf16 kernels keep, per (cut row tile, partition, row block), 128 rows x (128 fp16 + 2 floats)
 // in fragment order, or 128 fp32.)
-inline void place_partials(Plan &p, const std::vector<int32_t> &splits_of_q, std::vector<AttnItem> &items)
+inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, const std::vector<int32_t> &splits_of_q,
+                           std::vector<AttnItem> &items)
 {
+    const int64_t even = (int64_t)p.max_splits * p.total_S;       // (n_part_slots: packed, so far)
+    if (!p.fold && !knobs.compact && even <= 2 * p.n_part_slots &&
+        (knobs.part_cap == 0 || (size_t)even * c.n_q_heads * (c.head_dim + 2) <= knobs.part_cap)) {
+        p.part_stride = p.max_splits;
+        p.n_part_slots = even;
+    }
     std::vector<int64_t> first(p.B);
     int64_t at = 0;
     for (int i = 0; i < p.B; ++i) {
-        first[i] = at;
+        first[i] = p.part_stride ? (int64_t)p.cu_seqlens[i] * p.part_stride : at;
         if (p.decode || splits_of_q[i] > 1) at += (int64_t)p.suffix_len[i] * splits_of_q[i];
     }
     for (AttnItem &it : items)
         if (it.q >= 0) {
             it.part0 = (int32_t)first[it.q];
-            it.part_stride = it.n_splits;
+            it.part_stride = p.part_stride ? p.part_stride : it.n_splits;
         }
 }
 
@@ -489,7 +501,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = p.part_f32 = false;
     p.brief = false;
     p.n_part_slots = 0;
-    p.n_groups = p.n_arrivals = 0;
+    p.n_groups = p.n_arrivals = p.part_stride = 0;
+    p.fold = false;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
     // work is reading K and V once.  The decode kernels split the keys of a (query, KV head) over
@@ -570,8 +583,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.row_blocks = 1;
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
-        p.decode = true;
-        place_partials(p, splits_of_q, items);
+        p.decode = p.fold = true;
+        place_partials(c, knobs, p, splits_of_q, items);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -792,7 +805,11 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         }
     while (!items.empty() && items.back().q < 0) items.pop_back();
     p.n_items = (int32_t)items.size();
-    if (by_row && p.max_splits > 1) place_partials(p, splits_of_q, items);
+    // (the short-launch kernel: eight partials of a row in one round of loads; a launch of its own for them is 0.2 .. 1 us slower up
+    // to there, and beyond, where one CU has a second round, 0.5 .. 5 us faster)
+    p.fold = by_row && p.max_splits > 1 && (!p.brief || p.max_splits <= kShortFold);
+    if (!p.fold) p.n_arrivals = 0;
+    if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one
     // work-group per CU: nothing hides a work-group's start-up and drain.  It wins when a launch is a
     // single round of work-groups or when they are long; many short ones (measured: 1140 work-groups
@@ -836,6 +853,19 @@ inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode ||
 
 inline int part_row_floats(const Plan &p) { return p.part_f32 ? 128 : 64; }      // a row's partial in fragment order, without its (maximum, sum)
 
+// Does a launch of its own combine partials by row, and the table that it goes by (BatchDev::part_tab).
+inline bool merges_rows(const tc_config &c, const Plan &p) { return parts_by_row(c, p) && !p.fold; }
+inline size_t part_tab_ints(const Plan &p) { return (size_t)p.total_S + (p.part_stride == 0); }
+inline void fill_part_tab(const Plan &p, const std::vector<int32_t> &splits_of_q, int32_t *out)
+{
+    int32_t at = 0;
+    for (int i = 0; i < p.B; ++i) {
+        const int32_t count = splits_of_q[i] > 1 ? splits_of_q[i] : 0;
+        for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += count) out[n] = p.part_stride ? count : at;
+    }
+    if (!p.part_stride) out[p.total_S] = at;
+}
+
 inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the batch's partials, in floats
 {
     if (parts_by_row(c, p)) return (size_t)p.n_part_slots * c.n_q_heads * (c.head_dim + 2);
@@ -848,10 +878,10 @@ constexpr size_t kBigPlanInts = size_t(1) << 18;    // 1 MiB: in larger plans th
 // is there (`n_*`: how many of each).
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
-    size_t block_table, cu, prefix, suffix, tok_q, items, groups;
+    size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
-    bool lengths = false, tokens = false, merge_groups = false;
+    bool lengths = false, tokens = false, merge_rows = false, merge_groups = false;
     int arrival_stride = kArrivalStride;
 };
 inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
@@ -862,6 +892,7 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     auto take = [&](size_t n) { const size_t o = l.total; l.total += (n + 7) & ~size_t(7); return o; };
     l.tokens = !p.decode && !p.pingpong && !p.brief;             // appended token by token, in extra work-groups
     l.lengths = l.tokens || n_stitch > 0;
+    l.merge_rows = merges_rows(c, p);
     l.merge_groups = p.max_splits > 1 && !parts_by_row(c, p);
     // rows are padded to whole 16-byte chunks: the decode and short-launch kernels fetch them so, the long-launch
     // kernel where it can
@@ -871,6 +902,7 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.cu = take(l.tokens ? B + 1 : 0); l.suffix = take(l.tokens ? B : 0); l.tok_q = take(l.tokens ? p.total_S : 0);
     l.seg_start = take(n_seg); l.seg_len = take(n_seg); l.seg_slot = take(n_seg);
     l.stitch = take(n_stitch * (sizeof(StitchBlk) / 4));
+    l.part_tab = take(l.merge_rows ? part_tab_ints(p) : 0);
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
     if (l.total + (size_t)p.n_arrivals * kArrivalStride > kBigPlanInts) l.arrival_stride = kArrivalStrideBig;

@@ -16,8 +16,10 @@
 // and after the append of the same launch, which may run beside a tile's loads.)
 //
 // Where a query is cut all the same, the last of a row tile's ranges to end combines their partials (16 KB each) in the same
-// launch (arrive.h).  A launch of its own for that: one query of 1.5 k + 17 tokens, 28 / 4 heads, in 7 ranges 11.8 us a layer,
-// so 10.2; 28 layers of a short question 362 us, so 340.
+// launch (arrive.h), or, with more than eight ranges, a launch of its own does.  The same batches in the same ranges either way, us
+// a layer: one query of 1.4 k + 17 tokens, 28 / 4 heads, in 7 ranges 10.1 against 10.6 in two launches, in 10 11.4 against 10.3;
+// of 2.4 k + 8 in 8 ranges 10.5 either way, in 10 11.5 against 10.5, in 20 12.7 against 10.2; four of 2.4 k + 12, 32 / 8 heads, in 4 13.9
+// against 14.4, in 12 30.4 against 25.0.  28 layers of a short question 362 us in two launches, 340 in one.
 //
 // Measured per layer, against the pipelined or general kernel, partials combined by a launch of its own: 28 / 4
 // heads, one query of 1.1 k prefix and 17 new tokens 10.3 us (14.9); thirteen of 4 k and 3 .. 6 tokens 27.1
@@ -44,7 +46,6 @@ constexpr int kShIds = kShQ + kShortRows * 256;      // block ids of the range, 
 constexpr int kShMl = kShIds + kAttnMaxTiles * (kAttnKeys / kBlockTokens) * 4;     // (maximum, sum) per wave and row
 constexpr int kShLds = kShMl + kShWaves * kShortRows * 8 + 256;                    // + alignment slack
 constexpr float kShRescale = 8.f;
-constexpr int kShFold = 8;                           // partials of a row requested at once (a lane of 16 each, and one to spare)
 
 // Four columns of an output row.
 __device__ __forceinline__ void write_part(const AttnArgs &a, int64_t row, int ch, f32x4 acc, float l)
@@ -59,8 +60,10 @@ __device__ __forceinline__ void write_part(const AttnArgs &a, int64_t row, int c
     *(uint2 *)((unsigned short *)a.out + row * 128 + 4 * ch) = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
 }
 
-// kCut: some query of the batch is in several ranges.  (With their end compiled in, batches without any paid 0.1 us for it.)
-template <bool kCut>
+// Is some query of the batch in several ranges, and who combines them.  (With their end compiled in, batches without any paid
+// 0.1 us for it.)
+enum ShortCut { kUncut, kFolded, kMerged };
+template <ShortCut kCut>
 __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -340,18 +343,24 @@ __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom 
         return x;
     };
     const int ch = tid & 31;
-    if (!kCut || it.n_splits == 1) {
+    if (kCut != kFolded || it.n_splits == 1) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int row = (tid >> 5) + 16 * j, m = it.m0 + row;
             if (m > m_last) continue;
             const RowSum x = fold_waves(row, ch);
-            const int tok = m / G;
-            write_part(a, (int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (m - tok * G), ch, x.acc, x.L);
+            const int tok = m / G, head = it.kvh * G + (m - tok * G);
+            if (kCut == kMerged && it.n_splits > 1) {
+                const int64_t slot = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + head;
+                *(f32x4 *)(a.part_o + slot * 128 + 4 * ch) = x.acc;
+                if (ch == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(x.M, x.L);
+            } else {
+                write_part(a, (int64_t)(it.cu + tok) * g.Hq + head, ch, x.acc, x.L);
+            }
         }
     } else {
-        // A range of several: the last work-group of the row tile to end combines them (arrive.h).  32 threads take two rows
-        // at a time, four columns each; lanes 0 .. 15 and 16 .. 31 bring their weights.
+        // A range of several: the last work-group of the row tile to end combines them (arrive.h), up to eight in one round of
+        // loads.  32 threads take two rows at a time, four columns each; lanes 0 .. 15 and 16 .. 31 bring their weights.
         const int64_t first_slot = ((int64_t)it.part0 + (int64_t)tok0 * it.part_stride) * g.Hq + it.kvh * G;
         const uint32_t n_slots = (uint32_t)min((int64_t)(m_last / G - tok0 + 1) * it.part_stride * g.Hq, (int64_t)0x3fffff);
         const SharedPart part_o(a.part_o + first_slot * 128, n_slots * 512), part_ml(a.part_ml + first_slot * 2, n_slots * 8);
@@ -372,36 +381,28 @@ __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom 
         const uint32_t ml_at = (ch < 16 ? slot[0] : slot[1]) * 8 + (ch & 15) * (step >> 6);
         float *s_w = (float *)(lds + kShMl) + (tid >> 5) * 32;
         if (last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, ns, (int32_t *)(lds + kShIds))) {
+            const bool there = (ch & 15) < ns;
+            const float2 ml = part_ml.get2(there ? ml_at : kNowhere);
+            f32x4 o[kShortFold][2];
+#pragma unroll
+            for (int k = 0; k < kShortFold; ++k)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) o[k][j] = part_o.get4(k < ns ? slot[j] * 512 + ch * 16 + k * step : kNowhere);
+            const float m = there ? ml.x : -INFINITY, M = max16(m);
+            const float w = m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - M);     // (no maximum: its sums are 0, or NaN and so is the row)
+            s_w[ch] = w;
             f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-            float M = -INFINITY, l_lane = 0.f;         // of the lane's row
-            for (int s0 = 0; s0 < ns; s0 += kShFold) {
-                const bool there = (ch & 15) < min(ns - s0, kShFold);
-                const float2 ml = part_ml.get2(there ? ml_at + s0 * (step >> 6) : kNowhere);
-                f32x4 o[kShFold][2];
 #pragma unroll
-                for (int k = 0; k < kShFold; ++k)
+            for (int j = 0; j < 2; ++j) {
+                f32x4 wj[kShortFold / 4];
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) o[k][j] = part_o.get4(s0 + k < ns ? slot[j] * 512 + ch * 16 + (s0 + k) * step : kNowhere);
-                const float m = there ? ml.x : -INFINITY;
-                const float Mn = fmaxf(M, max16(m)), r = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
-                const float w = m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - Mn);     // (no maximum: its sums are 0, or NaN and so is the row)
-                l_lane = l_lane * r + w * ml.y;
-                M = Mn;
-                s_w[ch] = (ch & 15) == kShFold ? r : w;
+                for (int k = 0; k < kShortFold / 4; ++k) wj[k] = *(const f32x4 *)(s_w + 16 * j + 4 * k);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    f32x4 wj[kShFold / 4 + 1];
+                for (int k = 0; k < kShortFold; ++k)
 #pragma unroll
-                    for (int k = 0; k < kShFold / 4 + 1; ++k) wj[k] = *(const f32x4 *)(s_w + 16 * j + 4 * k);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[j][e] *= wj[kShFold / 4][0];
-#pragma unroll
-                    for (int k = 0; k < kShFold; ++k)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[j][e] += wj[k >> 2][k & 3] * o[k][j][e];
-                }
+                    for (int e = 0; e < 4; ++e) acc[j][e] += wj[k >> 2][k & 3] * o[k][j][e];
             }
-            s_w[ch] = sum16(l_lane);
+            s_w[ch] = sum16(w * ml.y);
 #pragma unroll
             for (int j = 0; j < 2; ++j)
                 if (it.m0 + (tid >> 5) + 16 * j <= m_last) write_part(a, orow[j], ch, acc[j], s_w[16 * j]);
@@ -426,14 +427,17 @@ hipError_t launch_attn_short_bf16(const Geom &g, const BatchDev &b, const AttnAr
     if (g.D != 128 || g.esize != 2) return hipErrorInvalidValue;
     static PerDeviceOnce configured;
     const hipError_t e = configured.run([] {
-        const hipError_t e0 = hipFuncSetAttribute((const void *)attn_bf16_short_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
-        return e0 != hipSuccess ? e0 : hipFuncSetAttribute((const void *)attn_bf16_short_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
+        for (const void *k : {(const void *)attn_bf16_short_kernel<kUncut>, (const void *)attn_bf16_short_kernel<kFolded>, (const void *)attn_bf16_short_kernel<kMerged>}) {
+            const hipError_t ek = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kShLds);
+            if (ek != hipSuccess) return ek;
+        }
+        return hipSuccess;
     });
     if (e != hipSuccess) return e;
-    if (a.part_o)
-        hipExtLaunchKernelGGL(attn_bf16_short_kernel<true>, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a);
-    else
-        hipExtLaunchKernelGGL(attn_bf16_short_kernel<false>, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a);
+    auto launch = [&](auto *kernel) { hipExtLaunchKernelGGL(kernel, dim3(a.n_items), dim3(64 * kShWaves), kShLds, L.stream, L.start, L.stop, 0, g, b, a); };
+    if (!a.part_o) launch(attn_bf16_short_kernel<kUncut>);
+    else if (a.arrivals) launch(attn_bf16_short_kernel<kFolded>);
+    else launch(attn_bf16_short_kernel<kMerged>);
     return hipGetLastError();
 }
 

@@ -277,6 +277,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         h[at.seg_start + k] = segs[k].start; h[at.seg_len + k] = segs[k].len; h[at.seg_slot + k] = segs[k].slot;
     }
     put(at.stitch, sblk);
+    if (at.merge_rows) fill_part_tab(p, splits_of_q, h + at.part_tab);
     put(at.items, items);
     put(at.groups, groups, at.merge_groups);
     put(at.rope_pos0, p.rope_pos0, p.rope);
@@ -305,7 +306,11 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     p.dev.n_stitch_blk = (int32_t)sblk.size();
     p.n_stitch_blk = (int32_t)sblk.size();
     p.items_dev = (const AttnItem *)(d + at.items);
-    p.arrivals_dev = d_dst + at.arrivals;
+    if (at.merge_rows) {
+        p.dev.part_tab = d + at.part_tab;
+        p.dev.part_stride = p.part_stride;
+    }
+    p.arrivals_dev = p.fold ? d_dst + at.arrivals : nullptr;
     p.arrival_stride = at.arrival_stride;
     p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
@@ -950,7 +955,9 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
              : bf16 ? launch_attn_bf16(ctx->geom, p.dev, a, p.row_blocks, p.pipelined, ln)
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
-    if (p.groups_dev)
+    if (p.dev.part_tab)
+        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, ln); }));
+    else if (p.groups_dev)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
             return launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln);
         }));

@@ -41,6 +41,18 @@ __device__ __forceinline__ int2 load_bids(const AttnArgs &a, unsigned k, int j)
     return make_int2(v.x, v.y);
 }
 
+// Where suffix token n's partials stand (kernels that keep them by row): its first slot, how many there are, and the
+// last slot that may be read in their place.  Evenly spaced slots are known before the table answers, so their
+// loads need not wait for it.
+struct PartSlots { int first, count, last; };
+template <bool kEven>
+__device__ __forceinline__ PartSlots part_slots(const BatchDev &b, int n)
+{
+    if (kEven) return PartSlots{n * b.part_stride, b.part_tab[n], (n + 1) * b.part_stride - 1};
+    const int first = b.part_tab[n], end = b.part_tab[n + 1];
+    return PartSlots{first, end - first, end - 1};
+}
+
 // A kernel's dynamic-LDS limit (hipFuncSetAttribute) is a property of the kernel on one device: each
 // launcher keeps one of these per kernel and raises the limit the first time it launches on a device.
 // (Two threads that race on a device's first launch both set the same value.)
@@ -74,6 +86,7 @@ hipError_t launch_attn_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a,
 // decode_attn_bf16.hip
 hipError_t launch_attn_pp_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
+hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L);
 hipError_t launch_attn_short_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup *groups, int n_groups,

@@ -19,6 +19,8 @@ constexpr int kF32Keys = 64;         // fp32 kernel: keys per tile of the plan
 constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item whose block ids are kept in LDS (those of longer ranges are fetched one by one)
 constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
+constexpr int kShortFold = 8;        // short-launch kernel: up to so many partitions the last one to end combines them
+
 constexpr int kArrivalStride = 32, kArrivalStrideBig = 8;   // integers from one arrival counter to the next: a cache line each, in large plans a quarter of one
 
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
@@ -66,6 +68,9 @@ struct BatchDev {
     const int32_t *seg_len;       // [n_seg]
     const int32_t *seg_slot;      // [n_seg] table slot holding the segment's table
     const StitchBlk *stitch_blk;  // [n_stitch_blk]
+    const int32_t *part_tab;      // where a launch of its own combines partials by row (else null): [sum S] partitions of each suffix token
+                                  // where slots are evenly spaced, [sum S + 1] first slot of each where they are packed
+    int32_t part_stride;          // slots from token to token, 0: packed
     const int32_t *tok_q;         // [sum S] query index of each suffix token
     const int32_t *rope_pos0;     // [B] position of each query's first schema token (re-encoding stitch), else null
     const double *rope_rev_freq;  // [D/2] theta^(-2i/D) / (2 pi): revolutions per position step, else null
@@ -112,7 +117,7 @@ struct AttnArgs {
     int32_t n_items;
     int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
-    int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches
+    int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches; null: a launch of its own combines them
     int32_t arrival_stride;
     int32_t part_f32;    // partials in fragment order are fp32 (else fp16)
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)

@@ -76,3 +76,11 @@ def test_range_of_the_whole_block_id_table(H):
 def test_chosen_for_a_short_question(H):
     """The automatic choice takes it for a few tokens against a few tables, and leaves it where rows abound."""
     _run(H, 28, 4, [300, 401, 233], [[0, 1, 2]], [17], (0,), kind=0)
+
+
+@pytest.mark.parametrize("hq,hkv", [(28, 4), (8, 8), (5, 1)])
+def test_up_to_eight_ranges_and_more(H, hq, hkv):
+    """Eight ranges are combined inside the launch, nine and more by one of its own: slots for the most ranges everywhere, or
+    packed where a query has too few key tiles for that."""
+    _run(H, hq, hkv, [1300, 700], [[0], [1], [0, 1]], [17, 33, 2], (7, 8, 9, 16, 17, 22))
+    _run(H, hq, hkv, [1300, 100], [[0], [1], [0, 1]], [5, 60, 2], (9, 22))

@@ -541,3 +541,19 @@ def test_long_launch_ranges_go_by_the_chiplets(exe, Hq, Hkv, PS):
     assert info["max_splits"] > 1
     others = [ends(_plan(exe, Hq, Hkv, PS, kernel=4, splits=ns)[1]) for ns in range(1, 13)]
     assert ends(items) <= 1.1 * min(others) + 3.0, (info["max_splits"], ends(items), others)
+
+
+def test_few_tokens_over_many_tables_stay_with_the_short_launch_kernel(exe):
+    """Nine ranges and more are combined by a launch of its own, which costs no more than before there was any other way: such
+    batches are not given to a kernel that keeps partials in fp16.  Up to eight need no table for that launch."""
+    for Hq, Hkv in ((28, 4), (32, 8), (40, 8)):
+        for PS in ([(2026, 7)], [(4800, 3)], [(8000, 8)]):
+            info, items = _plan(exe, Hq, Hkv, PS)
+            _check_plan(info, items, Hq, Hkv, PS)
+            assert info["brief"] and info["max_splits"] > 8, (Hq, Hkv, PS)
+    for PS, even in (([(1500, 17), (600, 3)], True), ([(1500, 3), (100, 17)], False)):
+        for splits in (2, 8, 9, 30):
+            info, items = _plan(exe, 28, 4, PS, kernel=5, splits=splits)
+            _check_plan(info, items, 28, 4, PS)
+            _check_slots(info, items, 28, 128, PS)
+            assert info["brief"] and info["max_splits"] == min(splits, 25) and (info["part_stride"] > 0) == (even and splits > 8)
