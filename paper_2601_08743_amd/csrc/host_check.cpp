@@ -141,7 +141,7 @@ int main()
             } else if (ok && parts_by_row(c, p)) {
                 int32_t at = 0;
                 for (int i = 0; i < p.B; ++i)
-                    for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += p.decode || splits[i] > 1 ? splits[i] : 0) slots.push_back(at);
+                    for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += splits[i] > 1 ? splits[i] : 0) slots.push_back(at);
                 slots.push_back(at);
             }
             std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, items.size(), groups.size()).total, p.compact ? 1 : 0);

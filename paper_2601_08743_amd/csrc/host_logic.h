@@ -470,7 +470,7 @@ inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
     int64_t at = 0;
     for (int i = 0; i < p.B; ++i) {
         first[i] = p.part_stride ? (int64_t)p.cu_seqlens[i] * p.part_stride : at;
-        if (p.decode || splits_of_q[i] > 1) at += (int64_t)p.suffix_len[i] * splits_of_q[i];
+        if (splits_of_q[i] > 1) at += (int64_t)p.suffix_len[i] * splits_of_q[i];
     }
     for (AttnItem &it : items)
         if (it.q >= 0) {
@@ -559,7 +559,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
             ns = std::max(1, std::min(ns, std::max(n_tiles, 1)));
             splits_of_q[i] = ns;
             p.max_splits = std::max(p.max_splits, ns);
-            p.n_part_slots += ns;
+            if (ns > 1) p.n_part_slots += ns;
             const int32_t *bt = p.block_table.data() + (size_t)i * p.max_blocks;
             const uint8_t *pad_of = p.block_pad.empty() ? nullptr : p.block_pad.data() + (size_t)i * p.max_blocks;
             for (int h = 0; h < c.n_kv_heads; ++h)
@@ -584,7 +584,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
         p.decode = p.fold = true;
-        place_partials(c, knobs, p, splits_of_q, items);
+        if (p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -849,7 +849,7 @@ inline bool plan_attention(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
     return true;
 }
 
-inline bool parts_by_row(const tc_config &c, const Plan &p) { return p.decode || ((c.dtype != TC_BF16 || p.brief) && p.max_splits > 1); }
+inline bool parts_by_row(const tc_config &c, const Plan &p) { return (p.decode || c.dtype != TC_BF16 || p.brief) && p.max_splits > 1; }
 
 inline int part_row_floats(const Plan &p) { return p.part_f32 ? 128 : 64; }      // a row's partial in fragment order, without its (maximum, sum)
 

@@ -933,7 +933,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
         a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
-        a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
+        if (p.part) a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
         return TC_OK;
     }

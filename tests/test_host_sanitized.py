@@ -190,13 +190,13 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
 
 
 def _check_slots(info, items, Hq, D, PS):
-    """Partials kept by row: every (token, partition) of a cut query - of any query in a decode step - has a slot
+    """Partials kept by row: every (token, partition) of a cut query, and no other, has a slot
     of its own inside the buffer, and the items write where the merge, going by its table, reads."""
     ns, base = {}, np.cumsum([0] + [S for _, S in PS])
     for it in items:
         if it[0] >= 0:
             ns[it[0]] = it[6]
-    counts = [n if info["decode"] or n > 1 else 0 for q, (_, S) in enumerate(PS) for n in [ns.get(q, 0)] * S]
+    counts = [n if n > 1 else 0 for q, (_, S) in enumerate(PS) for n in [ns.get(q, 0)] * S]
     if info["part_stride"]:                      # evenly spaced
         assert info["part_tab"] == counts and info["part_stride"] == info["max_splits"]
         first, n_slots = [n * info["part_stride"] for n in range(len(counts))], len(counts) * info["part_stride"]
@@ -206,7 +206,7 @@ def _check_slots(info, items, Hq, D, PS):
         first, n_slots = info["part_tab"][:-1], sum(counts)
     assert info["part_floats"] == n_slots * Hq * (D + 2)
     for it, (part0, stride) in zip(items, info["item_part"]):
-        if it[0] >= 0 and (info["decode"] or it[6] > 1):
+        if it[0] >= 0 and it[6] > 1:
             for t in range(PS[it[0]][1]):
                 assert part0 + t * stride + it[5] == first[base[it[0]] + t] + it[5] < n_slots
 
@@ -262,6 +262,16 @@ def test_plan_of_least_space(exe):
         rows = sum(S for _, S in PS) * Hkv * G
         if (rows <= 1e5 and dtype == 0) or rows <= 2e4:
             assert info["ints"] <= PLAN_INTS and info["part_floats"] <= WORKSPACE, (dtype, Hkv, G, PS)
+
+
+def test_sequences_in_one_range_need_no_partials(exe):
+    """A decode step writes the row of a sequence in one range directly: as many of them as the plan has room for fit the
+    workspace, and beside cut ones they take no slots."""
+    info, items = _plan(exe, 32, 1, [(300, 1)] * 3900, within=(PLAN_INTS, WORKSPACE))
+    assert info["decode"] and not info["compact"] and info["max_splits"] == 1 and info["part_floats"] == 0
+    info, items = _plan(exe, 32, 8, [(20000, 1)] + [(200, 1)] * 20)
+    _check_slots(info, items, 32, 128, [(20000, 1)] + [(200, 1)] * 20)
+    assert info["decode"] and info["part_floats"] == info["max_splits"] * 32 * 130 and info["max_splits"] > 1
 
 
 def test_planner_partition_limit_with_forced_splits(exe):
