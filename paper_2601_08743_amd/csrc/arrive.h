@@ -119,7 +119,7 @@ __device__ __forceinline__ float sum32(float x) { return reduce32(x, [](float a,
 // alone on its SIMD - and one round trip, so: up to 36 partials are requested at once, and slots
 // beyond the group's last read as zeros; their weights come from one lane each and go around through LDS, where
 // one shuffle and one branch a partial took three times as long (17 partials: 3.4 -> 1.3 us).
-constexpr int kFoldBatch = 36, kFoldGroup = 12;
+constexpr int kFoldBatch = kDecodeFold, kFoldGroup = 12;
 __device__ __forceinline__ RowSum fold_partials(const SharedPart &po, const SharedPart &pml, int row, int rows, int n, int first, int step, int lane, float *s_w)
 {
     RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};

@@ -20,7 +20,9 @@
 // At the end the four waves' (max, sum, O) are combined through LDS.  A work-group that has all the keys of its (query, KV
 // head) adds the new token itself (its key and value come from k_new / v_new: one dot product and one scaled row per
 // head) and writes the output; one of several stores one partial per row, and the last of them to end combines them
-// (arrive.h).  The new token's K/V are appended to the pool by the first key range of each (query, KV head): extra
+// (arrive.h): up to 36, one round of loads, of up to eight heads, a row for every 32 threads, 72 of up to four.  More are combined by a
+// launch of its own: a second round on one CU takes longer than that (one sequence of 4.7 k tokens in 37 ranges, 32 / 1
+// heads, 18.0 us in one launch, 10.0 in two; 24 / 2 heads 11.7 against 9.4; 28 / 4 heads in 33 8.7 against 9.5, in 72 13.9 against 12.8).  The new token's K/V are appended to the pool by the first key range of each (query, KV head): extra
 // work-groups for it, as in prefill, would each wait for a CU's LDS.
 //
 // Measured, a layer of a token step (28 / 4 heads unless said; in parentheses with a second launch that combined the
@@ -54,10 +56,10 @@ constexpr float kDecRescale = 8.f;
 
 // Four columns of the new token's key and value and of one head's query row.
 struct SelfRaw { uint2 q, k, v; };
-__device__ __forceinline__ SelfRaw load_self(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d)
+__device__ __forceinline__ SelfRaw load_self(const Geom &g, const AttnArgs &a, int token, int kvh, int head, int d)
 {
-    const int64_t kv = ((int64_t)it.cu * g.Hkv + it.kvh) * 128 + d;
-    return SelfRaw{*(const uint2 *)((const unsigned short *)a.q + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d),
+    const int64_t kv = ((int64_t)token * g.Hkv + kvh) * 128 + d;
+    return SelfRaw{*(const uint2 *)((const unsigned short *)a.q + ((int64_t)token * g.Hq + head) * 128 + d),
                 *(const uint2 *)((const unsigned short *)a.k_new + kv), *(const uint2 *)((const unsigned short *)a.v_new + kv)};
 }
 
@@ -91,6 +93,8 @@ __device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, con
     write_row((unsigned short *)a.out + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d, x);
 }
 
+// kFold: the last work-group of a (query, KV head) combines its ranges' partials; else they are left to a merge launch.
+template <bool kFold>
 __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -153,10 +157,12 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
     // loads are issued here, ahead of the counted ones, the stores come at the very end (a store counts
     // as an outstanding memory operation).  Behind the token the block is zero, as after every append.
     // K: thread -> 16 bytes of one token row.  V^T: thread d -> the 16 tokens of row d, merged.
-    // (The new token's own key and value, and the query row that meets them, are needed last of all: requested here, too.)
+    // (The new token's own key and value, and the query row that meets them, are needed last of all: requested here, too,
+    // where most work-groups or the last of each (query, KV head) will need them.)
     const bool appends = it.split == 0;
     const int slot8 = tid >> 5, d4 = 4 * (tid & 31);   // at the end: eight groups of 32 threads, four columns each
-    const SelfRaw self_raw = load_self(g, a, it, min(slot8, G - 1), d4);
+    SelfRaw self_raw{};
+    if (kFold) self_raw = load_self(g, a, it.cu, it.kvh, it.kvh * G + min(slot8, G - 1), d4);
     const int t_new = P & 15;
     char *k_dst = nullptr, *v_dst = nullptr;
     uint4 k_put = make_uint4(0, 0, 0, 0), v_old0 = k_put, v_old1 = k_put;
@@ -339,55 +345,62 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
         }
     }
     __syncthreads();
-    const Self self = score_self(self_raw, c);
+    Self self{};
+    if (kFold) self = score_self(self_raw, c);
     const int64_t first_slot = (int64_t)it.part0 * g.Hq + (int64_t)it.kvh * G * it.n_splits;
     const uint32_t n_slots = (uint32_t)(it.n_splits * G);
     const SharedPart part_o(a.part_o + first_slot * 128, n_slots * 512), part_ml(a.part_ml + first_slot * 2, n_slots * 8);
-    for (int idx = tid; idx < G * 32; idx += 256) {
-        const int row = idx >> 5, d = d4;
-        float M = -INFINITY;
+    auto fold_waves = [&](int row) {
+        RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) M = fmaxf(M, ((const float *)(lds + k * kDecWave))[32 * kDecRow + 2 * row]);
-        float L = 0.f;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 4; ++k) x.M = fmaxf(x.M, ((const float *)(lds + k * kDecWave))[32 * kDecRow + 2 * row]);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float *wk = (const float *)(lds + k * kDecWave);
             const float mk = wk[32 * kDecRow + 2 * row];
-            const float wgt = (mk == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mk - M);
-            L += wgt * wk[32 * kDecRow + 2 * row + 1];
-            const f32x4 v = *(const f32x4 *)(wk + row * kDecRow + d);
+            const float wgt = (mk == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mk - x.M);
+            x.L += wgt * wk[32 * kDecRow + 2 * row + 1];
+            const f32x4 v = *(const f32x4 *)(wk + row * kDecRow + d4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
+            for (int e = 0; e < 4; ++e) x.acc[e] += wgt * v[e];
         }
-        if (it.n_splits == 1) {
-            finish_row(g, a, it, row, d, row == slot8 ? self : score_self(load_self(g, a, it, row, d), c), RowSum{M, L, acc});
-        } else {
-            const uint32_t off = (uint32_t)(it.split * G + row);
-            part_o.put4(off * 512 + d * 4, acc);
-            if (d == 0) part_ml.put2(off * 8, M, L);
+        return x;
+    };
+    if (!kFold && it.n_splits > 1) {
+        for (int row = slot8; row < G; row += 8) {
+            const RowSum x = fold_waves(row);
+            const int64_t slot = (int64_t)(it.part0 + it.split) * g.Hq + it.kvh * G + row;
+            *(f32x4 *)(a.part_o + slot * 128 + d4) = x.acc;
+            if (d4 == 0) *(float2 *)(a.part_ml + slot * 2) = make_float2(x.M, x.L);
+        }
+    } else {
+        for (int row = slot8; row < G; row += 8) {
+            const RowSum x = fold_waves(row);
+            if (it.n_splits == 1) {
+                finish_row(g, a, it, row, d4, kFold && row == slot8 ? self : score_self(load_self(g, a, it.cu, it.kvh, it.kvh * G + row, d4), c), x);
+            } else {
+                const uint32_t off = (uint32_t)(it.split * G + row);
+                part_o.put4(off * 512 + d4 * 4, x.acc);
+                if (d4 == 0) part_ml.put2(off * 8, x.M, x.L);
+            }
         }
     }
-    if (it.n_splits > 1 && last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, it.n_splits, (int32_t *)(lds + kDecIds))) {
+    if (kFold && it.n_splits > 1 && last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, it.n_splits, (int32_t *)(lds + kDecIds))) {
         // a row to 32 threads; of up to four rows two such groups take every other partition each
         const bool two = G <= 4;
         float *s_w = (float *)lds + 8 * kDecRow + slot8 * kFoldBatch;
-        for (int r0 = 0; r0 < G; r0 += 8) {
-            const int row = two ? slot8 & 3 : r0 + slot8, half = two ? slot8 >> 2 : 0;
-            RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
-            if (row < G) x = fold_partials(part_o, part_ml, row, G, it.n_splits, half, two ? 2 : 1, tid & 31, s_w);
-            if (two) {
-                float *sx = (float *)lds + slot8 * kDecRow;
-                *(f32x4 *)(sx + d4) = x.acc;
-                if (d4 == 0) { sx[128] = x.M; sx[129] = x.L; }
-                __syncthreads();
-                const float *other = (const float *)lds + (slot8 | 4) * kDecRow;
-                if (half == 0) x.add(other[128], other[129], *(const f32x4 *)(other + d4));
-            }
-            if (row < G && half == 0) {
-                finish_row(g, a, it, row, d4, row == slot8 ? self : score_self(load_self(g, a, it, row, d4), c), x);
-            }
+        const int row = two ? slot8 & 3 : slot8, half = two ? slot8 >> 2 : 0;
+        RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
+        if (row < G) x = fold_partials(part_o, part_ml, row, G, it.n_splits, half, two ? 2 : 1, tid & 31, s_w);
+        if (two) {
+            float *sx = (float *)lds + slot8 * kDecRow;
+            *(f32x4 *)(sx + d4) = x.acc;
+            if (d4 == 0) { sx[128] = x.M; sx[129] = x.L; }
+            __syncthreads();
+            const float *other = (const float *)lds + (slot8 | 4) * kDecRow;
+            if (half == 0) x.add(other[128], other[129], *(const f32x4 *)(other + d4));
         }
+        if (row < G && half == 0) finish_row(g, a, it, row, d4, self, x);
     }
     if (appends) {
         if ((tid >> 4) >= t_new) *(uint4 *)k_dst = k_put;
@@ -413,10 +426,12 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
     if (g.D != 128 || g.esize != 2 || g.G > 32) return hipErrorInvalidValue;
     static PerDeviceOnce configured;
     const hipError_t e = configured.run([] {
-        return hipFuncSetAttribute((const void *)decode_attn_bf16_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDecLds);
+        const hipError_t e0 = hipFuncSetAttribute((const void *)decode_attn_bf16_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kDecLds);
+        return e0 != hipSuccess ? e0 : hipFuncSetAttribute((const void *)decode_attn_bf16_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kDecLds);
     });
     if (e != hipSuccess) return e;
-    TC_LAUNCH(decode_attn_bf16_kernel, a.n_items, kDecLds, L, g, b, a);
+    if (a.part_o && !a.arrivals) TC_LAUNCH(decode_attn_bf16_kernel<false>, a.n_items, kDecLds, L, g, b, a);
+    else TC_LAUNCH(decode_attn_bf16_kernel<true>, a.n_items, kDecLds, L, g, b, a);
     return hipGetLastError();
 }
 
@@ -424,8 +439,8 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
 // Partials by row combined by a launch of its own, where one CU would take longer over a row tile's than that: 32 threads, four
 // columns each, per (suffix token, query head) row and group of partitions; a row's kGroups groups take every kGroups-th
 // partition and are combined through LDS.  Bound: the latency of the loads of a short launch, so those of four partitions are issued
-// before the first use, and (kEven) before it is known how many there are.
-template <int kGroups, bool kEven>
+// before the first use, and (kEven) before it is known how many there are.  kSelf: a decode step, the new token joins.
+template <int kGroups, bool kSelf, bool kEven>
 __global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b, AttnArgs a, int max_splits)
 {
     constexpr int kBatch = 4, kRows = 8 / kGroups;
@@ -434,7 +449,7 @@ __global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b
     const int64_t n_rows = (int64_t)b.total_S * g.Hq;
     const int64_t want = (int64_t)blockIdx.x * kRows + slot8 / kGroups;
     const int row = (int)min(want, n_rows - 1);        // (the last work-group may have rows to spare: they repeat the last one)
-    const int n = row / g.Hq, head = row - n * g.Hq;
+    const int n = row / g.Hq, head = row - n * g.Hq;      // n: the token (queries may bring none)
     const PartSlots slots = part_slots<kEven>(b, n);
     float2 ml[kBatch];
     f32x4 po[kBatch];
@@ -447,6 +462,8 @@ __global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b
             po[j] = *(const f32x4 *)(a.part_o + slot * 128 + d);
         }
     };
+    SelfRaw self;
+    if (kSelf) self = load_self(g, a, n, head / g.G, head, d);
     if (kEven || slots.count > 0) fetch(grp);
     const int ns = slots.count;
     RowSum x{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
@@ -462,27 +479,32 @@ __global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b
         __syncthreads();
     }
     if (grp > 0 || want >= n_rows || ns <= 1) return;          // (a row in one range was written by the attention kernel)
+    if (kSelf) {
+        const Self s = score_self(self, a.scale_log2);
+        x.add(s.score, 1.f, s.v);
+    }
 #pragma unroll
     for (int k = 1; k < kGroups; ++k) x.add(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
     write_row((unsigned short *)a.out + (int64_t)row * 128 + d, x);
 }
 
-template <bool kEven>
+template <bool kSelf, bool kEven>
 static hipError_t launch_merge_rows(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
 {
     const int n_rows = b.total_S * g.Hq;
     if (n_rows == 0) return hipSuccess;
     if (max_splits < 1 || !b.part_tab) return hipErrorInvalidValue;
-    if (max_splits <= 4) TC_LAUNCH((merge_rows_bf16_kernel<1, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 8) TC_LAUNCH((merge_rows_bf16_kernel<2, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
-    else if (max_splits <= 16) TC_LAUNCH((merge_rows_bf16_kernel<4, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
-    else TC_LAUNCH((merge_rows_bf16_kernel<8, kEven>), n_rows, 0, L, g, b, a, max_splits);
+    if (max_splits <= 4) TC_LAUNCH((merge_rows_bf16_kernel<1, kSelf, kEven>), (n_rows + 7) / 8, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 8) TC_LAUNCH((merge_rows_bf16_kernel<2, kSelf, kEven>), (n_rows + 3) / 4, 0, L, g, b, a, max_splits);
+    else if (max_splits <= 16) TC_LAUNCH((merge_rows_bf16_kernel<4, kSelf, kEven>), (n_rows + 1) / 2, 0, L, g, b, a, max_splits);
+    else TC_LAUNCH((merge_rows_bf16_kernel<8, kSelf, kEven>), n_rows, 0, L, g, b, a, max_splits);
     return hipGetLastError();
 }
 
-hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, const Launch &L)
+hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, bool decode, const Launch &L)
 {
-    return b.part_stride > 0 ? launch_merge_rows<true>(g, b, a, max_splits, L) : launch_merge_rows<false>(g, b, a, max_splits, L);
+    if (decode) return b.part_stride > 0 ? launch_merge_rows<true, true>(g, b, a, max_splits, L) : launch_merge_rows<true, false>(g, b, a, max_splits, L);
+    return b.part_stride > 0 ? launch_merge_rows<false, true>(g, b, a, max_splits, L) : launch_merge_rows<false, false>(g, b, a, max_splits, L);
 }
 
 }  // namespace tc

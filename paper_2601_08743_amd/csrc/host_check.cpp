@@ -18,7 +18,7 @@
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
 //                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0 part_stride" per item,
 //                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, for kernels that keep partials by row, their table (without a launch that goes by one: where each suffix token's begin),
-//                                      "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
+//                                      "merges <0 or 1>" (partials by row have a merge launch), "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
 //   pipeline <n_queries> <capacity> <b_c> <b_m> <keep_pinned> <taper> then per query "<k> ids..."
@@ -148,6 +148,7 @@ int main()
             std::printf("parts %zu %d", part_floats(c, p), p.part_stride);
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");
+            std::printf("merges %d\n", merges_rows(c, p) ? 1 : 0);
             std::printf("part_f32 %d\n", p.part_f32 ? 1 : 0);
             std::printf("groups %d %d\n", (int)groups.size(), p.n_groups);
             for (const MergeGroup &mg : groups) std::printf("g %d %d %d %d %d\n", mg.kvh, mg.m0, mg.n_splits, mg.cu, mg.S);

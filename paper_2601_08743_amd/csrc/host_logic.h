@@ -537,13 +537,16 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 else lo = mid + 1;
             }
             L = lo;
-            // The last work-group of a (query, KV head) folds the partials of all of them: 36 in one round of loads, each
-            // one more 0.07 us, against 0.65 us for each unit more that a wave takes.  At least two thirds of the
-            // work-groups stay, for the loads that they have in flight.  (One sequence, 28 / 4 heads, us a launch: 7.2 k tokens in
-            // 57 ranges of two tiles 10.4, 38 of three 9.4; 14.4 k in 57 of four 14.1, 38 of six 12.5.)
-            auto cost = [&](int l) { return 0.65 * ((l + 1) / 2) + 0.07 * std::max((longest + l - 1) / l - 36, 0); };
-            for (int l = lo + 1; l <= std::min(lo * 3 / 2, kAttnMaxTiles); ++l)
-                if (cost(l) < cost(L) - 1e-9) L = l;
+            // Up to 36 partials of a (query, KV head), 72 of four heads or fewer, are folded by the last work-group of it to end,
+            // more by a launch of its own, which is 0.9 us.  Where the longest sequence would need that, ranges up to twice as
+            // long - half of the work-groups stay, for the loads that they have in flight - are taken if they come out ahead: each
+            // unit more that a wave takes is 0.65 us, each partial 0.035.  (One sequence, 28 / 4 heads, us a layer: 4.7 k tokens in 37
+            // ranges of two tiles 9.9, in 25 of three 8.3; 15.7 k in 62 of four 12.8, in 31 of eight 12.3.)
+            auto parts = [&](int l) { return (longest + l - 1) / l; };
+            auto cost = [&](int l) { return 0.65 * ((l + 1) / 2) + 0.035 * parts(l) + (decode_folds(G, parts(l)) ? 0.0 : 0.9); };
+            if (G <= 8 && !decode_folds(G, parts(lo)))
+                for (int l = lo + 1; l <= std::min(lo * 2, kAttnMaxTiles); ++l)
+                    if (cost(l) < cost(L) - 1e-9) L = l;
             // Up to six tiles - three units a wave - one range needs no partials and no arrival (one sequence of 200 tokens
             // 5.3 us against 7.0 in two ranges; of 500, eight tiles, 7.2 against 6.9 in four).
             if (longest <= 6) L = std::max(L, longest);
@@ -583,7 +586,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.row_blocks = 1;
         p.n_items = (int32_t)items.size();
         p.pipelined = false;
-        p.decode = p.fold = true;
+        p.decode = true;
+        p.fold = decode_folds(G, p.max_splits);
+        if (!p.fold) p.n_arrivals = 0;
         if (p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;

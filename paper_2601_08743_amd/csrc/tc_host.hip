@@ -935,6 +935,8 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
         if (p.part) a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
+        if (p.dev.part_tab)
+            TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, true, ln); }));
         return TC_OK;
     }
     AttnArgs a{};
@@ -956,7 +958,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
     if (p.dev.part_tab)
-        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, ln); }));
+        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, false, ln); }));
     else if (p.groups_dev)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
             return launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln);

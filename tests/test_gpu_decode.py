@@ -332,3 +332,29 @@ def test_decode_partials_folded_by_the_last_work_group(H, G):
     dw.close()
     # averages of thousands of N(0, 1) values: 2^-9 of a weight and of the output's ~0.05, as in the tests above
     assert worst <= 1e-2, worst
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 1), (7, 1), (24, 2)])
+def test_decode_partials_merged_by_a_launch(H, hq, hkv):
+    """More ranges, or heads, than the fold takes: one long sequence among short ones (packed slots; some sequences in one range,
+    one without a key), and alone (slots evenly spaced); every plan twice."""
+    for queries in ([list(range(8)), [0], [], [1], [], [2], [0]], [list(range(8))]):
+        cfg = W.WorkloadConfig(name="decmerge", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, dtype="bf16", n_tables=8,
+                               table_len=(640, 640), batch=len(queries), tables_per_query=(0, 8), choice="uniform", suffix_len=(1, 1),
+                               capacity=8, seed=409)
+        wl = W.make_workload(cfg)
+        wl.table_len[:3] = [640, 50, 100]
+        wl.queries[:] = [np.array(q, dtype=np.int32) for q in queries]
+        dw = H.DeviceWorkload(wl)
+        for splits in (40, 0):
+            dw.ctx.tc_set_kv_splits(splits)
+            bt, pl = dw.stitch()
+            (out, qkv), (again, _) = dw.attn_layer(0, bt, pl), dw.attn_layer(0, bt, pl)
+            assert dw.ctx.tc_attn_kernel() == 3 and torch.equal(out, again)
+            got, ref = H.out_to_f64(out, cfg), H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+            for i, r in ref.items():
+                # a key or two may dominate a row: 2 * 2^-9 of values up to 5.5, as in the tests above
+                err = float(np.abs(got[i:i + 1] - r).max())
+                assert err <= 2.2e-2, (splits, i, err)
+            dw.ctx.tc_release_seqs(bt)
+        dw.close()

@@ -134,6 +134,7 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0,
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
                 n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
+    info["merges"] = int([l for l in lines if l.startswith("merges")][0].split()[1])
     info["part_f32"] = int([l for l in lines if l.startswith("part_f32")][0].split()[1])
     info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
     info["part_floats"], info["part_stride"], *info["part_tab"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
@@ -567,3 +568,16 @@ def test_few_tokens_over_many_tables_stay_with_the_short_launch_kernel(exe):
             _check_plan(info, items, 28, 4, PS)
             _check_slots(info, items, 28, 128, PS)
             assert info["brief"] and info["max_splits"] == min(splits, 25) and (info["part_stride"] > 0) == (even and splits > 8)
+
+
+def test_decode_partials_are_folded_in_one_round_of_loads_or_merged(exe):
+    """Up to 36 ranges of up to eight query heads per KV head, 72 of up to four, are combined inside the launch, any other cut by a launch that
+    goes by the table of slots - and where that is needed, ranges are not made longer to have fewer of them."""
+    for Hq, Hkv, P, splits, merged in ((8, 1, 64 * 40, 36, 0), (8, 1, 64 * 40, 37, 1), (9, 1, 64 * 40, 2, 1), (32, 1, 64 * 40, 36, 1),
+                                       (64, 8, 64 * 40, 36, 0), (4, 1, 64 * 90, 72, 0), (4, 1, 64 * 90, 73, 1), (5, 1, 64 * 90, 37, 1), (28, 4, 4700, 0, 0), (32, 1, 4700, 0, 1), (8, 1, 18000, 0, 1)):
+        info, items = _plan(exe, Hq, Hkv, [(P, 1), (100, 1), (0, 1)], splits=splits)
+        _check_plan(info, items, Hq, Hkv, [(P, 1), (100, 1), (0, 1)])
+        _check_slots(info, items, Hq, 128, [(P, 1), (100, 1), (0, 1)])
+        assert info["decode"] and info["merges"] == merged, (Hq, Hkv, P, info["max_splits"])
+    info, items = _plan(exe, 32, 1, [(18000, 1)])
+    assert info["max_splits"] == -(-18000 // 128)          # ranges of two tiles: no fewer partials than CUs to read keys with
