@@ -232,7 +232,8 @@ struct PlanKnobs {
 // instructions), about one more for start and end; a CU does that for one item at 0.8 of the full rate
 // or for two at half the rate each.  Items are nearly equal, so they run in rounds of 512, and what
 // a launch takes is its full rounds plus the last one, however few items that holds: ranges are cut
-// so that the rounds come out full.  The merge costs a launch of ~2.5 us and its traffic.
+// so that the rounds come out full.  The merge costs a launch of ~2.5 us and its traffic (up to eight ranges of heads of 64, which
+// have none, 0.3 .. 1.5 us less, which the choice does not turn on).
 // Measured (8 queries, 23 k keys, 8 / 2 heads of 64): 102 us against 118..127 us for one or two ranges a query.
 inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap)
 {
@@ -811,8 +812,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     while (!items.empty() && items.back().q < 0) items.pop_back();
     p.n_items = (int32_t)items.size();
     // (the short-launch kernel: eight partials of a row in one round of loads; a launch of its own for them is 0.2 .. 1 us slower up
-    // to there, and beyond, where one CU has a second round, 0.5 .. 5 us faster)
-    p.fold = by_row && p.max_splits > 1 && (!p.brief || p.max_splits <= kShortFold);
+    // to there, and beyond, where one CU has a second round, 0.5 .. 5 us faster; the fp32 kernel: 0.3 .. 1.5 us slower up to eight
+    // partials of 64 columns, beyond 0 .. 5 us faster, of 128 columns 0 .. 9 us faster from five on)
+    p.fold = by_row && p.max_splits > 1 && (p.brief ? p.max_splits <= kShortFold : c.head_dim == 64 && !ctx->compact && p.max_splits <= kF32Fold);
     if (!p.fold) p.n_arrivals = 0;
     if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one

@@ -17,7 +17,10 @@
 // O^T += V^T . P^T for the key pair that its two lane halves stand for; V is read from its token rows
 // D/32 neighbouring columns at a time.
 //
-// A query in several ranges: the last of a row tile's ranges to end combines their partials (arrive.h).
+// A query in several ranges: the last of a row tile's ranges to end combines their partials (arrive.h), or a launch of its own does
+// where one CU would take longer: heads of 128, whose partials are twice as large, and more than eight ranges (two round
+// trips).  Us a layer, in one launch and in two: one query of 1.6 k + 64 tokens, 8 / 2 heads of 64, 4 ranges 18.4 and 19.5, 8 13.9
+// and 13.9, 16 13.7 and 12.6; of 128, 4 32.1 and 31.9, 8 23.8 and 22.2, 16 22.7 and 19.1.
 //
 // Measured (8 queries, 23 k prefix and 1.4 k suffix tokens, 8 query / 2 KV heads of 64: 8.3 GFLOP): 109 us a layer with
 // the ranges combined (110 with a launch of its own for that: 102 + 4.5 us and the gap between them); one wave per row
@@ -47,7 +50,8 @@ struct F32Lds {
 
 // kLong: some range of the batch has more key tiles than the table in LDS has block ids for; the planner makes such
 // ranges only for a workspace that has no room for the partials of shorter ones.
-template <int D, bool kLong>
+// kFold: the last work-group of a row tile combines its ranges' partials; else they are left to a merge launch.
+template <int D, bool kLong, bool kFold>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, BatchDev b, AttnArgs a)
 {
     typedef F32Lds<D> L;
@@ -300,20 +304,28 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         const int tok = mr / G;
         *(f32x4 *)((float *)a.out + ((int64_t)(it.cu + tok) * g.Hq + it.kvh * G + (mr - tok * G)) * D + 4 * d4) = acc;
     };
-    if (it.n_splits == 1) {
+    if (!kFold || it.n_splits == 1) {
 #pragma unroll 2
         for (int r = r0; r < kF32Rows; r += kPass) {
-            if (it.m0 + r >= n_rows) continue;
+            const int mr = it.m0 + r;
+            if (mr >= n_rows) continue;
             float M, sum;
             const f32x4 acc = fold_waves(r, M, sum);
-            write(it.m0 + r, acc, sum);
+            if (kFold || it.n_splits == 1) {
+                write(mr, acc, sum);
+            } else {
+                const int tok = mr / G;
+                const int64_t prow = (int64_t)(it.part0 + tok * it.part_stride + it.split) * g.Hq + it.kvh * G + (mr - tok * G);
+                *(f32x4 *)(a.part_o + prow * D + 4 * d4) = acc;
+                if (d4 == 0) *(float2 *)(a.part_ml + prow * 2) = make_float2(M, sum);
+            }
         }
         return;
     }
 
     // ---- a range of several: its partial, and by the last work-group of the row tile to end the rows from all of them (arrive.h):
     // with reference maxima m_s (log2 units), sums l_s and unnormalised outputs O_s, sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-    // All of a thread's rows at a time, four partials a round trip.
+    // All of a thread's rows at a time, four partials a round trip, eight at most.
     const int tok0 = it.m0 / G, m_last = min(it.m0 + kF32Rows, n_rows) - 1, ns = it.n_splits;
     const int64_t first_slot = ((int64_t)it.part0 + (int64_t)tok0 * it.part_stride) * g.Hq + it.kvh * G;
     const uint32_t n_slots = (uint32_t)min((int64_t)(m_last / G - tok0 + 1) * it.part_stride * g.Hq, (int64_t)(0x7fffffff / (D * 4)));
@@ -374,24 +386,104 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         if (it.m0 + r0 + j * kPass <= m_last) write(it.m0 + r0 + j * kPass, acc[j], den[j]);
 }
 
-template <int D, bool kLong>
+template <int D, bool kLong, bool kFold>
 static hipError_t launch_attn(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
     static PerDeviceOnce configured;
     const hipError_t e = configured.run([] {
-        return hipFuncSetAttribute((const void *)attn_f32_kernel<D, kLong>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<D>::kBytes);
+        return hipFuncSetAttribute((const void *)attn_f32_kernel<D, kLong, kFold>, hipFuncAttributeMaxDynamicSharedMemorySize, F32Lds<D>::kBytes);
     });
     if (e != hipSuccess) return e;
-    TC_LAUNCH((attn_f32_kernel<D, kLong>), a.n_items + a.n_append, F32Lds<D>::kBytes, L, g, b, a);
+    TC_LAUNCH((attn_f32_kernel<D, kLong, kFold>), a.n_items + a.n_append, F32Lds<D>::kBytes, L, g, b, a);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
 {
     if (a.n_items + a.n_append == 0) return hipSuccess;
-    if (g.D == 64) return a.long_ranges ? launch_attn<64, true>(g, b, a, L) : launch_attn<64, false>(g, b, a, L);
-    if (g.D == 128) return a.long_ranges ? launch_attn<128, true>(g, b, a, L) : launch_attn<128, false>(g, b, a, L);
+    const bool fold = a.part_o && a.arrivals;
+    if (fold && (g.D != 64 || a.long_ranges)) return hipErrorInvalidValue;        // (the planner's rule)
+    if (g.D == 64 && fold) return launch_attn<64, false, true>(g, b, a, L);
+    if (g.D == 64) return a.long_ranges ? launch_attn<64, true, false>(g, b, a, L) : launch_attn<64, false, false>(g, b, a, L);
+    if (g.D == 128) return a.long_ranges ? launch_attn<128, true, false>(g, b, a, L) : launch_attn<128, false, false>(g, b, a, L);
     return hipErrorInvalidValue;
+}
+
+// ------------------------------------------------------------------------------------ merge
+// Combine split-KV partials of one output row: with reference maxima m_s (log2 units), sums l_s
+// and unnormalised partial outputs O_s:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+// D/4 threads per (suffix token, head) row, four columns each.  Bound: the latency of the loads of a
+// short launch, so those of eight partitions are issued before the first use, and (kEven) before it is known how
+// many there are (slots beyond a token's last partition are loaded and ignored).
+// Measured (2 queries, 9 k keys, 2 + 59 tokens, 20 partitions): 5.3 us; one partition after the other 18.4 us.
+template <int D, bool kEven>
+__global__ __launch_bounds__(256) void merge_f32_kernel(Geom g, BatchDev b, AttnArgs a)
+{
+    constexpr int kThreads = D / 4;
+    constexpr int kBatch = 8;
+    const int64_t row = (int64_t)blockIdx.x * (256 / kThreads) + threadIdx.x / kThreads;
+    const int d = 4 * (threadIdx.x % kThreads);
+    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
+    if (row >= n_rows) return;
+    const int n = (int)(row / g.Hq), head = (int)(row - (int64_t)n * g.Hq);
+    const PartSlots slots = part_slots<kEven>(b, n);
+    if (!kEven && slots.count <= 1) return;      // written directly by the attention kernel
+    float2 ml[kBatch];
+    f32x4 po[kBatch];
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int64_t slot = (int64_t)min(slots.first + s0 + j, slots.last) * g.Hq + head;
+            ml[j] = *(const float2 *)(a.part_ml + slot * 2);
+            po[j] = *(const f32x4 *)(a.part_o + slot * D + d);
+        }
+    };
+    fetch(0);
+    const int ns = slots.count;
+    if (kEven && ns <= 1) return;
+    float M = -INFINITY, den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < ns; s0 += kBatch) {
+        if (s0 > 0) fetch(s0);
+        float Mc = M;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) Mc = s0 + j < ns ? fmaxf(Mc, ml[j].x) : Mc;
+        const float r = M == -INFINITY ? 0.f : exp2f(M - Mc);
+        den *= r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] *= r;
+        M = Mc;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (s0 + j >= ns) continue;
+            // a partition without a maximum saw no key of this row (sum and output are 0) or only scores that are NaN
+            // (so are they, and so is the row)
+            const float wgt = ml[j].x == -INFINITY ? 1.f : exp2f(ml[j].x - M);
+            den = fmaf(wgt, ml[j].y, den);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, po[j][e], acc[e]);
+        }
+    }
+    const float inv = 1.f / den;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= inv;
+    *(f32x4 *)((float *)a.out + row * D + d) = acc;
+}
+
+hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L)
+{
+    const int64_t n_rows = (int64_t)b.total_S * g.Hq;
+    if (n_rows == 0) return hipSuccess;
+    if (!b.part_tab) return hipErrorInvalidValue;
+    const int per = 256 / (g.D / 4);
+    const int grid = (int)((n_rows + per - 1) / per);
+    const bool even = b.part_stride > 0;
+    if (g.D == 64 && even) TC_LAUNCH((merge_f32_kernel<64, true>), grid, 0, L, g, b, a);
+    else if (g.D == 64) TC_LAUNCH((merge_f32_kernel<64, false>), grid, 0, L, g, b, a);
+    else if (g.D == 128 && even) TC_LAUNCH((merge_f32_kernel<128, true>), grid, 0, L, g, b, a);
+    else if (g.D == 128) TC_LAUNCH((merge_f32_kernel<128, false>), grid, 0, L, g, b, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 }  // namespace tc

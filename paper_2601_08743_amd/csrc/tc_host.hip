@@ -958,7 +958,9 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
                     : launch_attn_f32(ctx->geom, p.dev, a, ln);
     }));
     if (p.dev.part_tab)
-        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) { return launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, false, ln); }));
+        TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
+            return bf16 ? launch_merge_rows_bf16(ctx->geom, p.dev, a, p.max_splits, false, ln) : launch_merge_f32(ctx->geom, p.dev, a, ln);
+        }));
     else if (p.groups_dev)
         TC_HIP(ctx, timed_launch(ctx, 3, stream, [&](const Launch &ln) {
             return launch_merge_bf16(ctx->geom, a, p.groups_dev, p.n_groups, p.row_blocks, p.max_splits, ln);

@@ -89,6 +89,7 @@ hipError_t launch_decode_bf16(const Geom &g, const BatchDev &b, const AttnArgs &
 hipError_t launch_merge_rows_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, int max_splits, bool decode, const Launch &L);
 hipError_t launch_attn_short_bf16(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_attn_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
+hipError_t launch_merge_f32(const Geom &g, const BatchDev &b, const AttnArgs &a, const Launch &L);
 hipError_t launch_merge_bf16(const Geom &g, const AttnArgs &a, const MergeGroup *groups, int n_groups,
                              int row_blocks, int max_splits, const Launch &L);
 

@@ -20,8 +20,8 @@ constexpr int kF32MaxTiles = 512;    // fp32 kernel: key tiles per work item who
 constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append work-group (each holds the kernel's LDS while it runs)
 
 // Up to so many partitions the last one of a row tile to end combines them, one round of loads (decode kernel: 36 of a row for 32
-// threads, of up to four rows for twice as many); more are left to a launch of its own.
-constexpr int kDecodeFold = 36, kShortFold = 8;
+// threads, of up to four rows for twice as many; fp32 kernel, heads of 64: two rounds); more are left to a launch of its own.
+constexpr int kDecodeFold = 36, kShortFold = 8, kF32Fold = 8;
 constexpr inline bool decode_folds(int heads_per_group, int ns) { return heads_per_group <= 8 && ns <= (heads_per_group <= 4 ? 2 : 1) * kDecodeFold; }
 
 constexpr int kArrivalStride = 32, kArrivalStrideBig = 8;   // integers from one arrival counter to the next: a cache line each, in large plans a quarter of one

@@ -87,3 +87,32 @@ def test_values_of_later_tokens_reach_no_earlier_row(H, D, splits):
     assert float(np.abs(got - want)[~hit].max()) <= TOL
     dw.ctx.tc_release_seqs(bt)
     dw.close()
+
+
+@pytest.mark.parametrize("hq,hkv,D", [(8, 2, 64), (6, 2, 128), (5, 1, 64), (3, 3, 128)])
+def test_ranges_combined_inside_the_launch_and_by_one_of_its_own(hq, hkv, D):
+    """Heads of 64: partition counts around the fold's rounds of four and its limit of eight; beyond, and for heads of 128, the
+    merge launch.  Ragged row tiles, slots evenly spaced and packed, every plan twice (the arrival counters are found at zero again)."""
+    import harness as H
+    from paper_2601_08743_amd import workloads as W
+    cfg = W.WorkloadConfig("fold", 1, hq, hkv, D, "f32", 4, (300, 420), 3, (1, 3), "uniform", (5, 40), 4, 331)
+    for lens, suffix in ((None, None), ([20, 400, 900, 300], [60, 3, 5])):
+        wl = W.make_workload(cfg)
+        if lens:
+            wl.table_len[:], wl.suffix_len[:] = lens, suffix
+            wl.queries[:] = [np.array(q, dtype=np.int32) for q in ([0], [1, 2], [2, 3])]
+        dw = H.DeviceWorkload(wl)
+        ref = None
+        for splits in (1, 2, 4, 5, 8, 9, 16, 0):
+            dw.ctx.tc_set_kv_splits(splits)
+            bt, pl = dw.stitch()
+            outs = [dw.attn_layer(0, bt, pl) for _ in range(2)]
+            got = H.out_to_f64(outs[0][0], cfg)
+            np.testing.assert_array_equal(got, H.out_to_f64(outs[1][0], cfg))
+            if ref is None:
+                ref = H.oracle_attn_layer(wl, dw.tables_np, 0, outs[0][1])
+            for i, r in ref.items():
+                err = float(np.abs(got[int(wl.cu_seqlens[i]):int(wl.cu_seqlens[i + 1])] - r).max())
+                assert err <= TOL, (splits, i, err)
+            dw.ctx.tc_release_seqs(bt)
+        dw.close()

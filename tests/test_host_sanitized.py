@@ -581,3 +581,15 @@ def test_decode_partials_are_folded_in_one_round_of_loads_or_merged(exe):
         assert info["decode"] and info["merges"] == merged, (Hq, Hkv, P, info["max_splits"])
     info, items = _plan(exe, 32, 1, [(18000, 1)])
     assert info["max_splits"] == -(-18000 // 128)          # ranges of two tiles: no fewer partials than CUs to read keys with
+
+
+def test_fp32_partials_are_folded_or_merged(exe):
+    """Up to eight ranges of heads of 64 are combined inside the launch; more, heads of 128 and plans of least space by the
+    merge launch, from slots that are evenly spaced or, for one long query among short ones, packed."""
+    for D, PS, splits, merged, even in ((64, [(1000, 60)] * 2, 8, 0, 0), (64, [(1000, 60)] * 2, 9, 1, 1), (128, [(1000, 60)] * 2, 2, 1, 1),
+                                        (64, [(10, 60), (1300, 5)], 16, 1, 0), (128, [(10, 60), (1300, 5)], 16, 1, 0), (64, [(500, 60)], 1, 0, 0)):
+        info, items = _plan(exe, 8, 2, PS, splits=splits, dtype=0, D=D)
+        _check_plan(info, items, 8, 2, PS, dtype=0)
+        assert info["max_splits"] == splits and (info["merges"], info["part_stride"] > 0) == (merged, bool(even)), (D, PS, splits)
+        if splits > 1:
+            _check_slots(info, items, 8, D, PS)
