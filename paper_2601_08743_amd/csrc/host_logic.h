@@ -714,8 +714,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         // block ids of a range fit LDS (the fp32 kernel can fetch those that do not from memory, which is slower)
         const int cap = !bf16 ? (ctx->compact ? n_tiles : kF32MaxTiles) : pp ? kPpMaxTiles : general_cap;
         if (ns < (n_tiles + cap - 1) / cap) { ns = (n_tiles + cap - 1) / cap; cap_bound = true; }
-        // (the partials by row of a row tile's tokens, up to 33, are addressed with 31 bits)
-        if (by_row) ns = (int)std::min<int64_t>(ns, ((int64_t)1 << 31) / (33 * 512 * (int64_t)c.n_q_heads) - 1);
         ns = std::max(1, std::min(ns, n_tiles));
         const int n_mt = (S * G + RT - 1) / RT;
         // Partition boundaries.  A suffix tile of the bf16 kernel costs about 4 prefix tiles (its V
@@ -814,7 +812,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // (the short-launch kernel: eight partials of a row in one round of loads; a launch of its own for them is 0.2 .. 1 us slower up
     // to there, and beyond, where one CU has a second round, 0.5 .. 5 us faster; the fp32 kernel: 0.3 .. 1.5 us slower up to eight
     // partials of 64 columns, beyond 0 .. 5 us faster, of 128 columns 0 .. 9 us faster from five on)
-    p.fold = by_row && p.max_splits > 1 && (p.brief ? p.max_splits <= kShortFold : c.head_dim == 64 && !ctx->compact && p.max_splits <= kF32Fold);
+    // (inside the launch the partials of a row tile's tokens, up to 33, are addressed with 31 bits)
+    p.fold = by_row && p.max_splits > 1 && (int64_t)33 * p.max_splits * c.n_q_heads * 512 <= INT32_MAX && (p.brief ? p.max_splits <= kShortFold : c.head_dim == 64 && !ctx->compact && p.max_splits <= kF32Fold);
     if (!p.fold) p.n_arrivals = 0;
     if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one

@@ -593,3 +593,13 @@ def test_fp32_partials_are_folded_or_merged(exe):
         assert info["max_splits"] == splits and (info["merges"], info["part_stride"] > 0) == (merged, bool(even)), (D, PS, splits)
         if splits > 1:
             _check_slots(info, items, 8, D, PS)
+
+
+@pytest.mark.parametrize("dtype,kernel", [(0, 0), (1, 5)])
+def test_partitions_are_not_limited_by_the_addresses_of_the_fold(exe, dtype, kernel):
+    """A forced partition count is what a caller asked for, up to the key tiles, whatever the number of heads: where the
+    partials of a row tile cannot be addressed inside the launch, the merge launch combines them."""
+    for Hq, Hkv, P, splits, merged in ((128, 1, 64 * 1200 - 1, 1200, 1), (128, 1, 64 * 1200 - 1, 8, 0), (15000, 15000, 64 * 8 - 1, 8, 0),
+                                       (16384, 16384, 64 * 8 - 1, 8, 1)):
+        info, items = _plan(exe, Hq, Hkv, [(P, 1)], dtype=dtype, kernel=kernel, splits=splits, D=128 if dtype else 64)
+        assert info["ok"] and not info["decode"] and (info["max_splits"], info["merges"]) == (splits, merged), (Hq, splits)
