@@ -14,9 +14,11 @@
 // behind the barrier behind that thread's answer.  An agent-scope release and acquire in their place would write back and
 // invalidate whole L2s: 32 sequences' decode step 37.6 us a layer instead of 32.5.
 //
-// The counters are part of the plan, uploaded as zeros, and the last work-group sets its own back to zero, so that
-// every launch of the plan - replays of a graph, too - finds them so.  Each has 128 bytes of its own: 132 arrivals at four
-// neighbouring counters took 8 us.
+// A row tile's counter is a field of one of its work items, uploaded as zero with the plan, and the last work-group sets it
+// back to zero, so that every launch of the plan - replays of a graph, too - finds it so.  (Nobody else writes the items, and
+// a work-group's scalar load of its own item ignores the field.)  Items are 128 bytes, and so counters stand that far apart: 132
+// arrivals at four neighbouring counters took 8 us.  In the items they take no room in the plan and none of its way over the
+// host link: counters of their own, a line each, were up to 29 % of it.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -57,6 +59,11 @@ struct SharedPart {
         return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
     }
 };
+
+__device__ __forceinline__ int32_t *arrival_counter(const AttnArgs &a, const AttnItem &it)
+{
+    return a.arrivals + (int64_t)it.arrival * (sizeof(AttnItem) / sizeof(int32_t));
+}
 
 // Counts the work-group in as one of `n` behind its stores to shared memory; true, in all of its threads, for the last one.
 // `s_flag`: a word of LDS that nothing else uses by now.

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_bf16_kernel(Geom g, BatchD
             }
         }
     }
-    if (kFold && it.n_splits > 1 && last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, it.n_splits, (int32_t *)(lds + kDecIds))) {
+    if (kFold && it.n_splits > 1 && last_to_arrive(arrival_counter(a, it), it.n_splits, (int32_t *)(lds + kDecIds))) {
         // a row to 32 threads; of up to four rows two such groups take every other partition each
         const bool two = G <= 4;
         float *s_w = (float *)lds + 8 * kDecRow + slot8 * kFoldBatch;

@@ -16,9 +16,9 @@
 //   within <ints> <floats>          plan for a workspace of that many integers and floats of partials (0 0: as much as it takes)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
-//                                      one line "i q kvh m0 tile_begin tile_end split n_splits group part0 part_stride" per item,
+//                                      one line "i q kvh m0 tile_begin tile_end split n_splits arrival part0 part_stride" per item,
 //                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, for kernels that keep partials by row, their table (without a launch that goes by one: where each suffix token's begin),
-//                                      "merges <0 or 1>" (partials by row have a merge launch), "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S" per merge group
+//                                      "folds <0 or 1>", "merges <0 or 1>" (partials by row are combined inside the launch, by a merge launch), "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S part0" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
 //   pipeline <n_queries> <capacity> <b_c> <b_m> <keep_pinned> <taper> then per query "<k> ids..."
@@ -133,7 +133,7 @@ int main()
                         p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
             for (const AttnItem &it : items)
                 std::printf("i %d %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
-                            it.q < 0 ? -1 : it.group, it.part0, it.part_stride);
+                            it.q < 0 || !p.fold || it.n_splits == 1 ? -1 : it.arrival, it.part0, it.part_stride);
             std::vector<int32_t> slots;         // kernels that keep partials by row: first slot of each suffix token, and the end
             if (ok && merges_rows(c, p)) {
                 slots.resize(part_tab_ints(p));
@@ -148,10 +148,11 @@ int main()
             std::printf("parts %zu %d", part_floats(c, p), p.part_stride);
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");
+            std::printf("folds %d\n", p.fold && p.max_splits > 1 ? 1 : 0);
             std::printf("merges %d\n", merges_rows(c, p) ? 1 : 0);
             std::printf("part_f32 %d\n", p.part_f32 ? 1 : 0);
             std::printf("groups %d %d\n", (int)groups.size(), p.n_groups);
-            for (const MergeGroup &mg : groups) std::printf("g %d %d %d %d %d\n", mg.kvh, mg.m0, mg.n_splits, mg.cu, mg.S);
+            for (const MergeGroup &mg : groups) std::printf("g %d %d %d %d %d %d\n", mg.kvh, mg.m0, mg.n_splits, mg.cu, mg.S, mg.part0);
         } else if (cmd == "trie") {
             int n;
             std::cin >> n;

@@ -188,7 +188,7 @@ struct StageHalves {
 // The integer plan of one batch, host copy and layout of the device copy.
 struct Plan {
     bool valid = false;
-    int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, n_arrivals = 0, row_blocks = 1;
+    int32_t B = 0, max_blocks = 0, total_S = 0, n_stitch_blk = 0, n_items = 0, max_splits = 1, n_groups = 0, row_blocks = 1;
     int32_t longest_range = 0;  // key tiles of the longest work item (prefill)
     int64_t n_part_slots = 0;   // partial slots of the batch: by (token, partition) in kernels that keep them by row, else by (row tile, partition)
     bool pipelined = false;     // bf16, one row block per wave: the pipelined attention kernel
@@ -211,7 +211,6 @@ struct Plan {
     const AttnItem *items_dev = nullptr;
     const MergeGroup *groups_dev = nullptr;
     int32_t *arrivals_dev = nullptr;
-    int32_t arrival_stride = 0;
 };
 
 // What a caller may force about the attention launch (tc_set_kv_splits and friends); 0 = automatic.
@@ -480,6 +479,19 @@ inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
         }
 }
 
+// The counter of each row tile whose ranges' partials are folded inside the launch: the `arrived` of its first item.  Until here
+// `arrival` is the tile's number, below `n_tiles`.
+inline void place_arrivals(std::vector<AttnItem> &items, size_t n_tiles)
+{
+    std::vector<int32_t> first(n_tiles, -1);
+    for (size_t k = 0; k < items.size(); ++k)
+        if (items[k].q >= 0 && items[k].n_splits > 1) {
+            int32_t &at = first[items[k].arrival];
+            if (at < 0) at = (int32_t)k;
+            items[k].arrival = at;
+        }
+}
+
 // Attention work list for the batch in `p` (host arrays filled in).  Items of one
 // (query, KV head, split) read the same K/V; they are given work-group ids that are congruent
 // modulo 8 so that they land on the same XCD and share its L2 (work-groups go to the 8 XCDs
@@ -502,7 +514,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = p.part_f32 = false;
     p.brief = false;
     p.n_part_slots = 0;
-    p.n_groups = p.n_arrivals = p.part_stride = 0;
+    p.n_groups = p.part_stride = 0;
     p.fold = false;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
@@ -571,7 +583,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     AttnItem it{};
                     it.q = i; it.kvh = h; it.tile_begin = (int32_t)((int64_t)n_tiles * s / ns);
                     it.tile_end = (int32_t)((int64_t)n_tiles * (s + 1) / ns);
-                    it.split = s; it.n_splits = ns; it.arrival = p.n_arrivals + h; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
+                    it.split = s; it.n_splits = ns; it.arrival = i * c.n_kv_heads + h; it.P = P; it.S = 1; it.cu = p.cu_seqlens[i];
                     it.append_bid = bt[P / kBlockTokens];
                     for (int k = 0; k < 16; ++k) {          // entries of the range's first units, clamped to the prefix
                         const int idx = std::min(it.tile_begin * (KT / kBlockTokens) + k, std::max((P + kBlockTokens - 1) / kBlockTokens - 1, 0));
@@ -579,7 +591,6 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                     }
                     items.push_back(it);
                 }
-            if (ns > 1) p.n_arrivals += c.n_kv_heads;
         }
         std::stable_sort(items.begin(), items.end(), [](const AttnItem &x, const AttnItem &y) {
             return x.tile_end - x.tile_begin > y.tile_end - y.tile_begin;
@@ -589,8 +600,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.pipelined = false;
         p.decode = true;
         p.fold = decode_folds(G, p.max_splits);
-        if (!p.fold) p.n_arrivals = 0;
         if (p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
+        if (p.fold) place_arrivals(items, (size_t)p.B * c.n_kv_heads);
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -763,8 +774,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 for (int mt = 0; mt < n_mt; ++mt) {
                     flat.push_back(proto);
                     flat.back().m0 = mt * RT;
-                    flat.back().group = n_groups + mt;
-                    if (by_row && ns > 1) flat.back().arrival = p.n_arrivals + mt;
+                    flat.back().arrival = n_groups + mt;
                     if (!by_row && ns > 1) flat.back().part0 = (int32_t)(p.n_part_slots + (int64_t)mt * ns);
                     ++bucket.count;
                     // (32-row tiles: eight, or four, of them share their keys' way into one L2, the next may go to
@@ -776,9 +786,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 }
                 buckets.push_back(bucket);
             }
-            for (int mt = 0; mt < n_mt; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, (int32_t)(p.n_part_slots + (int64_t)mt * ns), {0, 0}});
+            for (int mt = 0; mt < n_mt && !by_row; ++mt) groups.push_back(MergeGroup{h, mt * RT, ns, p.cu_seqlens[i], S, (int32_t)(p.n_part_slots + (int64_t)mt * ns), {0, 0}});
             n_groups += n_mt;
-            if (by_row && ns > 1) p.n_arrivals += n_mt;
             if (!by_row && ns > 1) p.n_part_slots += (int64_t)n_mt * ns;
         }
     }
@@ -814,8 +823,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // partials of 64 columns, beyond 0 .. 5 us faster, of 128 columns 0 .. 9 us faster from five on)
     // (inside the launch the partials of a row tile's tokens, up to 33, are addressed with 31 bits)
     p.fold = by_row && p.max_splits > 1 && (int64_t)33 * p.max_splits * c.n_q_heads * 512 <= INT32_MAX && (p.brief ? p.max_splits <= kShortFold : c.head_dim == 64 && !ctx->compact && p.max_splits <= kF32Fold);
-    if (!p.fold) p.n_arrivals = 0;
     if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
+    if (p.fold) place_arrivals(items, (size_t)n_groups);
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one
     // work-group per CU: nothing hides a work-group's start-up and drain.  It wins when a launch is a
     // single round of work-groups or when they are long; many short ones (measured: 1140 work-groups
@@ -878,17 +887,14 @@ inline size_t part_floats(const tc_config &c, const Plan &p)      // all of the 
     return (size_t)p.n_part_slots * p.row_blocks * kAttnRows * (part_row_floats(p) + 2);
 }
 
-constexpr size_t kBigPlanInts = size_t(1) << 18;    // 1 MiB: in larger plans the arrival counters stand closer together
-
 // Where the parts of a plan stand in its device copy, in integers; only what the batch's kernels read
 // is there (`n_*`: how many of each).
 struct PlanLayout {
     size_t bt_row = 0;                     // integers per row of the block table
     size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
-    size_t seg_start, seg_len, seg_slot, stitch, arrivals, rope_pos0, rope_freq;
+    size_t seg_start, seg_len, seg_slot, stitch, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
     bool lengths = false, tokens = false, merge_rows = false, merge_groups = false;
-    int arrival_stride = kArrivalStride;
 };
 inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
                               size_t n_groups)
@@ -911,8 +917,6 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.part_tab = take(l.merge_rows ? part_tab_ints(p) : 0);
     l.items = take(n_items * (sizeof(AttnItem) / 4));
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
-    if (l.total + (size_t)p.n_arrivals * kArrivalStride > kBigPlanInts) l.arrival_stride = kArrivalStrideBig;
-    l.arrivals = take((size_t)p.n_arrivals * l.arrival_stride);
     l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     l.total = std::max(l.total, size_t(8));
     return l;

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_f32_kernel(Geom g, 
         part_o.put4(at * (D * 4) + d4 * 16, acc);
         if (d4 == 0) part_ml.put2(at * 8, M, sum);
     }
-    if (!last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, ns, s_bid)) return;
+    if (!last_to_arrive(arrival_counter(a, it), ns, s_bid)) return;
     constexpr int kBatch = 4;
     float M[kPasses], den[kPasses];
     f32x4 acc[kPasses];

@@ -380,7 +380,7 @@ __global__ __launch_bounds__(64 * kShWaves, 2) void attn_bf16_short_kernel(Geom 
         }
         const uint32_t ml_at = (ch < 16 ? slot[0] : slot[1]) * 8 + (ch & 15) * (step >> 6);
         float *s_w = (float *)(lds + kShMl) + (tid >> 5) * 32;
-        if (last_to_arrive(a.arrivals + it.arrival * a.arrival_stride, ns, (int32_t *)(lds + kShIds))) {
+        if (last_to_arrive(arrival_counter(a, it), ns, (int32_t *)(lds + kShIds))) {
             const bool there = (ch & 15) < ns;
             const float2 ml = part_ml.get2(there ? ml_at : kNowhere);
             f32x4 o[kShortFold][2];

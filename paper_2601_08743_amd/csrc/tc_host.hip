@@ -310,8 +310,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         p.dev.part_tab = d + at.part_tab;
         p.dev.part_stride = p.part_stride;
     }
-    p.arrivals_dev = p.fold ? d_dst + at.arrivals : nullptr;
-    p.arrival_stride = at.arrival_stride;
+    p.arrivals_dev = p.fold ? d_dst + at.items + offsetof(AttnItem, arrived) / sizeof(int32_t) : nullptr;
     p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
     p.fixed = fixed;
@@ -932,7 +931,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
         a.items = p.items_dev; a.n_items = p.n_items; a.layer = layer;
         a.scale_log2 = sm_scale * 1.4426950408889634f;
         a.part_o = p.part;
-        a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
+        a.arrivals = p.arrivals_dev;
         if (p.part) a.part_ml = p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;
         TC_HIP(ctx, timed_launch(ctx, 2, stream, [&](const Launch &ln) { return launch_decode_bf16(ctx->geom, p.dev, a, ln); }));
         if (p.dev.part_tab)
@@ -947,7 +946,7 @@ static tc_status prefill_common(tc_ctx *ctx, int32_t layer, const void *q, const
     a.part_f32 = p.part_f32 ? 1 : 0;
     a.long_ranges = p.longest_range > kF32MaxTiles ? 1 : 0;
     a.part_o = p.part;
-    a.arrivals = p.arrivals_dev; a.arrival_stride = p.arrival_stride;
+    a.arrivals = p.arrivals_dev;
     a.part_ml = !p.part ? nullptr
               : bf16 && !p.brief ? p.part + (size_t)p.n_part_slots * p.row_blocks * kAttnRows * part_row_floats(p)
                      : p.part + (size_t)p.n_part_slots * ctx->cfg.n_q_heads * ctx->cfg.head_dim;

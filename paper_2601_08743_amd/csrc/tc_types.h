@@ -24,8 +24,6 @@ constexpr int kF32AppendTokens = 8;  // fp32 kernel: suffix tokens per append wo
 constexpr int kDecodeFold = 36, kShortFold = 8, kF32Fold = 8;
 constexpr inline bool decode_folds(int heads_per_group, int ns) { return heads_per_group <= 8 && ns <= (heads_per_group <= 4 ? 2 : 1) * kDecodeFold; }
 
-constexpr int kArrivalStride = 32, kArrivalStrideBig = 8;   // integers from one arrival counter to the next: a cache line each, in large plans a quarter of one
-
 // Block-table entries as the kernels see them (device copies only; the caller's tables hold plain
 // ids): the low 27 bits are the block id; the bits above count the unused token positions at the
 // end of the block (0..15).  Only blocks of a table slot that a sequence aliases have any: a table
@@ -91,9 +89,9 @@ struct AttnItem {
     int32_t tile_end;    // one past the last key tile
     int32_t split;       // which partition this is (0 when n_splits == 1)
     int32_t n_splits;    // partitions of this query
-    int32_t group;       // index of the (query, KV head, row tile)
+    int32_t arrived;     // arrival counter (arrive.h), zero between launches: how many of its row tile's ranges have ended, in one item of the tile
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
-    int32_t arrival;     // which counter the work-groups of this group count themselves in at (kernels that keep partials by row, several partitions)
+    int32_t arrival;     // that item, where partials are folded inside the launch
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
@@ -120,8 +118,7 @@ struct AttnArgs {
     int32_t n_items;
     int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
-    int32_t *arrivals;   // one counter per group of work items whose last one to end combines their partials; zero between launches; null: a launch of its own combines them
-    int32_t arrival_stride;
+    int32_t *arrivals;   // AttnItem::arrived of the first item, where the last work-group of a row tile to end combines its partials; null: a launch of its own does
     int32_t part_f32;    // partials in fragment order are fp32 (else fp16)
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };

@@ -133,7 +133,8 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0,
     ghead = [l for l in lines if l.startswith("groups ")][0].split()
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
-                n_groups=int(ghead[2]), groups=groups, item_group=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
+                n_groups=int(ghead[2]), groups=groups, item_arrival=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
+    info["folds"] = int([l for l in lines if l.startswith("folds")][0].split()[1])
     info["merges"] = int([l for l in lines if l.startswith("merges")][0].split()[1])
     info["part_f32"] = int([l for l in lines if l.startswith("part_f32")][0].split()[1])
     info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
@@ -155,16 +156,26 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
         rt = 32 if dtype == 0 or info["brief"] else 128 * info["row_blocks"]      # what the kernels stride their rows by
         unified = dtype == 0 or bool(info["pingpong"])
     cover = {}
-    if not info["decode"] and dtype == 1:
-        # the merge launch goes by the group table: one entry per (query, KV head, row tile), in the
-        # order of the items' group numbers, each with the partition count its items carry
-        assert len(info["groups"]) == info["n_groups"]
-        for (q, kvh, m0, tb, te, split, ns), grp in zip(items, info["item_group"]):
-            if q < 0:
-                continue
-            assert 0 <= grp < info["n_groups"]
-            g_kvh, g_m0, g_ns, g_cu, g_S = info["groups"][grp]
-            assert (g_kvh, g_m0, g_ns, g_S) == (kvh, m0, ns, PS[q][1]), (q, kvh, m0, ns, info["groups"][grp])
+    if not info["decode"] and dtype == 1 and not info["brief"]:
+        # the merge launch goes by the group table: one entry per (query, KV head, row tile), each with the partition
+        # count that its items carry and, where that is more than one, the slots that they write: of nobody else's
+        base = np.cumsum([0] + [S for _, S in PS])
+        table = {(cu, kvh, m0): (ns, S, part0) for kvh, m0, ns, cu, S, part0 in info["groups"]}
+        assert len(table) == len(info["groups"]) == info["n_groups"]
+        for (q, kvh, m0, tb, te, split, ns), (part0, _) in zip(items, info["item_part"]):
+            if q >= 0:
+                assert table[base[q], kvh, m0][:2] == (ns, PS[q][1])
+                assert ns == 1 or table[base[q], kvh, m0][2] == part0
+        slots = sorted((part0, ns) for ns, _, part0 in table.values() if ns > 1)
+        assert all(a + n <= b for (a, n), (b, _) in zip(slots, slots[1:]))
+    # where ranges are combined inside the launch, a row tile's items count in at a counter of their own, in one of them
+    counted = {}
+    for (q, kvh, m0, tb, te, split, ns), at in zip(items, info["item_arrival"]):
+        assert (at >= 0) == (q >= 0 and ns > 1 and info["folds"] == 1)
+        if at >= 0:
+            counted.setdefault((q, kvh, m0), []).append((at, ns))
+    for (q, kvh, m0), who in counted.items():
+        assert len(set(who)) == 1 and len(who) == who[0][1] and items[who[0][0]][:3] == (q, kvh, m0)
     for q, kvh, m0, tb, te, split, ns in items:
         if q < 0:
             continue
@@ -603,3 +614,19 @@ def test_partitions_are_not_limited_by_the_addresses_of_the_fold(exe, dtype, ker
                                        (16384, 16384, 64 * 8 - 1, 8, 1)):
         info, items = _plan(exe, Hq, Hkv, [(P, 1)], dtype=dtype, kernel=kernel, splits=splits, D=128 if dtype else 64)
         assert info["ok"] and not info["decode"] and (info["max_splits"], info["merges"]) == (splits, merged), (Hq, splits)
+
+
+def test_counters_take_no_room_in_the_plan(exe):
+    """The arrival counters are in the work items: what fits the fixed workspace does not turn on how many (query, KV head)
+    pairs are cut, and nothing but the items, the block table and (where a merge launch goes by it) the table of slots is uploaded."""
+    for Hq, Hkv, n in ((32, 8, 640), (32, 8, 660), (28, 4, 790)):
+        PS = [(17000, 1)] * n                    # two ranges each, in the plan of least space
+        info, items = _plan(exe, Hq, Hkv, PS, within=(PLAN_INTS, WORKSPACE))
+        assert info["decode"] and info["folds"] and info["max_splits"] == 2
+        assert info["ints"] == len(items) * 32 + n * 1064 <= PLAN_INTS and info["part_floats"] <= WORKSPACE
+    PS = [(1500, 100), (2800, 200), (700, 64), (3100, 256)]
+    info, items = _plan(exe, 8, 2, PS, dtype=0, D=64)
+    _check_plan(info, items, 8, 2, PS, dtype=0)
+    up8 = lambda n: -(-n // 8) * 8
+    nb, S = max(-(-(p + s) // 16) for p, s in PS), sum(s for _, s in PS)
+    assert info["folds"] and info["ints"] == up8(4 * (-(-nb // 4) * 4)) + 3 * up8(4) + up8(S) + len(items) * 32
