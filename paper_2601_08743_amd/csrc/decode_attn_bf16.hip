@@ -86,10 +86,16 @@ __device__ __forceinline__ void write_row(unsigned short *out, const RowSum &x)
     *(uint2 *)out = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
 }
 
-// The new token joins the row's keys, and the row is written.
+// The new token joins the row's keys.  (One key: a score of -infinity is no weight, not the mark of a partial without keys.)
+__device__ __forceinline__ void add_self(RowSum &x, const Self &s)
+{
+    if (s.score != -INFINITY) x.add(s.score, 1.f, s.v);
+}
+
+// The new token joins, and the row is written.
 __device__ __forceinline__ void finish_row(const Geom &g, const AttnArgs &a, const AttnItem &it, int row, int d, const Self &s, RowSum x)
 {
-    x.add(s.score, 1.f, s.v);
+    add_self(x, s);
     write_row((unsigned short *)a.out + ((int64_t)it.cu * g.Hq + it.kvh * g.G + row) * 128 + d, x);
 }
 
@@ -479,10 +485,7 @@ __global__ __launch_bounds__(256) void merge_rows_bf16_kernel(Geom g, BatchDev b
         __syncthreads();
     }
     if (grp > 0 || want >= n_rows || ns <= 1) return;          // (a row in one range was written by the attention kernel)
-    if (kSelf) {
-        const Self s = score_self(self, a.scale_log2);
-        x.add(s.score, 1.f, s.v);
-    }
+    if (kSelf) add_self(x, score_self(self, a.scale_log2));
 #pragma unroll
     for (int k = 1; k < kGroups; ++k) x.add(s_ml[slot8 + k][0], s_ml[slot8 + k][1], *(const f32x4 *)&s_acc[slot8 + k][d]);
     write_row((unsigned short *)a.out + (int64_t)row * 128 + d, x);

@@ -358,3 +358,36 @@ def test_decode_partials_merged_by_a_launch(H, hq, hkv):
                 assert err <= 2.2e-2, (splits, i, err)
             dw.ctx.tc_release_seqs(bt)
         dw.close()
+
+
+@pytest.mark.parametrize("hq,hkv", [(28, 4), (32, 1)])
+def test_a_new_key_of_infinite_distance_has_no_weight(H, hq, hkv):
+    """An infinity in the new token's key: the heads whose query is negative there score it -infinity, and attend to the earlier
+    keys alone; the others +infinity, which is no number after the softmax.  In one range, folded and merged."""
+    cfg = W.WorkloadConfig(name="decinf", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, dtype="bf16", n_tables=3,
+                           table_len=(900, 900), batch=1, tables_per_query=(3, 3), choice="uniform", suffix_len=(1, 1),
+                           capacity=3, seed=411)
+    wl = W.make_workload(cfg)
+    dw = H.DeviceWorkload(wl)
+    q, k, v = wl.suffix_qkv(0)
+    k = k.copy()
+    k[:, :, 5] = np.array([0x7f80], dtype=np.uint16).view(k.dtype)[0]
+    ks, vs = (W.storage_to_f64(x, "bf16") for x in H.oracle_sequences(wl, dw.tables_np, 0, 0))
+    q64, G = W.storage_to_f64(q, "bf16")[0], hq // hkv
+    want = np.empty((hq, 128))
+    for h in range(hq):
+        s = ks[:, h // G] @ q64[h] * wl.sm_scale
+        w = np.exp(s - s.max())
+        want[h] = w @ vs[:, h // G] / w.sum()
+    away = q64[:, 5] < 0
+    assert away.any() and not away.all()
+    for splits in (1, 5, 40):
+        dw.ctx.tc_set_kv_splits(splits)
+        bt, pl = dw.stitch()
+        out, _ = dw.attn_layer(0, bt, pl, qkv=(q, k, v))
+        assert dw.ctx.tc_attn_kernel() == 3 and dw.ctx.tc_kv_splits() == splits
+        got = H.out_to_f64(out, cfg)[0]
+        assert np.isnan(got[~away]).all()
+        assert float(np.abs(got[away] - want[away]).max()) <= 1e-2          # averages of thousands of keys, as above
+        dw.ctx.tc_release_seqs(bt)
+    dw.close()
