@@ -363,7 +363,7 @@ def decode_extras(args, ctx, wl, prefill_layers, P, S, max_blocks, stream):
     f_us = pr["merge"][0] * 1e3 / max(pr["merge"][1], 1)
     kv_bytes = 2 * c.n_kv_heads * c.head_dim * c.elem_bytes * int((P + S).sum())
     return {"decode_ms_per_token_step": round(ms, 4), "decode_attn_kernel_us": round(a_us, 2),
-            "decode_finish_kernel_us": round(f_us, 2), "decode_kv_splits": n_splits,
+            "decode_merge_kernel_us": round(f_us, 2), "decode_kv_splits": n_splits,
             "decode_kernel": {3: "decode_attn_bf16_kernel"}.get(kernel, "prefill kernel %d" % kernel),
             "decode_kv_gbps": round(kv_bytes / (a_us * 1e-6) / 1e9, 1),
             "decode_frac_hbm": round(kv_bytes / (a_us * 1e-6) / 1e9 / PEAK_HBM_GBPS, 4)}
@@ -501,7 +501,6 @@ def bench_resident(args, name, steps, warmup, extras=True, cpu_baseline=True):
     stitch_bytes = 2 * kappa * c.n_layers * int(P.sum())
     attn_us = prof["attn"][0] * 1e3 / max(prof["attn"][1], 1)
     merge_us = prof["merge"][0] * 1e3 / max(prof["merge"][1], 1)
-    append_us = prof["append"][0] * 1e3 / max(prof["append"][1], 1)
     stitch_us = prof["stitch"][0] * 1e3 / max(prof["stitch"][1], 1)
     attn_tflops_kernel = flops_layer / (attn_us * 1e-6) / 1e12
     peak = PEAK_BF16_TFLOPS if c.dtype == "bf16" else PEAK_FP32_TFLOPS
@@ -616,7 +615,7 @@ def bench_resident(args, name, steps, warmup, extras=True, cpu_baseline=True):
                 "attention, split-KV merge)",
         "prefill_ms_per_query": round(ms_per_step / c.batch, 4),
         "attn_kernel_us": round(attn_us, 2), "merge_kernel_us": round(merge_us, 2),
-        "append_kernel_us": round(append_us, 2), "stitch_kernel_us": round(stitch_us, 2),
+        "stitch_kernel_us": round(stitch_us, 2),
         "attn_tflops_kernel_time": round(attn_tflops_kernel, 2),
         "stitch_gbps": round(stitch_gbps, 1),
         "stitch_frac_hbm": round(stitch_gbps / PEAK_HBM_GBPS, 4),

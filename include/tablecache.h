@@ -322,10 +322,11 @@ tc_status tc_set_row_blocks(tc_ctx *ctx, int32_t row_blocks);
  * direct-to-LDS K/V, fixed softmax reference with overflow fallback, one work-group per CU),
  * 3 = as 0 (the decode kernels serve batches in which no query brings more than one new token,
  * unless another kernel is forced: the keys of a KV head are split over waves and work-groups, the
- * last of which to end combines them), 4 = the kernel for long launches (256
+ * last of which to end, or a launch of its own where they are many, combines them), 4 = the kernel for long launches (256
  * rows per work-group in two groups of waves that alternate between matrix and vector work; ignored while tc_set_row_blocks forces a row count), 5 = the kernel for short
  * launches (32 rows per work-group, whose eight waves split the keys; ignored likewise).  Results do
- * not depend on it beyond rounding.  Invalidates the cached plan.
+ * not depend on it beyond rounding, as long as no output exceeds 65504 in magnitude: kernels 1, 2 and 4 keep the partial
+ * rows of a key range that is one of several in fp16 (4: in fp32 where it alone cuts the query), 3 and 5 in fp32.  Invalidates the cached plan.
  * tc_attn_kernel reports the kernel of the current plan (1 .. 5; 0 when no plan is cached, for
  * fp32 contexts and for forced 256-row work-groups of the general kernel). */
 tc_status tc_set_attn_kernel(tc_ctx *ctx, int32_t kind);

@@ -42,7 +42,7 @@ def test_decode_steps_after_prefill(H, splits, kind):
     if splits:
         dw.ctx.tc_set_kv_splits(splits)
     dw.ctx.tc_set_attn_kernel(kind)                    # 0: the decode kernels serve the steps; 1, 4: a prefill kernel does
-                                                       # (4 appends by blocks in a launch of its own: the pool check below covers it)
+                                                       # (4 appends at the end of a row tile's first range: the pool check below covers it)
     max_blocks = int(max(-(-(p + s + T) // 16) for p, s in zip(P, S))) + 1
     bt, pl = dw.stitch(max_blocks=max_blocks)
     # prefill: both layers (appends the prompt's own suffix to the pool)

@@ -137,8 +137,8 @@ def test_c3_full_batch(H):
 def test_c4_long_prefix(H, row_blocks):
     """c4's per-layer shape (60 tables, P = 24.6k, S = 512, B = 4, 32q/8kv) on 2 of its 32 layers.
     row_blocks 0 is the configuration the bench times: the automatic choice, which is the
-    long-launch kernel with the whole key range (392 tiles) in one work item and the suffix appended
-    by blocks first - the pool is therefore also read back behind the attention launch.  1 and 2
+    long-launch kernel with the whole key range (392 tiles) in one work item, which also
+    appends the suffix - the pool is therefore also read back behind the attention launch.  1 and 2
     force the other kernels' work-group shapes: 128 rows (the pipelined kernel, which also holds the
     whole range) and 256 rows in the general kernel (the long-prefix split-KV path)."""
     wl = W.make_workload(W.scaled(W.CONFIGS["c4"], n_layers=2))

@@ -272,8 +272,7 @@ def test_layer_loop_replayed_as_a_graph_matches_eager(H, kind, entry):
     """The per-layer calls captured into a HIP graph (kernel launches only: no memset nodes) and
     replayed several times, with eager stitches, releases and synchronisations in between, give
     bit-identical outputs to the eager calls every time - through the pipelined kernel with its
-    merge launch (the automatic choice here), the long-launch kernel with its append launch, the
-    general kernel, and through the entry point that allocates nothing, which exists for callers
+    merge launch (the automatic choice here), the long-launch kernel, the general kernel, and through the entry point that allocates nothing, which exists for callers
     like this one (the batch's plan is uploaded by the eager call before the capture)."""
     cfg = W.scaled(W.CONFIGS["c2"], n_layers=3, n_tables=8, tables_per_query=(6, 6), capacity=8)
     wl = W.make_workload(cfg)
