@@ -615,8 +615,9 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // the pipelined one.  The line is at 6 / 5, included, because five 128-row tiles that make three of 256 rows (40 / 8 heads,
     // 128 new tokens: the micro-batches of a cold cache) gain: 40 of those 1.085 times as fast as in the other kernels with
     // one partition count for all their queries, and another 1.1 .. 1.35 with plan_long's.
-    // Shorter launches take it where plan_long puts it 15 % below the general and the pipelined kernel's model, 25 % where rows
-    // are padded by more than that; what the short-launch kernel would take stays there, whose softmax weights, over eight
+    // Shorter launches take it where plan_long puts it 20 % below the general and the pipelined kernel's model, 25 % where rows
+    // are padded by more than that (of 160 batches of 4 .. 14 us those 32 are 1.08 .. 1.62 times as fast, 1.26 on average;
+    // of ten between 15 % and 20 % four were 2 .. 13 % slower); what the short-launch kernel would take stays there, whose softmax weights, over eight
     // times as many key ranges, and partials lose less to rounding.
     //
     // The type of its partials (`wide`: fp32).  This kernel cuts queries that the others, or one partition count for the batch,
@@ -650,7 +651,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 if (!brief_wins()) {
                     wide = free_cut && general.splits == 1;
                     lng = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap, wide);
-                    pp = lng.us < (5 * work_pp <= 6 * work ? 0.85 : 0.75) * std::min(general.us, brief.us);
+                    pp = lng.us < (5 * work_pp <= 6 * work ? 0.8 : 0.75) * std::min(general.us, brief.us);
                 }
             }
         }
