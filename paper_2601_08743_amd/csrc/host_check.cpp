@@ -17,7 +17,7 @@
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
 //                                      one line "i q kvh m0 tile_begin tile_end split n_splits arrival part0 part_stride" per item,
-//                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, for kernels that keep partials by row, their table (without a launch that goes by one: where each suffix token's begin),
+//                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, where a launch merges partials by row, the table that it goes by,
 //                                      "folds <0 or 1>", "merges <0 or 1>" (partials by row are combined inside the launch, by a merge launch), "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S part0" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
@@ -134,15 +134,10 @@ int main()
             for (const AttnItem &it : items)
                 std::printf("i %d %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
                             it.q < 0 || !p.fold || it.n_splits == 1 ? -1 : it.arrival, it.part0, it.part_stride);
-            std::vector<int32_t> slots;         // kernels that keep partials by row: first slot of each suffix token, and the end
+            std::vector<int32_t> slots;         // the table that a merge of partials by row goes by
             if (ok && merges_rows(c, p)) {
                 slots.resize(part_tab_ints(p));
                 fill_part_tab(p, splits, slots.data());
-            } else if (ok && parts_by_row(c, p)) {
-                int32_t at = 0;
-                for (int i = 0; i < p.B; ++i)
-                    for (int n = p.cu_seqlens[i]; n < p.cu_seqlens[i + 1]; ++n, at += splits[i] > 1 ? splits[i] : 0) slots.push_back(at);
-                slots.push_back(at);
             }
             std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, items.size(), groups.size()).total, p.compact ? 1 : 0);
             std::printf("parts %zu %d", part_floats(c, p), p.part_stride);

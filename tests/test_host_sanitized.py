@@ -212,10 +212,11 @@ def _check_slots(info, items, Hq, D, PS):
     if info["part_stride"]:                      # evenly spaced
         assert info["part_tab"] == counts and info["part_stride"] == info["max_splits"]
         first, n_slots = [n * info["part_stride"] for n in range(len(counts))], len(counts) * info["part_stride"]
-        assert n_slots <= 2 * sum(counts)
-    else:
-        assert info["part_tab"] == np.cumsum([0] + counts).tolist()
-        first, n_slots = info["part_tab"][:-1], sum(counts)
+        assert n_slots <= 2 * sum(counts) and info["merges"]
+    else:                                        # packed; only a merge launch has a table
+        at = np.cumsum([0] + counts).tolist()
+        assert info["part_tab"] == (at if info["merges"] else [])
+        first, n_slots = at[:-1], sum(counts)
     assert info["part_floats"] == n_slots * Hq * (D + 2)
     for it, (part0, stride) in zip(items, info["item_part"]):
         if it[0] >= 0 and it[6] > 1:
