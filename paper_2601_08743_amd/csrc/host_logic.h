@@ -278,7 +278,8 @@ inline int plan_f32_range(const tc_config &c, const Plan &p, int row_tile, int k
 // other kernels (three: 1.04 times as fast as those, two: 1.3, one: 1.4).  Fitted to
 // 740 batches (1 .. 16 queries of 350 .. 10500 prefix and 2 .. 330 new tokens, 28 / 4, 32 / 8 and 40 / 8
 // heads) in 1 .. 9 ranges, all merged by a launch of its own: 8 % rms.  Up to eight ranges are combined without one, which
-// saves 0.2 .. 1 us (0.4 here).
+// saves 0.2 .. 1 us; charged 0.4 us less for it, queries of three units a wave (450 .. 700 keys) would be cut in three ranges: of 17
+// such batches 15 lose 0.1 .. 0.9 us by that (one of 538 + 22 tokens, 28 / 4 heads, 9.7 us, in one range 9.0).
 inline double batch_mb(const tc_config &c, const Plan &p)
 {
     double tokens = 0;
@@ -301,7 +302,7 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
         if (range > max_tiles) continue;
         int64_t n = 0;
         double units = 0, rows_cut = 0;
-        int most = 0, most_ns = 1;
+        int most = 0;
         bool split = false, wide = false;
         for (int i = 0; i < p.B; ++i) {
             const int S = p.suffix_len[i];
@@ -312,12 +313,11 @@ inline BriefPlan plan_brief(const tc_config &c, const Plan &p, int row_tile, int
             n += k;
             units += (double)k * per_wave;
             most = std::max(most, per_wave);
-            most_ns = std::max(most_ns, ns);
             if (ns > 1) { split = true; wide = wide || S * G > 512; rows_cut += (double)S * c.n_q_heads * ns; }
         }
         if (n == 0 || n > 512 || (split && (n > 256 || wide))) break;          // (n grows with the cuts)
         const double rounds = (double)((n + 255) / 256);
-        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? (most_ns <= kShortFold ? 3.1 : 3.5) + 3e-5 * rows_cut : 0.0) + 0.1 * mb;
+        const double us = std::max(4.4 + 1.6 * most, rounds * (4.4 + 1.6 * units / (double)n)) + (split ? 3.5 + 3e-5 * rows_cut : 0.0) + 0.1 * mb;
         if (us < best.us - 1e-9) best = BriefPlan{range, us};
         if (range == 1) break;
     }
