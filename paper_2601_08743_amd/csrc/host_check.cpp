@@ -16,8 +16,8 @@
 //   within <ints> <floats>          plan for a workspace of that many integers and floats of partials (0 0: as much as it takes)
 //   plan <dtype> <Hq> <Hkv> <D> <splits> <row_blocks> <kernel> <B> then B pairs "P S"
 //                                   -> "plan <n_items> <max_splits> <decode> <pingpong> <pipelined> <row_blocks> <ok> <short>"
-//                                      one line "i q kvh m0 tile_begin tile_end split n_splits arrival part0 part_stride" per item,
-//                                      "ints <size of the device copy> <compact>", "parts <floats> <stride>" and, where a launch merges partials by row, the table that it goes by,
+//                                      one line "i q kvh m0 tile_begin tile_end split n_splits arrival part0 part_stride item" per item (arrival: its row tile's counter; item: the one that holds it where counters have no place of their own),
+//                                      "ints <size of the device copy> <compact> <where counters begin> <their size>", "parts <floats> <stride>" and, where a launch merges partials by row, the table that it goes by,
 //                                      "folds <0 or 1>", "merges <0 or 1>" (partials by row are combined inside the launch, by a merge launch), "part_f32 <0 or 1>", "groups <entries> <n_groups>" and one line "g kvh m0 n_splits cu S part0" per merge group
 //   trie <n> then n lines "<id> <len> tok..."; match <len> tok... -> "match <n> (id start)..."
 //   rerank <n_queries> <n_tables> <anchor> then per query "<k> ids..." -> "rerank order..."
@@ -131,15 +131,21 @@ int main()
                                      : plan_attention(c, knobs, p, items, splits, groups);
             std::printf("plan %d %d %d %d %d %d %d %d\n", (int)items.size(), p.max_splits, p.decode ? 1 : 0,
                         p.pingpong ? 1 : 0, p.pipelined ? 1 : 0, p.row_blocks, ok ? 1 : 0, p.brief ? 1 : 0);
-            for (const AttnItem &it : items)
-                std::printf("i %d %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
-                            it.q < 0 || !p.fold || it.n_splits == 1 ? -1 : it.arrival, it.part0, it.part_stride);
+            std::vector<AttnItem> placed = items;
+            if (p.fold) place_arrivals(placed, (size_t)p.n_arrivals);
+            for (size_t k = 0; k < items.size(); ++k) {
+                const AttnItem &it = items[k];
+                const bool counts = it.q >= 0 && p.fold && it.n_splits > 1;
+                std::printf("i %d %d %d %d %d %d %d %d %d %d %d\n", it.q, it.kvh, it.m0, it.tile_begin, it.tile_end, it.split, it.n_splits,
+                            counts ? it.arrival : -1, it.part0, it.part_stride, counts ? placed[k].arrival : -1);
+            }
             std::vector<int32_t> slots;         // the table that a merge of partials by row goes by
             if (ok && merges_rows(c, p)) {
                 slots.resize(part_tab_ints(p));
                 fill_part_tab(p, splits, slots.data());
             }
-            std::printf("ints %zu %d\n", plan_layout(c, p, 0, 0, items.size(), groups.size()).total, p.compact ? 1 : 0);
+            const PlanLayout at = plan_layout(c, p, 0, 0, items.size(), groups.size());
+            std::printf("ints %zu %d %zu %zu\n", at.total, p.compact ? 1 : 0, at.counters, at.n_counter_ints);
             std::printf("parts %zu %d", part_floats(c, p), p.part_stride);
             for (int32_t s : slots) std::printf(" %d", s);
             std::printf("\n");

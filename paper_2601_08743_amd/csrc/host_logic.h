@@ -195,6 +195,7 @@ struct Plan {
     bool decode = false;        // bf16, at most one new token per query: the decode kernels
     bool pingpong = false;      // bf16, 256 rows per work-group in two alternating wave groups
     int32_t part_stride = 0;    // kernels that keep partials by row: slots from token to token, 0: packed
+    int32_t n_arrivals = 0;     // row tiles that may need an arrival counter (fold)
     bool fold = false;          // partials by row are combined inside the launch that makes them (else by one of its own)
     bool part_f32 = false;      // partials in fragment order are fp32 (the long-launch kernel's, by a rule of the planner), else fp16
     bool compact = false;       // planned for the least space (a batch that did not fit the static workspace otherwise)
@@ -479,8 +480,8 @@ inline void place_partials(const tc_config &c, const PlanKnobs &knobs, Plan &p, 
         }
 }
 
-// The counter of each row tile whose ranges' partials are folded inside the launch: the `arrived` of its first item.  Until here
-// `arrival` is the tile's number, below `n_tiles`.
+// Where the workspace has no room for counters of their own (PlanLayout::counters): the counter of each row tile whose ranges' partials
+// are folded inside the launch is the `arrived` of its first item.  Until here `arrival` is the tile's number, below `n_tiles`.
 inline void place_arrivals(std::vector<AttnItem> &items, size_t n_tiles)
 {
     std::vector<int32_t> first(n_tiles, -1);
@@ -514,7 +515,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     p.pingpong = p.part_f32 = false;
     p.brief = false;
     p.n_part_slots = 0;
-    p.n_groups = p.part_stride = 0;
+    p.n_groups = p.part_stride = p.n_arrivals = 0;
     p.fold = false;
     p.compact = ctx->compact;
     // Decode step: every query brings at most one new token, so a KV head has only G rows and the
@@ -601,7 +602,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
         p.decode = true;
         p.fold = decode_folds(G, p.max_splits);
         if (p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
-        if (p.fold) place_arrivals(items, (size_t)p.B * c.n_kv_heads);
+        p.n_arrivals = p.fold && p.max_splits > 1 ? p.B * c.n_kv_heads : 0;
         for (const AttnItem &it : items)
             if (it.tile_end - it.tile_begin > kAttnMaxTiles) return false;
         return true;
@@ -825,7 +826,7 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // (inside the launch the partials of a row tile's tokens, up to 33, are addressed with 31 bits)
     p.fold = by_row && p.max_splits > 1 && (int64_t)33 * p.max_splits * c.n_q_heads * 512 <= INT32_MAX && (p.brief ? p.max_splits <= kShortFold : c.head_dim == 64 && !ctx->compact && p.max_splits <= kF32Fold);
     if (by_row && p.max_splits > 1) place_partials(c, knobs, p, splits_of_q, items);
-    if (p.fold) place_arrivals(items, (size_t)n_groups);
+    p.n_arrivals = p.fold ? n_groups : 0;
     // Which bf16 kernel (one row block per wave).  The pipelined one holds 132 KB of LDS, so one
     // work-group per CU: nothing hides a work-group's start-up and drain.  It wins when a launch is a
     // single round of work-groups or when they are long; many short ones (measured: 1140 work-groups
@@ -895,6 +896,9 @@ struct PlanLayout {
     size_t block_table, cu, prefix, suffix, tok_q, part_tab, items, groups;
     size_t seg_start, seg_len, seg_slot, stitch, rope_pos0, rope_freq;
     size_t total = 0;                      // a multiple of 8: the upload moves 16 bytes at a time
+    // Arrival counters, behind what is uploaded and zeroed with it: 128 bytes each, as far apart as work items.  They are in the items
+    // where the workspace of fixed size has no room for them, which is 0.1 .. 0.4 us a launch slower (arrive.h).
+    size_t counters = 0, n_counter_ints = 0;
     bool lengths = false, tokens = false, merge_rows = false, merge_groups = false;
 };
 inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, size_t n_stitch, size_t n_items,
@@ -920,6 +924,8 @@ inline PlanLayout plan_layout(const tc_config &c, const Plan &p, size_t n_seg, s
     l.groups = take(l.merge_groups ? n_groups * (sizeof(MergeGroup) / 4) : 0);
     l.rope_pos0 = take(p.rope ? B : 0); l.rope_freq = take(p.rope ? p.rope_rev_freq.size() * 2 : 0);
     l.total = std::max(l.total, size_t(8));
+    l.counters = (l.total + 31) & ~size_t(31);
+    l.n_counter_ints = (size_t)p.n_arrivals * (sizeof(AttnItem) / sizeof(int32_t));
     return l;
 }
 

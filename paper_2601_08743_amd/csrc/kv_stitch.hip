@@ -158,17 +158,20 @@ __device__ __forceinline__ void copy_block_kv(const Geom &g, const char *k_src, 
 // engine, and handing the stream over and back leaves the compute units idle.  Measured between
 // trains of 8 small kernels (20.7 us): copy of 64 KB 43.5 us, this kernel 23.5 (its launch is hidden
 // like the others'); 256 KB 40.6 against 27.7; 1 MB 54.2 against 42.0.
-__global__ __launch_bounds__(256) void upload_kernel(const uint4 *src, uint4 *dst, int n)
+// Behind it `zeros` integers (a multiple of 4) at dst + zeros_at that do not cross the link: the arrival counters.
+__global__ __launch_bounds__(256) void upload_kernel(const uint4 *src, uint4 *dst, int n, uint4 *zeros, int n_zeros)
 {
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n_zeros; i += gridDim.x * 256) zeros[i] = make_uint4(0, 0, 0, 0);
 }
 
-hipError_t launch_upload(int32_t *dst, const int32_t *pinned_src, size_t ints, const Launch &L)
+hipError_t launch_upload(int32_t *dst, const int32_t *pinned_src, size_t ints, size_t zeros_at, size_t zeros, const Launch &L)
 {
-    const size_t n = ints / 4;
+    const size_t n = ints / 4, n_zeros = zeros / 4;
     if (n == 0) return hipSuccess;
-    if (n > (size_t)INT32_MAX || ints % 4 || (((uintptr_t)dst | (uintptr_t)pinned_src) & 15)) return hipErrorInvalidValue;
-    TC_LAUNCH(upload_kernel, (int)std::min<size_t>((n + 255) / 256, 64), 0, L, (const uint4 *)pinned_src, (uint4 *)dst, (int)n);
+    if (n > (size_t)INT32_MAX || n_zeros > (size_t)INT32_MAX || ints % 4 || zeros_at % 4 || zeros % 4 || (((uintptr_t)dst | (uintptr_t)pinned_src) & 15)) return hipErrorInvalidValue;
+    TC_LAUNCH(upload_kernel, (int)std::min<size_t>((n + 255) / 256, 64), 0, L, (const uint4 *)pinned_src, (uint4 *)dst, (int)n,
+              (uint4 *)(dst + zeros_at), (int)n_zeros);
     return hipGetLastError();
 }
 

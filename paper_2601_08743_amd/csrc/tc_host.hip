@@ -195,10 +195,10 @@ bool config_ok(const tc_config *c)
 int esize_of(const tc_config &c) { return c.dtype == TC_F32 ? 4 : 2; }
 
 // Make room for a plan of `ints` integers: the pinned staging buffer on the host and, unless the
-// plan goes to the static workspace (`fixed`), the device buffer.  The staging buffer is created
+// plan goes to the static workspace (`fixed`), the device buffer, `device_ints` with the arrival counters.  The staging buffer is created
 // by tc_create with the static workspace's plan capacity, so a fixed plan never allocates.
 // `at`: where in the staging buffer the plan goes; `parts`: the halves of it whose events its upload records.
-tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, unsigned *parts)
+tc_status ensure_stage(tc_ctx *ctx, size_t ints, size_t device_ints, bool fixed, int32_t **at, unsigned *parts)
 {
     if (fixed && (ints > kScratchPlanInts || ints > ctx->h_stage_ints))
         return fail(ctx, TC_ERR_CAPACITY, "attn (no allocation): the batch's plan needs %zu integers, the fixed workspace holds %zu",
@@ -225,10 +225,10 @@ tc_status ensure_stage(tc_ctx *ctx, size_t ints, bool fixed, int32_t **at, unsig
     if (st != TC_OK) return st;
     *at = ctx->h_stage + spot.at;
     *parts = spot.parts;
-    if (!fixed && ints > ctx->d_plan_ints) {
+    if (!fixed && device_ints > ctx->d_plan_ints) {
         if (ctx->d_plan) TC_HIP(ctx, hipFree(ctx->d_plan));   // hipFree waits for work that may use it
         ctx->d_plan = nullptr; ctx->d_plan_ints = 0;
-        const size_t cap = std::max(ints * 2, size_t(1) << 16);
+        const size_t cap = std::max(device_ints * 2, size_t(1) << 16);
         TC_HIP(ctx, hipMalloc((void **)&ctx->d_plan, cap * sizeof(int32_t)));
         ctx->d_plan_ints = cap;
     }
@@ -260,7 +260,9 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
                     part_need, kScratchPartFloats);
     int32_t *h = nullptr;
     unsigned parts = 0;
-    tc_status st = ensure_stage(ctx, total, fixed, &h, &parts);
+    const bool own_counters = p.fold && (!fixed || at.counters + at.n_counter_ints <= kScratchPlanInts);
+    if (p.fold && !own_counters) place_arrivals(items, (size_t)p.n_arrivals);
+    tc_status st = ensure_stage(ctx, total, own_counters ? at.counters + at.n_counter_ints : total, fixed, &h, &parts);
     if (st != TC_OK) return st;
     std::memset(h, 0, total * sizeof(int32_t));
     for (size_t i = 0; i < B; ++i)
@@ -284,7 +286,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
     put(at.rope_freq, p.rope_rev_freq, p.rope);
 
     int32_t *d_dst = fixed ? (int32_t *)ctx->scratch_dev : ctx->d_plan;
-    TC_HIP(ctx, launch_upload(d_dst, h, total, Launch{stream, nullptr, nullptr}));
+    TC_HIP(ctx, launch_upload(d_dst, h, total, at.counters, own_counters ? at.n_counter_ints : 0, Launch{stream, nullptr, nullptr}));
     for (int k = 0; k < 2; ++k)
         if (parts >> k & 1) {
             TC_HIP(ctx, hipEventRecord(ctx->stage_ev[k], stream));
@@ -310,7 +312,7 @@ tc_status upload_plan(tc_ctx *ctx, Plan &p, const std::vector<SegInfo> &segs,
         p.dev.part_tab = d + at.part_tab;
         p.dev.part_stride = p.part_stride;
     }
-    p.arrivals_dev = p.fold ? d_dst + at.items + offsetof(AttnItem, arrived) / sizeof(int32_t) : nullptr;
+    p.arrivals_dev = !p.fold ? nullptr : own_counters ? d_dst + at.counters : d_dst + at.items + offsetof(AttnItem, arrived) / sizeof(int32_t);
     p.groups_dev = at.merge_groups ? (const MergeGroup *)(d + at.groups) : nullptr;
 
     p.fixed = fixed;

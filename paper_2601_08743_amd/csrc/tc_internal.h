@@ -74,7 +74,7 @@ struct PerDeviceOnce {
 };
 
 // kv_stitch.hip
-hipError_t launch_upload(int32_t *dst, const int32_t *pinned_src, size_t ints, const Launch &L);
+hipError_t launch_upload(int32_t *dst, const int32_t *pinned_src, size_t ints, size_t zeros_at, size_t zeros, const Launch &L);
 hipError_t launch_stitch(const Geom &g, const BatchDev &b, int l0, int l1, bool rope, const Launch &L);
 hipError_t launch_format(const Geom &g, const void *raw, int64_t v_part, int n_tokens, int first_block, int l0,
                          int l1, const Launch &L);

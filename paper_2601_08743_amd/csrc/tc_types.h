@@ -89,9 +89,9 @@ struct AttnItem {
     int32_t tile_end;    // one past the last key tile
     int32_t split;       // which partition this is (0 when n_splits == 1)
     int32_t n_splits;    // partitions of this query
-    int32_t arrived;     // arrival counter (arrive.h), zero between launches: how many of its row tile's ranges have ended, in one item of the tile
+    int32_t arrived;     // arrival counter (arrive.h) where there is no other place for it, zero between launches: how many of its row tile's ranges have ended, in one item of the tile
     int32_t P, S, cu;    // prefix length, suffix length, first suffix row of the query
-    int32_t arrival;     // that item, where partials are folded inside the launch
+    int32_t arrival;     // which counter, where partials are folded inside the launch: the row tile's number, or that item's
     int32_t bid[16];     // block-table entries of the first four key tiles of the range (clamped to the sequence)
     int32_t n_pad_fast;  // unused token positions inside the leading run of full prefix tiles of the range
     int32_t append_bid;  // decode step: the block that takes the new token
@@ -118,7 +118,7 @@ struct AttnArgs {
     int32_t n_items;
     int32_t n_append;    // append units run by the attention launch, 0 = none
     int32_t long_ranges; // fp32 kernel: some item has more than kF32MaxTiles key tiles
-    int32_t *arrivals;   // AttnItem::arrived of the first item, where the last work-group of a row tile to end combines its partials; null: a launch of its own does
+    int32_t *arrivals;   // the first arrival counter, the next an AttnItem's size further, where the last work-group of a row tile to end combines its partials; null: a launch of its own does
     int32_t part_f32;    // partials in fragment order are fp32 (else fp16)
     int32_t has_pads;    // some block-table entry of the batch carries unused tail positions (aliased table blocks)
 };

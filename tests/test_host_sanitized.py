@@ -133,11 +133,11 @@ def _plan(exe, Hq, Hkv, PS, splits=0, rb=0, kernel=0, dtype=1, D=128, within=(0,
     ghead = [l for l in lines if l.startswith("groups ")][0].split()
     groups = [tuple(map(int, l.split()[1:])) for l in lines if l.startswith("g ")]
     info = dict(max_splits=head[1], decode=head[2], pingpong=head[3], pipelined=head[4], row_blocks=head[5], ok=head[6], brief=head[7],
-                n_groups=int(ghead[2]), groups=groups, item_arrival=[r[7] for r in rows], item_part=[r[8:10] for r in rows])
+                n_groups=int(ghead[2]), groups=groups, item_arrival=[r[7] for r in rows], item_holder=[r[10] for r in rows], item_part=[r[8:10] for r in rows])
     info["folds"] = int([l for l in lines if l.startswith("folds")][0].split()[1])
     info["merges"] = int([l for l in lines if l.startswith("merges")][0].split()[1])
     info["part_f32"] = int([l for l in lines if l.startswith("part_f32")][0].split()[1])
-    info["ints"], info["compact"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
+    info["ints"], info["compact"], info["counters"], info["counter_ints"] = map(int, [l for l in lines if l.startswith("ints")][0].split()[1:])
     info["part_floats"], info["part_stride"], *info["part_tab"] = map(int, [l for l in lines if l.startswith("parts")][0].split()[1:])
     assert int(ghead[1]) == len(groups)
     return info, items
@@ -168,14 +168,18 @@ def _check_plan(info, items, Hq, Hkv, PS, dtype=1):
                 assert ns == 1 or table[base[q], kvh, m0][2] == part0
         slots = sorted((part0, ns) for ns, _, part0 in table.values() if ns > 1)
         assert all(a + n <= b for (a, n), (b, _) in zip(slots, slots[1:]))
-    # where ranges are combined inside the launch, a row tile's items count in at a counter of their own, in one of them
+    # where ranges are combined inside the launch, a row tile's items count in at a counter of their own: 128 bytes behind the plan,
+    # or in one of those items
     counted = {}
-    for (q, kvh, m0, tb, te, split, ns), at in zip(items, info["item_arrival"]):
-        assert (at >= 0) == (q >= 0 and ns > 1 and info["folds"] == 1)
+    for (q, kvh, m0, tb, te, split, ns), at, holder in zip(items, info["item_arrival"], info["item_holder"]):
+        assert (at >= 0) == (holder >= 0) == (q >= 0 and ns > 1 and info["folds"] == 1)
         if at >= 0:
-            counted.setdefault((q, kvh, m0), []).append((at, ns))
+            counted.setdefault((q, kvh, m0), []).append((at, ns, holder))
     for (q, kvh, m0), who in counted.items():
-        assert len(set(who)) == 1 and len(who) == who[0][1] and items[who[0][0]][:3] == (q, kvh, m0)
+        assert len(set(who)) == 1 and len(who) == who[0][1] and items[who[0][2]][:3] == (q, kvh, m0)
+    assert len({who[0][0] for who in counted.values()}) == len(counted)
+    assert all(32 * who[0][0] + 32 <= info["counter_ints"] for who in counted.values())
+    assert info["counters"] % 32 == 0 and info["counters"] >= info["ints"] and (info["folds"] or info["counter_ints"] == 0)
     for q, kvh, m0, tb, te, split, ns in items:
         if q < 0:
             continue
@@ -626,8 +630,8 @@ def test_partitions_are_not_limited_by_the_addresses_of_the_fold(exe, dtype, ker
 
 
 def test_counters_take_no_room_in_the_plan(exe):
-    """The arrival counters are in the work items: what fits the fixed workspace does not turn on how many (query, KV head)
-    pairs are cut, and nothing but the items, the block table and (where a merge launch goes by it) the table of slots is uploaded."""
+    """The arrival counters are behind the plan where there is room and else in the work items: what fits the fixed workspace does not
+    turn on how many (query, KV head) pairs are cut, and nothing but the items, the block table and (where a merge launch goes by it) the table of slots is uploaded."""
     for Hq, Hkv, n in ((32, 8, 640), (32, 8, 660), (28, 4, 790)):
         PS = [(17000, 1)] * n                    # two ranges each, in the plan of least space
         info, items = _plan(exe, Hq, Hkv, PS, within=(PLAN_INTS, WORKSPACE))
@@ -639,6 +643,15 @@ def test_counters_take_no_room_in_the_plan(exe):
     up8 = lambda n: -(-n // 8) * 8
     nb, S = max(-(-(p + s) // 16) for p, s in PS), sum(s for _, s in PS)
     assert info["folds"] and info["ints"] == up8(4 * (-(-nb // 4) * 4)) + 3 * up8(4) + up8(S) + len(items) * 32
+
+
+def test_counters_have_a_place_of_their_own_or_are_in_the_items(exe):
+    """The batch of the GPU test of counters in the work items: its plan fits the fixed workspace, with the counters behind it it would not."""
+    PS = [(620, 1)] * 64 + [(5120, 0)] + [(620, 0)] * 3096
+    info, items = _plan(exe, 28, 4, PS, splits=4, within=(PLAN_INTS, WORKSPACE))
+    _check_plan(info, items, 28, 4, PS)
+    assert info["decode"] and info["folds"] and not info["compact"] and info["max_splits"] == 4
+    assert info["ints"] <= PLAN_INTS < info["counters"] + info["counter_ints"]
 
 
 def test_short_launches_that_gain_little_stay_with_the_other_kernels(exe):

@@ -188,6 +188,35 @@ def test_noalloc_plan_of_least_space():
     dw.close()
 
 
+def test_noalloc_counters_in_the_work_items():
+    """A decode step of 64 sequences in four ranges each beside 3097 queries without new tokens, whose table rows leave the plan less room
+    than 256 arrival counters take: they are counted in at their work items, with the bits of the counters behind the plan."""
+    import harness as H
+    n, total, blocks = 64, 3161, 320
+    cfg = W.WorkloadConfig("n", 1, 28, 4, 128, "bf16", 8, (600, 640), n, (1, 1), "uniform", (1, 1), 8, 323)
+    wl = W.make_workload(cfg)
+    dw = H.DeviceWorkload(wl)
+    dw.ctx.tc_set_kv_splits(4)
+    bt, pl = dw.stitch(max_blocks=blocks)
+    out, qkv = dw.attn_layer(0, bt, pl)
+    assert dw.ctx.tc_attn_kernel() == 3 and dw.ctx.tc_kv_splits() == 4
+    idle = total - n
+    bt, pl = np.concatenate([bt, np.repeat(bt[:1], idle, axis=0)]), np.concatenate([pl, np.repeat(pl[:1], idle)])
+    sl = np.concatenate([wl.suffix_len, np.zeros(idle, dtype=np.int32)]).astype(np.int32)
+    cu = np.concatenate([[0], np.cumsum(sl)]).astype(np.int32)
+    dev = [H.to_dev(x, cfg) for x in qkv]
+    for _ in range(3):                           # the counters are found at zero again
+        got = torch.full_like(out, float("nan"))
+        dw.ctx.tc_prefill_attn_noalloc(0, *dev, got, cu, bt, pl, sl, wl.sm_scale)
+        torch.cuda.synchronize()
+        assert dw.ctx.tc_attn_kernel() == 3 and dw.ctx.tc_kv_splits() == 4
+        assert torch.equal(got, out)
+    ref = H.oracle_attn_layer(wl, dw.tables_np, 0, qkv)
+    g64 = H.out_to_f64(out, cfg)
+    assert max(float(np.abs(g64[i:i + 1] - r).max()) for i, r in ref.items()) <= 1e-2
+    dw.close()
+
+
 def test_noalloc_refuses_what_does_not_fit():
     """A batch whose partials exceed the fixed workspace is refused with TC_ERR_CAPACITY and
     enqueues nothing; the allocating entry point still serves it."""
