@@ -385,7 +385,7 @@ inline GeneralPlan plan_general(const tc_config &c, const Plan &p, int row_tile,
 // within 0.6 % of the fastest on average, 12 % at worst.  (Placed on 256 CUs alike: 1.3 %, and 40 % at worst - one query of 4.4 k
 // + 400 tokens, 28 / 4 heads, in five ranges: 20 buckets of 11 items put 33 on some XCD, 59.8 us against 42.0 in four; with one
 // partition count for all, taken from a batch's mean length: 11 % behind it.)
-struct LongPlan { int range = 0; double us = 1e30; };
+struct LongPlan { int range = 0; double us = 1e30; bool cut = false; };
 inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int key_tile, size_t part_cap, bool part_f32)
 {
     constexpr int kCus = 256, kXcds = 8;
@@ -444,7 +444,7 @@ inline LongPlan plan_long(const tc_config &c, const Plan &p, int row_tile, int k
         int64_t ends = 0;
         for (Xcd *x = xcds; x < xcds + kXcds / alike; ++x) ends = std::max(ends, x->cus.front().first);
         const double us = 3.0 + merge + 0.01 * (double)ends;
-        if (us < best.us - 1e-9 && (uncut == 0.0 || us < 0.95 * uncut)) best = LongPlan{range, us};
+        if (us < best.us - 1e-9 && (uncut == 0.0 || us < 0.95 * uncut)) best = LongPlan{range, us, cut_rows > 0};
         if (cut_rows == 0 && uncut == 0.0) uncut = us;
     }
     return best;
@@ -617,8 +617,11 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     // 128 new tokens: the micro-batches of a cold cache) gain: 40 of those 1.085 times as fast as in the other kernels with
     // one partition count for all their queries, and another 1.1 .. 1.35 with plan_long's.
     // Shorter launches take it where plan_long puts it 20 % below the general and the pipelined kernel's model, 25 % where rows
-    // are padded by more than that (of 160 batches of 4 .. 14 us those 32 are 1.08 .. 1.62 times as fast, 1.26 on average;
-    // of ten between 15 % and 20 % four were 2 .. 13 % slower); what the short-launch kernel would take stays there, whose softmax weights, over eight
+    // are padded by more than that (of 160 batches of 4 .. 14 us those 32 are 1.08 .. 1.62 times as fast, 1.26 on average), and
+    // from 15 % on where those leave the queries whole and this kernel does, too, or they have two of its row tiles each on average.
+    // Of 84 batches between 15 and 20 % 28 are whole either way: 1.04 .. 1.57 times as fast, 1.27 on average; 20 are cut here alone and have the rows:
+    // 0.96 .. 1.16, 1.07 on average (with fp16 partials 1.17); 11 have not: 0.93 .. 1.18 with fp16; 25 are cut by the others as well:
+    // 0.89 .. 1.27, seven lose 2 .. 11 %.  What the short-launch kernel would take stays there, whose softmax weights, over eight
     // times as many key ranges, and partials lose less to rounding.
     //
     // The type of its partials (`wide`: fp32).  This kernel cuts queries that the others, or one partition count for the batch,
@@ -638,9 +641,10 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
     if (bf16 && ctx->forced_row_blocks == 0) {
         if (ctx->forced_attn_kernel == 4) pp = true;
         else if (ctx->forced_attn_kernel == 0) {
-            int64_t work = 0, work_pp = 0;              // in 128-row tiles; the same with rows padded to this kernel's 256
+            int64_t work = 0, work_pp = 0, n_q = 0;     // in 128-row tiles; the same with rows padded to this kernel's 256
             for (int i = 0; i < p.B; ++i)
                 if (p.suffix_len[i] > 0) {
+                    ++n_q;
                     const int64_t per_row_tile = (int64_t)c.n_kv_heads * (((int64_t)p.prefix_len[i] + p.suffix_len[i] + KT - 1) / KT);
                     work += per_row_tile * (((int64_t)p.suffix_len[i] * G + kAttnRows - 1) / kAttnRows);
                     work_pp += per_row_tile * 2 * (((int64_t)p.suffix_len[i] * G + 2 * kAttnRows - 1) / (2 * kAttnRows));
@@ -652,7 +656,8 @@ inline bool plan_attention_pass(const tc_config &c, const PlanKnobs &knobs, Plan
                 if (!brief_wins()) {
                     wide = free_cut && general.splits == 1;
                     lng = plan_long(c, p, 2 * kAttnRows, KT, ctx->part_cap, wide);
-                    pp = lng.us < (5 * work_pp <= 6 * work ? 0.8 : 0.75) * std::min(general.us, brief.us);
+                    const bool sure = general.splits == 1 && (!lng.cut || (int64_t)p.total_S * G >= 4 * kAttnRows * n_q);
+                    pp = lng.us < (5 * work_pp > 6 * work ? 0.75 : sure ? 0.85 : 0.8) * std::min(general.us, brief.us);
                 }
             }
         }
